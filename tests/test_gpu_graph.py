@@ -124,3 +124,21 @@ def test_error_codes(lib, ctx):
     rc = L.gp_edges_count(ctx._h, C.c_void_p(pos.data_ptr()), C.c_void_p(gptr.data_ptr()), C.c_int64(-4), C.c_int32(1),
                           C.c_float(2.0), C.c_int32(0), C.c_void_p(ws.data_ptr()), C.c_size_t(4096), C.byref(n))
     assert rc == -1
+
+
+@pytest.mark.parametrize("case", ["one shell of equal distances", "more candidates in range than the list holds", "cap of all but one"])
+def test_cap_selection_edges(lib, ctx, case):
+    # the kept neighbours end inside a run of equal squared distances / the selection recomputes distances / the cap is one
+    # below the number in range
+    if case == "one shell of equal distances":
+        g = np.stack(np.meshgrid(*[np.arange(5.0)] * 3, indexing="ij"), -1).reshape(-1, 3).astype(np.float32)
+        for cap in (3, 6, 10, 18):
+            _check(lib, ctx, g, np.array([0, len(g)], np.int32), 2.3, cap)
+    elif case == "more candidates in range than the list holds":
+        pos, gptr = synth.cube_positions(530, 10.0, 0.5, seed=2)
+        ref = _check(lib, ctx, pos, gptr, 30.0, 7)
+        assert np.all(np.diff(ref["row_ptr"]) == 7)
+    else:
+        pos, gptr = synth.cube_positions(66, 8.0, 0.9, seed=4)
+        ref = _check(lib, ctx, pos, gptr, 30.0, 64)
+        assert np.all(np.diff(ref["row_ptr"]) == 64)
