@@ -16,29 +16,42 @@ struct bessel_table {
   double norm[MAX_S * MAX_R_BESSEL];  // sqrt(2 / (c^3 j_{l+1}(z)^2))
 };
 
-// j_l(x), x > 0: ascending series below the turning point, upward recurrence above it.
-__host__ __device__ inline double sph_bessel(int l, double x) {
-  if (x < (double)l + 1.0 && l >= 2) {
-    double q = -0.5 * x * x, term = 1.0, sum = 1.0;
-    for (int k = 1; k <= 40; ++k) {
-      term *= q / ((double)k * (double)(2 * l + 2 * k + 1));
-      sum += term;
-    }
-    double pref = 1.0;
-    for (int k = 1; k <= l; ++k) pref *= x / (double)(2 * k + 1);
-    return pref * sum;
+// j_{l-1}(x) and j_l(x) (the former only for l >= 1), x > 0: ascending series below the turning point, upward recurrence
+// above it.  The series stops when its terms no longer reach the sum.
+__host__ __device__ inline double bessel_series(int l, double x) {
+  const double q = -0.5 * x * x;
+  double term = 1.0, sum = 1.0;
+  for (int k = 1; k <= 40 && fabs(term) > 1e-18 * fabs(sum); ++k) {
+    term *= q / ((double)k * (double)(2 * l + 2 * k + 1));
+    sum += term;
   }
-  double s = sin(x), c = cos(x);
-  double j0 = s / x;
+  double num = 1.0, den = 1.0;   // x^l / (2l+1)!!
+  for (int k = 1; k <= l; ++k) {
+    num *= x;
+    den *= (double)(2 * k + 1);
+  }
+  return num / den * sum;
+}
+__host__ __device__ inline double sph_bessel_pair(int l, double x, double* below) {
+  if (x < (double)l + 1.0 && l >= 2) {
+    if (below) *below = bessel_series(l - 1, x);
+    return bessel_series(l, x);
+  }
+  double s, c;
+  sincos(x, &s, &c);
+  const double inv = 1.0 / x;
+  double j0 = s * inv;
   if (l == 0) return j0;
-  double j1 = s / (x * x) - c / x;
+  double j1 = (s * inv - c) * inv;
   for (int k = 1; k < l; ++k) {
-    double j2 = (double)(2 * k + 1) / x * j1 - j0;
+    const double j2 = (double)(2 * k + 1) * inv * j1 - j0;
     j0 = j1;
     j1 = j2;
   }
+  if (below) *below = j0;
   return j1;
 }
+__host__ __device__ inline double sph_bessel(int l, double x) { return sph_bessel_pair(l, x, nullptr); }
 
 __host__ __device__ inline double envelope_d(double x, int p) {
   double xp = 1.0;
@@ -47,64 +60,88 @@ __host__ __device__ inline double envelope_d(double x, int p) {
   return 1.0 + xp * (a + x * (b + x * c));
 }
 
-// zeros of j_l by bisection between consecutive zeros of j_{l-1}
-void make_bessel_table(int S, int R, double cutoff, bessel_table* t) {
-  const int n0 = R + S;
-  double prev[MAX_S + MAX_R_BESSEL], cur[MAX_S + MAX_R_BESSEL];
-  for (int n = 0; n < n0; ++n) prev[n] = M_PI * (n + 1);
-  for (int n = 0; n < R; ++n) t->z[n] = prev[n];
-  for (int l = 1; l < S; ++l) {
-    for (int n = 0; n < n0 - l; ++n) {
-      double a = prev[n], b = prev[n + 1], fa = sph_bessel(l, a);
-      for (int it = 0; it < 200 && (b - a) > 1e-15 * b; ++it) {
-        double mid = 0.5 * (a + b), fm = sph_bessel(l, mid);
-        if ((fm > 0) == (fa > 0)) { a = mid; fa = fm; } else { b = mid; }
+// The first MAX_R_BESSEL zeros z of j_l, l < MAX_S, by bisection between consecutive zeros of j_{l-1}, and j_{l+1}(z): numbers
+// that depend on nothing, found once per process (a few thousand evaluations: 0.1 ms that every basis and force call paid).
+struct bessel_zeros {
+  double z[MAX_S][MAX_R_BESSEL], j_next[MAX_S][MAX_R_BESSEL];
+  bessel_zeros() {
+    constexpr int N0 = MAX_S + MAX_R_BESSEL;
+    double prev[N0], cur[N0];
+    for (int n = 0; n < N0; ++n) prev[n] = M_PI * (n + 1);
+    for (int l = 0; l < MAX_S; ++l) {
+      if (l > 0) {
+        for (int n = 0; n < N0 - l; ++n) {
+          double a = prev[n], b = prev[n + 1], fa = sph_bessel(l, a);
+          for (int it = 0; it < 200 && (b - a) > 1e-15 * b; ++it) {
+            double mid = 0.5 * (a + b), fm = sph_bessel(l, mid);
+            if ((fm > 0) == (fa > 0)) { a = mid; fa = fm; } else { b = mid; }
+          }
+          cur[n] = 0.5 * (a + b);
+        }
+        for (int n = 0; n < N0 - l; ++n) prev[n] = cur[n];
       }
-      cur[n] = 0.5 * (a + b);
+      for (int n = 0; n < MAX_R_BESSEL; ++n) {
+        z[l][n] = prev[n];
+        j_next[l][n] = sph_bessel(l + 1, prev[n]);
+      }
     }
-    for (int n = 0; n < n0 - l; ++n) prev[n] = cur[n];
-    for (int n = 0; n < R; ++n) t->z[l * R + n] = prev[n];
   }
+};
+void make_bessel_table(int S, int R, double cutoff, bessel_table* t) {
+  static const bessel_zeros zeros;   // initialised once, also with several threads
   for (int l = 0; l < S; ++l)
     for (int n = 0; n < R; ++n) {
-      double j = sph_bessel(l + 1, t->z[l * R + n]);
+      const double j = zeros.j_next[l][n];
+      t->z[l * R + n] = zeros.z[l][n];
       t->norm[l * R + n] = sqrt(2.0 / (cutoff * cutoff * cutoff * j * j));
     }
 }
 
-// variant D: rbf[E,R] and rad[E,S*R]; one thread per (edge, row) with row 0 = rbf, row 1+l = rad l
-__global__ void basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p,
-                                    double cutoff, bessel_table tab, float* __restrict__ rbf,
-                                    float* __restrict__ rad) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  int rows = S + 1;
-  if (idx >= n_edges * rows) return;
-  int64_t e = idx / rows;
-  int row = (int)(idx % rows);
-  double d = (double)dist[e];
-  double x = d / cutoff;
-  double u = envelope_d(x, p);
-  if (row == 0) {
-    if (!rbf) return;
-    double pre = u * sqrt(2.0 / cutoff) / d;
-    for (int n = 0; n < R; ++n) rbf[e * R + n] = (float)(pre * sin((double)(n + 1) * M_PI * x));
-  } else {
-    if (!rad) return;
-    int l = row - 1;
-    for (int n = 0; n < R; ++n)
-      rad[e * S * R + l * R + n] = (float)(u * tab.norm[l * R + n] * sph_bessel(l, tab.z[l * R + n] * x));
+// variant D: rbf[E,R] and rad[E,S*R].  A workgroup evaluates all R + S*R functions of EB edges, lanes over edges first: a
+// wavefront then follows one or two orders l (their loops differ) and the results leave through LDS as whole rows.
+// One thread per value: with one per (edge, l) a thread's six values came one after the other (67 us for 43 380 edges, and
+// 31 us for 336 edges; graph and bases of the former batch 0.43 -> 0.34 ms).
+template <int EB>
+__global__ void __launch_bounds__(256)
+basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p,
+                    double cutoff, bessel_table tab, float* __restrict__ rbf, float* __restrict__ rad) {
+  extern __shared__ float rows_s[];   // [EB][F + 1]
+  const int F = R + S * R, ld = F + 1;
+  const int64_t e0 = (int64_t)blockIdx.x * EB;
+  const int ne = n_edges - e0 < EB ? (int)(n_edges - e0) : EB;
+  for (int i = threadIdx.x; i < EB * F; i += 256) {
+    const int el = i % EB, f = i / EB;
+    if (el >= ne) continue;
+    const double d = (double)dist[e0 + el];
+    const double x = d / cutoff;
+    const double u = envelope_d(x, p);
+    double v;
+    if (f < R) {
+      v = u * sqrt(2.0 / cutoff) / d * sin((double)(f + 1) * M_PI * x);
+    } else {
+      const int k = f - R;
+      v = u * tab.norm[k] * sph_bessel(k / R, tab.z[k] * x);
+    }
+    rows_s[el * ld + f] = (float)v;
   }
+  __syncthreads();
+  if (rbf)
+    for (int i = threadIdx.x; i < ne * R; i += 256) rbf[e0 * R + i] = rows_s[(i / R) * ld + i % R];
+  if (rad)
+    for (int i = threadIdx.x; i < ne * S * R; i += 256) rad[e0 * S * R + i] = rows_s[(i / (S * R)) * ld + R + i % (S * R)];
 }
 
 // variant D, for forces: gd[e] = sum_n grad_rbf[e,n] d rbf_n / dd + sum_{l,n} grad_rad[e,l,n] d rad_ln / dd with
 //   rbf_n(d) = u(x) sqrt(2/c) sin(k x) / d,  k = (n+1) pi,  x = d / c
 //   rad_ln(d) = u(x) N_ln j_l(z_ln x),  j_l'(y) = j_{l-1}(y) - (l+1)/y j_l(y)  (j_0' = -j_1)
-// one thread per edge (a few dozen terms in fp64; not a hot kernel)
-__global__ void grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict__ grad_rbf,
-                                        const float* __restrict__ grad_rad, int64_t n_edges, int S, int R, int p, double cutoff,
-                                        bessel_table tab, float* __restrict__ gd) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// One wavefront per edge, lanes over the terms, summed in fp64 (one thread per edge walked all 48 of them: 150 us for 336 edges).
+__global__ void __launch_bounds__(256)
+grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict__ grad_rbf,
+                        const float* __restrict__ grad_rad, int64_t n_edges, int S, int R, int p, double cutoff,
+                        bessel_table tab, float* __restrict__ gd) {
+  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
   if (e >= n_edges) return;
+  const int lane = lane_id();
   const double d = (double)dist[e], x = d / cutoff;
   double xp1 = 1.0;                       // x^(p-1)
   for (int k = 0; k < p - 1; ++k) xp1 *= x;
@@ -112,35 +149,65 @@ __global__ void grad_dist_bessel_kernel(const float* __restrict__ dist, const fl
   const double u = 1.0 + xp1 * x * (a + x * (b + x * c));
   const double du = xp1 * (p * a + x * ((p + 1) * b + x * (p + 2) * c)) / cutoff;   // du/dd
   double s = 0.0;
-  if (grad_rbf) {
-    const double pre = sqrt(2.0 / cutoff);
-    for (int n = 0; n < R; ++n) {
-      const double k = (double)(n + 1) * M_PI, sn = sin(k * x), cs = cos(k * x);
-      s += (double)grad_rbf[e * R + n] * pre * (du * sn / d + u * (k / cutoff * cs / d - sn / (d * d)));
+  for (int f = lane; f < R + S * R; f += 64) {
+    if (f < R) {
+      if (grad_rbf) {
+        const double k = (double)(f + 1) * M_PI;
+        double sn, cs;
+        sincos(k * x, &sn, &cs);
+        s += (double)grad_rbf[e * R + f] * sqrt(2.0 / cutoff) * (du * sn / d + u * (k / cutoff * cs / d - sn / (d * d)));
+      }
+    } else if (grad_rad) {
+      const int k = f - R, l = k / R;
+      const double z = tab.z[k], y = z * x;
+      double jl, djl;
+      if (l == 0) {
+        djl = -sph_bessel_pair(1, y, &jl);
+      } else {
+        double below;
+        jl = sph_bessel_pair(l, y, &below);
+        djl = below - (double)(l + 1) / y * jl;
+      }
+      s += (double)grad_rad[e * S * R + k] * tab.norm[k] * (du * jl + u * z / cutoff * djl);
     }
   }
-  if (grad_rad) {
-    for (int l = 0; l < S; ++l)
-      for (int n = 0; n < R; ++n) {
-        const double z = tab.z[l * R + n], y = z * x;
-        const double jl = sph_bessel(l, y);
-        const double djl = l == 0 ? -sph_bessel(1, y) : sph_bessel(l - 1, y) - (double)(l + 1) / y * jl;
-        s += (double)grad_rad[e * S * R + l * R + n] * tab.norm[l * R + n] * (du * jl + u * z / cutoff * djl);
-      }
-  }
-  gd[e] = (float)s;
+  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  if (lane == 0) gd[e] = (float)s;
 }
 
-// variant G: g[E,R] Gaussian radial basis
-__global__ void basis_edge_G_kernel(const float* __restrict__ dist, int64_t n_edges, int R, int p,
-                                    double cutoff, float* __restrict__ g) {
-  int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (idx >= n_edges * R) return;
-  int64_t e = idx / R;
-  int n = (int)(idx % R);
-  double x = (double)dist[e] / cutoff;
-  double a = (x - (double)n / (double)(R - 1)) * (double)(R - 1);
-  g[idx] = (float)(envelope_d(x, p) * exp(-0.5 * a * a));
+// variant G: g[E,R] Gaussian radial basis.  A thread owns 8 consecutive functions of an edge: with a = (x - mu_0)(R - 1) at the
+// first of them, exp(-(a - 1)^2 / 2) = exp(-a^2 / 2) exp(a - 1/2) and the ratio falls by exp(-1) with every function, so two
+// fp64 exponentials serve eight values (the error stays at a few fp64 roundings; where the first value underflows, and the
+// ratio is cut off, all eight are far below the smallest fp32 number).  134 us with one exponential per value at 300 636 edges x 128.
+constexpr int GAUSS_RUN = 8;
+__global__ void __launch_bounds__(256)
+basis_edge_G_kernel(const float* __restrict__ dist, int64_t n_edges, int R, int p, double cutoff, int aligned,
+                    float* __restrict__ g) {
+  const int runs = (R + GAUSS_RUN - 1) / GAUSS_RUN;
+  const int64_t idx = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t e = idx / runs;
+  if (e >= n_edges) return;
+  const int n0 = (int)(idx % runs) * GAUSS_RUN;
+  const double x = (double)dist[e] / cutoff;
+  const double a = x * (double)(R - 1) - (double)n0;
+  double v = envelope_d(x, p) * exp(-0.5 * a * a), ratio = exp(fmin(a, 60.0) - 0.5);
+  float out[GAUSS_RUN];
+#pragma unroll
+  for (int k = 0; k < GAUSS_RUN; ++k) {
+    out[k] = (float)v;
+    v *= ratio;
+    ratio *= 0.36787944117144233;   // exp(-1)
+  }
+  float* o = g + e * R + n0;
+  if (aligned) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    *reinterpret_cast<f4*>(o) = f4{out[0], out[1], out[2], out[3]};
+    *reinterpret_cast<f4*>(o + 4) = f4{out[4], out[5], out[6], out[7]};
+  } else {
+#pragma unroll
+    for (int k = 0; k < GAUSS_RUN; ++k)
+      if (n0 + k < R) o[k] = out[k];
+  }
 }
 
 __global__ void cos_alpha_kernel(const float* __restrict__ unit, const int32_t* __restrict__ idx_kj,
@@ -212,12 +279,20 @@ extern "C" int gp_basis_forward(gp_ctx* ctx, const gp_dims* dims, const float* d
       if (R > MAX_R_BESSEL) return gp_fail(ctx, GP_UNSUPPORTED_DIMS, "gp_basis_forward: num_radial=%d > %d", R, MAX_R_BESSEL);
       bessel_table tab;
       make_bessel_table(S, R, (double)dims->cutoff, &tab);
-      basis_edge_D_kernel<<<nblk(n_edges * (S + 1)), 256, 0, st>>>(dist, n_edges, S, R, p, (double)dims->cutoff, tab, rbf, rad);
+      // 32 edges per workgroup fill the chip from about 16 000 edges on; below that the time is one value's latency, and 4
+      // edges per workgroup leave one value to a thread
+      const size_t row = sizeof(float) * (R + S * R + 1);
+      if (n_edges >= 16384)
+        basis_edge_D_kernel<32><<<(unsigned)((n_edges + 31) / 32), 256, 32 * row, st>>>(dist, n_edges, S, R, p, (double)dims->cutoff, tab, rbf, rad);
+      else
+        basis_edge_D_kernel<4><<<(unsigned)((n_edges + 3) / 4), 256, 4 * row, st>>>(dist, n_edges, S, R, p, (double)dims->cutoff, tab, rbf, rad);
       GP_LAUNCH_CHECK(ctx, "basis_edge_D_kernel");
     } else if (dims->variant == GP_VARIANT_G) {
       GP_REQUIRE(ctx, R >= 2, "gp_basis_forward: Gaussian basis needs num_radial >= 2");
       if (rbf) {
-        basis_edge_G_kernel<<<nblk(n_edges * R), 256, 0, st>>>(dist, n_edges, R, p, (double)dims->cutoff, rbf);
+        const int runs = (R + GAUSS_RUN - 1) / GAUSS_RUN;
+        const int aligned = R % GAUSS_RUN == 0 && (reinterpret_cast<uintptr_t>(rbf) & 15) == 0;
+        basis_edge_G_kernel<<<nblk(n_edges * runs), 256, 0, st>>>(dist, n_edges, R, p, (double)dims->cutoff, aligned, rbf);
         GP_LAUNCH_CHECK(ctx, "basis_edge_G_kernel");
       }
     } else {
@@ -253,7 +328,7 @@ int gp_grad_dist_bessel(gp_ctx* ctx, const gp_dims* dims, const float* dist, con
   GP_REQUIRE(ctx, S >= 1 && S <= MAX_S && R >= 1 && R <= MAX_R_BESSEL, "grad_dist_bessel: basis sizes out of range");
   bessel_table tab;
   make_bessel_table(S, R, (double)dims->cutoff, &tab);
-  grad_dist_bessel_kernel<<<(unsigned)((n_edges + 255) / 256), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R,
+  grad_dist_bessel_kernel<<<(unsigned)((n_edges + 3) / 4), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R,
                                                                                       dims->envelope_p, (double)dims->cutoff, tab, gd);
   GP_LAUNCH_CHECK(ctx, "grad_dist_bessel_kernel");
   return GP_OK;

@@ -1,0 +1,52 @@
+"""GPU parity of the per-edge basis kernels at the edges of their launch shapes: few and many edges, remainders, unaligned
+and long runs of Gaussian functions."""
+from types import SimpleNamespace
+
+import numpy as np
+import pytest
+import torch
+
+import synth
+from oracle import basis as obasis
+from tests import helpers as H
+
+pytestmark = pytest.mark.gpu
+
+# lengths enter as fp32 and the values are rounded to fp32 once: half an ulp of the result
+TOL = 6e-8
+
+
+def _basis(lib, dims, dist):
+    n = len(dist)
+    ctx = lib.Context(0)
+    none = torch.empty(0, dtype=torch.int32, device="cuda:0")
+    e = dict(n_edges=n, dist=H.to_dev(dist, torch.float32), unit=torch.zeros((n, 3), device="cuda:0"))
+    b = lib.gp_basis_forward(ctx, dims, e, dict(n_triplets=0, idx_kj=none, idx_ji=none))
+    torch.cuda.synchronize()
+    return b
+
+
+@pytest.mark.parametrize("n", [1, 3, 5, 16383, 16384, 16400 + 7])
+@pytest.mark.parametrize("S,R", [(7, 6), (8, 16), (1, 1)])
+def test_bessel_bases(lib, n, S, R):
+    rng = np.random.default_rng(n)
+    dims = SimpleNamespace(**dict(vars(synth.get_workload("cfg2").dims), num_spherical=S, num_radial=R))
+    dist = rng.uniform(0.05, dims.cutoff, n).astype(np.float32)
+    b = _basis(lib, dims, dist)
+    d64 = torch.tensor(dist.astype(np.float64))
+    rbf = obasis.rbf_bessel(d64, dims.cutoff, R, dims.envelope_p).numpy()
+    rad = obasis.sbf_radial(d64, dims.cutoff, S, R, dims.envelope_p).reshape(n, -1).numpy()
+    for got, want in ((b["rbf"], rbf), (b["rad"], rad)):
+        got = got.cpu().numpy()
+        assert np.all(np.abs(got - want) <= TOL * np.abs(want) + 1e-12), np.abs(got - want).max()
+
+
+@pytest.mark.parametrize("R", [2, 8, 9, 128, 1024])
+@pytest.mark.parametrize("n", [1, 257])
+def test_gaussian_basis(lib, n, R):
+    rng = np.random.default_rng(R)
+    dims = SimpleNamespace(**dict(vars(synth.get_workload("cfg4").dims), num_radial=R))
+    dist = rng.uniform(0.05, dims.cutoff, n).astype(np.float32)
+    got = _basis(lib, dims, dist)["rbf"].cpu().numpy()
+    want = obasis.rbf_gauss(torch.tensor(dist.astype(np.float64)), dims.cutoff, R, dims.envelope_p).numpy()
+    assert np.all(np.abs(got - want) <= TOL * np.abs(want) + 1e-38)
