@@ -183,6 +183,21 @@ int gp_triplets_fill_pbc(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
                          int32_t* idx_kj, int32_t* idx_ji, int32_t* seg_ptr_ji,
                          int32_t* perm_kj, int32_t* idx_ji_kj, int32_t* seg_ptr_kj);
 
+/* All lists of a graph together: what gp_triplets_count/fill, gp_edges_by_source, gp_reverse_edges and two calls of
+ * gp_csr_max_degree return, in half the launches and with one wait of the host.  offset: NULL for open boundaries, else the
+ * cell offsets of a periodic edge list.  n_atoms and n_edges positive.  _count writes seg_ptr_ji[E+1], seg_ptr_kj[E+1],
+ * out_ptr[N+1], id_swap[E] and returns the number of triplets and the largest degrees on the host; the caller allocates;
+ * _fill (same arguments, same workspace of gp_triplets_workspace bytes, the arrays that _count wrote) writes out_list[E],
+ * idx_kj[T], idx_ji[T], perm_kj[T], idx_ji_kj[T].  Meanings, orders and errors as in those calls. */
+int gp_graph_lists_count(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
+                         int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes,
+                         int32_t* seg_ptr_ji, int32_t* seg_ptr_kj, int32_t* out_ptr, int32_t* id_swap,
+                         int64_t* n_triplets /*host*/, int32_t* max_in_degree /*host*/, int32_t* max_out_degree /*host*/);
+int gp_graph_lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* offset, const int32_t* row_ptr, int64_t n_atoms,
+                        int64_t n_edges, void* ws, size_t ws_bytes, const int32_t* seg_ptr_ji, const int32_t* seg_ptr_kj,
+                        const int32_t* out_ptr, const int32_t* id_swap, int64_t n_triplets, int32_t* out_list,
+                        int32_t* idx_kj, int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj);
+
 /* Largest row length ptr[i+1] - ptr[i], i < n, of a device-resident offsets array with n+1
  * entries (e.g. the largest in-degree, for gp_graph.max_in_degree).  ws: device scratch of at
  * least 4 bytes.  Synchronises the context's stream; *max_degree is a host variable. */

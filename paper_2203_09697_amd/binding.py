@@ -28,7 +28,7 @@ EXPORTED_SYMBOLS = [
     "gp_profile_enable", "gp_profile_reset", "gp_profile_count", "gp_profile_get", "gp_set_side_stream", "gp_set_triplet_mfma", "gp_set_f32_gemm", "gp_deferred_status", "gp_measure_peaks",
     "gp_edges_workspace", "gp_edges_count", "gp_edges_fill", "gp_edges_count_pbc", "gp_edges_fill_pbc",
     "gp_triplets_count_pbc", "gp_triplets_fill_pbc",
-    "gp_triplets_workspace", "gp_triplets_count", "gp_triplets_fill", "gp_csr_max_degree", "gp_reverse_edges",
+    "gp_triplets_workspace", "gp_triplets_count", "gp_triplets_fill", "gp_graph_lists_count", "gp_graph_lists_fill", "gp_csr_max_degree", "gp_reverse_edges",
     "gp_basis_forward", "gp_block_workspace", "gp_block_forward_D", "gp_block_backward_D", "gp_block_backward_D_basis",
     "gp_block_forward_G", "gp_block_backward_G", "gp_block_G_stacks_bf16", "gp_block_forward_G_stacked", "gp_block_backward_G_stacked",
     "gp_energy_workspace", "gp_energy_forward", "gp_energy_backward",
@@ -274,16 +274,32 @@ def gp_edges(ctx, pos, graph_ptr, cutoff, max_neighbors=0, cell=None, rep=None):
 
 
 def gp_triplets(ctx, edges, with_kj=True):
-    """gp_triplets_workspace + gp_triplets_count + gp_triplets_fill on an edge dict from gp_edges."""
+    """The triplets of an edge dict from gp_edges; with_kj adds their kj-major order, the lists by centre atom and the opposite
+    edges (gp_graph_lists_count/fill; without it, or for a graph without edges, gp_triplets_count/fill)."""
     lib = load()
     N, E = edges["n_atoms"], edges["n_edges"]
     nbytes = C.c_size_t()
     ctx.check(lib.gp_triplets_workspace(C.c_int64(N), C.c_int64(E), C.byref(nbytes)))
     ws = _empty(ctx, max(nbytes.value, 8), torch.uint8)
     n_trip = C.c_int64()
-    pbc = edges.get("offset") is not None     # periodic edge list: image-aware exclusion of k = i
-    args = (ctx._h, _ptr(edges["src"]), _ptr(edges["dst"])) + ((_ptr(edges["offset"]),) if pbc else ()) + (
-        _ptr(edges["row_ptr"]), C.c_int64(N), C.c_int64(E), _ptr(ws), C.c_size_t(ws.numel()))
+    off = edges.get("offset")     # periodic edge list: image-aware exclusion of k = i
+    src, row_ptr = _ptr(edges["src"]), _ptr(edges["row_ptr"])
+    size = (C.c_int64(N), C.c_int64(E), _ptr(ws), C.c_size_t(ws.numel()))
+    if with_kj and E > 0:
+        seg_ji, seg_kj, swap, out_list, out_ptr = (_empty(ctx, n, torch.int32) for n in (E + 1, E + 1, E, E, N + 1))
+        lists = (_ptr(seg_ji), _ptr(seg_kj), _ptr(out_ptr), _ptr(swap))
+        max_in, max_out = C.c_int32(), C.c_int32()
+        ctx.check(lib.gp_graph_lists_count(ctx._h, src, _ptr(edges["dst"]), _ptr(off), row_ptr, *size, *lists, C.byref(n_trip),
+                                           C.byref(max_in), C.byref(max_out)))
+        T = n_trip.value
+        idx_kj, idx_ji, perm_kj, idx_ji_kj = (_empty(ctx, T, torch.int32) for _ in range(4))
+        ctx.check(lib.gp_graph_lists_fill(ctx._h, src, _ptr(off), row_ptr, *size, *lists, n_trip, _ptr(out_list), _ptr(idx_kj),
+                                          _ptr(idx_ji), _ptr(perm_kj), _ptr(idx_ji_kj)))
+        return dict(n_edges=E, n_triplets=T, idx_kj=idx_kj, idx_ji=idx_ji, seg_ptr_ji=seg_ji, perm_kj=perm_kj, idx_ji_kj=idx_ji_kj,
+                    seg_ptr_kj=seg_kj, n_atoms=N, row_ptr=edges["row_ptr"], out_ptr=out_ptr, out_list=out_list,
+                    max_in_degree=max_in.value, max_out_degree=max_out.value, id_swap=swap)
+    pbc = off is not None
+    args = (ctx._h, src, _ptr(edges["dst"])) + ((_ptr(off),) if pbc else ()) + (row_ptr,) + size
     ctx.check((lib.gp_triplets_count_pbc if pbc else lib.gp_triplets_count)(*args, C.byref(n_trip)))
     T = n_trip.value
     out = dict(n_edges=E, n_triplets=T, idx_kj=_empty(ctx, T, torch.int32), idx_ji=_empty(ctx, T, torch.int32),
@@ -294,16 +310,6 @@ def gp_triplets(ctx, edges, with_kj=True):
     ctx.check((lib.gp_triplets_fill_pbc if pbc else lib.gp_triplets_fill)(*args, C.c_int64(T), _ptr(out["idx_kj"]), _ptr(out["idx_ji"]),
                                    _ptr(out["seg_ptr_ji"]), _ptr(out.get("perm_kj")), _ptr(out.get("idx_ji_kj")),
                                    _ptr(out.get("seg_ptr_kj"))))
-    if with_kj and E > 0:
-        # lists by centre atom (optional members of gp_graph)
-        out_ptr, out_list = gp_edges_by_source(ctx, edges)
-        md = C.c_int32()
-        ctx.check(lib.gp_csr_max_degree(ctx._h, _ptr(edges["row_ptr"]), C.c_int64(N), _ptr(ws), C.c_size_t(ws.numel()),
-                                        C.byref(md)))
-        mo = C.c_int32()
-        ctx.check(lib.gp_csr_max_degree(ctx._h, _ptr(out_ptr), C.c_int64(N), _ptr(ws), C.c_size_t(ws.numel()), C.byref(mo)))
-        out.update(n_atoms=N, row_ptr=edges["row_ptr"], out_ptr=out_ptr, out_list=out_list, max_in_degree=md.value,
-                   max_out_degree=mo.value, id_swap=gp_reverse_edges(ctx, edges))
     return out
 
 

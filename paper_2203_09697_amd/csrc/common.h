@@ -41,6 +41,11 @@ struct gp_ctx {
   // gp_deferred_status.
   int* dflag = nullptr;       // host address
   int* dflag_dev = nullptr;   // the same word as the device sees it
+  // Results of the *_count calls: a few words of pinned host memory that kernels write (a copy and its wait cost more than the
+  // counting kernels of a small graph), and the event after which they are there.
+  int64_t* hwords = nullptr;
+  int64_t* hwords_dev = nullptr;
+  hipEvent_t count_event = nullptr;
 };
 
 // Launches the check of gp_graph.max_in_degree / max_out_degree against the lists (sets the deferred-error word).
@@ -111,6 +116,12 @@ inline int gp_fail(gp_ctx* ctx, int code, const char* fmt, ...) {
 #define GP_REQUIRE(ctx, cond, ...)                                                         \
   do {                                                                                     \
     if (!(cond)) return gp_fail((ctx), GP_BAD_ARG, __VA_ARGS__);                           \
+  } while (0)
+
+#define GP_REQUIRE_HOST_WORDS(ctx, who)                                                     \
+  do {                                                                                      \
+    if (!(ctx)->hwords_dev || !(ctx)->count_event)                                          \
+      return gp_fail((ctx), GP_HIP_ERROR, "%s: the context has no pinned host memory", who); \
   } while (0)
 
 #define GP_TRY(expr)                                                                       \

@@ -10,12 +10,12 @@ namespace {
 
 // ------------------------------------------------------------------ exclusive scan
 // One workgroup walks the array in chunks of its own size, carrying the running total.
-// in[n] (int32) -> out[n+1] (int32, exclusive prefix, out[n] = total); total64 gets the
+// in[n] (int32) -> out[n+1] (int32, exclusive prefix, out[n] = total); host_total, a word of pinned host memory, gets the
 // untruncated sum so the host can detect int32 overflow.
 constexpr int SCAN_THREADS = 1024;
 __global__ void __launch_bounds__(SCAN_THREADS)
 scan_exclusive_kernel(const int32_t* __restrict__ in, int32_t* __restrict__ out, int64_t n,
-                      int64_t* __restrict__ total64) {
+                      int64_t* __restrict__ host_total) {
   __shared__ int64_t wave_tot[SCAN_THREADS / WAVE];
   __shared__ int64_t carry_s;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -41,92 +41,9 @@ scan_exclusive_kernel(const int32_t* __restrict__ in, int32_t* __restrict__ out,
   }
   if (tid == 0) {
     out[n] = (int32_t)carry_s;
-    *total64 = carry_s;
+    *host_total = carry_s;
   }
 }
-
-// The same scan for long arrays as three launches: every workgroup sums its chunk of SCAN_CHUNK elements, one
-// workgroup scans the chunk sums, every workgroup scans its chunk again from its offset.  (The single-workgroup
-// kernel above took 0.2-0.4 ms for the 3e5 edges of the largest workload.)
-constexpr int SCAN_CHUNK = 4 * SCAN_THREADS;
-__device__ __forceinline__ int64_t block_sum_i64(int64_t v, int64_t* wave_tot) {
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, WAVE);
-  if (lane == 0) wave_tot[w] = v;
-  __syncthreads();
-  int64_t s = 0;
-  for (int k = 0; k < SCAN_THREADS / WAVE; ++k) s += wave_tot[k];
-  return s;
-}
-__global__ void __launch_bounds__(SCAN_THREADS)
-scan_chunk_sums_kernel(const int32_t* __restrict__ in, int64_t n, int64_t* __restrict__ sums) {
-  __shared__ int64_t wave_tot[SCAN_THREADS / WAVE];
-  const int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + 4 * (int64_t)threadIdx.x;
-  int64_t v = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) v += base + i < n ? (int64_t)in[base + i] : 0;
-  const int64_t s = block_sum_i64(v, wave_tot);
-  if (threadIdx.x == 0) sums[blockIdx.x] = s;
-}
-// one workgroup: sums[nb] -> exclusive offsets in place, total64 = the grand total
-__global__ void __launch_bounds__(SCAN_THREADS)
-scan_sums_kernel(int64_t* __restrict__ sums, int64_t nb, int64_t* __restrict__ total64) {
-  __shared__ int64_t wave_tot[SCAN_THREADS / WAVE];
-  __shared__ int64_t carry_s;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) carry_s = 0;
-  __syncthreads();
-  for (int64_t base = 0; base < nb; base += SCAN_THREADS) {
-    const int64_t i = base + tid;
-    const int64_t v = i < nb ? sums[i] : 0;
-    int64_t incl = v;
-#pragma unroll
-    for (int o = 1; o < WAVE; o <<= 1) {
-      const int64_t u = __shfl_up(incl, o, WAVE);
-      if (lane >= o) incl += u;
-    }
-    if (lane == WAVE - 1) wave_tot[w] = incl;
-    __syncthreads();
-    int64_t before = carry_s;
-    for (int k = 0; k < w; ++k) before += wave_tot[k];
-    if (i < nb) sums[i] = before + incl - v;
-    __syncthreads();
-    if (tid == SCAN_THREADS - 1) carry_s = before + incl;
-    __syncthreads();
-  }
-  if (tid == 0) *total64 = carry_s;
-}
-__global__ void __launch_bounds__(SCAN_THREADS)
-scan_chunk_apply_kernel(const int32_t* __restrict__ in, const int64_t* __restrict__ offs, const int64_t* __restrict__ total64,
-                        int64_t n, int32_t* __restrict__ out) {
-  __shared__ int64_t wave_tot[SCAN_THREADS / WAVE];
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int64_t base = (int64_t)blockIdx.x * SCAN_CHUNK + 4 * (int64_t)tid;
-  int64_t v[4], mine = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    v[i] = base + i < n ? (int64_t)in[base + i] : 0;
-    mine += v[i];
-  }
-  int64_t incl = mine;
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const int64_t u = __shfl_up(incl, o, WAVE);
-    if (lane >= o) incl += u;
-  }
-  if (lane == WAVE - 1) wave_tot[w] = incl;
-  __syncthreads();
-  int64_t run = offs[blockIdx.x] + incl - mine;
-  for (int k = 0; k < w; ++k) run += wave_tot[k];
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    if (base + i < n) out[base + i] = (int32_t)run;
-    run += v[i];
-  }
-  if (blockIdx.x == 0 && tid == 0) out[n] = (int32_t)*total64;
-}
-inline int64_t scan_chunks(int64_t n) { return (n + SCAN_CHUNK - 1) / SCAN_CHUNK; }
 
 // ------------------------------------------------------------------ edges
 // The distance predicate: every operation rounded once to fp32, no fused multiply-add.
@@ -179,8 +96,8 @@ template <bool FILL>
 __global__ void __launch_bounds__(256)
 edges_kernel(const float* __restrict__ pos, const int32_t* __restrict__ graph_ptr, int n_atoms,
              int n_graphs, float c2, int max_nb, images_t im, int32_t* __restrict__ deg, uint2* __restrict__ cap,
-             const int32_t* __restrict__ row_ptr, int32_t* __restrict__ src, int32_t* __restrict__ dst,
-             int32_t* __restrict__ offset, float* __restrict__ dist, float* __restrict__ unit) {
+             const int32_t* __restrict__ row_ptr, int32_t* __restrict__ row_out, int32_t* __restrict__ src,
+             int32_t* __restrict__ dst, int32_t* __restrict__ offset, float* __restrict__ dist, float* __restrict__ unit) {
   __shared__ uint32_t near_s[FILL ? 1 : 256 / WAVE][FILL ? 1 : CAP_LDS];
   const int i = blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x >> 6);
   if (i >= n_atoms) return;
@@ -274,6 +191,10 @@ edges_kernel(const float* __restrict__ pos, const int32_t* __restrict__ graph_pt
 
   const uint2 keep_below = max_nb > 0 ? cap[i] : make_uint2(0xffffffffu, 0u);
   const int row = row_ptr[i];
+  if (lane == 0) {
+    row_out[i] = row;
+    if (i == n_atoms - 1) row_out[n_atoms] = row_ptr[n_atoms];
+  }
   int total = 0;
   uint32_t ties = 0;   // candidates of exactly the last kept value so far
   for (int base = 0; base < n_cand; base += WAVE) {
@@ -331,166 +252,274 @@ __device__ __forceinline__ int find_edge(const int32_t* __restrict__ src, const 
   return lo;
 }
 
-// Per edge e = (j->i): cnt[e] = indeg(j) - [the opposite edge exists]; skip[e] = position of the opposite
-// edge (source i, negated offset: the image of k that is atom i itself) inside the in-list of j, or -1.
-// Also histograms out-degrees.
-__global__ void triplet_count_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                     const int32_t* __restrict__ off, const int32_t* __restrict__ row_ptr, int n_edges,
-                                     int32_t* __restrict__ cnt, int32_t* __restrict__ skip,
-                                     int32_t* __restrict__ out_deg) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
+// The lists of a graph.  For an edge e = (j->i) let opp(e) = id_swap[e] be the edge (i->j) with the negated cell offset, -1 if
+// the list has none.  The triplets of target edge e are the in-edges of j minus opp(e); those of source edge e' = (k->j) are
+// the out-edges of j minus opp(e').  Everything follows from opp: links_kernel finds it (and counts the out-edges of every
+// atom), lists_sums / lists_mid / lists_apply turn the segment lengths into offsets for both orders at once, out_lists_kernel
+// orders the out-edges of every atom, triplet_fill_kernel writes both orders.  (Each list used to be built by kernels of its
+// own, with the opposite edge searched three times, five scans and four waits of the host: 27 launches where this takes 8.)
+
+// id_swap[e] = opp(e); arrival[e] = how many edges of the same source came before (in the order the atomics happen to run)
+__global__ void __launch_bounds__(256)
+links_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ off,
+             const int32_t* __restrict__ row_ptr, int n_edges, int32_t* __restrict__ id_swap, int32_t* __restrict__ out_deg,
+             int32_t* __restrict__ arrival) {
+  const int e = blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= n_edges) return;
-  int j = src[e], i = dst[e];
-  int b = row_ptr[j], n = row_ptr[j + 1] - b;
-  int p = off ? find_edge(src, off, b, n, i, -off[3 * e], -off[3 * e + 1], -off[3 * e + 2])
-              : find_edge(src, nullptr, b, n, i, 0, 0, 0);
-  skip[e] = p;
-  cnt[e] = n - (p >= 0 ? 1 : 0);
-  if (out_deg) atomicAdd(&out_deg[j], 1);
+  const int j = src[e], i = dst[e];
+  const int b = row_ptr[j], n = row_ptr[j + 1] - b;
+  const int p = off ? find_edge(src, off, b, n, i, -off[3 * (int64_t)e], -off[3 * (int64_t)e + 1], -off[3 * (int64_t)e + 2])
+                    : find_edge(src, nullptr, b, n, i, 0, 0, 0);
+  id_swap[e] = p >= 0 ? b + p : -1;
+  if (out_deg) arrival[e] = atomicAdd(&out_deg[j], 1);
 }
 
-// One wavefront per target edge: its triplets are the in-edges of j minus the one from i.
+// number of triplets of edge e as the target and as the source edge
+__device__ __forceinline__ int2 triplet_counts(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
+                                               const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ id_swap,
+                                               const int32_t* __restrict__ out_deg, int64_t e) {
+  const int j = src[e], has = id_swap[e] >= 0 ? 1 : 0;
+  return make_int2(row_ptr[j + 1] - row_ptr[j] - has, out_deg[dst[e]] - has);
+}
+
+// Sum over the 4 or 16 wavefronts of a workgroup; every thread must call it.  Returns the exclusive prefix of v over the
+// threads and the total of the workgroup; lds holds one value per wavefront and is free again after the next barrier.
+template <class T>
+__device__ __forceinline__ T block_prefix(T v, T* lds, T* total) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, nw = blockDim.x >> 6;
+  T incl = v;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const T u = __shfl_up(incl, o, WAVE);
+    if (lane >= o) incl += u;
+  }
+  if (lane == WAVE - 1) lds[w] = incl;
+  __syncthreads();
+  T before = 0, all = 0;
+  for (int k = 0; k < nw; ++k) {
+    before += k < w ? lds[k] : 0;
+    all += lds[k];
+  }
+  *total = all;
+  return before + incl - v;
+}
+
+constexpr int CHUNK = 1024;   // edges per workgroup of the two edge-wide passes, 4 per thread
+inline int64_t chunks_of(int64_t n) { return (n + CHUNK - 1) / CHUNK; }
+
 __global__ void __launch_bounds__(256)
-triplet_fill_ji_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ row_ptr,
-                       const int32_t* __restrict__ seg, const int32_t* __restrict__ skip, int n_edges,
-                       int32_t* __restrict__ idx_kj, int32_t* __restrict__ idx_ji) {
-  const int e = blockIdx.x * (blockDim.x / WAVE) + (threadIdx.x >> 6);
-  if (e >= n_edges) return;
-  const int j = src[e];
-  const int b = row_ptr[j], n = row_ptr[j + 1] - b;
-  const int sk = skip[e], out = seg[e];
-  for (int r = lane_id(); r < n; r += WAVE) {
-    if (r == sk) continue;
-    int slot = out + r - ((sk >= 0 && r > sk) ? 1 : 0);
-    idx_kj[slot] = b + r;
-    idx_ji[slot] = e;
+lists_sums_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ row_ptr,
+                  const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_deg, int64_t n_edges,
+                  int64_t* __restrict__ sums /*[chunks][2]*/) {
+  __shared__ int64_t lds[2][4];
+  int64_t a = 0, b = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t e = (int64_t)blockIdx.x * CHUNK + u * 256 + threadIdx.x;
+    if (e < n_edges) {
+      const int2 c = triplet_counts(src, dst, row_ptr, id_swap, out_deg, e);
+      a += c.x;
+      b += c.y;
+    }
+  }
+  int64_t ta, tb;
+  block_prefix(a, lds[0], &ta);
+  block_prefix(b, lds[1], &tb);
+  if (threadIdx.x == 0) {
+    sums[2 * (int64_t)blockIdx.x] = ta;
+    sums[2 * (int64_t)blockIdx.x + 1] = tb;
   }
 }
 
-// Out-edge lists: first in arrival order (atomic cursor), then ordered by edge id by counting.
-__global__ void out_scatter_kernel(const int32_t* __restrict__ src, int n_edges,
-                                   const int32_t* __restrict__ out_ptr, int32_t* __restrict__ cursor,
-                                   int32_t* __restrict__ out_tmp) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n_edges) return;
-  int j = src[e];
-  out_tmp[out_ptr[j] + atomicAdd(&cursor[j], 1)] = e;
+// One workgroup: out_ptr from out_deg, the largest degrees, the work items of the kj-major fill (atom, group of KJ_ROWS
+// in-edge rows), the chunks' offsets; host (pinned memory) = {triplets, largest in-degree, largest out-degree}.
+constexpr int KJ_ROWS = 32, KJ_CHUNK = 256;
+__global__ void __launch_bounds__(1024)
+lists_mid_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_deg, int n_atoms, int64_t n_chunks,
+                 int32_t* __restrict__ out_ptr, int32_t* __restrict__ n_items, int32_t* __restrict__ item,
+                 int64_t* __restrict__ sums, int64_t* __restrict__ total, int64_t* __restrict__ host) {
+  __shared__ int32_t lds_i[2][2][16];
+  __shared__ int64_t lds_l[2][2][16];
+  __shared__ int32_t red[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int carry_out = 0, carry_item = 0, max_in = 0, max_out = 0, flip = 0;
+  for (int base = 0; base < n_atoms; base += 1024, flip ^= 1) {   // two sets of LDS words: one barrier per scan
+    const int j = base + tid;
+    const int d = j < n_atoms ? row_ptr[j + 1] - row_ptr[j] : 0, o = j < n_atoms ? out_deg[j] : 0;
+    const int v = (d + KJ_ROWS - 1) / KJ_ROWS;
+    max_in = max_in > d ? max_in : d;
+    max_out = max_out > o ? max_out : o;
+    int tot_o, tot_v;
+    const int po = carry_out + block_prefix(o, lds_i[flip][0], &tot_o);
+    const int pv = carry_item + block_prefix(v, lds_i[flip][1], &tot_v);
+    if (j < n_atoms) out_ptr[j] = po;
+    for (int k = 0; k < v; ++k) {
+      item[2 * (int64_t)(pv + k)] = j;
+      item[2 * (int64_t)(pv + k) + 1] = KJ_ROWS * k;
+    }
+    carry_out += tot_o;
+    carry_item += tot_v;
+  }
+  int64_t carry_a = 0, carry_b = 0;
+  flip = 0;
+  for (int64_t base = 0; base < n_chunks; base += 1024, flip ^= 1) {
+    const int64_t c = base + tid;
+    int64_t ta, tb;
+    const int64_t pa = carry_a + block_prefix(c < n_chunks ? sums[2 * c] : (int64_t)0, lds_l[flip][0], &ta);
+    const int64_t pb = carry_b + block_prefix(c < n_chunks ? sums[2 * c + 1] : (int64_t)0, lds_l[flip][1], &tb);
+    if (c < n_chunks) {
+      sums[2 * c] = pa;
+      sums[2 * c + 1] = pb;
+    }
+    carry_a += ta;
+    carry_b += tb;
+  }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const int u = __shfl_xor(max_in, o, 64), v = __shfl_xor(max_out, o, 64);
+    max_in = u > max_in ? u : max_in;
+    max_out = v > max_out ? v : max_out;
+  }
+  if (lane == 0) { red[0][w] = max_in; red[1][w] = max_out; }
+  __syncthreads();
+  if (tid == 0) {
+    for (int k = 1; k < 16; ++k) {
+      max_in = red[0][k] > max_in ? red[0][k] : max_in;
+      max_out = red[1][k] > max_out ? red[1][k] : max_out;
+    }
+    out_ptr[n_atoms] = carry_out;
+    n_items[0] = carry_item;
+    *total = carry_a;
+    host[0] = carry_a;
+    host[1] = max_in;
+    host[2] = max_out;
+  }
 }
 
+// seg_ji, seg_kj from the chunks' offsets; the out-edges of every atom in arrival order
 __global__ void __launch_bounds__(256)
-out_sort_kernel(const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_tmp, int n_atoms,
-                int32_t* __restrict__ out_list) {
+lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ row_ptr,
+                   const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_deg, const int32_t* __restrict__ out_ptr,
+                   const int32_t* __restrict__ arrival, int64_t n_edges, const int64_t* __restrict__ sums,
+                   const int64_t* __restrict__ total, int32_t* __restrict__ seg_ji, int32_t* __restrict__ seg_kj,
+                   int32_t* __restrict__ out_tmp) {
+  __shared__ int64_t lds[2][4];
+  const int64_t e0 = (int64_t)blockIdx.x * CHUNK + 4 * (int64_t)threadIdx.x;
+  int2 c[4];
+  int64_t a = 0, b = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    c[u] = e0 + u < n_edges ? triplet_counts(src, dst, row_ptr, id_swap, out_deg, e0 + u) : make_int2(0, 0);
+    a += c[u].x;
+    b += c[u].y;
+  }
+  int64_t ta, tb;
+  int64_t pa = sums[2 * (int64_t)blockIdx.x] + block_prefix(a, lds[0], &ta);
+  int64_t pb = sums[2 * (int64_t)blockIdx.x + 1] + block_prefix(b, lds[1], &tb);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int64_t e = e0 + u;
+    if (e < n_edges) {
+      seg_ji[e] = (int32_t)pa;
+      seg_kj[e] = (int32_t)pb;
+      out_tmp[out_ptr[src[e]] + arrival[e]] = (int32_t)e;
+    }
+    pa += c[u].x;
+    pb += c[u].y;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    seg_ji[n_edges] = (int32_t)*total;
+    seg_kj[n_edges] = (int32_t)*total;
+  }
+}
+
+// Out-edges of every atom in ascending edge id, one workgroup per atom.  With open boundaries the in-edges of j come sorted by
+// their source k and the edges j->k by k as well: where every out-edge is the opposite of an in-edge (always so without a
+// cap) the list is opp of the in-edges with the gaps closed, no sorting (74 -> 10 us for the lists of 300 on average of the
+// 1000-atom box).
+__global__ void __launch_bounds__(256)
+out_lists_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_ptr,
+                 const int32_t* __restrict__ out_tmp, int periodic, int32_t* __restrict__ out_list) {
   __shared__ int32_t lds[SORT_LDS];
-  const int j = blockIdx.x;   // one workgroup per atom
+  __shared__ int32_t cnt[2][4];
+  const int j = blockIdx.x;
   const int b = out_ptr[j], n = out_ptr[j + 1] - b;
+  const int r0 = row_ptr[j], d = row_ptr[j + 1] - r0;
+  if (!periodic) {
+    int have = 0;
+    for (int r = threadIdx.x; r < d; r += 256) have += id_swap[r0 + r] >= 0 ? 1 : 0;
+    int all;
+    block_prefix(have, cnt[0], &all);
+    if (all == n) {
+      int done = 0, flip = 1;
+      for (int base = 0; base < d; base += 256, flip ^= 1) {
+        const int e = base + (int)threadIdx.x < d ? id_swap[r0 + base + threadIdx.x] : -1;
+        int tot;
+        const int at = done + block_prefix(e >= 0 ? 1 : 0, cnt[flip], &tot);
+        if (e >= 0) out_list[b + at] = e;
+        done += tot;
+      }
+      return;
+    }
+  }
   sort_list_block(out_tmp + b, n, out_list + b, lds);
 }
 
-// Per source edge e' = (k->j): number of out-edges of j that do not end in k.
-__global__ void triplet_count_kj_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                        const int32_t* __restrict__ off, const int32_t* __restrict__ row_ptr,
-                                        const int32_t* __restrict__ out_ptr, int n_edges,
-                                        int32_t* __restrict__ cnt_kj) {
-  int e = blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n_edges) return;
-  int k = src[e], j = dst[e];
-  int b = row_ptr[k], n = row_ptr[k + 1] - b;           // in-list of k: does it contain the opposite edge ?
-  int p = off ? find_edge(src, off, b, n, j, -off[3 * e], -off[3 * e + 1], -off[3 * e + 2])
-              : find_edge(src, nullptr, b, n, j, 0, 0, 0);
-  cnt_kj[e] = out_ptr[j + 1] - out_ptr[j] - (p >= 0 ? 1 : 0);
-}
-
-// Slots of source edge e' = (k->j) in the kj-major view: the out-edges e = (j->i) of j in ascending edge id, i == k
-// dropped, each with the ji-major triplet id of (e', e).
-// The same lists per centre atom j: all in-edges e' = (k->j) walk the same out-edges of j, so a workgroup stages
-// what it needs of them (edge id, target atom, first ji-major triplet, skipped position; the cell offset of periodic
-// edges) in LDS once, 256 out-edges at a time, for the up to 32 in-edge rows it owns, instead of gathering three
-// values per triplet from memory (0.96 -> 0.3 ms for the 1e8 triplets of the largest workload).
-// Work items (atom, group of 32 in-edge rows): item[w] = {atom, first row of the group}; n_items[0] = their number.
-constexpr int KJ_ROWS = 32, KJ_CHUNK = 256;
-__global__ void __launch_bounds__(1024)
-kj_items_kernel(const int32_t* __restrict__ row_ptr, int n_atoms, int32_t* __restrict__ n_items, int32_t* __restrict__ item) {
-  __shared__ int32_t wave_tot[16];
-  __shared__ int32_t carry;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  if (tid == 0) carry = 0;
-  __syncthreads();
-  for (int base = 0; base < n_atoms; base += 1024) {
-    const int j = base + tid;
-    const int d = j < n_atoms ? row_ptr[j + 1] - row_ptr[j] : 0;
-    const int v = (d + KJ_ROWS - 1) / KJ_ROWS;
-    int incl = v;
-    for (int o = 1; o < 64; o <<= 1) {
-      const int u = __shfl_up(incl, o, 64);
-      if (lane >= o) incl += u;
-    }
-    if (lane == 63) wave_tot[w] = incl;
-    __syncthreads();
-    int before = carry;
-    for (int k = 0; k < w; ++k) before += wave_tot[k];
-    for (int k = 0; k < v; ++k) {
-      item[2 * (int64_t)(before + incl - v + k)] = j;
-      item[2 * (int64_t)(before + incl - v + k) + 1] = KJ_ROWS * k;
-    }
-    __syncthreads();
-    if (tid == 1023) carry = before + incl;
-    __syncthreads();
-  }
-  if (tid == 0) n_items[0] = carry;
-}
-
-template <bool PBC>
+// Both orders of the triplets.
+// Workgroups [0, ji_blocks): one wavefront per target edge e = (j->i), its triplets are the in-edge rows of j minus opp(e).
+// The others, ji-major order's mirror: all in-edges e' = (k->j) of an atom walk the same out-edges of j, so a workgroup stages
+// what it needs of them (edge id, first ji-major triplet, left-out row) in LDS once, KJ_CHUNK at a time, for the up to
+// KJ_ROWS in-edge rows it owns, instead of gathering three values per triplet from memory.
 __global__ void __launch_bounds__(256)
-triplet_fill_kj_atom_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ off,
-                            const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_ptr,
-                            const int32_t* __restrict__ out_list, const int32_t* __restrict__ seg_ji,
-                            const int32_t* __restrict__ skip, const int32_t* __restrict__ seg_kj,
-                            const int32_t* __restrict__ n_items, const int32_t* __restrict__ item,
-                            int32_t* __restrict__ perm_kj, int32_t* __restrict__ idx_ji_kj) {
-  if ((int)blockIdx.x >= n_items[0]) return;
-  __shared__ int32_t t_e[KJ_CHUNK], t_dst[KJ_CHUNK], t_seg[KJ_CHUNK], t_skip[KJ_CHUNK], t_off[PBC ? 3 * KJ_CHUNK : 1];
+triplet_fill_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ id_swap,
+                    const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_list,
+                    const int32_t* __restrict__ seg_ji, const int32_t* __restrict__ seg_kj, int n_edges, int ji_blocks,
+                    const int32_t* __restrict__ n_items, const int32_t* __restrict__ item, int32_t* __restrict__ idx_kj,
+                    int32_t* __restrict__ idx_ji, int32_t* __restrict__ perm_kj, int32_t* __restrict__ idx_ji_kj) {
+  __shared__ int32_t t_e[KJ_CHUNK], t_seg[KJ_CHUNK], t_skip[KJ_CHUNK];
   __shared__ int32_t tot[KJ_ROWS];
-  const int j = item[2 * (int64_t)blockIdx.x], r_lo = item[2 * (int64_t)blockIdx.x + 1];
+  const int lane = lane_id(), wave = threadIdx.x >> 6;
+  if ((int)blockIdx.x < ji_blocks) {
+    const int e = blockIdx.x * 4 + wave;
+    if (e >= n_edges) return;
+    const int j = src[e];
+    const int b = row_ptr[j], n = row_ptr[j + 1] - b;
+    const int opp = id_swap[e], sk = opp >= 0 ? opp - b : n, out = seg_ji[e];
+    for (int r = lane; r < n; r += WAVE) {
+      if (r == sk) continue;
+      const int slot = out + r - (r > sk ? 1 : 0);
+      idx_kj[slot] = b + r;
+      idx_ji[slot] = e;
+    }
+    return;
+  }
+  const int it = blockIdx.x - ji_blocks;
+  if (it >= n_items[0]) return;
+  const int j = item[2 * (int64_t)it], r_lo = item[2 * (int64_t)it + 1];
   const int r0 = row_ptr[j], d = row_ptr[j + 1] - r0;
   const int r_hi = r_lo + KJ_ROWS < d ? r_lo + KJ_ROWS : d;
   const int ob = out_ptr[j], on = out_ptr[j + 1] - ob;
-  const int lane = lane_id(), wave = threadIdx.x >> 6;
   if (threadIdx.x < KJ_ROWS) tot[threadIdx.x] = 0;
   for (int c0 = 0; c0 < on; c0 += KJ_CHUNK) {
     __syncthreads();   // the previous chunk has been consumed (and tot is initialised)
     const int n = on - c0 < KJ_CHUNK ? on - c0 : KJ_CHUNK;
     if ((int)threadIdx.x < n) {
-      const int e = out_list[ob + c0 + threadIdx.x];
+      const int e = out_list[ob + c0 + threadIdx.x], opp = id_swap[e];
       t_e[threadIdx.x] = e;
-      t_dst[threadIdx.x] = dst[e];
       t_seg[threadIdx.x] = seg_ji[e];
-      t_skip[threadIdx.x] = skip[e];
-      if (PBC) {
-        t_off[3 * threadIdx.x] = off[3 * (int64_t)e];
-        t_off[3 * threadIdx.x + 1] = off[3 * (int64_t)e + 1];
-        t_off[3 * threadIdx.x + 2] = off[3 * (int64_t)e + 2];
-      }
+      t_skip[threadIdx.x] = opp >= 0 ? opp - r0 : INT32_MAX;
     }
     __syncthreads();
     for (int r_in = r_lo + wave; r_in < r_hi; r_in += 4) {   // a row is handled by the same wavefront in every chunk
-      const int ep = r0 + r_in, k = src[ep];
-      int o0 = 0, o1 = 0, o2 = 0;
-      if (PBC) o0 = -off[3 * (int64_t)ep], o1 = -off[3 * (int64_t)ep + 1], o2 = -off[3 * (int64_t)ep + 2];
+      const int ep = r0 + r_in, opp = id_swap[ep], seg = seg_kj[ep];
       int total = tot[r_in - r_lo];
-      const int seg = seg_kj[ep];
       for (int base = 0; base < n; base += WAVE) {
         const int q = base + lane;
-        bool keep = false;
-        if (q < n) {
-          keep = t_dst[q] != k;
-          if (PBC && !keep)   // ends in atom k: excluded only if it is the opposite edge (negated offset)
-            keep = t_off[3 * q] != o0 || t_off[3 * q + 1] != o1 || t_off[3 * q + 2] != o2;
-        }
+        const bool keep = q < n && t_e[q] != opp;
         const uint64_t mask = __ballot(keep);
         if (keep) {
           const int slot = seg + total + mbcnt(mask);
-          const int sk = t_skip[q];
-          perm_kj[slot] = t_seg[q] + r_in - ((sk >= 0 && r_in > sk) ? 1 : 0);
+          perm_kj[slot] = t_seg[q] + r_in - (r_in > t_skip[q] ? 1 : 0);
           idx_ji_kj[slot] = t_e[q];
         }
         total += __popcll(mask);
@@ -503,73 +532,40 @@ triplet_fill_kj_atom_kernel(const int32_t* __restrict__ src, const int32_t* __re
 struct edges_ws {
   int32_t* deg;      // [N]
   int32_t* row_ptr;  // [N+1]
-  int64_t* total;    // [1]
   uint2* cap;        // [N] largest kept squared distance of a capped atom and how many of that value are kept
 };
 inline size_t carve_edges(void* p, int64_t n_atoms, edges_ws* w) {
   gp_carver c(p);
   w->deg = c.take<int32_t>(n_atoms);
   w->row_ptr = c.take<int32_t>(n_atoms + 1);
-  w->total = c.take<int64_t>(1);
   w->cap = c.take<uint2>(n_atoms);
   return c.off;
 }
 
 struct triplets_ws {
-  int32_t *cnt, *skip, *seg_ji, *cnt_kj, *seg_kj, *out_tmp, *out_list;  // [E] / [E+1]
-  int32_t *out_deg, *out_ptr, *cursor;                                   // [N] / [N+1]
-  int64_t* totals;                                                       // [3]
-  int64_t* scan_tmp;                                                     // chunk sums of the long scans
-  int32_t *kj_n, *kj_item;                                               // work items of the per-atom kj fill
+  int32_t *id_swap, *seg_ji, *seg_kj, *out_list, *out_ptr;   // the lists, for callers that do not take them
+  int32_t *arrival, *out_tmp, *out_deg;
+  int64_t *sums, *total;                                     // chunk sums of the two segment lengths, number of triplets
+  int32_t *n_items, *item;                                   // work items of the kj-major fill
 };
 inline size_t carve_triplets(void* p, int64_t n_atoms, int64_t n_edges, triplets_ws* w) {
   gp_carver c(p);
-  w->cnt = c.take<int32_t>(n_edges);
-  w->skip = c.take<int32_t>(n_edges);
+  w->id_swap = c.take<int32_t>(n_edges);
   w->seg_ji = c.take<int32_t>(n_edges + 1);
-  w->cnt_kj = c.take<int32_t>(n_edges);
   w->seg_kj = c.take<int32_t>(n_edges + 1);
-  w->out_tmp = c.take<int32_t>(n_edges);
   w->out_list = c.take<int32_t>(n_edges);
-  w->out_deg = c.take<int32_t>(n_atoms);
   w->out_ptr = c.take<int32_t>(n_atoms + 1);
-  w->cursor = c.take<int32_t>(n_atoms);
-  w->totals = c.take<int64_t>(3);
-  w->scan_tmp = c.take<int64_t>((size_t)scan_chunks(n_edges) + 1);
-  w->kj_n = c.take<int32_t>(4);
-  w->kj_item = c.take<int32_t>(2 * (size_t)(n_edges / KJ_ROWS + n_atoms + 1));
+  w->arrival = c.take<int32_t>(n_edges);
+  w->out_tmp = c.take<int32_t>(n_edges);
+  w->out_deg = c.take<int32_t>(n_atoms);
+  w->sums = c.take<int64_t>(2 * (size_t)chunks_of(n_edges));
+  w->total = c.take<int64_t>(1);
+  w->n_items = c.take<int32_t>(4);
+  w->item = c.take<int32_t>(2 * (size_t)(n_edges / KJ_ROWS + n_atoms + 1));
   return c.off;
 }
 
-// exclusive scan of in[n] into out[n+1] (out[n] = total, also written untruncated to total64) on the stream
-int scan_exclusive(gp_ctx* ctx, const int32_t* in, int32_t* out, int64_t n, int64_t* total64, int64_t* tmp) {
-  hipStream_t st = ctx->stream;
-  if (n <= 4 * SCAN_CHUNK || !tmp) {
-    scan_exclusive_kernel<<<1, SCAN_THREADS, 0, st>>>(in, out, n, total64);
-  } else {
-    const int64_t nb = scan_chunks(n);
-    scan_chunk_sums_kernel<<<(unsigned)nb, SCAN_THREADS, 0, st>>>(in, n, tmp);
-    scan_sums_kernel<<<1, SCAN_THREADS, 0, st>>>(tmp, nb, total64);
-    scan_chunk_apply_kernel<<<(unsigned)nb, SCAN_THREADS, 0, st>>>(in, tmp, total64, n, out);
-  }
-  GP_LAUNCH_CHECK(ctx, "scan kernels");
-  return GP_OK;
-}
-
 inline int blocks_for(int64_t n, int per_block) { return (int)((n + per_block - 1) / per_block); }
-
-// id_swap[e] = the edge dst[e] -> src[e] with the negated cell offset, found in the row of target src[e]
-__global__ void reverse_edges_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                                     const int32_t* __restrict__ off, const int32_t* __restrict__ row_ptr,
-                                     int64_t n_edges, int32_t* __restrict__ id_swap) {
-  const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e >= n_edges) return;
-  const int j = src[e], i = dst[e];
-  const int b = row_ptr[j], n = row_ptr[j + 1] - b;
-  const int p = off ? find_edge(src, off, b, n, i, -off[3 * e], -off[3 * e + 1], -off[3 * e + 2])
-                    : find_edge(src, nullptr, b, n, i, 0, 0, 0);
-  id_swap[e] = p >= 0 ? b + p : -1;
-}
 
 // largest ptr[i+1] - ptr[i]; one workgroup
 __global__ void __launch_bounds__(1024)
@@ -605,8 +601,8 @@ int gp_reverse_edges(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const 
   if (n_edges == 0) return GP_OK;
   GP_REQUIRE(ctx, src && dst && row_ptr && id_swap, "gp_reverse_edges: NULL pointer");
   GP_HIP(ctx, hipSetDevice(ctx->device));
-  reverse_edges_kernel<<<blocks_for(n_edges, 256), 256, 0, ctx->stream>>>(src, dst, offset, row_ptr, n_edges, id_swap);
-  GP_LAUNCH_CHECK(ctx, "reverse_edges_kernel");
+  links_kernel<<<blocks_for(n_edges, 256), 256, 0, ctx->stream>>>(src, dst, offset, row_ptr, (int)n_edges, id_swap, nullptr, nullptr);
+  GP_LAUNCH_CHECK(ctx, "links_kernel");
   return GP_OK;
 }
 
@@ -660,13 +656,13 @@ int edges_count_impl(gp_ctx* ctx, const char* who, const float* pos, const int32
   GP_HIP(ctx, hipSetDevice(ctx->device));
   const float c2 = cutoff * cutoff;
   edges_kernel<false><<<blocks_for(n_atoms, 4), 256, 0, ctx->stream>>>(
-      pos, graph_ptr, (int)n_atoms, n_graphs, c2, max_neighbors, im, w.deg, w.cap, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
+      pos, graph_ptr, (int)n_atoms, n_graphs, c2, max_neighbors, im, w.deg, w.cap, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
   GP_LAUNCH_CHECK(ctx, "edges_kernel<count>");
-  scan_exclusive_kernel<<<1, SCAN_THREADS, 0, ctx->stream>>>(w.deg, w.row_ptr, n_atoms, w.total);
+  GP_REQUIRE_HOST_WORDS(ctx, who);
+  scan_exclusive_kernel<<<1, SCAN_THREADS, 0, ctx->stream>>>(w.deg, w.row_ptr, n_atoms, ctx->hwords_dev);
   GP_LAUNCH_CHECK(ctx, "scan_exclusive_kernel");
-  int64_t total = 0;
-  GP_HIP(ctx, hipMemcpyAsync(&total, w.total, sizeof(total), hipMemcpyDeviceToHost, ctx->stream));
   GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  const int64_t total = *(volatile int64_t*)ctx->hwords;
   *n_edges = total;
   if (total > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld edges exceed int32", who, (long long)total);
   return GP_OK;
@@ -689,11 +685,13 @@ int edges_fill_impl(gp_ctx* ctx, const char* who, const float* pos, const int32_
   edges_ws w;
   size_t need = carve_edges(const_cast<void*>(ws), n_atoms, &w);
   if (ws_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "%s: workspace %zu < %zu", who, ws_bytes, need);
-  GP_HIP(ctx, hipMemcpyAsync(row_ptr, w.row_ptr, sizeof(int32_t) * (n_atoms + 1), hipMemcpyDeviceToDevice, ctx->stream));
-  if (n_edges == 0) return GP_OK;
+  if (n_edges == 0) {
+    GP_HIP(ctx, (hipError_t)gp_zero_async(ctx->stream, row_ptr, sizeof(int32_t) * (n_atoms + 1)));
+    return GP_OK;
+  }
   const float c2 = cutoff * cutoff;
   edges_kernel<true><<<blocks_for(n_atoms, 4), 256, 0, ctx->stream>>>(
-      pos, graph_ptr, (int)n_atoms, n_graphs, c2, max_neighbors, im, nullptr, w.cap, w.row_ptr, src, dst, offset, dist, unit);
+      pos, graph_ptr, (int)n_atoms, n_graphs, c2, max_neighbors, im, nullptr, w.cap, w.row_ptr, row_ptr, src, dst, offset, dist, unit);
   GP_LAUNCH_CHECK(ctx, "edges_kernel<fill>");
   return GP_OK;
 }
@@ -751,83 +749,91 @@ int gp_triplets_workspace(int64_t n_atoms, int64_t n_edges, size_t* bytes) {
 
 namespace {
 
+int check_lists(gp_ctx* ctx, const char* who, int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes, triplets_ws* w) {
+  GP_REQUIRE(ctx, n_atoms >= 0 && n_edges >= 0, "%s: negative size", who);
+  if (n_atoms > INT32_MAX - 1 || n_edges > INT32_MAX - 1) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: sizes exceed int32", who);
+  if (n_edges == 0 || n_atoms == 0) return GP_OK;
+  GP_REQUIRE(ctx, ws, "%s: NULL pointer", who);
+  const size_t need = carve_triplets(ws, n_atoms, n_edges, w);
+  if (ws_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "%s: workspace %zu < %zu", who, ws_bytes, need);
+  GP_HIP(ctx, hipSetDevice(ctx->device));
+  return GP_OK;
+}
+
+// lists.seg_ji, seg_kj, out_ptr, id_swap point where the results belong (the caller's arrays or the workspace's)
+int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
+                int64_t n_atoms, int64_t n_edges, const triplets_ws& w, int64_t* n_triplets, int32_t* max_in, int32_t* max_out) {
+  GP_REQUIRE_HOST_WORDS(ctx, who);
+  hipStream_t st = ctx->stream;
+  GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.out_deg, sizeof(int32_t) * n_atoms));
+  links_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.id_swap, w.out_deg, w.arrival);
+  const int64_t nc = chunks_of(n_edges);
+  lists_sums_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, w.out_deg, n_edges, w.sums);
+  lists_mid_kernel<<<1, 1024, 0, st>>>(row_ptr, w.out_deg, (int)n_atoms, nc, w.out_ptr, w.n_items, w.item, w.sums, w.total,
+                                       ctx->hwords_dev);
+  GP_LAUNCH_CHECK(ctx, "list kernels");
+  GP_HIP(ctx, hipEventRecord(ctx->count_event, st));   // the host words are there; the pass below runs while the caller allocates
+  lists_apply_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, w.out_deg, w.out_ptr, w.arrival, n_edges, w.sums,
+                                                   w.total, w.seg_ji, w.seg_kj, w.out_tmp);
+  GP_LAUNCH_CHECK(ctx, "lists_apply_kernel");
+  GP_HIP(ctx, hipEventSynchronize(ctx->count_event));
+  volatile int64_t* h = ctx->hwords;
+  *n_triplets = h[0];
+  if (max_in) *max_in = (int32_t)h[1];
+  if (max_out) *max_out = (int32_t)h[2];
+  if (*n_triplets > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld triplets exceed int32", who, (long long)*n_triplets);
+  return GP_OK;
+}
+
+int lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* row_ptr, int64_t n_atoms, int64_t n_edges, int64_t n_triplets,
+               bool periodic, const triplets_ws& w, int32_t* idx_kj, int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj) {
+  hipStream_t st = ctx->stream;
+  out_lists_kernel<<<(unsigned)n_atoms, 256, 0, st>>>(row_ptr, w.id_swap, w.out_ptr, w.out_tmp, periodic ? 1 : 0, w.out_list);
+  GP_LAUNCH_CHECK(ctx, "out_lists_kernel");
+  if (n_triplets == 0) return GP_OK;
+  const unsigned ji = (unsigned)blocks_for(n_edges, 4);
+  const unsigned kj = perm_kj ? (unsigned)(n_edges / KJ_ROWS + n_atoms) : 0u;   // an upper bound of the number of work items
+  triplet_fill_kernel<<<ji + kj, 256, 0, st>>>(src, row_ptr, w.id_swap, w.out_ptr, w.out_list, w.seg_ji, w.seg_kj, (int)n_edges,
+                                               (int)ji, w.n_items, w.item, idx_kj, idx_ji, perm_kj, idx_ji_kj);
+  GP_LAUNCH_CHECK(ctx, "triplet_fill_kernel");
+  return GP_OK;
+}
+
 int triplets_count_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
                         int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes, int64_t* n_triplets) {
   GP_REQUIRE(ctx, n_triplets, "gp_triplets_count: n_triplets is NULL");
-  GP_REQUIRE(ctx, n_atoms >= 0 && n_edges >= 0, "gp_triplets_count: negative size");
-  if (n_atoms > INT32_MAX - 1 || n_edges > INT32_MAX - 1) return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_triplets_count: sizes exceed int32");
   *n_triplets = 0;
-  if (n_edges == 0 || n_atoms == 0) return GP_OK;
-  GP_REQUIRE(ctx, src && dst && row_ptr && ws, "gp_triplets_count: NULL pointer");
   triplets_ws w;
-  size_t need = carve_triplets(ws, n_atoms, n_edges, &w);
-  if (ws_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_triplets_count: workspace %zu < %zu", ws_bytes, need);
-  GP_HIP(ctx, hipSetDevice(ctx->device));
-  hipStream_t st = ctx->stream;
-  GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.out_deg, sizeof(int32_t) * n_atoms));
-  GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.cursor, sizeof(int32_t) * n_atoms));
-  triplet_count_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.cnt, w.skip, w.out_deg);
-  GP_LAUNCH_CHECK(ctx, "triplet_count_kernel");
-  GP_TRY(scan_exclusive(ctx, w.cnt, w.seg_ji, n_edges, w.totals + 0, w.scan_tmp));
-  int64_t total = 0;
-  GP_HIP(ctx, hipMemcpyAsync(&total, w.totals, sizeof(total), hipMemcpyDeviceToHost, st));
-  GP_HIP(ctx, hipStreamSynchronize(st));
-  *n_triplets = total;
-  if (total > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_triplets_count: %lld triplets exceed int32", (long long)total);
-  return GP_OK;
+  GP_TRY(check_lists(ctx, "gp_triplets_count", n_atoms, n_edges, ws, ws_bytes, &w));
+  if (n_edges == 0 || n_atoms == 0) return GP_OK;
+  GP_REQUIRE(ctx, src && dst && row_ptr, "gp_triplets_count: NULL pointer");
+  return lists_count(ctx, "gp_triplets_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, n_triplets, nullptr, nullptr);
 }
 
 int triplets_fill_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
                        int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes, int64_t n_triplets,
                        int32_t* idx_kj, int32_t* idx_ji, int32_t* seg_ptr_ji, int32_t* perm_kj,
                        int32_t* idx_ji_kj, int32_t* seg_ptr_kj) {
-  GP_REQUIRE(ctx, n_atoms >= 0 && n_edges >= 0 && n_triplets >= 0, "gp_triplets_fill: negative size");
-  if (n_atoms > INT32_MAX - 1 || n_edges > INT32_MAX - 1 || n_triplets > INT32_MAX)
-    return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_triplets_fill: sizes exceed int32");
+  GP_REQUIRE(ctx, n_triplets >= 0, "gp_triplets_fill: negative size");
+  if (n_triplets > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_triplets_fill: sizes exceed int32");
   GP_REQUIRE(ctx, seg_ptr_ji, "gp_triplets_fill: seg_ptr_ji is NULL");
   const bool want_kj = perm_kj || idx_ji_kj || seg_ptr_kj;
   GP_REQUIRE(ctx, !want_kj || (seg_ptr_kj && (n_triplets == 0 || (perm_kj && idx_ji_kj))),
              "gp_triplets_fill: perm_kj, idx_ji_kj, seg_ptr_kj must be given together");
-  GP_HIP(ctx, hipSetDevice(ctx->device));
+  triplets_ws w;
+  GP_TRY(check_lists(ctx, "gp_triplets_fill", n_atoms, n_edges, ws, ws_bytes, &w));
   hipStream_t st = ctx->stream;
   if (n_edges == 0 || n_atoms == 0) {
+    GP_HIP(ctx, hipSetDevice(ctx->device));
     GP_HIP(ctx, (hipError_t)gp_zero_async(st, seg_ptr_ji, sizeof(int32_t) * (n_edges + 1)));
     if (seg_ptr_kj) GP_HIP(ctx, (hipError_t)gp_zero_async(st, seg_ptr_kj, sizeof(int32_t) * (n_edges + 1)));
     return GP_OK;
   }
-  GP_REQUIRE(ctx, src && dst && row_ptr && ws, "gp_triplets_fill: NULL pointer");
+  GP_REQUIRE(ctx, src && dst && row_ptr, "gp_triplets_fill: NULL pointer");
   GP_REQUIRE(ctx, n_triplets == 0 || (idx_kj && idx_ji), "gp_triplets_fill: idx_kj/idx_ji is NULL");
-  triplets_ws w;
-  size_t need = carve_triplets(ws, n_atoms, n_edges, &w);
-  if (ws_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_triplets_fill: workspace %zu < %zu", ws_bytes, need);
   GP_HIP(ctx, hipMemcpyAsync(seg_ptr_ji, w.seg_ji, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
-  if (n_triplets > 0) {
-    triplet_fill_ji_kernel<<<blocks_for(n_edges, 4), 256, 0, st>>>(src, row_ptr, w.seg_ji, w.skip, (int)n_edges, idx_kj, idx_ji);
-    GP_LAUNCH_CHECK(ctx, "triplet_fill_ji_kernel");
-  }
-  if (!want_kj) return GP_OK;
-  GP_TRY(scan_exclusive(ctx, w.out_deg, w.out_ptr, n_atoms, w.totals + 1, nullptr));
-  GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.cursor, sizeof(int32_t) * n_atoms));
-  out_scatter_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, (int)n_edges, w.out_ptr, w.cursor, w.out_tmp);
-  GP_LAUNCH_CHECK(ctx, "out_scatter_kernel");
-  out_sort_kernel<<<(unsigned)n_atoms, 256, 0, st>>>(w.out_ptr, w.out_tmp, (int)n_atoms, w.out_list);
-  GP_LAUNCH_CHECK(ctx, "out_sort_kernel");
-  triplet_count_kj_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, w.out_ptr, (int)n_edges, w.cnt_kj);
-  GP_LAUNCH_CHECK(ctx, "triplet_count_kj_kernel");
-  GP_TRY(scan_exclusive(ctx, w.cnt_kj, w.seg_kj, n_edges, w.totals + 2, w.scan_tmp));
-  GP_HIP(ctx, hipMemcpyAsync(seg_ptr_kj, w.seg_kj, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
-  if (n_triplets > 0) {
-    kj_items_kernel<<<1, 1024, 0, st>>>(row_ptr, (int)n_atoms, w.kj_n, w.kj_item);
-    const unsigned grid = (unsigned)(n_edges / KJ_ROWS + n_atoms);   // an upper bound of the number of work items
-    if (offset)
-      triplet_fill_kj_atom_kernel<true><<<grid, 256, 0, st>>>(src, dst, offset, row_ptr, w.out_ptr, w.out_list, w.seg_ji, w.skip,
-                                                              w.seg_kj, w.kj_n, w.kj_item, perm_kj, idx_ji_kj);
-    else
-      triplet_fill_kj_atom_kernel<false><<<grid, 256, 0, st>>>(src, dst, offset, row_ptr, w.out_ptr, w.out_list, w.seg_ji, w.skip,
-                                                               w.seg_kj, w.kj_n, w.kj_item, perm_kj, idx_ji_kj);
-    GP_LAUNCH_CHECK(ctx, "triplet_fill_kj_atom_kernel");
-  }
-  return GP_OK;
+  if (seg_ptr_kj) GP_HIP(ctx, hipMemcpyAsync(seg_ptr_kj, w.seg_kj, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
+  return lists_fill(ctx, src, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
 }
 
 }  // namespace
@@ -865,6 +871,38 @@ int gp_triplets_fill_pbc(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
   GP_REQUIRE(ctx, n_edges == 0 || offset, "gp_triplets_fill_pbc: offset is NULL");
   return triplets_fill_impl(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, ws, ws_bytes, n_triplets, idx_kj, idx_ji,
                             seg_ptr_ji, perm_kj, idx_ji_kj, seg_ptr_kj);
+}
+
+int gp_graph_lists_count(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
+                         int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes, int32_t* seg_ptr_ji, int32_t* seg_ptr_kj,
+                         int32_t* out_ptr, int32_t* id_swap, int64_t* n_triplets, int32_t* max_in_degree,
+                         int32_t* max_out_degree) {
+  if (!ctx) return GP_BAD_ARG;
+  GP_REQUIRE(ctx, n_triplets && max_in_degree && max_out_degree, "gp_graph_lists_count: NULL pointer");
+  GP_REQUIRE(ctx, n_atoms > 0 && n_edges > 0, "gp_graph_lists_count: empty graph");
+  GP_REQUIRE(ctx, src && dst && row_ptr && seg_ptr_ji && seg_ptr_kj && out_ptr && id_swap, "gp_graph_lists_count: NULL pointer");
+  *n_triplets = 0;
+  triplets_ws w;
+  GP_TRY(check_lists(ctx, "gp_graph_lists_count", n_atoms, n_edges, ws, ws_bytes, &w));
+  w.seg_ji = seg_ptr_ji; w.seg_kj = seg_ptr_kj; w.out_ptr = out_ptr; w.id_swap = id_swap;
+  return lists_count(ctx, "gp_graph_lists_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, n_triplets, max_in_degree,
+                     max_out_degree);
+}
+
+int gp_graph_lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* offset, const int32_t* row_ptr, int64_t n_atoms,
+                        int64_t n_edges, void* ws, size_t ws_bytes, const int32_t* seg_ptr_ji, const int32_t* seg_ptr_kj,
+                        const int32_t* out_ptr, const int32_t* id_swap, int64_t n_triplets, int32_t* out_list, int32_t* idx_kj,
+                        int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj) {
+  if (!ctx) return GP_BAD_ARG;
+  GP_REQUIRE(ctx, n_atoms > 0 && n_edges > 0 && n_triplets >= 0, "gp_graph_lists_fill: bad sizes");
+  if (n_triplets > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_graph_lists_fill: sizes exceed int32");
+  GP_REQUIRE(ctx, src && row_ptr && seg_ptr_ji && seg_ptr_kj && out_ptr && id_swap && out_list, "gp_graph_lists_fill: NULL pointer");
+  GP_REQUIRE(ctx, n_triplets == 0 || (idx_kj && idx_ji && perm_kj && idx_ji_kj), "gp_graph_lists_fill: NULL pointer");
+  triplets_ws w;
+  GP_TRY(check_lists(ctx, "gp_graph_lists_fill", n_atoms, n_edges, ws, ws_bytes, &w));
+  w.seg_ji = const_cast<int32_t*>(seg_ptr_ji); w.seg_kj = const_cast<int32_t*>(seg_ptr_kj);
+  w.out_ptr = const_cast<int32_t*>(out_ptr); w.id_swap = const_cast<int32_t*>(id_swap); w.out_list = out_list;
+  return lists_fill(ctx, src, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
 }
 
 }  // extern "C"

@@ -142,3 +142,29 @@ def test_cap_selection_edges(lib, ctx, case):
         pos, gptr = synth.cube_positions(66, 8.0, 0.9, seed=4)
         ref = _check(lib, ctx, pos, gptr, 30.0, 64)
         assert np.all(np.diff(ref["row_ptr"]) == 64)
+
+
+@pytest.mark.parametrize("n_struct,n", [(1, 3), (60, 5), (2900, 20)])   # below one chunk, a few chunks, over 1024 chunks of edges
+def test_lists_of_complete_structures(lib, ctx, n_struct, n):
+    # every atom of a structure sees every other one: all lists in closed form
+    rng = np.random.default_rng(n)
+    pos = rng.uniform(0, 3.0, (n_struct * n, 3)).astype(np.float32)
+    e, t = _gpu_graph(lib, ctx, pos, (np.arange(n_struct + 1) * n).astype(np.int32), 50.0, 0)
+    E = n_struct * n * (n - 1)
+    assert e["n_edges"] == E and t["n_triplets"] == E * (n - 2)
+    assert t["max_in_degree"] == n - 1 and t["max_out_degree"] == n - 1
+    src, dst = e["src"].cpu().numpy().astype(np.int64), e["dst"].cpu().numpy().astype(np.int64)
+    a = np.arange(n_struct * n, dtype=np.int64)
+    edge_id = lambda s, d: d * (n - 1) + s % n - (s % n > d % n)     # in-edges of d in order of their source
+    swap = edge_id(dst, src)
+    assert np.array_equal(edge_id(src, dst), np.arange(E)) and np.array_equal(t["id_swap"].cpu().numpy(), swap)
+    assert np.array_equal(t["out_list"].cpu().numpy(), np.lexsort((np.arange(E), src)))
+    assert np.array_equal(t["out_ptr"].cpu().numpy(), np.concatenate([a, [len(a)]]) * (n - 1))
+    seg = np.arange(E + 1) * (n - 2)
+    assert np.array_equal(t["seg_ptr_ji"].cpu().numpy(), seg) and np.array_equal(t["seg_ptr_kj"].cpu().numpy(), seg)
+    rows = src[:, None] * (n - 1) + np.arange(n - 1)                  # in-edges of the source, the opposite edge dropped
+    kj = rows[rows != swap[:, None]]
+    ji = np.repeat(np.arange(E), n - 2)
+    assert np.array_equal(t["idx_kj"].cpu().numpy(), kj) and np.array_equal(t["idx_ji"].cpu().numpy(), ji)
+    order = np.lexsort((ji, kj))
+    assert np.array_equal(t["perm_kj"].cpu().numpy(), order) and np.array_equal(t["idx_ji_kj"].cpu().numpy(), ji[order])
