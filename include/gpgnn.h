@@ -193,8 +193,8 @@ int gp_graph_lists_count(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
                          int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes,
                          int32_t* seg_ptr_ji, int32_t* seg_ptr_kj, int32_t* out_ptr, int32_t* id_swap,
                          int64_t* n_triplets /*host*/, int32_t* max_in_degree /*host*/, int32_t* max_out_degree /*host*/);
-int gp_graph_lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* offset, const int32_t* row_ptr, int64_t n_atoms,
-                        int64_t n_edges, void* ws, size_t ws_bytes, const int32_t* seg_ptr_ji, const int32_t* seg_ptr_kj,
+int gp_graph_lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
+                        int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes, const int32_t* seg_ptr_ji, const int32_t* seg_ptr_kj,
                         const int32_t* out_ptr, const int32_t* id_swap, int64_t n_triplets, int32_t* out_list,
                         int32_t* idx_kj, int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj);
 
@@ -287,6 +287,13 @@ typedef struct {
   const float* cos_alpha;      /* [T] ji-major           */
   const float* cos_alpha_kj;   /* [T] kj-major           */
 } gp_basis;
+
+/* gp_basis_forward (without the materialised basis) for a graph with all its lists: src and dst of its edges and every member of
+ * gp_graph but idx_kj, idx_ji_kj and perm_kj are needed.  Both orders of the cosines follow from the edges of each centre atom,
+ * so no index of a triplet is read. */
+int gp_basis_forward_graph(gp_ctx* ctx, const gp_dims* dims, const float* dist, const float* unit, const int32_t* src,
+                           const int32_t* dst, const gp_graph* graph, float* rbf, float* rad, float* cos_alpha,
+                           float* cos_alpha_kj);
 
 /* Variant D weights, fp32, W[in,out].  The same struct (non-const use) receives gradients. */
 typedef struct {

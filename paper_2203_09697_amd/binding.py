@@ -29,7 +29,7 @@ EXPORTED_SYMBOLS = [
     "gp_edges_workspace", "gp_edges_count", "gp_edges_fill", "gp_edges_count_pbc", "gp_edges_fill_pbc",
     "gp_triplets_count_pbc", "gp_triplets_fill_pbc",
     "gp_triplets_workspace", "gp_triplets_count", "gp_triplets_fill", "gp_graph_lists_count", "gp_graph_lists_fill", "gp_csr_max_degree", "gp_reverse_edges",
-    "gp_basis_forward", "gp_block_workspace", "gp_block_forward_D", "gp_block_backward_D", "gp_block_backward_D_basis",
+    "gp_basis_forward", "gp_basis_forward_graph", "gp_block_workspace", "gp_block_forward_D", "gp_block_backward_D", "gp_block_backward_D_basis",
     "gp_block_forward_G", "gp_block_backward_G", "gp_block_G_stacks_bf16", "gp_block_forward_G_stacked", "gp_block_backward_G_stacked",
     "gp_energy_workspace", "gp_energy_forward", "gp_energy_backward",
     "gp_output_workspace", "gp_output_forward", "gp_output_backward",
@@ -293,7 +293,7 @@ def gp_triplets(ctx, edges, with_kj=True):
                                            C.byref(max_in), C.byref(max_out)))
         T = n_trip.value
         idx_kj, idx_ji, perm_kj, idx_ji_kj = (_empty(ctx, T, torch.int32) for _ in range(4))
-        ctx.check(lib.gp_graph_lists_fill(ctx._h, src, _ptr(off), row_ptr, *size, *lists, n_trip, _ptr(out_list), _ptr(idx_kj),
+        ctx.check(lib.gp_graph_lists_fill(ctx._h, src, _ptr(edges["dst"]), _ptr(off), row_ptr, *size, *lists, n_trip, _ptr(out_list), _ptr(idx_kj),
                                           _ptr(idx_ji), _ptr(perm_kj), _ptr(idx_ji_kj)))
         return dict(n_edges=E, n_triplets=T, idx_kj=idx_kj, idx_ji=idx_ji, seg_ptr_ji=seg_ji, perm_kj=perm_kj, idx_ji_kj=idx_ji_kj,
                     seg_ptr_kj=seg_kj, n_atoms=N, row_ptr=edges["row_ptr"], out_ptr=out_ptr, out_list=out_list,
@@ -364,6 +364,12 @@ def gp_basis_forward(ctx, dims, edges, trip, want_sbf=False):
     if want_sbf:
         out["sbf"] = torch.empty((T, S * R), dtype=torch.float32, device=ctx.device)
     d = Dims(dims)
+    if not want_sbf and "id_swap" in trip and "cos_alpha_kj" in out and "src" in edges:   # all lists by centre atom are there
+        g = Graph(trip)
+        ctx.check(lib.gp_basis_forward_graph(ctx._h, C.byref(d), _ptr(edges["dist"]), _ptr(edges["unit"]), _ptr(edges["src"]),
+                                             _ptr(edges["dst"]), C.byref(g), _ptr(out["rbf"]), _ptr(out.get("rad")),
+                                             _ptr(out["cos_alpha"]), _ptr(out["cos_alpha_kj"])))
+        return out
     ctx.check(lib.gp_basis_forward(ctx._h, C.byref(d), _ptr(edges["dist"]), _ptr(edges["unit"]), _ptr(trip["idx_kj"]),
                                    _ptr(trip["idx_ji"]), _ptr(trip.get("perm_kj")), C.c_int64(E), C.c_int64(T),
                                    _ptr(out["rbf"]), _ptr(out.get("rad")), _ptr(out["cos_alpha"]),

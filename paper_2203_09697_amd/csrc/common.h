@@ -160,6 +160,47 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// ---- Writing the triplets of whole edges (graph.hip, basis.hip).  The triplets of an edge are the entries of a list of its
+// centre atom's edges with at most one position left out (the opposite edge).  A team of TEAM threads (a workgroup for long
+// lists, a wavefront for short ones) takes ROWS consecutive edges, mostly of one atom: it parks the atom's list in LDS, CHUNK
+// entries at a time, and then writes the edges' runs with no load in between, LANES lanes per run, 4 consecutive slots per lane
+// and store, of 5 list entries (one more past a left-out position).
+// What counts is that a run is completed before the next one is started: 1e8 slots x 2 arrays in runs of 334 take 146 us so and
+// 265 us with 8 runs of a wavefront advancing side by side (119 us is a linear fill), and that few memory round trips come
+// before the first store.
+template <bool LONG>
+struct run_team {
+  static constexpr int TEAM = LONG ? 256 : 64, ROWS = LONG ? 64 : 16, LANES = LONG ? 64 : 16, CHUNK = LONG ? 512 : 64;
+  static constexpr int TEAMS = 256 / TEAM, PAR = TEAM / LANES;   // teams of a workgroup, runs written at the same time
+};
+constexpr int LONG_LISTS = 96;   // mean number of triplets per edge from which the teams are workgroups
+typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));       // 16 bytes at any 4-byte boundary
+typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
+// slots s0 .. s0+3 of a run of cnt values: value i is c[i], or c[i+1] from position gap on
+template <class V, class T>
+__device__ __forceinline__ void store_run4(T* __restrict__ run, int s0, int cnt, int gap, const T (&c)[5]) {
+  V v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = s0 + i >= gap ? c[i + 1] : c[i];
+  if (s0 + 4 <= cnt) {
+    *reinterpret_cast<V*>(run + s0) = v;
+  } else {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      if (s0 + i < cnt) run[s0 + i] = v[i];
+  }
+}
+// LDS written by the team is visible to the team (a wavefront needs no barrier, only the order)
+template <bool LONG>
+__device__ __forceinline__ void team_sync() {
+  if (LONG) {
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // Orders the distinct values tmp[0..n) ascending into out[0..n) by rank counting, one workgroup per list: the list is
 // parked in LDS (lists longer than SORT_LDS values are read from memory instead), every thread counts, for its
 // elements, the smaller ones.  All threads of the workgroup must call it.

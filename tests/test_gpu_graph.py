@@ -168,3 +168,25 @@ def test_lists_of_complete_structures(lib, ctx, n_struct, n):
     assert np.array_equal(t["idx_kj"].cpu().numpy(), kj) and np.array_equal(t["idx_ji"].cpu().numpy(), ji)
     order = np.lexsort((ji, kj))
     assert np.array_equal(t["perm_kj"].cpu().numpy(), order) and np.array_equal(t["idx_ji_kj"].cpu().numpy(), ji[order])
+
+
+@pytest.mark.parametrize("n,cutoff,cap", [(2, 5.0, 0), (66, 3.0, 0), (99, 20.0, 0), (131, 20.0, 0), (560, 30.0, 0), (140, 6.0, 20)])
+def test_cosines_of_both_orders(lib, ctx, n, cutoff, cap):
+    # lists shorter and longer than a chunk of either team size, several atoms per team, atoms whose out-list has no opposite edge
+    from types import SimpleNamespace
+    pos, gptr = synth.cube_positions(n, (n / 0.5) ** (1 / 3), 0.3, seed=n)
+    e, t = _gpu_graph(lib, ctx, pos, gptr, cutoff, cap)
+    dims = SimpleNamespace(**dict(vars(synth.get_workload("cfg4").dims), cutoff=cutoff, num_radial=2))
+    b = lib.gp_basis_forward(ctx, dims, e, t)
+    torch.cuda.synchronize()
+    kj, ji, perm = (t[k].long() for k in ("idx_kj", "idx_ji", "perm_kj"))
+    u = e["unit"].double()
+    want = -(u[ji] * u[kj]).sum(1)
+    # three products and two sums of numbers below one in fp32: within 5 half ulps of one
+    assert t["n_triplets"] == 0 or (b["cos_alpha"].double() - want.clamp(-1, 1)).abs().max() < 3e-7
+    assert torch.equal(b["cos_alpha_kj"], b["cos_alpha"][perm])
+    # the fill of the index lists, checked against each other: every order lists every triplet once
+    assert torch.equal(t["idx_ji_kj"].long(), ji[perm])
+    key = kj[perm] * e["n_edges"] + t["idx_ji_kj"].long()
+    assert bool((key[1:] > key[:-1]).all()) and torch.equal(e["dst"].long()[kj], e["src"].long()[ji])
+    assert bool((e["src"].long()[kj] != e["dst"].long()[ji]).all())
