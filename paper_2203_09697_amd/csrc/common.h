@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <mutex>
 #include <unordered_map>
 #include <vector>
 
@@ -42,10 +43,12 @@ struct gp_ctx {
   int* dflag = nullptr;       // host address
   int* dflag_dev = nullptr;   // the same word as the device sees it
   // Results of the *_count calls: a few words of pinned host memory that kernels write (a copy and its wait cost more than the
-  // counting kernels of a small graph), and the event after which they are there.
+  // counting kernels of a small graph), and the event after which they are there.  The mutex is held from the launch that writes
+  // the words until they have been read: threads may count graphs on one context at the same time.
   int64_t* hwords = nullptr;
   int64_t* hwords_dev = nullptr;
   hipEvent_t count_event = nullptr;
+  std::mutex count_mutex;
 };
 
 // Launches the check of gp_graph.max_in_degree / max_out_degree against the lists (sets the deferred-error word).

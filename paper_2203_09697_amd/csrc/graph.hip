@@ -655,6 +655,7 @@ int edges_count_impl(gp_ctx* ctx, const char* who, const float* pos, const int32
       pos, graph_ptr, (int)n_atoms, n_graphs, c2, max_neighbors, im, w.deg, w.cap, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr);
   GP_LAUNCH_CHECK(ctx, "edges_kernel<count>");
   GP_REQUIRE_HOST_WORDS(ctx, who);
+  std::lock_guard<std::mutex> words(ctx->count_mutex);
   scan_exclusive_kernel<<<1, SCAN_THREADS, 0, ctx->stream>>>(w.deg, w.row_ptr, n_atoms, ctx->hwords_dev);
   GP_LAUNCH_CHECK(ctx, "scan_exclusive_kernel");
   GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
@@ -760,6 +761,7 @@ int check_lists(gp_ctx* ctx, const char* who, int64_t n_atoms, int64_t n_edges, 
 int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
                 int64_t n_atoms, int64_t n_edges, const triplets_ws& w, int64_t* n_triplets, int32_t* max_in, int32_t* max_out) {
   GP_REQUIRE_HOST_WORDS(ctx, who);
+  std::lock_guard<std::mutex> words(ctx->count_mutex);
   hipStream_t st = ctx->stream;
   GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.out_deg, sizeof(int32_t) * n_atoms));
   links_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.id_swap, w.out_deg, w.arrival);

@@ -190,3 +190,21 @@ def test_cosines_of_both_orders(lib, ctx, n, cutoff, cap):
     key = kj[perm] * e["n_edges"] + t["idx_ji_kj"].long()
     assert bool((key[1:] > key[:-1]).all()) and torch.equal(e["dst"].long()[kj], e["src"].long()[ji])
     assert bool((e["src"].long()[kj] != e["dst"].long()[ji]).all())
+
+
+def test_threads_count_on_one_context(lib, ctx):
+    # the counts of a graph go through words that belong to the context: every thread gets its own graph's
+    from concurrent.futures import ThreadPoolExecutor
+    sizes = [20, 33, 47, 60]
+    graphs = [tuple(H.to_dev(a, t) for a, t in zip(synth.cube_positions(n, 8.0, 0.5, seed=n), (torch.float32, torch.int32))) for n in sizes]
+
+    def counts(k):
+        e, t = lib.build_graph(ctx, *graphs[k % len(sizes)], 30.0, 0)     # every atom sees every other one
+        return e["n_edges"], t["n_triplets"], t["max_in_degree"], t["max_out_degree"]
+
+    with ThreadPoolExecutor(4) as pool:
+        got = list(pool.map(counts, range(40)))
+    torch.cuda.synchronize()
+    for k, c in enumerate(got):
+        n = sizes[k % len(sizes)]
+        assert c == (n * (n - 1), n * (n - 1) * (n - 2), n - 1, n - 1)
