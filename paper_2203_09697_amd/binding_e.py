@@ -67,6 +67,13 @@ def gp_forces_from_basis_grad_D(ctx, dims, edges, trip, out_ptr, out_list, grad_
     return forces
 
 
+def _out_lists(ctx, edges, trip):
+    """Out-edges of every atom: those that gp_triplets left with the triplets, built anew where it had no edges to list."""
+    if trip.get("out_list") is not None and trip.get("out_ptr") is not None:
+        return trip["out_ptr"], trip["out_list"]
+    return gp_edges_by_source(ctx, edges)
+
+
 class ForceModelD:
     """Variant-D block stack + energy head; energy_and_forces() runs forward, backward and the position-gradient
     assembly.  Allocation and call sequencing only."""
@@ -87,7 +94,7 @@ class ForceModelD:
                             "grad_rad": torch.empty((E, dims.num_spherical * dims.num_radial), dtype=torch.float32, device=dev),
                             "grad_cos_kj": torch.empty(max(T, 1), dtype=torch.float32, device=dev)}
         self.forces = torch.empty((N, 3), dtype=torch.float32, device=dev)
-        self.out_ptr, self.out_list = gp_edges_by_source(ctx, edges)
+        self.out_ptr, self.out_list = _out_lists(ctx, edges, trip)
         nb = C.c_size_t()
         ctx.check(B.load().gp_forces_workspace(C.c_int64(E), C.c_int64(T), C.byref(nb)))
         self.f_ws = torch.empty(max(nb.value, 8), dtype=torch.uint8, device=dev)
@@ -125,7 +132,7 @@ class ForceModelG:
         self.grad_rbf = torch.empty((E, dims.num_radial), dtype=torch.float32, device=dev)
         self.grad_cos_kj = torch.empty(T, dtype=torch.float32, device=dev)
         self.forces = torch.empty((N, 3), dtype=torch.float32, device=dev)
-        self.out_ptr, self.out_list = gp_edges_by_source(ctx, edges)
+        self.out_ptr, self.out_list = _out_lists(ctx, edges, trip)
         nb = C.c_size_t()
         ctx.check(B.load().gp_forces_workspace(C.c_int64(E), C.c_int64(T), C.byref(nb)))
         self.f_ws = torch.empty(max(nb.value, 8), dtype=torch.uint8, device=dev)
