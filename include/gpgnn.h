@@ -290,7 +290,9 @@ typedef struct {
 
 /* gp_basis_forward (without the materialised basis) for a graph with all its lists: src and dst of its edges and every member of
  * gp_graph but idx_kj, idx_ji_kj and perm_kj are needed.  Both orders of the cosines follow from the edges of each centre atom,
- * so no index of a triplet is read. */
+ * so no index of a triplet is read: the lists have to be those of the graph, complete and in the orders of the calls above.  Where
+ * triplets have been taken out of a finished graph (seg_ptr_ji and seg_ptr_kj shorter than the lists, with idx_kj and idx_ji_kj to
+ * match) a run with a changed length is read from those two arrays, and left unwritten where they are NULL. */
 int gp_basis_forward_graph(gp_ctx* ctx, const gp_dims* dims, const float* dist, const float* unit, const int32_t* src,
                            const int32_t* dst, const gp_graph* graph, float* rbf, float* rad, float* cos_alpha,
                            float* cos_alpha_kj);

@@ -351,6 +351,18 @@ def build_graph(ctx, pos, graph_ptr, cutoff, max_neighbors=0, cell=None, rep=Non
 
 
 # ------------------------------------------------------------------ basis
+def _has_lists(edges, trip):
+    """Whether edges and triplets carry everything that gp_basis_forward_graph reads, in the sizes that belong together (a dict may
+    have lost its lists by centre atom, or kept them while triplets were taken out)."""
+    E, T, get = edges["n_edges"], trip["n_triplets"], trip.get
+    row_ptr, out_ptr = get("row_ptr"), get("out_ptr")
+    for t, n in ((get("id_swap"), E), (get("out_list"), E), (get("perm_kj"), T), (get("idx_ji_kj"), T), (get("seg_ptr_kj"), E + 1),
+                 (get("seg_ptr_ji"), E + 1), (edges.get("src"), E), (edges.get("dst"), E)):
+        if t is None or t.numel() != n:
+            return False
+    return row_ptr is not None and out_ptr is not None and row_ptr.numel() == out_ptr.numel()
+
+
 def gp_basis_forward(ctx, dims, edges, trip, want_sbf=False):
     lib = load()
     E, T = edges["n_edges"], trip["n_triplets"]
@@ -364,7 +376,7 @@ def gp_basis_forward(ctx, dims, edges, trip, want_sbf=False):
     if want_sbf:
         out["sbf"] = torch.empty((T, S * R), dtype=torch.float32, device=ctx.device)
     d = Dims(dims)
-    if not want_sbf and "id_swap" in trip and "cos_alpha_kj" in out and "src" in edges:   # all lists by centre atom are there
+    if not want_sbf and _has_lists(edges, trip):
         g = Graph(trip)
         ctx.check(lib.gp_basis_forward_graph(ctx._h, C.byref(d), _ptr(edges["dist"]), _ptr(edges["unit"]), _ptr(edges["src"]),
                                              _ptr(edges["dst"]), C.byref(g), _ptr(out["rbf"]), _ptr(out.get("rad")),

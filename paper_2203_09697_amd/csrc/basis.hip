@@ -227,14 +227,17 @@ __global__ void cos_alpha_kernel(const float* __restrict__ unit, const int32_t* 
 // Both orders of the cosines of a graph with its lists by centre atom: they are the entries of the d_in x d_out matrix
 // -unit[in-edge] . unit[out-edge] of every atom, left out where the two edges are opposite.  Teams (see run_team) of in-edge rows
 // write the kj-major order from the out-edges' unit vectors in LDS, teams of consecutive positions of the out-edge lists the
-// ji-major order from the in-edges'.  Bound by the 8 bytes written per triplet: 1e8 triplets in 0.26 ms.
-// (From the index arrays, 12 bytes read per triplet, and the second order as a gathered copy of the first: 0.36 + 0.61 ms; every
-// wavefront fetching its own list: 0.33 - 0.38 ms.)
+// ji-major order from the in-edges'.  Bound by the 8 bytes written per triplet: 1e8 triplets in 0.22 ms (0.26 with the values of
+// a run's edge fetched by LDS permutes instead of of_lane's scalar reads; from the index arrays, 12 bytes read per triplet, and
+// the second order as a gathered copy of the first: 0.36 + 0.61 ms; every wavefront fetching its own list: 0.33 - 0.38 ms).
+// A run that seg_ptr gives another length than the lists do (triplets were taken out of a finished graph) follows its index array
+// other[n_triplets], the edge on the far side of every slot; no run is written past n_triplets.
 template <bool LONG, bool KJ>
 __device__ __forceinline__ void cos_runs(int block, const float* __restrict__ unit, const int32_t* __restrict__ centre,
                                          const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_ptr,
                                          const int32_t* __restrict__ out_list, const int32_t* __restrict__ id_swap,
-                                         const int32_t* __restrict__ seg_ptr, int n_edges, float* __restrict__ out) {
+                                         const int32_t* __restrict__ seg_ptr, const int32_t* __restrict__ other, int n_edges,
+                                         int n_triplets, float* __restrict__ out) {
   using R = run_team<LONG>;
   __shared__ __align__(16) float t_x[R::TEAMS][R::CHUNK + 4], t_y[R::TEAMS][R::CHUNK + 4], t_z[R::TEAMS][R::CHUNK + 4];
   __shared__ int32_t t_gap[R::TEAMS][R::ROWS];
@@ -245,6 +248,7 @@ __device__ __forceinline__ void cos_runs(int block, const float* __restrict__ un
   const int n_own = n_edges - p0 < R::ROWS ? n_edges - p0 : R::ROWS;
   // lane u holds edge u of the team
   const int pl = p0 + (lane < n_own ? lane : 0), el = KJ ? pl : out_list[pl], jl = centre[el], oppl = id_swap[el], segl = seg_ptr[el];
+  const int endl = seg_ptr[el + 1];
   const float uxl = unit[3 * (int64_t)el], uyl = unit[3 * (int64_t)el + 1], uzl = unit[3 * (int64_t)el + 2];
   for (int done = 0; done < n_own;) {
     const int atom = __builtin_amdgcn_readlane(jl, done);
@@ -268,10 +272,17 @@ __device__ __forceinline__ void cos_runs(int block, const float* __restrict__ un
       }
       team_sync<LONG>();
       for (int u = par; u < len; u += R::PAR) {
-        const int opp = __shfl(oppl, done + u, WAVE), seg = __shfl(segl, done + u, WAVE);
-        const float ux = __shfl(uxl, done + u, WAVE), uy = __shfl(uyl, done + u, WAVE), uz = __shfl(uzl, done + u, WAVE);
+        const int opp = of_lane<LONG>(oppl, done + u), seg = of_lane<LONG>(segl, done + u), stop = of_lane<LONG>(endl, done + u);
+        const float ux = of_lane<LONG>(uxl, done + u), uy = of_lane<LONG>(uyl, done + u), uz = of_lane<LONG>(uzl, done + u);
         const int gap = KJ ? t_gap[team][u] : opp >= 0 ? opp - sb : INT32_MAX;
-        const int cnt = n - (opp >= 0 ? 1 : 0), end = cnt < b0 + R::CHUNK ? cnt : b0 + R::CHUNK;
+        const int cnt = (stop < n_triplets ? stop : n_triplets) - seg, end = cnt < b0 + R::CHUNK ? cnt : b0 + R::CHUNK;
+        if (cnt != n - (opp >= 0 ? 1 : 0)) {
+          for (int t = seg + ln; b0 == 0 && other && t < seg + cnt; t += R::LANES) {
+            const float* v = unit + 3 * (int64_t)other[t];
+            out[t] = cos_of(ux, uy, uz, v[0], v[1], v[2]);
+          }
+          continue;
+        }
         for (int s0 = b0 + 4 * ln; s0 < end; s0 += 4 * R::LANES) {
           const int q = s0 - b0;
           const float4 x4 = *reinterpret_cast<const float4*>(&t_x[team][q]), y4 = *reinterpret_cast<const float4*>(&t_y[team][q]),
@@ -293,10 +304,11 @@ __global__ void __launch_bounds__(256)
 cos_graph_kernel(const float* __restrict__ unit, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                  const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_list,
                  const int32_t* __restrict__ id_swap, const int32_t* __restrict__ seg_ji, const int32_t* __restrict__ seg_kj,
-                 int n_edges, int n_blocks, float* __restrict__ cos_ji, float* __restrict__ cos_kj) {
+                 const int32_t* __restrict__ idx_kj, const int32_t* __restrict__ idx_ji_kj, int n_edges, int n_triplets,
+                 int n_blocks, float* __restrict__ cos_ji, float* __restrict__ cos_kj) {
   const int b = blockIdx.x;
-  if (b < n_blocks) cos_runs<LONG, true>(b, unit, dst, row_ptr, out_ptr, out_list, id_swap, seg_kj, n_edges, cos_kj);
-  else cos_runs<LONG, false>(b - n_blocks, unit, src, row_ptr, out_ptr, out_list, id_swap, seg_ji, n_edges, cos_ji);
+  if (b < n_blocks) cos_runs<LONG, true>(b, unit, dst, row_ptr, out_ptr, out_list, id_swap, seg_kj, idx_ji_kj, n_edges, n_triplets, cos_kj);
+  else cos_runs<LONG, false>(b - n_blocks, unit, src, row_ptr, out_ptr, out_list, id_swap, seg_ji, idx_kj, n_edges, n_triplets, cos_ji);
 }
 
 // out[q] = in[perm[q]].  For the kj-major copy of cos alpha the gathered values of neighbouring q lie a whole in-degree apart
@@ -419,8 +431,8 @@ extern "C" int gp_basis_forward_graph(gp_ctx* ctx, const gp_dims* dims, const fl
              graph->id_swap && graph->seg_ptr_ji && graph->seg_ptr_kj, "gp_basis_forward_graph: NULL pointer");
   const int blocks = (int)((E + 63) / 64);   // 64 edges per workgroup in both forms
   (T >= LONG_LISTS * E ? cos_graph_kernel<true> : cos_graph_kernel<false>)<<<2 * (unsigned)blocks, 256, 0, ctx->stream>>>(
-      unit, src, dst, graph->row_ptr, graph->out_ptr, graph->out_list, graph->id_swap, graph->seg_ptr_ji, graph->seg_ptr_kj, (int)E, blocks,
-      cos_alpha, cos_alpha_kj);
+      unit, src, dst, graph->row_ptr, graph->out_ptr, graph->out_list, graph->id_swap, graph->seg_ptr_ji, graph->seg_ptr_kj,
+      graph->idx_kj, graph->idx_ji_kj, (int)E, (int)T, blocks, cos_alpha, cos_alpha_kj);
   GP_LAUNCH_CHECK(ctx, "cos_graph_kernel");
   return GP_OK;
 }

@@ -193,6 +193,13 @@ __device__ __forceinline__ void store_run4(T* __restrict__ run, int s0, int cnt,
       if (s0 + i < cnt) run[s0 + i] = v[i];
   }
 }
+// the value of lane u of the wavefront (a run is a whole wavefront's where lists are long: u is the same in all its lanes)
+template <bool LONG>
+__device__ __forceinline__ int of_lane(int v, int u) {
+  return LONG ? __builtin_amdgcn_readlane(v, __builtin_amdgcn_readfirstlane(u)) : __shfl(v, u, WAVE);
+}
+template <bool LONG>
+__device__ __forceinline__ float of_lane(float v, int u) { return __int_as_float(of_lane<LONG>(__float_as_int(v), u)); }
 // LDS written by the team is visible to the team (a wavefront needs no barrier, only the order)
 template <bool LONG>
 __device__ __forceinline__ void team_sync() {

@@ -208,3 +208,57 @@ def test_threads_count_on_one_context(lib, ctx):
     for k, c in enumerate(got):
         n = sizes[k % len(sizes)]
         assert c == (n * (n - 1), n * (n - 1) * (n - 2), n - 1, n - 1)
+
+
+def _cosines(lib, ctx, e, t):
+    """Both orders as gp_basis_forward gives them, checked against the index arrays of t."""
+    from types import SimpleNamespace
+    dims = SimpleNamespace(**dict(vars(synth.get_workload("cfg4").dims), cutoff=50.0, num_radial=2))
+    b = lib.gp_basis_forward(ctx, dims, e, t)
+    torch.cuda.synchronize()
+    kj, ji, perm = (t[k].long() for k in ("idx_kj", "idx_ji", "perm_kj"))
+    u = e["unit"].double()
+    assert b["cos_alpha"].shape == kj.shape and b["cos_alpha_kj"].shape == kj.shape
+    # three products and two sums of numbers below one in fp32: within 5 half ulps of one
+    assert (b["cos_alpha"].double() - (-(u[ji] * u[kj]).sum(1)).clamp(-1, 1)).abs().max() < 3e-7
+    assert torch.equal(b["cos_alpha_kj"], b["cos_alpha"][perm])
+    return b
+
+
+def _without(t, drop, segments):
+    """The triplets of t without those marked; segments: also the arrays that gp_basis_forward has no use for."""
+    kj, ji = t["idx_kj"][~drop].long(), t["idx_ji"][~drop].long()
+    E = t["n_edges"]
+    perm = torch.argsort(kj * E + ji)
+    out = dict(t, n_triplets=len(kj), idx_kj=kj.int(), idx_ji=ji.int(), perm_kj=perm.int())
+    if segments:
+        ptr = lambda i: torch.cat([torch.zeros(1, dtype=torch.int64, device=i.device), torch.cumsum(torch.bincount(i, minlength=E), 0)]).int()
+        out.update(idx_ji_kj=ji[perm].int(), seg_ptr_ji=ptr(ji), seg_ptr_kj=ptr(kj))
+    return out
+
+
+@pytest.mark.parametrize("n,cap", [(140, 20), (131, 0)])   # short lists, long lists
+def test_cosines_of_triplet_dicts_without_all_lists(lib, ctx, n, cap):
+    # the lists by centre atom are optional members of a graph: without any of them the cosines follow from the index arrays
+    pos, gptr = synth.cube_positions(n, (n / 0.5) ** (1 / 3), 0.3, seed=n)
+    e, t = _gpu_graph(lib, ctx, pos, gptr, 20.0, cap)
+    want = _cosines(lib, ctx, e, t)
+    dicts = [(e, {k: v for k, v in t.items() if k not in gone}) for gone in (["out_list", "out_ptr", "row_ptr"], ["out_list"], ["id_swap"], ["seg_ptr_kj"])]
+    dicts += [(e, dict(t, id_swap=None)), (e, dict(t, out_ptr=None)), ({k: v for k, v in e.items() if k != "dst"}, t)]
+    for edges, trip in dicts:
+        got = _cosines(lib, ctx, edges, trip)
+        assert torch.equal(got["cos_alpha"], want["cos_alpha"]) and torch.equal(got["cos_alpha_kj"], want["cos_alpha_kj"])
+
+
+@pytest.mark.parametrize("n,cap", [(140, 20), (131, 0)])   # short lists, long lists
+@pytest.mark.parametrize("share", ["few", "third", "all but few", "one edge's"])
+@pytest.mark.parametrize("segments", [False, True])
+def test_cosines_after_triplets_were_taken_out(lib, ctx, n, cap, share, segments):
+    # a dict whose triplets were filtered while the lists of the graph stayed: the index arrays count
+    pos, gptr = synth.cube_positions(n, (n / 0.5) ** (1 / 3), 0.3, seed=n)
+    e, t = _gpu_graph(lib, ctx, pos, gptr, 20.0, cap)
+    T = t["n_triplets"]
+    rnd = torch.as_tensor(np.random.default_rng(n).uniform(size=T)).to("cuda:0")
+    drop = {"few": rnd < 30.0 / T, "third": rnd < 0.33, "all but few": rnd > 30.0 / T, "one edge's": t["idx_ji"] == e["n_edges"] // 2}[share]
+    assert 0 < int(drop.sum()) < T
+    _cosines(lib, ctx, e, _without(t, drop, segments))
