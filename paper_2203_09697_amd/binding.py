@@ -160,7 +160,7 @@ class Context:
             raise RuntimeError("gpgnn needs a GPU: torch.cuda.is_available() is False")
         self.device = torch.device("cuda", device_id)
         st = stream if stream is not None else torch.cuda.current_stream(self.device)
-        self.stream = st
+        self.stream, self._raw_stream = st, st.cuda_stream
         self._h = C.c_void_p()
         rc = lib.gp_create(C.byref(self._h), C.c_int(device_id), C.c_void_p(st.cuda_stream))
         if rc != 0:
@@ -169,6 +169,12 @@ class Context:
     def check(self, rc):
         if rc != 0:
             raise GpError(rc, load().gp_last_error(self._h).decode())
+
+    def settle(self):
+        """Waits for the context's stream where torch's current one is another: the allocator orders the memory of a dead workspace,
+        and a caller its first reads of the results, by the current stream."""
+        if torch._C._cuda_getCurrentRawStream(self.device.index) != self._raw_stream:
+            self.stream.synchronize()
 
     def close(self):
         if self._h:
@@ -270,6 +276,7 @@ def gp_edges(ctx, pos, graph_ptr, cutoff, max_neighbors=0, cell=None, rep=None):
     else:
         ctx.check(lib.gp_edges_fill(*args, C.c_int64(E), _ptr(out["src"]), _ptr(out["dst"]), _ptr(out["row_ptr"]),
                                     _ptr(out["dist"]), _ptr(out["unit"])))
+    ctx.settle()
     return out
 
 
@@ -295,6 +302,7 @@ def gp_triplets(ctx, edges, with_kj=True):
         idx_kj, idx_ji, perm_kj, idx_ji_kj = (_empty(ctx, T, torch.int32) for _ in range(4))
         ctx.check(lib.gp_graph_lists_fill(ctx._h, src, _ptr(edges["dst"]), _ptr(off), row_ptr, *size, *lists, n_trip, _ptr(out_list), _ptr(idx_kj),
                                           _ptr(idx_ji), _ptr(perm_kj), _ptr(idx_ji_kj)))
+        ctx.settle()
         return dict(n_edges=E, n_triplets=T, idx_kj=idx_kj, idx_ji=idx_ji, seg_ptr_ji=seg_ji, perm_kj=perm_kj, idx_ji_kj=idx_ji_kj,
                     seg_ptr_kj=seg_kj, n_atoms=N, row_ptr=edges["row_ptr"], out_ptr=out_ptr, out_list=out_list,
                     max_in_degree=max_in.value, max_out_degree=max_out.value, id_swap=swap)
@@ -310,6 +318,7 @@ def gp_triplets(ctx, edges, with_kj=True):
     ctx.check((lib.gp_triplets_fill_pbc if pbc else lib.gp_triplets_fill)(*args, C.c_int64(T), _ptr(out["idx_kj"]), _ptr(out["idx_ji"]),
                                    _ptr(out["seg_ptr_ji"]), _ptr(out.get("perm_kj")), _ptr(out.get("idx_ji_kj")),
                                    _ptr(out.get("seg_ptr_kj"))))
+    ctx.settle()
     return out
 
 

@@ -262,3 +262,26 @@ def test_cosines_after_triplets_were_taken_out(lib, ctx, n, cap, share, segments
     drop = {"few": rnd < 30.0 / T, "third": rnd < 0.33, "all but few": rnd > 30.0 / T, "one edge's": t["idx_ji"] == e["n_edges"] // 2}[share]
     assert 0 < int(drop.sum()) < T
     _cosines(lib, ctx, e, _without(t, drop, segments))
+
+
+@pytest.mark.parametrize("own", [True, False])   # the context on a stream of its own / on the default one while another is current
+@pytest.mark.parametrize("with_kj", [True, False])
+def test_graph_is_finished_on_a_stream_that_is_not_current(lib, own, with_kj):
+    # the workspaces die with the calls, and a caller on the current stream reads the lists as soon as it has them
+    other = torch.cuda.Stream()
+    c = lib.Context(0, stream=other if own else None)
+    pos, gptr = synth.cube_positions(300, (300 / 0.5) ** (1 / 3), 0.3, seed=5)
+    dpos, dptr = H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32)
+    torch.cuda.synchronize()
+    with torch.cuda.stream(torch.cuda.current_stream() if own else other):
+        e = lib.gp_edges(c, dpos, dptr, 30.0)
+        assert c.stream.query()
+        t = lib.gp_triplets(c, e, with_kj=with_kj)
+        assert c.stream.query()
+        kj, ji = t["idx_kj"].clone(), t["idx_ji"].clone()   # on the current stream
+    torch.cuda.synchronize()
+    src, dst = e["src"].cpu().numpy().astype(np.int64), e["dst"].cpu().numpy().astype(np.int64)
+    rows = src[:, None] * 299 + np.arange(299)              # every atom sees every other one
+    back = dst * 1 + src * 299 - (dst > src)
+    assert np.array_equal(kj.cpu().numpy(), rows[rows != back[:, None]])
+    assert np.array_equal(ji.cpu().numpy(), np.repeat(np.arange(300 * 299), 298))
