@@ -188,7 +188,9 @@ int gp_triplets_fill_pbc(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
  * cell offsets of a periodic edge list.  n_atoms and n_edges positive.  _count writes seg_ptr_ji[E+1], seg_ptr_kj[E+1],
  * out_ptr[N+1], id_swap[E] and returns the number of triplets and the largest degrees on the host; the caller allocates;
  * _fill (same arguments, same workspace of gp_triplets_workspace bytes, the arrays that _count wrote) writes out_list[E],
- * idx_kj[T], idx_ji[T], perm_kj[T], idx_ji_kj[T].  Meanings, orders and errors as in those calls. */
+ * idx_kj[T], idx_ji[T], perm_kj[T], idx_ji_kj[T].  Meanings, orders and errors as in those calls.  Unlike in the other _count calls
+ * only the host values are complete when _count returns GP_OK: its arrays and the workspace may still be written by work on the
+ * context's stream (GP_INT32_OVERFLOW leaves none behind). */
 int gp_graph_lists_count(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
                          int64_t n_atoms, int64_t n_edges, void* ws, size_t ws_bytes,
                          int32_t* seg_ptr_ji, int32_t* seg_ptr_kj, int32_t* out_ptr, int32_t* id_swap,

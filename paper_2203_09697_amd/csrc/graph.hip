@@ -757,9 +757,11 @@ int check_lists(gp_ctx* ctx, const char* who, int64_t n_atoms, int64_t n_edges, 
   return GP_OK;
 }
 
-// lists.seg_ji, seg_kj, out_ptr, id_swap point where the results belong (the caller's arrays or the workspace's)
+// lists.seg_ji, seg_kj, out_ptr, id_swap point where the results belong (the caller's arrays or the workspace's).  pending: the
+// last pass may still run on the context's stream when this returns GP_OK
 int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
-                int64_t n_atoms, int64_t n_edges, const triplets_ws& w, int64_t* n_triplets, int32_t* max_in, int32_t* max_out) {
+                int64_t n_atoms, int64_t n_edges, const triplets_ws& w, bool pending, int64_t* n_triplets, int32_t* max_in,
+                int32_t* max_out) {
   GP_REQUIRE_HOST_WORDS(ctx, who);
   std::lock_guard<std::mutex> words(ctx->count_mutex);
   hipStream_t st = ctx->stream;
@@ -778,6 +780,7 @@ int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t*
   *n_triplets = h[0];
   if (max_in) *max_in = (int32_t)h[1];
   if (max_out) *max_out = (int32_t)h[2];
+  if (!pending || *n_triplets > INT32_MAX) GP_HIP(ctx, hipStreamSynchronize(st));
   if (*n_triplets > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld triplets exceed int32", who, (long long)*n_triplets);
   return GP_OK;
 }
@@ -805,7 +808,7 @@ int triplets_count_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, con
   GP_TRY(check_lists(ctx, "gp_triplets_count", n_atoms, n_edges, ws, ws_bytes, &w));
   if (n_edges == 0 || n_atoms == 0) return GP_OK;
   GP_REQUIRE(ctx, src && dst && row_ptr, "gp_triplets_count: NULL pointer");
-  return lists_count(ctx, "gp_triplets_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, n_triplets, nullptr, nullptr);
+  return lists_count(ctx, "gp_triplets_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, false, n_triplets, nullptr, nullptr);
 }
 
 int triplets_fill_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
@@ -883,7 +886,7 @@ int gp_graph_lists_count(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
   triplets_ws w;
   GP_TRY(check_lists(ctx, "gp_graph_lists_count", n_atoms, n_edges, ws, ws_bytes, &w));
   w.seg_ji = seg_ptr_ji; w.seg_kj = seg_ptr_kj; w.out_ptr = out_ptr; w.id_swap = id_swap;
-  return lists_count(ctx, "gp_graph_lists_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, n_triplets, max_in_degree,
+  return lists_count(ctx, "gp_graph_lists_count", src, dst, offset, row_ptr, n_atoms, n_edges, w, true, n_triplets, max_in_degree,
                      max_out_degree);
 }
 

@@ -285,3 +285,27 @@ def test_graph_is_finished_on_a_stream_that_is_not_current(lib, own, with_kj):
     back = dst * 1 + src * 299 - (dst > src)
     assert np.array_equal(kj.cpu().numpy(), rows[rows != back[:, None]])
     assert np.array_equal(ji.cpu().numpy(), np.repeat(np.arange(300 * 299), 298))
+
+
+@pytest.mark.parametrize("n", [1000, 1300])   # below / above 2^31 triplets
+def test_no_work_is_left_behind_by_a_count(lib, n):
+    # gp_triplets_count returns with its stream idle, and so does every count that ends in an overflow: the workspace may go at once
+    import ctypes as C
+    from paper_2203_09697_amd.binding import GpError
+    c = lib.Context(0, stream=torch.cuda.Stream())
+    L = lib.load()
+    pos = np.random.default_rng(6).uniform(0.0, 10.0, (n, 3))
+    e = lib.gp_edges(c, H.to_dev(pos, torch.float32), H.to_dev(np.array([0, n]), torch.int32), 100.0)   # every atom sees every other one
+    E, T = n * (n - 1), n * (n - 1) * (n - 2)
+    assert e["n_edges"] == E
+    nb, got = C.c_size_t(), C.c_int64()
+    L.gp_triplets_workspace(C.c_int64(n), C.c_int64(E), C.byref(nb))
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda:0")
+    torch.cuda.synchronize()
+    rc = L.gp_triplets_count(c._h, *(C.c_void_p(e[k].data_ptr()) for k in ("src", "dst", "row_ptr")), C.c_int64(n), C.c_int64(E),
+                             C.c_void_p(ws.data_ptr()), C.c_size_t(nb.value), C.byref(got))
+    assert c.stream.query() and got.value == T and rc == (0 if T < 2 ** 31 else -3)
+    if rc:
+        with pytest.raises(GpError) as err:
+            lib.gp_triplets(c, e)
+        assert c.stream.query() and err.value.code == -3
