@@ -682,8 +682,8 @@ int edges_fill_impl(gp_ctx* ctx, const char* who, const float* pos, const int32_
   edges_ws w;
   size_t need = carve_edges(const_cast<void*>(ws), n_atoms, &w);
   if (ws_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "%s: workspace %zu < %zu", who, ws_bytes, need);
-  if (n_edges == 0) {
-    GP_HIP(ctx, (hipError_t)gp_zero_async(ctx->stream, row_ptr, sizeof(int32_t) * (n_atoms + 1)));
+  if (n_edges == 0) {   // nothing to write but the offsets
+    GP_HIP(ctx, hipMemcpyAsync(row_ptr, w.row_ptr, sizeof(int32_t) * (n_atoms + 1), hipMemcpyDeviceToDevice, ctx->stream));
     return GP_OK;
   }
   const float c2 = cutoff * cutoff;

@@ -309,3 +309,22 @@ def test_no_work_is_left_behind_by_a_count(lib, n):
         with pytest.raises(GpError) as err:
             lib.gp_triplets(c, e)
         assert c.stream.query() and err.value.code == -3
+
+
+def test_offsets_without_an_edge_list(lib, ctx):
+    # gp_edges_fill with n_edges = 0 writes the offsets that the count left, and nothing else
+    import ctypes as C
+    L = lib.load()
+    pos, gptr = synth.cube_positions(70, 6.0, 0.5, seed=7)
+    want = lib.gp_edges(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), 3.0)
+    dpos, dptr = H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32)
+    nb, n = C.c_size_t(), C.c_int64()
+    L.gp_edges_workspace(C.c_int64(70), C.byref(nb))
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda:0")
+    row_ptr = torch.full((71,), -1, dtype=torch.int32, device="cuda:0")
+    args = (ctx._h, C.c_void_p(dpos.data_ptr()), C.c_void_p(dptr.data_ptr()), C.c_int64(70), C.c_int32(1), C.c_float(3.0), C.c_int32(0),
+            C.c_void_p(ws.data_ptr()), C.c_size_t(nb.value))
+    ctx.check(L.gp_edges_count(*args, C.byref(n)))
+    ctx.check(L.gp_edges_fill(*args, C.c_int64(0), None, None, C.c_void_p(row_ptr.data_ptr()), None, None))
+    torch.cuda.synchronize()
+    assert n.value == want["n_edges"] > 0 and torch.equal(row_ptr, want["row_ptr"])
