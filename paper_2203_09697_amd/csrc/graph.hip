@@ -274,12 +274,12 @@ links_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, c
   if (out_deg) arrival[e] = atomicAdd(&out_deg[j], 1);
 }
 
-// number of triplets of edge e as the target and as the source edge
+// number of triplets of edge e as the target and, where the out-degrees are there, as the source edge
 __device__ __forceinline__ int2 triplet_counts(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ id_swap,
                                                const int32_t* __restrict__ out_deg, int64_t e) {
   const int j = src[e], has = id_swap[e] >= 0 ? 1 : 0;
-  return make_int2(row_ptr[j + 1] - row_ptr[j] - has, out_deg[dst[e]] - has);
+  return make_int2(row_ptr[j + 1] - row_ptr[j] - has, out_deg ? out_deg[dst[e]] - has : 0);
 }
 
 // Sum over the 4 or 16 wavefronts of a workgroup; every thread must call it.  Returns the exclusive prefix of v over the
@@ -331,8 +331,8 @@ lists_sums_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ d
   }
 }
 
-// One workgroup: out_ptr from out_deg, the largest degrees, the chunks' offsets; host (pinned memory) = {triplets, largest
-// in-degree, largest out-degree}.
+// One workgroup: out_ptr from out_deg and the largest degrees (not with n_atoms = 0), the chunks' offsets; host (pinned memory, or
+// NULL) = {triplets, largest in-degree, largest out-degree}.
 __global__ void __launch_bounds__(1024)
 lists_mid_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_deg, int n_atoms, int64_t n_chunks,
                  int32_t* __restrict__ out_ptr, int64_t* __restrict__ sums, int64_t* __restrict__ total,
@@ -381,13 +381,15 @@ lists_mid_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict_
     }
     out_ptr[n_atoms] = carry_out;
     *total = carry_a;
-    host[0] = carry_a;
-    host[1] = max_in;
-    host[2] = max_out;
+    if (host) {
+      host[0] = carry_a;
+      host[1] = max_in;
+      host[2] = max_out;
+    }
   }
 }
 
-// seg_ji, seg_kj from the chunks' offsets; the out-edges of every atom in arrival order
+// seg_ji from the chunks' offsets; with out_deg also seg_kj, and the out-edges of every atom in arrival order
 __global__ void __launch_bounds__(256)
 lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ row_ptr,
                    const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_deg, const int32_t* __restrict__ out_ptr,
@@ -412,15 +414,17 @@ lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ 
     const int64_t e = e0 + u;
     if (e < n_edges) {
       seg_ji[e] = (int32_t)pa;
-      seg_kj[e] = (int32_t)pb;
-      out_tmp[out_ptr[src[e]] + arrival[e]] = (int32_t)e;
+      if (out_deg) {
+        seg_kj[e] = (int32_t)pb;
+        out_tmp[out_ptr[src[e]] + arrival[e]] = (int32_t)e;
+      }
     }
     pa += c[u].x;
     pb += c[u].y;
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     seg_ji[n_edges] = (int32_t)*total;
-    seg_kj[n_edges] = (int32_t)*total;
+    if (out_deg) seg_kj[n_edges] = (int32_t)*total;
   }
 }
 
@@ -757,43 +761,55 @@ int check_lists(gp_ctx* ctx, const char* who, int64_t n_atoms, int64_t n_edges, 
   return GP_OK;
 }
 
-// lists.seg_ji, seg_kj, out_ptr, id_swap point where the results belong (the caller's arrays or the workspace's).  pending: the
-// last pass may still run on the context's stream when this returns GP_OK
+// Opposite edges and both segment orders with the out-edge offsets, or the ji-major order alone.  w.seg_ji, seg_kj, out_ptr, id_swap
+// point where the results belong (the caller's arrays or the workspace's).  counted is recorded once the host words are there.
+int lists_pass(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr, int64_t n_atoms,
+               int64_t n_edges, const triplets_ws& w, bool with_kj, int64_t* host_words, hipEvent_t counted) {
+  hipStream_t st = ctx->stream;
+  int32_t* out_deg = with_kj ? w.out_deg : nullptr;
+  if (with_kj) GP_HIP(ctx, (hipError_t)gp_zero_async(st, out_deg, sizeof(int32_t) * n_atoms));
+  links_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.id_swap, out_deg, w.arrival);
+  const int64_t nc = chunks_of(n_edges);
+  lists_sums_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, n_edges, w.sums);
+  lists_mid_kernel<<<1, 1024, 0, st>>>(row_ptr, out_deg, with_kj ? (int)n_atoms : 0, nc, w.out_ptr, w.sums, w.total, host_words);
+  GP_LAUNCH_CHECK(ctx, "list kernels");
+  if (counted) GP_HIP(ctx, hipEventRecord(counted, st));
+  lists_apply_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, w.out_ptr, w.arrival, n_edges, w.sums,
+                                                   w.total, w.seg_ji, w.seg_kj, w.out_tmp);
+  GP_LAUNCH_CHECK(ctx, "lists_apply_kernel");
+  return GP_OK;
+}
+
+// with_kj: the counts are waited for alone, and the last pass runs while the caller allocates; without it, and after an overflow,
+// the stream is idle on return
 int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr,
-                int64_t n_atoms, int64_t n_edges, const triplets_ws& w, bool pending, int64_t* n_triplets, int32_t* max_in,
+                int64_t n_atoms, int64_t n_edges, const triplets_ws& w, bool with_kj, int64_t* n_triplets, int32_t* max_in,
                 int32_t* max_out) {
   GP_REQUIRE_HOST_WORDS(ctx, who);
   std::lock_guard<std::mutex> words(ctx->count_mutex);
-  hipStream_t st = ctx->stream;
-  GP_HIP(ctx, (hipError_t)gp_zero_async(st, w.out_deg, sizeof(int32_t) * n_atoms));
-  links_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.id_swap, w.out_deg, w.arrival);
-  const int64_t nc = chunks_of(n_edges);
-  lists_sums_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, w.out_deg, n_edges, w.sums);
-  lists_mid_kernel<<<1, 1024, 0, st>>>(row_ptr, w.out_deg, (int)n_atoms, nc, w.out_ptr, w.sums, w.total, ctx->hwords_dev);
-  GP_LAUNCH_CHECK(ctx, "list kernels");
-  GP_HIP(ctx, hipEventRecord(ctx->count_event, st));   // the host words are there; the pass below runs while the caller allocates
-  lists_apply_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, w.out_deg, w.out_ptr, w.arrival, n_edges, w.sums,
-                                                   w.total, w.seg_ji, w.seg_kj, w.out_tmp);
-  GP_LAUNCH_CHECK(ctx, "lists_apply_kernel");
-  GP_HIP(ctx, hipEventSynchronize(ctx->count_event));
+  GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, with_kj, ctx->hwords_dev, with_kj ? ctx->count_event : nullptr));
+  GP_HIP(ctx, with_kj ? hipEventSynchronize(ctx->count_event) : hipStreamSynchronize(ctx->stream));
   volatile int64_t* h = ctx->hwords;
   *n_triplets = h[0];
   if (max_in) *max_in = (int32_t)h[1];
   if (max_out) *max_out = (int32_t)h[2];
-  if (!pending || *n_triplets > INT32_MAX) GP_HIP(ctx, hipStreamSynchronize(st));
-  if (*n_triplets > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld triplets exceed int32", who, (long long)*n_triplets);
-  return GP_OK;
+  if (*n_triplets <= INT32_MAX) return GP_OK;
+  GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld triplets exceed int32", who, (long long)*n_triplets);
 }
 
+// with_kj: the out-edges in order and both orders of the triplets, else the ji-major one alone
 int lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* row_ptr, int64_t n_atoms, int64_t n_edges, int64_t n_triplets,
-               bool periodic, const triplets_ws& w, int32_t* idx_kj, int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj) {
+               bool periodic, bool with_kj, const triplets_ws& w, int32_t* idx_kj, int32_t* idx_ji, int32_t* perm_kj, int32_t* idx_ji_kj) {
   hipStream_t st = ctx->stream;
-  out_lists_kernel<<<(unsigned)n_atoms, 256, 0, st>>>(row_ptr, w.id_swap, w.out_ptr, w.out_tmp, periodic ? 1 : 0, w.out_list);
-  GP_LAUNCH_CHECK(ctx, "out_lists_kernel");
+  if (with_kj) {
+    out_lists_kernel<<<(unsigned)n_atoms, 256, 0, st>>>(row_ptr, w.id_swap, w.out_ptr, w.out_tmp, periodic ? 1 : 0, w.out_list);
+    GP_LAUNCH_CHECK(ctx, "out_lists_kernel");
+  }
   if (n_triplets == 0) return GP_OK;
   const bool wide = n_triplets >= LONG_LISTS * n_edges;
   const int ji = blocks_for(n_edges, wide ? 4 : 16);
-  const int kj = perm_kj ? blocks_for(n_edges, 64) : 0;   // 64 rows per workgroup in both forms
+  const int kj = with_kj ? blocks_for(n_edges, 64) : 0;   // 64 rows per workgroup in both forms
   (wide ? triplet_fill_kernel<true> : triplet_fill_kernel<false>)<<<(unsigned)(ji + kj), 256, 0, st>>>(
       src, dst, row_ptr, w.id_swap, w.out_ptr, w.out_list, w.seg_ji, w.seg_kj, (int)n_edges, ji, idx_kj, idx_ji, perm_kj, idx_ji_kj);
   GP_LAUNCH_CHECK(ctx, "triplet_fill_kernel");
@@ -832,9 +848,13 @@ int triplets_fill_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, cons
   }
   GP_REQUIRE(ctx, src && dst && row_ptr, "gp_triplets_fill: NULL pointer");
   GP_REQUIRE(ctx, n_triplets == 0 || (idx_kj && idx_ji), "gp_triplets_fill: idx_kj/idx_ji is NULL");
-  GP_HIP(ctx, hipMemcpyAsync(seg_ptr_ji, w.seg_ji, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
-  if (seg_ptr_kj) GP_HIP(ctx, hipMemcpyAsync(seg_ptr_kj, w.seg_kj, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
-  return lists_fill(ctx, src, dst, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
+  if (want_kj) {
+    w.seg_ji = seg_ptr_ji; w.seg_kj = seg_ptr_kj;
+    GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, true, nullptr, nullptr));
+  } else {
+    GP_HIP(ctx, hipMemcpyAsync(seg_ptr_ji, w.seg_ji, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
+  }
+  return lists_fill(ctx, src, dst, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, want_kj, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
 }
 
 }  // namespace
@@ -903,7 +923,7 @@ int gp_graph_lists_fill(gp_ctx* ctx, const int32_t* src, const int32_t* dst, con
   GP_TRY(check_lists(ctx, "gp_graph_lists_fill", n_atoms, n_edges, ws, ws_bytes, &w));
   w.seg_ji = const_cast<int32_t*>(seg_ptr_ji); w.seg_kj = const_cast<int32_t*>(seg_ptr_kj);
   w.out_ptr = const_cast<int32_t*>(out_ptr); w.id_swap = const_cast<int32_t*>(id_swap); w.out_list = out_list;
-  return lists_fill(ctx, src, dst, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
+  return lists_fill(ctx, src, dst, row_ptr, n_atoms, n_edges, n_triplets, offset != nullptr, true, w, idx_kj, idx_ji, perm_kj, idx_ji_kj);
 }
 
 }  // extern "C"

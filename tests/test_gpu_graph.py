@@ -4,6 +4,7 @@ import pytest
 import torch
 
 import synth
+from oracle import graph as ograph
 from tests import helpers as H
 
 pytestmark = pytest.mark.gpu
@@ -328,3 +329,76 @@ def test_offsets_without_an_edge_list(lib, ctx):
     ctx.check(L.gp_edges_fill(*args, C.c_int64(0), None, None, C.c_void_p(row_ptr.data_ptr()), None, None))
     torch.cuda.synchronize()
     assert n.value == want["n_edges"] > 0 and torch.equal(row_ptr, want["row_ptr"])
+
+
+# short lists with missing opposites / long lists with missing opposites / periodic ones, short and long
+LIST_CASES = {"capped": dict(n=140, cutoff=6.0, cap=20), "capped, long": dict(n=420, cutoff=30.0, cap=150), "open, long": dict(n=131, cutoff=20.0, cap=0),
+              "periodic, capped": dict(n=40, cutoff=5.0, cap=30, rep=(1, 1, 0)), "periodic, long": dict(n=60, cutoff=4.5, cap=0, rep=(1, 1, 1)),
+              "no triplets": dict(n=2, cutoff=20.0, cap=0)}
+
+
+def _list_case(lib, ctx, name):
+    """edges of the case and its lists as the oracle gives them"""
+    c = LIST_CASES[name]
+    side = (c["n"] / 0.5) ** (1 / 3)
+    pos, gptr = synth.cube_positions(c["n"], side, 0.3, seed=c["n"])
+    if "rep" in c:
+        cells = (side * np.array([[[1.0, 0.1, 0.0], [0.0, 1.0, -0.1], [0.0, 0.0, 1.0]]])).astype(np.float32)
+        s, d, o, rp = ograph.edges_pbc(pos, gptr, cells, c["cutoff"], c["rep"], c["cap"])
+        e = lib.gp_edges(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), c["cutoff"], c["cap"], H.to_dev(cells, torch.float32), c["rep"])
+    else:
+        o = None
+        s, d, rp = ograph.edges(pos, gptr, c["cutoff"], c["cap"])
+        e = lib.gp_edges(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), c["cutoff"], c["cap"])
+    kj, ji, seg = ograph.triplets(s, d, rp) if o is None else ograph.triplets(s, d, rp, o)
+    swap = ograph.reverse_edges(s, d) if o is None else ograph.reverse_edges(s, d, o)
+    order = np.lexsort((ji, kj))
+    count = lambda i, n: np.concatenate([[0], np.cumsum(np.bincount(i, minlength=n))])
+    want = dict(idx_kj=kj, idx_ji=ji, seg_ptr_ji=seg, perm_kj=order, idx_ji_kj=np.asarray(ji)[order], seg_ptr_kj=count(kj, len(s)),
+                id_swap=swap, out_ptr=count(s, c["n"]), out_list=np.lexsort((np.arange(len(s)), s)))
+    assert np.array_equal(e["src"].cpu().numpy(), s) and np.array_equal(e["dst"].cpu().numpy(), d)
+    if "long" in name:
+        assert len(kj) >= 96 * len(s)
+    if "capped" in name:
+        assert (np.asarray(swap) < 0).any() and (np.diff(want["out_ptr"]) != np.diff(rp)).any()
+    return e, want
+
+
+@pytest.mark.parametrize("name", list(LIST_CASES))
+def test_lists_of_every_entry_point(lib, ctx, name):
+    # gp_graph_lists_count/fill, gp_triplets_count/fill (with and without the kj-major order, twice on one workspace),
+    # gp_reverse_edges, gp_edges_by_source and gp_csr_max_degree against the oracle
+    import ctypes as C
+    from paper_2203_09697_amd import binding as B
+    L = lib.load()
+    e, want = _list_case(lib, ctx, name)
+    N, E, T = e["n_atoms"], e["n_edges"], len(want["idx_kj"])
+    t = lib.gp_triplets(ctx, e)
+    _cosines(lib, ctx, e, t) if T else None
+    got = [t, lib.gp_triplets(ctx, e, with_kj=False), dict(id_swap=lib.gp_reverse_edges(ctx, e)),
+           dict(zip(("out_ptr", "out_list"), lib.gp_edges_by_source(ctx, e)))]
+    off = e.get("offset")
+    nb, n = C.c_size_t(), C.c_int64()
+    L.gp_triplets_workspace(C.c_int64(N), C.c_int64(E), C.byref(nb))
+    ws = torch.empty(nb.value, dtype=torch.uint8, device="cuda:0")
+    args = (ctx._h, B._ptr(e["src"]), B._ptr(e["dst"])) + ((B._ptr(off),) if off is not None else ()) + (
+        B._ptr(e["row_ptr"]), C.c_int64(N), C.c_int64(E), B._ptr(ws), C.c_size_t(nb.value))
+    count, fill = (L.gp_triplets_count, L.gp_triplets_fill) if off is None else (L.gp_triplets_count_pbc, L.gp_triplets_fill_pbc)
+    ctx.check(count(*args, C.byref(n)))
+    assert n.value == T == t["n_triplets"]
+    size = dict(idx_kj=T, idx_ji=T, seg_ptr_ji=E + 1, perm_kj=T, idx_ji_kj=T, seg_ptr_kj=E + 1)
+    for kj in (True, False, True):
+        a = {k: torch.full((v,), -7, dtype=torch.int32, device="cuda:0") for k, v in size.items()}
+        if not kj:
+            a.update(perm_kj=None, idx_ji_kj=None, seg_ptr_kj=None)
+        ctx.check(fill(*args, C.c_int64(T), *(B._ptr(a[k]) for k in size)))
+        got.append({k: v for k, v in a.items() if v is not None})
+    torch.cuda.synchronize()
+    for g in got:
+        for k in want:
+            if k in g:
+                assert np.array_equal(g[k].cpu().numpy(), want[k]), k
+    word, most = torch.empty(8, dtype=torch.uint8, device="cuda:0"), C.c_int32()
+    for ptr, have in (("row_ptr", t["max_in_degree"]), ("out_ptr", t["max_out_degree"])):
+        ctx.check(L.gp_csr_max_degree(ctx._h, B._ptr(t[ptr]), C.c_int64(N), B._ptr(word), C.c_size_t(8), C.byref(most)))
+        assert most.value == have == int(t[ptr].diff().max())
