@@ -107,10 +107,11 @@ basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int 
                     double cutoff, bessel_table tab, float* __restrict__ rbf, float* __restrict__ rad) {
   extern __shared__ float rows_s[];   // [EB][F + 1]
   const int F = R + S * R, ld = F + 1;
+  const int first = rbf ? 0 : R, last = rad ? F : R;   // the functions that are wanted
   const int64_t e0 = (int64_t)blockIdx.x * EB;
   const int ne = n_edges - e0 < EB ? (int)(n_edges - e0) : EB;
-  for (int i = threadIdx.x; i < EB * F; i += 256) {
-    const int el = i % EB, f = i / EB;
+  for (int i = threadIdx.x; i < EB * (last - first); i += 256) {
+    const int el = i % EB, f = first + i / EB;
     if (el >= ne) continue;
     const double d = (double)dist[e0 + el];
     const double x = d / cutoff;

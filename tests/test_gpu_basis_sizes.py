@@ -50,3 +50,21 @@ def test_gaussian_basis(lib, n, R):
     got = _basis(lib, dims, dist)["rbf"].cpu().numpy()
     want = obasis.rbf_gauss(torch.tensor(dist.astype(np.float64)), dims.cutoff, R, dims.envelope_p).numpy()
     assert np.all(np.abs(got - want) <= TOL * np.abs(want) + 1e-38)
+
+
+@pytest.mark.parametrize("n", [5, 16384 + 3])
+@pytest.mark.parametrize("S,R", [(7, 6), (1, 1)])
+def test_bessel_bases_one_at_a_time(lib, n, S, R):
+    # either output may be left out; the other one is the same to the bit and nothing else is written
+    import ctypes as C
+    from paper_2203_09697_amd import binding as B
+    dims = SimpleNamespace(**dict(vars(synth.get_workload("cfg2").dims), num_spherical=S, num_radial=R))
+    dist = np.random.default_rng(n).uniform(0.05, dims.cutoff, n).astype(np.float32)
+    want, d, ctx = _basis(lib, dims, dist), B.Dims(dims), lib.Context(0)
+    x = H.to_dev(dist, torch.float32)
+    for name in ("rbf", "rad"):
+        got = torch.full((want[name].numel() + 64,), -7.0, device="cuda:0")
+        ctx.check(lib.load().gp_basis_forward(ctx._h, C.byref(d), B._ptr(x), None, None, None, None, C.c_int64(n), C.c_int64(0),
+                                              *(B._ptr(got) if k == name else None for k in ("rbf", "rad")), None, None, None))
+        torch.cuda.synchronize()
+        assert torch.equal(got[:-64], want[name].reshape(-1)) and bool((got[-64:] == -7.0).all())
