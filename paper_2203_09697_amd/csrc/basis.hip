@@ -135,14 +135,16 @@ basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int 
 // variant D, for forces: gd[e] = sum_n grad_rbf[e,n] d rbf_n / dd + sum_{l,n} grad_rad[e,l,n] d rad_ln / dd with
 //   rbf_n(d) = u(x) sqrt(2/c) sin(k x) / d,  k = (n+1) pi,  x = d / c
 //   rad_ln(d) = u(x) N_ln j_l(z_ln x),  j_l'(y) = j_{l-1}(y) - (l+1)/y j_l(y)  (j_0' = -j_1)
-// One wavefront per edge, lanes over the terms, summed in fp64 (one thread per edge walked all 48 of them: 150 us for 336 edges).
+// LANES lanes of a wavefront per edge, over the terms, summed in fp64.  Bound by the latency of a term's fp64 chain where edges
+// are few, by the arithmetic of lanes that follow different orders l where they are many; see the rule at the launch.
+template <int LANES>
 __global__ void __launch_bounds__(256)
 grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict__ grad_rbf,
                         const float* __restrict__ grad_rad, int64_t n_edges, int S, int R, int p, double cutoff,
                         bessel_table tab, float* __restrict__ gd) {
-  const int64_t e = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int64_t e = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   if (e >= n_edges) return;
-  const int lane = lane_id();
+  const int lane = threadIdx.x % LANES;
   const double d = (double)dist[e], x = d / cutoff;
   double xp1 = 1.0;                       // x^(p-1)
   for (int k = 0; k < p - 1; ++k) xp1 *= x;
@@ -150,7 +152,7 @@ grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict_
   const double u = 1.0 + xp1 * x * (a + x * (b + x * c));
   const double du = xp1 * (p * a + x * ((p + 1) * b + x * (p + 2) * c)) / cutoff;   // du/dd
   double s = 0.0;
-  for (int f = lane; f < R + S * R; f += 64) {
+  for (int f = lane; f < R + S * R; f += LANES) {
     if (f < R) {
       if (grad_rbf) {
         const double k = (double)(f + 1) * M_PI;
@@ -172,7 +174,7 @@ grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict_
       s += (double)grad_rad[e * S * R + k] * tab.norm[k] * (du * jl + u * z / cutoff * djl);
     }
   }
-  for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
+  for (int o = LANES / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
   if (lane == 0) gd[e] = (float)s;
 }
 
@@ -447,8 +449,18 @@ int gp_grad_dist_bessel(gp_ctx* ctx, const gp_dims* dims, const float* dist, con
   GP_REQUIRE(ctx, S >= 1 && S <= MAX_S && R >= 1 && R <= MAX_R_BESSEL, "grad_dist_bessel: basis sizes out of range");
   bessel_table tab;
   make_bessel_table(S, R, (double)dims->cutoff, &tab);
-  grad_dist_bessel_kernel<<<(unsigned)((n_edges + 3) / 4), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R,
-                                                                                      dims->envelope_p, (double)dims->cutoff, tab, gd);
+  // Few terms: one thread per edge is not slower anywhere (9 terms: 7 us up to 16 000 edges; 36 us at 900 000, 77 with 4 lanes).
+  // From 16 terms on the lanes that keep the chip busy, 48 terms with 64 / 16 / 4 lanes per edge: 9 / 14 / 36 us at 336 edges,
+  // 15 / 12 / 36 at 4000, 42 / 24 / 35 at 16 000, 138 / 77 / 75 at 64 000, 612 / 336 / 299 at 300 000.
+  auto launch = [&](auto kernel, int lanes) {
+    const int per = 256 / lanes;
+    kernel<<<(unsigned)((n_edges + per - 1) / per), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R, dims->envelope_p,
+                                                                           (double)dims->cutoff, tab, gd);
+  };
+  if (R + S * R < 16) launch(grad_dist_bessel_kernel<1>, 1);
+  else if (n_edges < 4096) launch(grad_dist_bessel_kernel<64>, 64);
+  else if (n_edges < 32768) launch(grad_dist_bessel_kernel<16>, 16);
+  else launch(grad_dist_bessel_kernel<4>, 4);
   GP_LAUNCH_CHECK(ctx, "grad_dist_bessel_kernel");
   return GP_OK;
 }
