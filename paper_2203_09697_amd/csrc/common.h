@@ -176,7 +176,10 @@ struct run_team {
   static constexpr int TEAM = LONG ? 256 : 64, ROWS = LONG ? 64 : 16, LANES = LONG ? 64 : 16, CHUNK = LONG ? 512 : 64;
   static constexpr int TEAMS = 256 / TEAM, PAR = TEAM / LANES;   // teams of a workgroup, runs written at the same time
 };
-constexpr int LONG_LISTS = 96;   // mean number of triplets per edge from which the teams are workgroups
+// Mean number of triplets per edge from which the teams are workgroups.  Wavefronts / workgroups, complete structures of 340 to 455
+// thousand edges: 80 triplets per edge, fill 154 / 184 us and cosines 83 / 96; 112, 179 / 212 and 127 / 116; 130, 222 / 231 and
+// 152 / 132; 200, 351 / 310 and 260 / 178; 300, 717 / 523 and 418 / 327 (a box with 131: 183 / 176 and 82 / 72).
+constexpr int LONG_LISTS = 128;
 typedef int int4u __attribute__((ext_vector_type(4), aligned(4)));       // 16 bytes at any 4-byte boundary
 typedef float float4u __attribute__((ext_vector_type(4), aligned(4)));
 // slots s0 .. s0+3 of a run of cnt values: value i is c[i], or c[i+1] from position gap on
