@@ -97,6 +97,14 @@ def _ptr(t):
     return C.c_void_p(t.data_ptr())
 
 
+def _addr(t):
+    """The same for a pointer member of a struct."""
+    if t is None:
+        return None
+    assert t.is_cuda and t.is_contiguous(), "device-resident contiguous tensor required"
+    return t.data_ptr()
+
+
 def Dims(d):
     """gp_dims from a synth.BlockDims-like object (attribute access only)."""
     return _Dims(variant=0 if d.variant == "D" else 1, dtype=0 if d.dtype == "f32" else 1, emb=d.emb,
@@ -109,17 +117,17 @@ def Dims(d):
 
 def Graph(g):
     """gp_graph from the dict returned by build_graph / gp_triplets."""
-    return _Graph(n_edges=g["n_edges"], n_triplets=g["n_triplets"], idx_kj=_ptr(g["idx_kj"]),
-                  seg_ptr_ji=_ptr(g["seg_ptr_ji"]), idx_ji_kj=_ptr(g.get("idx_ji_kj")),
-                  seg_ptr_kj=_ptr(g.get("seg_ptr_kj")),
+    return _Graph(n_edges=g["n_edges"], n_triplets=g["n_triplets"], idx_kj=_addr(g["idx_kj"]),
+                  seg_ptr_ji=_addr(g["seg_ptr_ji"]), idx_ji_kj=_addr(g.get("idx_ji_kj")),
+                  seg_ptr_kj=_addr(g.get("seg_ptr_kj")),
                   n_atoms=g.get("n_atoms", 0) if g.get("out_list") is not None else 0,
-                  max_in_degree=g.get("max_in_degree", 0), max_out_degree=g.get("max_out_degree", 0), row_ptr=_ptr(g.get("row_ptr")),
-                  out_ptr=_ptr(g.get("out_ptr")), out_list=_ptr(g.get("out_list")), perm_kj=_ptr(g.get("perm_kj")), id_swap=_ptr(g.get("id_swap")))
+                  max_in_degree=g.get("max_in_degree", 0), max_out_degree=g.get("max_out_degree", 0), row_ptr=_addr(g.get("row_ptr")),
+                  out_ptr=_addr(g.get("out_ptr")), out_list=_addr(g.get("out_list")), perm_kj=_addr(g.get("perm_kj")), id_swap=_addr(g.get("id_swap")))
 
 
 def Basis(b):
-    return _Basis(rbf=_ptr(b.get("rbf")), rad=_ptr(b.get("rad")), cos_alpha=_ptr(b.get("cos_alpha")),
-                  cos_alpha_kj=_ptr(b.get("cos_alpha_kj")))
+    return _Basis(rbf=_addr(b.get("rbf")), rad=_addr(b.get("rad")), cos_alpha=_addr(b.get("cos_alpha")),
+                  cos_alpha_kj=_addr(b.get("cos_alpha_kj")))
 
 
 def D_WEIGHT_ORDER(dims):
@@ -290,24 +298,22 @@ def gp_triplets(ctx, edges, with_kj=True):
     ws = _empty(ctx, max(nbytes.value, 8), torch.uint8)
     n_trip = C.c_int64()
     off = edges.get("offset")     # periodic edge list: image-aware exclusion of k = i
-    src, row_ptr = _ptr(edges["src"]), _ptr(edges["row_ptr"])
+    src, dst, row_ptr = _ptr(edges["src"]), _ptr(edges["dst"]), _ptr(edges["row_ptr"])
     size = (C.c_int64(N), C.c_int64(E), _ptr(ws), C.c_size_t(ws.numel()))
     if with_kj and E > 0:
         seg_ji, seg_kj, swap, out_list, out_ptr = (_empty(ctx, n, torch.int32) for n in (E + 1, E + 1, E, E, N + 1))
-        lists = (_ptr(seg_ji), _ptr(seg_kj), _ptr(out_ptr), _ptr(swap))
+        lists = (ctx._h, src, dst, _ptr(off), row_ptr, *size, _ptr(seg_ji), _ptr(seg_kj), _ptr(out_ptr), _ptr(swap))
         max_in, max_out = C.c_int32(), C.c_int32()
-        ctx.check(lib.gp_graph_lists_count(ctx._h, src, _ptr(edges["dst"]), _ptr(off), row_ptr, *size, *lists, C.byref(n_trip),
-                                           C.byref(max_in), C.byref(max_out)))
+        ctx.check(lib.gp_graph_lists_count(*lists, C.byref(n_trip), C.byref(max_in), C.byref(max_out)))
         T = n_trip.value
         idx_kj, idx_ji, perm_kj, idx_ji_kj = (_empty(ctx, T, torch.int32) for _ in range(4))
-        ctx.check(lib.gp_graph_lists_fill(ctx._h, src, _ptr(edges["dst"]), _ptr(off), row_ptr, *size, *lists, n_trip, _ptr(out_list), _ptr(idx_kj),
-                                          _ptr(idx_ji), _ptr(perm_kj), _ptr(idx_ji_kj)))
+        ctx.check(lib.gp_graph_lists_fill(*lists, n_trip, _ptr(out_list), _ptr(idx_kj), _ptr(idx_ji), _ptr(perm_kj), _ptr(idx_ji_kj)))
         ctx.settle()
         return dict(n_edges=E, n_triplets=T, idx_kj=idx_kj, idx_ji=idx_ji, seg_ptr_ji=seg_ji, perm_kj=perm_kj, idx_ji_kj=idx_ji_kj,
                     seg_ptr_kj=seg_kj, n_atoms=N, row_ptr=edges["row_ptr"], out_ptr=out_ptr, out_list=out_list,
                     max_in_degree=max_in.value, max_out_degree=max_out.value, id_swap=swap)
     pbc = off is not None
-    args = (ctx._h, src, _ptr(edges["dst"])) + ((_ptr(off),) if pbc else ()) + (row_ptr,) + size
+    args = (ctx._h, src, dst) + ((_ptr(off),) if pbc else ()) + (row_ptr,) + size
     ctx.check((lib.gp_triplets_count_pbc if pbc else lib.gp_triplets_count)(*args, C.byref(n_trip)))
     T = n_trip.value
     out = dict(n_edges=E, n_triplets=T, idx_kj=_empty(ctx, T, torch.int32), idx_ji=_empty(ctx, T, torch.int32),
@@ -363,13 +369,13 @@ def build_graph(ctx, pos, graph_ptr, cutoff, max_neighbors=0, cell=None, rep=Non
 def _has_lists(edges, trip):
     """Whether edges and triplets carry everything that gp_basis_forward_graph reads, in the sizes that belong together (a dict may
     have lost its lists by centre atom, or kept them while triplets were taken out)."""
-    E, T, get = edges["n_edges"], trip["n_triplets"], trip.get
-    row_ptr, out_ptr = get("row_ptr"), get("out_ptr")
-    for t, n in ((get("id_swap"), E), (get("out_list"), E), (get("perm_kj"), T), (get("idx_ji_kj"), T), (get("seg_ptr_kj"), E + 1),
-                 (get("seg_ptr_ji"), E + 1), (edges.get("src"), E), (edges.get("dst"), E)):
-        if t is None or t.numel() != n:
-            return False
-    return row_ptr is not None and out_ptr is not None and row_ptr.numel() == out_ptr.numel()
+    E, T = edges["n_edges"], trip["n_triplets"]
+    try:
+        return (trip["perm_kj"].numel() == trip["idx_ji_kj"].numel() == T and trip["id_swap"].numel() == trip["out_list"].numel() == E
+                and trip["seg_ptr_ji"].numel() == trip["seg_ptr_kj"].numel() == E + 1
+                and trip["row_ptr"] is not None and trip["out_ptr"] is not None and edges["src"] is not None and edges["dst"] is not None)
+    except (KeyError, AttributeError):   # not there, or None
+        return False
 
 
 def gp_basis_forward(ctx, dims, edges, trip, want_sbf=False):

@@ -274,12 +274,13 @@ links_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, c
   if (out_deg) arrival[e] = atomicAdd(&out_deg[j], 1);
 }
 
-// number of triplets of edge e as the target and, where the out-degrees are there, as the source edge
+// number of triplets of edge e as the target and, with KJ, as the source edge
+template <bool KJ>
 __device__ __forceinline__ int2 triplet_counts(const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
                                                const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ id_swap,
                                                const int32_t* __restrict__ out_deg, int64_t e) {
   const int j = src[e], has = id_swap[e] >= 0 ? 1 : 0;
-  return make_int2(row_ptr[j + 1] - row_ptr[j] - has, out_deg ? out_deg[dst[e]] - has : 0);
+  return make_int2(row_ptr[j + 1] - row_ptr[j] - has, KJ ? out_deg[dst[e]] - has : 0);
 }
 
 // Sum over the 4 or 16 wavefronts of a workgroup; every thread must call it.  Returns the exclusive prefix of v over the
@@ -307,6 +308,7 @@ __device__ __forceinline__ T block_prefix(T v, T* lds, T* total) {
 constexpr int CHUNK = 1024;   // edges per workgroup of the two edge-wide passes, 4 per thread
 inline int64_t chunks_of(int64_t n) { return (n + CHUNK - 1) / CHUNK; }
 
+template <bool KJ>
 __global__ void __launch_bounds__(256)
 lists_sums_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ row_ptr,
                   const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_deg, int64_t n_edges,
@@ -317,7 +319,7 @@ lists_sums_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ d
   for (int u = 0; u < 4; ++u) {
     const int64_t e = (int64_t)blockIdx.x * CHUNK + u * 256 + threadIdx.x;
     if (e < n_edges) {
-      const int2 c = triplet_counts(src, dst, row_ptr, id_swap, out_deg, e);
+      const int2 c = triplet_counts<KJ>(src, dst, row_ptr, id_swap, out_deg, e);
       a += c.x;
       b += c.y;
     }
@@ -389,7 +391,8 @@ lists_mid_kernel(const int32_t* __restrict__ row_ptr, const int32_t* __restrict_
   }
 }
 
-// seg_ji from the chunks' offsets; with out_deg also seg_kj, and the out-edges of every atom in arrival order
+// seg_ji from the chunks' offsets; with KJ also seg_kj, and the out-edges of every atom in arrival order
+template <bool KJ>
 __global__ void __launch_bounds__(256)
 lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ dst, const int32_t* __restrict__ row_ptr,
                    const int32_t* __restrict__ id_swap, const int32_t* __restrict__ out_deg, const int32_t* __restrict__ out_ptr,
@@ -402,7 +405,7 @@ lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ 
   int64_t a = 0, b = 0;
 #pragma unroll
   for (int u = 0; u < 4; ++u) {
-    c[u] = e0 + u < n_edges ? triplet_counts(src, dst, row_ptr, id_swap, out_deg, e0 + u) : make_int2(0, 0);
+    c[u] = e0 + u < n_edges ? triplet_counts<KJ>(src, dst, row_ptr, id_swap, out_deg, e0 + u) : make_int2(0, 0);
     a += c[u].x;
     b += c[u].y;
   }
@@ -414,7 +417,7 @@ lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ 
     const int64_t e = e0 + u;
     if (e < n_edges) {
       seg_ji[e] = (int32_t)pa;
-      if (out_deg) {
+      if (KJ) {
         seg_kj[e] = (int32_t)pb;
         out_tmp[out_ptr[src[e]] + arrival[e]] = (int32_t)e;
       }
@@ -424,7 +427,7 @@ lists_apply_kernel(const int32_t* __restrict__ src, const int32_t* __restrict__ 
   }
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     seg_ji[n_edges] = (int32_t)*total;
-    if (out_deg) seg_kj[n_edges] = (int32_t)*total;
+    if (KJ) seg_kj[n_edges] = (int32_t)*total;
   }
 }
 
@@ -770,12 +773,12 @@ int lists_pass(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_
   if (with_kj) GP_HIP(ctx, (hipError_t)gp_zero_async(st, out_deg, sizeof(int32_t) * n_atoms));
   links_kernel<<<blocks_for(n_edges, 256), 256, 0, st>>>(src, dst, offset, row_ptr, (int)n_edges, w.id_swap, out_deg, w.arrival);
   const int64_t nc = chunks_of(n_edges);
-  lists_sums_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, n_edges, w.sums);
+  (with_kj ? lists_sums_kernel<true> : lists_sums_kernel<false>)<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, n_edges, w.sums);
   lists_mid_kernel<<<1, 1024, 0, st>>>(row_ptr, out_deg, with_kj ? (int)n_atoms : 0, nc, w.out_ptr, w.sums, w.total, host_words);
   GP_LAUNCH_CHECK(ctx, "list kernels");
   if (counted) GP_HIP(ctx, hipEventRecord(counted, st));
-  lists_apply_kernel<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, w.out_ptr, w.arrival, n_edges, w.sums,
-                                                   w.total, w.seg_ji, w.seg_kj, w.out_tmp);
+  (with_kj ? lists_apply_kernel<true> : lists_apply_kernel<false>)<<<(unsigned)nc, 256, 0, st>>>(
+      src, dst, row_ptr, w.id_swap, out_deg, w.out_ptr, w.arrival, n_edges, w.sums, w.total, w.seg_ji, w.seg_kj, w.out_tmp);
   GP_LAUNCH_CHECK(ctx, "lists_apply_kernel");
   return GP_OK;
 }
