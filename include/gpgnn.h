@@ -184,7 +184,7 @@ int gp_triplets_fill_pbc(gp_ctx* ctx, const int32_t* src, const int32_t* dst, co
                          int32_t* perm_kj, int32_t* idx_ji_kj, int32_t* seg_ptr_kj);
 
 /* All lists of a graph together: what gp_triplets_count/fill, gp_edges_by_source, gp_reverse_edges and two calls of
- * gp_csr_max_degree return, in half the launches and with one wait of the host.  offset: NULL for open boundaries, else the
+ * gp_csr_max_degree return, in a third of the launches and with one wait of the host.  offset: NULL for open boundaries, else the
  * cell offsets of a periodic edge list.  n_atoms and n_edges positive.  _count writes seg_ptr_ji[E+1], seg_ptr_kj[E+1],
  * out_ptr[N+1], id_swap[E] and returns the number of triplets and the largest degrees on the host; the caller allocates;
  * _fill (same arguments, same workspace of gp_triplets_workspace bytes, the arrays that _count wrote) writes out_list[E],
