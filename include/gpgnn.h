@@ -66,10 +66,12 @@ int gp_set_side_stream(gp_ctx* ctx, int on);
  * sets the mode at gp_create. */
 int gp_set_triplet_mfma(gp_ctx* ctx, int mode);
 
-/* GEMMs with fp32 operands and results (the fp32 blocks, Sec. 3.3; the energy head).  split = 1 (default): on the bf16
- * matrix cores, every operand element entering as three bf16 numbers whose sum is the fp32 value (24 significant
- * bits) and six of the nine plane products accumulated in fp32, the dropped ones below 2^-24 of the product: results
- * agree with fp32 arithmetic to its rounding error, at 2.7 times the fp32-operand matrix-core rate of this chip.
+/* GEMMs with fp32 operands and results (the fp32 blocks, Sec. 3.3; the energy head).  split = 1 (default): on the 16-bit
+ * matrix cores with fp32 accumulation, in one of two forms, chosen by shape.  Products of edge rows with the wide weights: every
+ * operand element as two fp16 numbers under a power-of-two scale (per row and 32 contraction indices; per column of the
+ * weights), three products.  The others: every element as three bf16 numbers whose sum is the fp32 value (24 significant
+ * bits), six of the nine products, the dropped ones below 2^-24.  Either agrees with 64-bit results at least as closely as
+ * the fp32 instruction does, at 2.7 to 5 times its rate.
  * split = 0: the fp32-operand matrix-core instruction.  GP_F32_GEMM=0/1 in the environment sets it at gp_create. */
 int gp_set_f32_gemm(gp_ctx* ctx, int split);
 

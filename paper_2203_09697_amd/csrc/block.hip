@@ -66,6 +66,7 @@ struct scratch_D {
   float* part;
   float* part_aux;   // split-K partials of the GEMMs issued on the side stream
   size_t part_bytes;
+  void* planes;      // the weights of a call as operand planes (gemm_planes.hip)
 };
 
 size_t part_bytes_D(const gp_dims* d, int64_t E) {
@@ -90,6 +91,13 @@ bool bwd_mfma_D(const gp_ctx* ctx, const gp_dims* d, const gp_graph* g) {
          gp_tripD_mfma_bwd_scratch(g, F) <= part_bytes_D(d, g->n_edges);
 }
 
+// room for the planes of every weight matrix that meets the edges, for the products of either pass
+size_t planes_bytes_D(const gp_dims* d) {
+  const int H = d->emb, F = d->int_emb;
+  auto both = [](int a, int b) { return std::max(gp_align(gp_planes_bytes(a, b)), gp_align(gp_planes_bytes(b, a))); };
+  return (size_t)(3 + 2 * d->n_res_before + 2 * d->n_res_after) * both(H, H) + 2 * both(H, F);
+}
+
 size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   gp_carver c(p);
   const size_t H = d->emb, F = d->int_emb, B = d->basis_emb, S = d->num_spherical, R = d->num_radial;
@@ -102,6 +110,7 @@ size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   s->part_bytes = part_bytes_D(d, E);
   s->part = (float*)c.take<char>(s->part_bytes);
   s->part_aux = (float*)c.take<char>(s->part_bytes);
+  s->planes = c.take<char>(planes_bytes_D(d));
   return c.off;
 }
 
@@ -131,32 +140,32 @@ int check_weights_D(gp_ctx* ctx, const gp_dims* d, const gp_weights_D* w, const 
   return GP_OK;
 }
 
-// one residual layer forward: hout = hin + act(act(hin W1 + b1) W2 + b2)
-int res_forward(gp_ctx* ctx, const float* hin, float* const* w, const res_saved& s, float* hout, int64_t E, int H) {
+// one residual layer forward: hout = hin + act(act(hin W1 + b1) W2 + b2); pl: the planes of W1 and W2
+int res_forward(gp_ctx* ctx, const float* hin, float* const* w, const void* const* pl, const res_saved& s, float* hout, int64_t E, int H) {
   gp_epilogue e1;
   e1.bias = w[1]; e1.save_pre = s.z1; e1.act = 1; e1.out = s.y1;
-  GP_TRY(gp_gemm_nn(ctx, hin, w[0], E, H, H, e1));
+  GP_TRY(gp_gemm_nn_w(ctx, hin, w[0], pl[0], E, H, H, e1));
   gp_epilogue e2;
   e2.bias = w[3]; e2.save_pre = s.z2; e2.act = 1; e2.add_post = hin; e2.out = hout;
-  return gp_gemm_nn(ctx, s.y1, w[2], E, H, H, e2);
+  return gp_gemm_nn_w(ctx, s.y1, w[2], pl[1], E, H, H, e2);
 }
 
 // One residual layer backward.  dz2 = dh * silu'(z2) is given (written by the producer of dh).
 // dh_out = dh + d(hin through the layer); if z_next != NULL also dz_next = dh_out * silu'(z_next).
 // The two weight-gradient GEMMs go to the side stream.
-int res_backward(gp_ctx* ctx, gp_aux& aux, const float* hin, float* const* w, float* const* gw, const res_saved& s,
-                 const float* dh, const float* dz2, float* dh_out, float* t2, const float* z_next, float* dz_next,
+int res_backward(gp_ctx* ctx, gp_aux& aux, const float* hin, float* const* w, const void* const* pl, float* const* gw,
+                 const res_saved& s, const float* dh, const float* dz2, float* dh_out, float* t2, const float* z_next, float* dz_next,
                  scratch_D& sc, int64_t E, int H) {
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.y1, dz2, E, H, H, gw[2], gw[3], sc.part_aux, sc.part_bytes); }, {dz2}));
   gp_epilogue e;
   e.act = 2; e.zsrc = s.z1; e.out = t2;
   GP_TRY(aux.before_write(t2));
-  GP_TRY(gp_gemm_nt(ctx, dz2, w[2], E, H, H, e));                                       // dz1
+  GP_TRY(gp_gemm_nt_w(ctx, dz2, w[2], pl[1], E, H, H, e));                                       // dz1
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, hin, t2, E, H, H, gw[0], gw[1], sc.part_aux, sc.part_bytes); }, {t2}));
   gp_epilogue e2;
   e2.add_post = dh; e2.out = dh_out; e2.out2 = z_next ? dz_next : nullptr; e2.z2src = z_next;
   if (z_next) GP_TRY(aux.before_write(dz_next));
-  return gp_gemm_nt(ctx, t2, w[0], E, H, H, e2);
+  return gp_gemm_nt_w(ctx, t2, w[0], pl[0], E, H, H, e2);
 }
 
 }  // namespace
@@ -202,6 +211,16 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   const int H = dims->emb, F = dims->int_emb, B = dims->basis_emb, S = dims->num_spherical, R = dims->num_radial;
   float* x_ji = sc.buf[0];
 
+  gp_weight_planes wp(ctx, sc.planes);
+  const void *p_ji = wp.add(w->W_ji, E, H, H, 1), *p_kj = wp.add(w->W_kj, E, H, H, 1), *p_down = wp.add(w->W_down, E, F, H, 1),
+             *p_up = wp.add(w->W_up, E, H, F, 1), *p_lin = wp.add(w->W_lin, E, H, H, 1);
+  const void *p_before[GP_MAX_RES][2] = {}, *p_after[GP_MAX_RES][2] = {};
+  for (int r = 0; r < dims->n_res_before; ++r)
+    for (int q = 0; q < 2; ++q) p_before[r][q] = wp.add(w->res_before[r][2 * q], E, H, H, 1);
+  for (int r = 0; r < dims->n_res_after; ++r)
+    for (int q = 0; q < 2; ++q) p_after[r][q] = wp.add(w->res_after[r][2 * q], E, H, H, 1);
+  GP_TRY(wp.run());
+
   // Side stream, before the triplet sum: the projected radial table is needed only by the triplet kernel and the
   // projection of the target-edge message only by the epilogue of the up-projection, so both run next to the chain
   // that leads to the triplet sum.  After it: the layers act on every edge by itself, and a GEMM over all E rows at
@@ -219,16 +238,16 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   auto ji_rows = [&](int64_t r0, int64_t n) {
     const int64_t o = r0 * H;
     gp_epilogue q; q.bias = w->b_ji; q.save_pre = s.z_ji + o; q.act = 1; q.out = x_ji + o;
-    return gp_gemm_nn(ctx, m_in + o, w->W_ji, n, H, H, q);
+    return gp_gemm_nn_w(ctx, m_in + o, w->W_ji, p_ji, n, H, H, q);
   };
   auto kj_rows = [&](int64_t r0, int64_t n) -> int {
     const int64_t o = r0 * H;
     gp_epilogue q; q.out = s.gate + o;
     GP_TRY(gp_gemm_nn(ctx, basis->rbf + r0 * R, s.Wrbf, n, H, R, q));
     q = gp_epilogue(); q.bias = w->b_kj; q.save_pre = s.z_kj + o; q.act = 1; q.mul = s.gate + o; q.out = s.xg + o;
-    GP_TRY(gp_gemm_nn(ctx, m_in + o, w->W_kj, n, H, H, q));
+    GP_TRY(gp_gemm_nn_w(ctx, m_in + o, w->W_kj, p_kj, n, H, H, q));
     q = gp_epilogue(); q.save_pre = s.z_dn + r0 * F; q.act = 1; q.out = s.x_kj + r0 * F;
-    return gp_gemm_nn(ctx, s.xg + o, w->W_down, n, F, H, q);
+    return gp_gemm_nn_w(ctx, s.xg + o, w->W_down, p_down, n, F, H, q);
   };
   GP_TRY(aux.on_aux([&] { return project_radial(); }, {s.Q}));
   GP_TRY(aux.on_aux([&] { return ji_rows(0, E); }, {}));
@@ -249,21 +268,21 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
     const int64_t o = r0 * H;
     auto at = [&](const res_saved& q) { return res_saved{q.z1 + o, q.y1 + o, q.z2 + o, q.hout + o}; };
     gp_epilogue eu; eu.save_pre = s.z_up + o; eu.act = 1; eu.add_post = x_ji + o; eu.out = s.h0 + o;
-    GP_TRY(gp_gemm_nn(ctx, s.a + r0 * F, w->W_up, n, H, F, eu));
+    GP_TRY(gp_gemm_nn_w(ctx, s.a + r0 * F, w->W_up, p_up, n, H, F, eu));
     const float* h = s.h0 + o;
     for (int r = 0; r < dims->n_res_before; ++r) {
       const res_saved q = at(s.before[r]);
-      GP_TRY(res_forward(ctx, h, w->res_before[r], q, q.hout, n, H));
+      GP_TRY(res_forward(ctx, h, w->res_before[r], p_before[r], q, q.hout, n, H));
       h = q.hout;
     }
     float* lin_out = (dims->n_res_after == 0 ? m_out : s.h_lin) + o;
     gp_epilogue el; el.bias = w->b_lin; el.save_pre = s.z_lin + o; el.act = 1; el.add_post = m_in + o; el.out = lin_out;
-    GP_TRY(gp_gemm_nn(ctx, h, w->W_lin, n, H, H, el));
+    GP_TRY(gp_gemm_nn_w(ctx, h, w->W_lin, p_lin, n, H, H, el));
     h = lin_out;
     for (int r = 0; r < dims->n_res_after; ++r) {
       const res_saved q = at(s.after[r]);
       float* out = (r == dims->n_res_after - 1) ? m_out + o : q.hout;
-      GP_TRY(res_forward(ctx, h, w->res_after[r], q, out, n, H));
+      GP_TRY(res_forward(ctx, h, w->res_after[r], p_after[r], q, out, n, H));
       h = out;
     }
     return GP_OK;
@@ -336,6 +355,15 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     return nullptr;
   };
 
+  gp_weight_planes wp(ctx, sc.planes);
+  const void *p_ji = wp.add(w->W_ji, E, H, H, 0), *p_kj = wp.add(w->W_kj, E, H, H, 0), *p_down = wp.add(w->W_down, E, H, F, 0),
+             *p_up = wp.add(w->W_up, E, F, H, 0), *p_lin = wp.add(w->W_lin, E, H, H, 0);
+  const void *p_before[GP_MAX_RES][2] = {}, *p_after[GP_MAX_RES][2] = {};
+  for (int r = 0; r < dims->n_res_before; ++r)
+    for (int q = 0; q < 2; ++q) p_before[r][q] = wp.add(w->res_before[r][2 * q], E, H, H, 0);
+  for (int r = 0; r < dims->n_res_after; ++r)
+    for (int q = 0; q < 2; ++q) p_after[r][q] = wp.add(w->res_after[r][2 * q], E, H, H, 0);
+  GP_TRY(wp.run());
   gp_aux aux(ctx);
   // dz of the last activation in the block: the only elementwise pass that has no producer GEMM
   const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
@@ -349,7 +377,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     const float* z_next = (r > 0) ? s.after[r - 1].z2 : s.z_lin;
     float* out = next_buf();
     float* dznext = other_dz();
-    GP_TRY(res_backward(ctx, aux, hin, w->res_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, T2, z_next,
+    GP_TRY(res_backward(ctx, aux, hin, w->res_after[r], p_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, T2, z_next,
                         dznext, sc, E, H));
     dh = out;
     dzcur = dznext;
@@ -365,7 +393,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     float* dznext = other_dz();
     GP_TRY(aux.before_write(dznext));
     gp_epilogue e; e.out = out; e.out2 = dznext; e.z2src = z_next;
-    GP_TRY(gp_gemm_nt(ctx, dzcur, w->W_lin, E, H, H, e));
+    GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_lin, p_lin, E, H, H, e));
     dh = out;
     dzcur = dznext;
   }
@@ -374,7 +402,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     const float* z_next = (r > 0) ? s.before[r - 1].z2 : s.z_up;
     float* out = next_buf();
     float* dznext = other_dz();
-    GP_TRY(res_backward(ctx, aux, hin, w->res_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, T2, z_next,
+    GP_TRY(res_backward(ctx, aux, hin, w->res_before[r], p_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, T2, z_next,
                         dznext, sc, E, H));
     dh = out;
     dzcur = dznext;
@@ -393,12 +421,12 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
         GP_TRY(gp_ew_dsilu_mul(ctx, dh, s.z_ji, dz_ji, EH));
         GP_TRY(gp_gemm_tn(ctx, m_in, dz_ji, E, H, H, gw->W_ji, gw->b_ji, sc.part_aux, sc.part_bytes));
         gp_epilogue e; e.out = dm_ji;
-        return gp_gemm_nt(ctx, dz_ji, w->W_ji, E, H, H, e);
+        return gp_gemm_nt_w(ctx, dz_ji, w->W_ji, p_ji, E, H, H, e);
       },
       {dz_ji, dm_ji}));
   {
     gp_epilogue e; e.out = sc.dF1;
-    GP_TRY(gp_gemm_nt(ctx, dzcur, w->W_up, E, F, H, e));                                     // da
+    GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_up, p_up, E, F, H, e));                                     // da
   }
   // triplet interaction
   const bool bwd_mfma = bwd_mfma_D(ctx, dims, graph);
@@ -440,7 +468,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   {
     GP_TRY(aux.before_write(T2));
     gp_epilogue e; e.out = T2;
-    GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));                                  // dxg
+    GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                                  // dxg
   }
   GP_TRY(aux.before_write(dz_kj));
   GP_TRY(gp_ew_gate_bwd(ctx, T2, s.z_kj, s.gate, dz_kj, dgate, EH));                         // dz_kj, dgate
@@ -459,7 +487,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   {
     GP_TRY(aux.before_write(dm_ji));   // the side stream's input gradient of the ji path
     gp_epilogue e; e.add_pre = dm_ji; e.add_post = keep; e.out = grad_m_in;
-    GP_TRY(gp_gemm_nt(ctx, dz_kj, w->W_kj, E, H, H, e));                                     // dm = kj path + ji path + skip
+    GP_TRY(gp_gemm_nt_w(ctx, dz_kj, w->W_kj, p_kj, E, H, H, e));                                     // dm = kj path + ji path + skip
   }
   return aux.join();
 }

@@ -81,3 +81,36 @@ struct gp_bf16_scope {
 };
 // out[i] = sum_z part[z*n + i], z < splits
 int gp_reduce_parts(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out);
+
+// ---- fp32 products A W and A W^T with fp32 operands as two fp16 numbers each; the weights are converted ahead (gemm_planes.hip)
+constexpr int GP_PLANE_JOBS_MAX = 24;
+struct gp_plane_job {
+  const float* src;
+  void* dst;      // gp_planes_bytes(N, K)
+  int N, K;       // columns and contraction length of the product
+  int k_rows;     // src is [K, N] (A W), else [N, K] (A W^T)
+};
+size_t gp_planes_bytes(int N, int K);
+// whether a product of this shape is better off in that form (M rows of A)
+bool gp_planes_take(const gp_ctx* ctx, int64_t M, int N, int K);
+
+// The weights of a call, converted by one launch.
+struct gp_weight_planes {
+  gp_ctx* ctx;
+  char* next;     // room for the planes: gp_planes_bytes of every matrix added, each rounded up to 256
+  gp_plane_job jobs[GP_PLANE_JOBS_MAX];
+  int n = 0;
+  gp_weight_planes(gp_ctx* c, void* room) : ctx(c), next(static_cast<char*>(room)) {}
+  // planes of W for products with M rows (NULL where the general kernels take them)
+  const void* add(const float* W, int64_t M, int N, int K, int k_rows) {
+    if (n == GP_PLANE_JOBS_MAX || !gp_planes_take(ctx, M, N, K)) return nullptr;
+    jobs[n++] = gp_plane_job{W, next, N, K, k_rows};
+    void* p = next;
+    next += gp_align(gp_planes_bytes(N, K));
+    return p;
+  }
+  int run();
+};
+// gp_gemm_nn / gp_gemm_nt with the planes of the weight matrix at hand (NULL: the general kernels)
+int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
+int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);

@@ -1,0 +1,495 @@
+// fp32 products A W and A W^T (edge and atom rows times a weight matrix) on the fp16 matrix cores: every element enters as
+// the sum of two fp16 numbers, v 2^k = hi + lo (22 to 23 significant bits), and three of the four products of the parts are
+// formed (lo.lo is below 2^-22 of the product).  The power of two is chosen so that the largest of the values that share it
+// lies in [2^14, 2^15): the values of a row of A over 32 consecutive k, and a column of W.  Smaller values of the group keep
+// all their bits down to 2^-17 of the largest and lose at most 2^-40 of the largest below that: nothing overflows, fp16's
+// exponents do not matter, and subnormal parts count (this target's matrix instruction takes them).
+// The 32 k are summed from zero and enter the result with their scale taken back: K / 32 additions into the fp32 sum.
+//
+// Against the form with three bf16 parts and six products (gemm_split_kernel: 24 bits, 6 K / 16 additions) that is half the
+// matrix instructions and a smaller error, because the additions are what that form's error is made of.  Relative error
+// against 64 bits, operands uniform in +-1 (three bf16 parts / two fp16 parts / fp32 matrix instruction): K = 32 6.9e-8 / 6.3e-8 /
+// 1.0e-7, K = 64 1.1e-7 / 7.1e-8 / 1.4e-7, K = 256 2.3e-7 / 8.8e-8 / 2.9e-7, K = 2048 7.0e-7 / 1.6e-7 / 8.1e-7.  At K = 16 it is
+// the larger one (3.3e-8 / 4.7e-8 / 7.4e-8): shapes with K < 64 stay with the other kernels.
+//
+// What bounds these products is power as much as anything: with random operands the matrix units of the whole chip sustain 1.87
+// PFLOP/s in bf16 and 1.72 in fp16 from registers alone (2.47 with zeros), so fewer matrix instructions is what helps.
+#include <stdarg.h>
+
+#include <algorithm>
+
+#include "gemm_common.h"
+
+namespace {
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef const __attribute__((address_space(1))) void* global_void_ptr;
+
+constexpr int PL = 2;                   // planes: hi, lo
+constexpr int FRAG_B = 1024;            // one operand fragment of a wavefront: 64 lanes x 8 fp16
+constexpr int GROUP_B = PL * FRAG_B;    // both planes of 32 columns x 16 k
+
+// v = hi + lo, both rounded to nearest
+__device__ __forceinline__ void split8(const float* v, f16x8& hi, f16x8& lo) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) hi[c] = (_Float16)v[c];
+#pragma unroll
+  for (int c = 0; c < 8; ++c) lo[c] = (_Float16)(v[c] - (float)hi[c]);
+}
+
+// The power of two 2^k that brings the largest of some values into [2^14, 2^15), for the bits of its absolute value: k = 0 where
+// that is 0, an infinity or a NaN, and at most 112 (below 2^-98 not all of the way), so that the factors back are normal numbers.
+__device__ __forceinline__ int scale_exp(uint32_t bits) {
+  const int e = (int)(bits >> 23);   // biased exponent
+  const int k = 141 - e;
+  return e == 255 || bits == 0u ? 0 : k < 112 ? k : 112;
+}
+__device__ __forceinline__ float pow2(int k) { return __int_as_float((k + 127) << 23); }   // -126 <= k <= 127
+
+// the larger of lanes l and l ^ 32
+__device__ __forceinline__ uint32_t max_halves(uint32_t m) {
+  const auto h = __builtin_amdgcn_permlane32_swap(m, m, false, false);
+  return h[0] > h[1] ? h[0] : h[1];
+}
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lgkmcnt0() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
+  __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
+}
+
+struct plane_jobs {
+  gp_plane_job j[GP_PLANE_JOBS_MAX];
+};
+
+// One workgroup per 32 columns n: the scales of the columns first (largest |w| over all k), then the planes, a wavefront per
+// 16 k: lane (kh, n) takes 8 consecutive k of column n.  Behind the planes: the columns' factors back, 2^14 / scale.
+constexpr int PREP_WAVES = 16, PREP_KEEP = 8;   // 16-k pieces a wavefront keeps in registers between the two passes
+__global__ void __launch_bounds__(64 * PREP_WAVES) make_planes_kernel(const plane_jobs jobs) {
+  const gp_plane_job& q = jobs.j[blockIdx.y];
+  const int k16 = (q.K + 31) / 32 * 2, nb = (q.N + 31) / 32;
+  const int blk = blockIdx.x;
+  if (blk >= nb) return;
+  __shared__ uint32_t big[32];
+  if (threadIdx.x < 32) big[threadIdx.x] = 0u;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int n = blk * 32 + (lane & 31);
+  auto load = [&](int u, float* v) __attribute__((always_inline)) {
+    const int k = u * 16 + (lane >> 5) * 8;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] = 0.f;
+    if (u >= k16 || n >= q.N || k >= q.K) return;   // K is a multiple of 16
+    if (q.k_rows) {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) v[c] = q.src[(int64_t)(k + c) * q.N + n];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 8; ++c) v[c] = q.src[(int64_t)n * q.K + k + c];
+    }
+  };
+  float keep[PREP_KEEP][8];
+  uint32_t m = 0;
+  auto most = [&](const float* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const uint32_t b = __float_as_uint(v[c]) & 0x7FFFFFFFu;
+      m = b > m ? b : m;
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < PREP_KEEP; ++i) load(wave + i * PREP_WAVES, keep[i]);
+#pragma unroll
+  for (int i = 0; i < PREP_KEEP; ++i) most(keep[i]);
+  for (int u = wave + PREP_KEEP * PREP_WAVES; u < k16; u += PREP_WAVES) {
+    float v[8];
+    load(u, v);
+    most(v);
+  }
+  atomicMax(&big[lane & 31], m);
+  __syncthreads();
+  const int se = scale_exp(big[lane & 31]);
+  const float s = pow2(se);
+  auto put = [&](int u, float* v) __attribute__((always_inline)) {
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v[c] *= s;
+    f16x8 hi, lo;
+    split8(v, hi, lo);
+    char* dst = static_cast<char*>(q.dst) + ((int64_t)blk * k16 + u) * GROUP_B + lane * 16;
+    *reinterpret_cast<f16x8*>(dst) = hi;
+    *reinterpret_cast<f16x8*>(dst + FRAG_B) = lo;
+  };
+#pragma unroll
+  for (int i = 0; i < PREP_KEEP; ++i)
+    if (wave + i * PREP_WAVES < k16) put(wave + i * PREP_WAVES, keep[i]);
+  for (int u = wave + PREP_KEEP * PREP_WAVES; u < k16; u += PREP_WAVES) {
+    float v[8];
+    load(u, v);
+    put(u, v);
+  }
+  if (threadIdx.x < 32) reinterpret_cast<float*>(static_cast<char*>(q.dst) + (int64_t)nb * k16 * GROUP_B)[n] = pow2(14 - se);
+}
+
+// Epilogue of a wavefront's MB x NB blocks for the steps EMASK names (see tile_epilogue_f32 for the register layout and the
+// order of steps).  The matrices it reads are requested one block ahead of the block that is stored: block by block, each
+// block waited for its own loads.  Rows past M read row M - 1 and columns past N the last four; nothing is stored there.
+template <unsigned M>
+struct epi_in {
+  f32x4 bias, pre[4], z[4], mul[4], post[4], z2[4];
+  __device__ __forceinline__ void load(const gp_epilogue& e, const int64_t (&o)[4], int col) {
+    if constexpr ((M & EM_BIAS) != 0) bias = ld4(e.bias + col);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      if constexpr ((M & EM_ADD_PRE) != 0) pre[it] = ld4(e.add_pre + o[it]);
+      if constexpr ((M & EM_ACT2) != 0) z[it] = ld4(e.zsrc + o[it]);
+      if constexpr ((M & EM_MUL) != 0) mul[it] = ld4(e.mul + o[it]);
+      if constexpr ((M & EM_ADD_POST) != 0) post[it] = ld4(e.add_post + o[it]);
+      if constexpr ((M & EM_OUT2) != 0) z2[it] = ld4(e.z2src + o[it]);
+    }
+  }
+};
+
+template <int MB, int NB, unsigned M>
+__device__ __forceinline__ void epilogue_blocks(const gemm_args& g, f32x16 (&acc)[MB][NB], float* stage, int64_t row0, int col0, const float* inv) {
+  const int lane = threadIdx.x & 63;
+  const int kh = lane >> 5, l32 = lane & 31, c4 = (lane & 7) * 4;
+  epi_in<M> in[2];
+  auto at = [&](int b, int64_t (&o)[4], int& col) __attribute__((always_inline)) {
+    const int c = col0 + (b % NB) * 32 + c4;
+    col = c < g.N ? c : g.N - 4;
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      const int64_t r = row0 + (b / NB) * 32 + it * 8 + (lane >> 3);
+      o[it] = (r < g.M ? r : g.M - 1) * g.N + col;
+    }
+  };
+  int64_t o[4];
+  int col;
+  at(0, o, col);
+  in[0].load(g.epi, o, col);
+#pragma unroll
+  for (int b = 0; b < MB * NB; ++b) {
+    const int i = b / NB, j = b % NB;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4)
+      *reinterpret_cast<f32x4*>(&stage[l32 * EPI_LD + q4 * 8 + kh * 4]) =
+          f32x4{acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]};
+    if (b + 1 < MB * NB) {
+      int64_t o1[4];
+      int col1;
+      at(b + 1, o1, col1);
+      in[(b + 1) & 1].load(g.epi, o1, col1);
+    }
+    wave_lds_sync();
+    const epi_in<M>& q = in[b & 1];
+    at(b, o, col);
+    const bool col_in = col0 + j * 32 + c4 < g.N;
+    const f32x4 inv4 = ld4(inv + col);
+#pragma unroll
+    for (int it = 0; it < 4; ++it) {
+      f32x4 v = *reinterpret_cast<const f32x4*>(&stage[(it * 8 + (lane >> 3)) * EPI_LD + c4]);
+      const bool in_m = col_in && row0 + i * 32 + it * 8 + (lane >> 3) < g.M;
+      v *= inv4;
+      if constexpr ((M & EM_BIAS) != 0) v += q.bias;
+      if constexpr ((M & EM_ADD_PRE) != 0) v += q.pre[it];
+      if constexpr ((M & EM_SAVE_PRE) != 0) {
+        if (in_m) st4(g.epi.save_pre + o[it], v);
+      }
+      if constexpr ((M & EM_ACT1) != 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = silu_f(v[c]);
+      }
+      if constexpr ((M & EM_ACT2) != 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] *= dsilu_f(q.z[it][c]);
+      }
+      if constexpr ((M & EM_MUL) != 0) v *= q.mul[it];
+      if constexpr ((M & EM_ADD_POST) != 0) v += q.post[it];
+      if constexpr ((M & EM_OUT) != 0) {
+        if (in_m) st4(g.epi.out + o[it], v);
+      }
+      if constexpr ((M & EM_OUT2) != 0) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] *= dsilu_f(q.z2[it][c]);
+        if (in_m) st4(g.epi.out2 + o[it], v);
+      }
+    }
+    wave_lds_sync();
+  }
+}
+
+bool epilogue_listed(unsigned mask) {
+  switch (mask) {
+#define GP_EM_CASE(M) case M:
+    GP_EM_LIST(GP_EM_CASE)
+#undef GP_EM_CASE
+    return true;
+    default: return false;
+  }
+}
+
+// WAVES wavefronts stacked along M, each with MB x NB blocks of 32x32.  A goes from memory straight into the registers of the
+// wavefront that multiplies it, in operand order, and is split there: no LDS traffic, no barrier and no second split of the
+// same values by another wavefront of the workgroup.  The planes of W, 4 KB per 32 columns and 32 k, come through LDS by
+// global->LDS loads, NBUF chunks of them, and are read once per wavefront.  JB column blocks are multiplied together; TD and
+// WD: whether the sums of a group (added to the result while the next group is multiplied) and its planes are double.
+// The activations of the next chunk are requested as soon as this one's are split.  (Splitting the next chunk beside the
+// products of this one, or wavefronts of 64 x 128, ran out of registers: 1.41 -> 1.8 ms at 43380 x 2048 x 2048.)
+template <int MB, int NB, int WAVES, int NBUF, int OCC, int JB, int TD, int WD>
+__global__ void __launch_bounds__(64 * WAVES, OCC)
+gemm_planes_kernel(const gemm_args g) {
+  constexpr int BM = 32 * MB * WAVES, BN = 32 * NB, NG = NB / JB;   // NG groups of column blocks
+  constexpr int CHUNK_B = NB * 2 * GROUP_B;             // bytes of a chunk
+  constexpr int PB = CHUNK_B / 1024 / WAVES;            // global->LDS loads per wavefront and chunk
+  static_assert(CHUNK_B % (1024 * WAVES) == 0, "the loads of a chunk are dealt evenly");
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  char* lds = reinterpret_cast<char*>(smem);
+
+  const int tiles_n = (g.N + BN - 1) / BN;
+  const int tiles_m = (int)((g.M + BM - 1) / BM);
+  const int tile = xcd_remap(blockIdx.x, tiles_m * tiles_n);
+  const int64_t m0 = (int64_t)(tile / tiles_n) * BM;
+  const int n0 = (tile % tiles_n) * BN;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm0 = wave * (32 * MB);
+  const int kh = lane >> 5, l32 = lane & 31;
+  const int n_ch = (g.K + 31) / 32, n_st = 2 * n_ch;   // the planes of a K that is no multiple of 32 end in zeros
+
+  const char* srcA[MB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int64_t row = m0 + wm0 + i * 32 + l32;
+    srcA[i] = reinterpret_cast<const char*>(g.A + (row < g.M ? row : g.M - 1) * g.lda + kh * 8);
+  }
+  f32x4 ra[2][MB][2];   // [step][block][half]: a chunk on its way
+  auto fetchA = [&](int c) __attribute__((always_inline)) {
+    c = c < n_ch ? c : n_ch - 1;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const int k = c * 32 + ks * 16 < g.K ? c * 32 + ks * 16 : 0;   // past the end: any values, their weights are zero
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) ra[ks][i][h] = *reinterpret_cast<const f32x4*>(srcA[i] + (int64_t)k * 4 + h * 16);
+    }
+  };
+  // KB q of a chunk: column block q / 4, step (q % 4) / 2, plane q % 2
+  const int nb = (g.N + 31) / 32;                       // column blocks of the planes; past the last: that one again, never stored
+  const char* srcB = reinterpret_cast<const char*>(g.B) + lane * 16;
+  auto issueB = [&](int c, int buf) __attribute__((always_inline)) {
+    c = c < n_ch ? c : n_ch - 1;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+      const int q = wave * PB + i;
+      const int blk = n0 / 32 + q / 4 < nb ? n0 / 32 + q / 4 : nb - 1;
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(srcB + ((int64_t)blk * n_st + 2 * c) * GROUP_B + (q % 4) * FRAG_B),
+                                       (lds_void_ptr)(lds + buf * CHUNK_B + q * 1024), 16, 0, 0);
+    }
+  };
+
+  // W takes the place of the first operand, so a lane's column of the result is one row of A, whose scale is then a lane's
+  f16x8 hi[2][MB], lo[2][MB];   // [step][block]
+  float inv[MB];
+  auto splitA = [&]() __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      uint32_t m = 0;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            const uint32_t b = __float_as_uint(ra[ks][i][h][c]) & 0x7FFFFFFFu;
+            m = b > m ? b : m;
+          }
+      m = max_halves(m);   // the other 8 k of the row's steps
+      const int se = scale_exp(m);
+      const float sc = pow2(se);
+      inv[i] = pow2(-14 - se);   // the columns' factors carry 2^14 back: the sums stay where the products of the fp32 values are
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        float v[8];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) v[c] = ra[ks][i][0][c] * sc, v[4 + c] = ra[ks][i][1][c] * sc;
+        split8(v, hi[ks][i], lo[ks][i]);
+      }
+    }
+  };
+
+  f32x16 acc[MB][NB], t[TD][MB][JB];
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; ++j)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+  f16x8 w[WD][2][PL][JB];   // [parity of the group][step][plane][block]
+  auto readW = [&](int buf, int q) __attribute__((always_inline)) {
+    const char* sb = lds + buf * CHUNK_B + lane * 16 + q * JB * 2 * GROUP_B;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int jj = 0; jj < JB; ++jj)
+#pragma unroll
+        for (int p = 0; p < PL; ++p) w[q % WD][ks][p][jj] = *reinterpret_cast<const f16x8*>(sb + (jj * 2 + ks) * GROUP_B + p * FRAG_B);
+  };
+  auto products = [&](int q) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int jj = 0; jj < JB; ++jj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) t[q % TD][i][jj][v] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int x = 0; x < 3; ++x)
+#pragma unroll
+        for (int i = 0; i < MB; ++i)
+#pragma unroll
+          for (int jj = 0; jj < JB; ++jj)
+            t[q % TD][i][jj] = __builtin_amdgcn_mfma_f32_32x32x16_f16(w[q % WD][ks][x == 1][jj], x == 0 ? lo[ks][i] : hi[ks][i],
+                                                                     t[q % TD][i][jj], 0, 0, 0);
+  };
+  auto add = [&](int q) __attribute__((always_inline)) {   // a group's sums over the chunk
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int jj = 0; jj < JB; ++jj)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[i][q * JB + jj][v] = __builtin_fmaf(t[q % TD][i][jj][v], inv[i], acc[i][q * JB + jj][v]);
+  };
+
+#pragma unroll
+  for (int c = 0; c < NBUF - 1; ++c) issueB(c, c);
+  __builtin_amdgcn_sched_barrier(0);
+  fetchA(0);
+  __builtin_amdgcn_sched_barrier(0);
+  wait_vmcnt_lgkmcnt0<4 * MB>();
+  __syncthreads();
+  int bb = 0;
+  for (int c = 0; c < n_ch; ++c) {
+    readW(bb, 0);
+    splitA();
+    issueB(c + NBUF - 1, bb == 0 ? NBUF - 1 : bb - 1);
+    __builtin_amdgcn_sched_barrier(0);   // the wait at the end counts on this order of the loads
+    fetchA(c + 1);
+#pragma unroll
+    for (int q = 0; q < NG; ++q) {
+      if (WD == 2 && q + 1 < NG) readW(bb, q + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      products(q);
+      if (WD == 1 && q + 1 < NG) readW(bb, q + 1);
+      if (TD == 2 && q > 0) add(q - 1);   // while this group's products run
+      if (TD == 1) add(q);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (TD == 2) add(NG - 1);
+    wait_vmcnt_lgkmcnt0<4 * MB + (NBUF - 2) * (PB + 4 * MB)>();
+    __syncthreads();
+    bb = bb == NBUF - 1 ? 0 : bb + 1;
+  }
+  wait_vmcnt_lgkmcnt0<0>();
+  __syncthreads();
+  float* stage = smem + wave * (32 * EPI_LD);
+  const float* inv_n = reinterpret_cast<const float*>(reinterpret_cast<const char*>(g.B) + (int64_t)nb * n_st * GROUP_B);
+  switch (g.epi_mask) {   // uniform
+#define GP_EM_CASE(M) case M: epilogue_blocks<MB, NB, M>(g, acc, stage, m0 + wm0, n0, inv_n); break;
+    GP_EM_LIST(GP_EM_CASE)
+#undef GP_EM_CASE
+    default: break;   // not launched with any other mask
+  }
+}
+
+template <int MB, int NB, int WAVES, int NBUF, int OCC, int JB, int TD, int WD>
+int launch_planes(gp_ctx* ctx, gemm_args& g) {
+  constexpr int BM = 32 * MB * WAVES, BN = 32 * NB;
+  const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
+  if (tiles > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
+  static char name[48];
+  if (!name[0]) snprintf(name, sizeof(name), "gemm_f32x2_%dx%d", BM, BN);
+  const double mnk = (double)g.M * g.N * g.K;
+  gp_prof_scope prof(ctx, name, 2.0 * mnk, 4.0 * ((double)g.M * g.K + (double)g.K * g.N + (double)g.M * g.N));
+  constexpr size_t lds_main = (size_t)NBUF * NB * 2 * GROUP_B;
+  constexpr size_t lds_epi = sizeof(float) * WAVES * 32 * EPI_LD;
+  constexpr size_t lds = lds_main > lds_epi ? lds_main : lds_epi;
+  static bool raised = false;
+  if (!raised && lds > 64 * 1024) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_planes_kernel<MB, NB, WAVES, NBUF, OCC, JB, TD, WD>),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+      return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
+    raised = true;
+  }
+  gemm_planes_kernel<MB, NB, WAVES, NBUF, OCC, JB, TD, WD><<<dim3((unsigned)tiles), 64 * WAVES, lds, ctx->stream>>>(g);
+  GP_LAUNCH_CHECK(ctx, "gemm_planes_kernel");
+  return GP_OK;
+}
+
+inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
+
+}  // namespace
+
+size_t gp_planes_bytes(int N, int K) {
+  const size_t nb = (size_t)(N + 31) / 32;
+  return nb * (size_t)((K + 31) / 32 * 2) * GROUP_B + nb * 32 * sizeof(float);
+}
+
+// From K = 64 on the error is the smaller one (above).  At K = 64 a short product is launch and epilogue, which both forms have
+// (13323 x 256 x 64: 10.7 us, three bf16 parts 10.0; 43380 x 256 x 64, A W^T: 19.7, 25.4); the conversion of all weights of a call
+// is one launch of 4 to 5 us.
+bool gp_planes_take(const gp_ctx* ctx, int64_t M, int N, int K) {
+  return ctx->f32_split && !ctx->gemm_bf16 && K % 16 == 0 && N % 4 == 0 && N >= 64 && N <= 8192 && K <= 8192 &&
+         (K >= 128 || (K >= 64 && M >= 16384));
+}
+
+int gp_weight_planes::run() {
+  if (n == 0) return GP_OK;
+  plane_jobs pj{};
+  int most = 0;
+  double bytes = 0.0;
+  for (int i = 0; i < n; ++i) {
+    pj.j[i] = jobs[i];
+    most = std::max(most, (jobs[i].N + 31) / 32);
+    bytes += 8.0 * jobs[i].N * jobs[i].K;
+  }
+  gp_prof_scope prof(ctx, "make_planes", 0.0, bytes);
+  make_planes_kernel<<<dim3((unsigned)most, (unsigned)n), 64 * PREP_WAVES, 0, ctx->stream>>>(pj);
+  GP_LAUNCH_CHECK(ctx, "make_planes_kernel");
+  return GP_OK;
+}
+
+namespace {
+
+// GP_OK, an error, or 1: not taken
+int gemm_planes(gp_ctx* ctx, const float* A, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
+  gemm_args g{};
+  g.A = A; g.B = static_cast<const float*>(planes); g.M = M; g.N = N; g.K = K; g.lda = K;
+  g.epi = epi;
+  g.vecC = al16(epi.bias) && al16(epi.add_pre) && al16(epi.save_pre) && al16(epi.zsrc) && al16(epi.mul) && al16(epi.add_post) &&
+           al16(epi.out) && al16(epi.out2) && al16(epi.z2src);
+  g.epi_mask = gp_epilogue_mask(g.epi, g.vecC);
+  if (!planes || !al16(A) || !epilogue_listed(g.epi_mask)) return 1;
+  GP_REQUIRE(ctx, M >= 0 && gp_planes_take(ctx, 16384, N, K), "gemm: planes of a shape that has none");
+  if (M == 0) return GP_OK;
+  // Tiles: 128 x 256 where there are enough of them for several rounds of two per compute unit (43380 x 2048 x 2048: 1.41 ms, with
+  // 128 x 128 1.57; 13323 x 1024 x 1024: 0.124, 0.139; 22000 x 512 x 512, 344 tiles: 0.060, 0.055); 64 x 64 where a launch of 128 x
+  // 128 leaves compute units idle or the matrix has 64 columns (3000 x 256 x 256: 10.0 us, 128 x 128 14.1; 20000 x 128 x 128: 9.8,
+  // 11.0; 13323 x 256 x 256, 210 tiles: 16.2, 15.3).  The values of the result do not depend on the choice.
+  const int64_t rows = (M + 127) / 128;
+  if (N >= 512 && rows * ((N + 255) / 256) >= 400) return launch_planes<1, 8, 4, 2, 2, 1, 2, 2>(ctx, g);
+  if (N > 64 && rows * ((N + 127) / 128) >= 192) return launch_planes<1, 4, 4, 2, 3, 1, 1, 1>(ctx, g);
+  return launch_planes<1, 2, 2, 3, 3, 1, 2, 2>(ctx, g);
+}
+
+}  // namespace
+
+int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
+  const int rc = gemm_planes(ctx, A, planes, M, N, K, epi);
+  return rc == 1 ? gp_gemm_nn(ctx, A, W, M, N, K, epi) : rc;
+}
+int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
+  const int rc = gemm_planes(ctx, A, planes, M, N, K, epi);
+  return rc == 1 ? gp_gemm_nt(ctx, A, W, M, N, K, epi) : rc;
+}

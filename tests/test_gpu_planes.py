@@ -1,0 +1,90 @@
+"""fp32 products with operands as two fp16 parts (csrc/gemm_planes.hip), through the Hadamard block whose dense layers they are."""
+import pytest
+import torch
+
+import synth
+from tests import helpers as H
+from tests.test_gpu_block_D import _case
+
+pytestmark = pytest.mark.gpu
+
+
+# (emb, int_emb, slabs, nx, ny): which tile of the forward products, and what is partial in it
+SHAPES = [
+    (128, 64, 1, 2, 2),      # 64 x 64 tiles, the last rows a part of one; K = 64 of the up-projection stays with the other kernels
+    (272, 144, 2, 2, 2),     # K = 272 and 144 end in half a chunk of 32, N = 272 in half a block of 32 columns
+    (192, 64, 12, 4, 3),     # 128 x 128 tiles, the second one half empty
+    (64, 64, 16, 4, 4),      # K = 64, taken for its many rows
+    (512, 64, 16, 5, 4),     # 128 x 256 tiles
+]
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2203_09697_amd as gp
+    gp.load()
+    return gp
+
+
+@pytest.fixture(scope="module")
+def ctx(lib):
+    return lib.Context(0)
+
+
+def _block(lib, ctx, w, t, e, W, m, gup, split):
+    from paper_2203_09697_amd.stack import StackD
+    lib.gp_set_f32_gemm(ctx, split)
+    try:
+        st = StackD(ctx, w.dims, [lib.weights_to_device(W)], t, lib.gp_basis_forward(ctx, w.dims, e, t))
+        out = st.forward(H.to_dev(m, torch.float32)).cpu().numpy()
+        gm, gw = st.backward(H.to_dev(gup, torch.float32))
+        return out, gm.cpu().numpy(), {k: v.cpu().numpy() for k, v in gw[0].items()}
+    finally:
+        lib.gp_set_f32_gemm(ctx, 1)
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("emb,int_emb,slabs,nx,ny", SHAPES, ids=["%d_%d_%d" % s[:3] for s in SHAPES])
+def test_block_against_the_oracle(lib, ctx, emb, int_emb, slabs, nx, ny):
+    # Relative error of a product: 1.6e-7 at K = 2048 and less below; ten layers in a row and back keep it under 2e-6.  Sums over
+    # all edges (weights) collect what the edges' rounding has in common: 1e-5 of their norm.  The fp32 instruction on the same
+    # inputs is no closer (its products are 2 to 5 times further off); 1.5 leaves room for luck in a single norm.
+    w = synth.get_workload("cfg2", emb=emb, int_emb=int_emb)
+    pos, ref, e, t = _case(lib, ctx, w, 3, synth.slab_adsorbate_positions(slabs, nx, ny, 3, 5, seed=3))
+    E = len(ref["src"])
+    W = synth.weights_D(w.dims, seed=5, bias_scale=0.1)
+    m, gup = synth.edge_embeddings(E, emb, seed=6)
+    want = H.oracle_stack_D(ref, H.oracle_basis_D(pos, ref, w.dims), w.dims, [W], m, gup)
+    got, plain = (_block(lib, ctx, w, t, e, W, m, gup, s) for s in (1, 0))
+    for i in range(2):
+        err = H.rel_l2(got[i], want[i])
+        print("E=%d %s: two fp16 parts %.2e, fp32 instruction %.2e" % (E, ("out", "grad_m")[i], err, H.rel_l2(plain[i], want[i])))
+        assert err < 2e-6 and err < 1.5 * H.rel_l2(plain[i], want[i])
+        assert H.row_err(got[i], want[i]) < 1e-5
+    for k, ref_g in want[2][0].items():
+        assert H.rel_l2(got[2][k], ref_g) < 1e-5, k
+
+
+def test_values_of_every_size(lib, ctx):
+    # Gradient rows 2^-90 to 2^60 of each other's size, a row of zeros, values over 2^12 within every row and weights over 2^40
+    # within every column: a row keeps its relative error, since the scale is its own.  All weights but two are zero and so is m,
+    # which makes the block linear in its gradient: silu'(0) = 1/2 in both layers.
+    w = synth.get_workload("cfg2", emb=128, int_emb=64, n_res_before=0, n_res_after=0)
+    pos, ref, e, t = _case(lib, ctx, w, 4, synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4))
+    E = len(ref["src"])
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(1)
+    W_lin = torch.randn(128, 128, generator=rng) * torch.exp2(torch.randint(-20, 21, (1, 128), generator=rng).float())
+    W_ji = torch.randn(128, 128, generator=rng)
+    W["W_lin"], W["W_ji"] = W_lin.numpy(), W_ji.numpy()
+    m = torch.zeros(E, 128)
+    rows = torch.exp2(torch.randint(-90, 61, (E, 1), generator=rng).float())
+    gup = torch.randn(E, 128, generator=rng) * rows * torch.exp2(-torch.randint(0, 13, (E, 128), generator=rng).float())
+    gup[7] = 0
+    _, gm, _ = _block(lib, ctx, w, t, e, W, m.numpy(), gup.numpy(), 1)
+    # dm = gup + (gup / 2) W_lin^T / 2 W_ji^T
+    g = gup.double()
+    want = g + 0.25 * (g @ W_lin.double().t()) @ W_ji.double().t()
+    err = (torch.as_tensor(gm).double() - want).norm(dim=1) / want.norm(dim=1).clamp_min(1e-300)
+    err[7] = torch.as_tensor(gm)[7].abs().max()
+    assert float(err.max()) < 1e-6, err.max()
