@@ -114,3 +114,12 @@ struct gp_weight_planes {
 // gp_gemm_nn / gp_gemm_nt with the planes of the weight matrix at hand (NULL: the general kernels)
 int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
+// A^T B over the rows in the same form: tiles, splits of the rows, whether it is taken, launch with gp_gemm_tn's argument block
+struct gp_tn_planes_plan {
+  bool big;       // 256 x 256 tiles instead of 128 x 128
+  int tiles_m, splits;
+  int64_t per;    // rows of a split
+};
+gp_tn_planes_plan gp_planes_tn_plan(int64_t rows, int M, int N);
+bool gp_planes_tn_take(const gp_ctx* ctx, int64_t rows);
+int gp_planes_tn_launch(gp_ctx* ctx, void* args, const gp_tn_planes_plan& plan);

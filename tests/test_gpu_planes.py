@@ -61,8 +61,9 @@ def test_block_against_the_oracle(lib, ctx, emb, int_emb, slabs, nx, ny):
         print("E=%d %s: two fp16 parts %.2e, fp32 instruction %.2e" % (E, ("out", "grad_m")[i], err, H.rel_l2(plain[i], want[i])))
         assert err < 2e-6 and err < 1.5 * H.rel_l2(plain[i], want[i])
         assert H.row_err(got[i], want[i]) < 1e-5
-    for k, ref_g in want[2][0].items():
-        assert H.rel_l2(got[2][k], ref_g) < 1e-5, k
+    worst = {s: max(H.rel_l2(r[2][k], g) for k, g in want[2][0].items()) for s, r in (("parts", got), ("instruction", plain))}
+    print("weight gradients: two fp16 parts %.2e, fp32 instruction %.2e" % (worst["parts"], worst["instruction"]))
+    assert worst["parts"] < 1e-5 and worst["parts"] < 1.5 * worst["instruction"]
 
 
 def test_values_of_every_size(lib, ctx):
@@ -88,3 +89,27 @@ def test_values_of_every_size(lib, ctx):
     err = (torch.as_tensor(gm).double() - want).norm(dim=1) / want.norm(dim=1).clamp_min(1e-300)
     err[7] = torch.as_tensor(gm)[7].abs().max()
     assert float(err.max()) < 1e-6, err.max()
+
+
+def test_weight_gradient_columns_of_every_size(lib, ctx):
+    # Columns of the activations over 2^16 and rows over 2^20, a column of zeros: with W_ji = 0 the layer's gradient is m^T dz with dz =
+    # (gup / 2) W_lin^T / 2 for any m.  A column that is not far below 2^-17 of the largest of its 32 keeps its relative error.
+    w = synth.get_workload("cfg2", emb=128, int_emb=64, n_res_before=0, n_res_after=0)
+    pos, ref, e, t = _case(lib, ctx, w, 4, synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4))
+    E = len(ref["src"])
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(2)
+    W_lin = torch.randn(128, 128, generator=rng)
+    W["W_lin"] = W_lin.numpy()
+    m = torch.randn(E, 128, generator=rng) * torch.exp2(-torch.randint(0, 17, (1, 128), generator=rng).float())
+    m *= torch.exp2(torch.randint(-10, 11, (E, 1), generator=rng).float())
+    m[:, 5] = 0
+    gup = torch.randn(E, 128, generator=rng)
+    _, _, gw = _block(lib, ctx, w, t, e, W, m.numpy(), gup.numpy(), 1)
+    want = 0.25 * m.double().t() @ (gup.double() @ W_lin.double().t())
+    got = torch.as_tensor(gw["W_ji"]).double()
+    err = (got - want).norm(dim=1) / want.norm(dim=1).clamp_min(1e-300)
+    err[5] = got[5].abs().max()
+    assert float(err.max()) < 1e-6, err.max()
+    want_b = 0.25 * (gup.double() @ W_lin.double().t()).sum(0)
+    assert H.rel_l2(gw["b_ji"], want_b.numpy()) < 1e-6
