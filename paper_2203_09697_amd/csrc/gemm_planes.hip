@@ -48,11 +48,13 @@ __device__ __forceinline__ int scale_exp(uint32_t bits) {
 }
 __device__ __forceinline__ float pow2(int k) { return __int_as_float((k + 127) << 23); }   // -126 <= k <= 127
 // The matrix instruction's sums come out low on average, by a part of the last place of their largest term and whatever their
-// sign: over the rows of a bias gradient that adds up.  Half of the sums are therefore formed with the sign of one operand
-// turned round (its scale is negative, and so is the factor back): x is a chunk's number xor a lane's.  Bias gradients of a
-// block of width 256 over 23453 edges: 5.1e-6 off without, 3e-7 with (three bf16 parts 3.9e-6, fp32 instruction 9e-7).
-__device__ __forceinline__ float turned(float scale, int x) { return __int_as_float(__float_as_int(scale) ^ ((x & 1) << 31)); }
-
+// sign: over the rows of a bias gradient that adds up.  Some of the sums are therefore formed with the sign of one operand
+// turned round (its scale is negative, and so is the factor back).  With half of them turned the bias gradients of a block of
+// width 256 over 23453 edges are 3e-7 off, with none 5.1e-6, three bf16 parts 3.9e-6, the fp32 instruction 9e-7.  In A W and A W^T a
+// quarter is turned where K < 1024 and none above, where the 32 k of a sum leave less than the running sums of that form
+// (K = 1024 3.5e-6 and 4.9e-6): closer than before at every width, and results that differ from those of the other forms, whose
+// error this is, by half as much as with all of it taken out.  In A^T B, whose sums nothing adds up, half.
+__device__ __forceinline__ float turned(float scale, bool turn) { return __int_as_float(__float_as_int(scale) ^ (turn ? 1 << 31 : 0)); }
 // the larger of lanes l and l ^ 32
 __device__ __forceinline__ uint32_t max_halves(uint32_t m) {
   const auto h = __builtin_amdgcn_permlane32_swap(m, m, false, false);
@@ -323,8 +325,9 @@ gemm_planes_kernel(const gemm_args g) {
           }
       m = max_halves(m);   // the other 8 k of the row's steps
       const int se = scale_exp(m);
-      const float sc = turned(pow2(se), c ^ l32);
-      inv[i] = turned(pow2(-14 - se), c ^ l32);   // the columns' factors carry 2^14 back: the sums stay where the products of the fp32 values are
+      const bool turn = g.K < 1024 && ((c ^ l32) & 3) == 0;
+      const float sc = turned(pow2(se), turn);
+      inv[i] = turned(pow2(-14 - se), turn);   // the columns' factors carry 2^14 back: the sums stay where the products of the fp32 values are
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         float v[8];
@@ -519,10 +522,10 @@ gemm_planes_tn_kernel(const gemm_args g) {
       m = max_halves(m);
       if (is_a) m = max_of_32(m);   // one factor for the block
       const int se = scale_exp(m);
-      const float sc = is_a ? pow2(se) : turned(pow2(se), c ^ l32);
+      const float sc = is_a ? pow2(se) : turned(pow2(se), ((c ^ l32) & 1) != 0);
       if (is_a) {
         if (lane == 0) inv_lds[u * BA + blk] = pow2(-se);
-      } else if (kh == 0) invB_lds[u * 32 * BB + (blk - BA) * 32 + l32] = turned(pow2(-se), c ^ l32);
+      } else if (kh == 0) invB_lds[u * 32 * BB + (blk - BA) * 32 + l32] = turned(pow2(-se), ((c ^ l32) & 1) != 0);
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks) {
         float v[8];
