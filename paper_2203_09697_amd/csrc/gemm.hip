@@ -467,7 +467,7 @@ int gp_gemm_nt(gp_ctx* ctx, const float* A, const float* Bt, int64_t M, int N, i
 
 // the conditions of the global->LDS bf16 kernel on the shape (its operands must also be bf16 and 16-byte aligned)
 bool gp_gemm_nt_takes_lowrank(const gp_ctx* ctx, int64_t M, int N, int K) {
-  return ctx->gemm_bf16 && M >= 8192 && N > 128 && N % 4 == 0 && K % 64 == 0 && K >= 128;
+  return ctx->gemm_bf16 && M >= 8192 && N > 128 && N % 4 == 0 && K % 64 == 0 && K > 128;
 }
 
 // whether gp_gemm_nt2 can run as one launch (the conditions of the global->LDS bf16 kernel)

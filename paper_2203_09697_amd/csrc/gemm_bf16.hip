@@ -967,9 +967,7 @@ __device__ __forceinline__ void wait_vmcnt_lgkmcnt0() {
   __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
 }
 
-// REFILL = false: the contraction is at most STAGES slabs long, the prologue has requested all of it and the loop requests
-// nothing more (with refills, a 128-long contraction re-read its last slab twice: twice the load traffic).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES, bool REFILL = true>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int BK, int STAGES>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, WAVES_M * WAVES_N == 8 ? 1 : 2)
 gemm_dl_kernel(const gemm_args g) {
   constexpr int NW = WAVES_M * WAVES_N;
@@ -1084,8 +1082,7 @@ gemm_dl_kernel(const gemm_args g) {
       mfma_group(ks);
       __builtin_amdgcn_sched_barrier(0);
     }
-    if (REFILL) wait_vmcnt_lgkmcnt0<(STAGES - 2) * PER>();
-    else wait_vmcnt_lgkmcnt0<0>();   // nothing is requested in the loop: every slab's loads were issued in the prologue
+    wait_vmcnt_lgkmcnt0<(STAGES - 2) * PER>();
     __syncthreads();
     read_frags(st1, 0);
     __builtin_amdgcn_sched_barrier(0);
@@ -1106,7 +1103,7 @@ gemm_dl_kernel(const gemm_args g) {
 #pragma unroll
           for (int u = 0; u < LPM; ++u) {
             const int q = (i * NB + j) * LPM + u;
-            if (REFILL && q < PER) {
+            if (q < PER) {
               const int64_t d2 = second ? (wave * PER + q < A_LOADS ? dA : dB) : 0;   // uniform
               __builtin_amdgcn_global_load_lds((global_void_ptr)(src[q] + kb + d2), (lds_void_ptr)(dst + q * 1024), 16, 0, 0);
             }
@@ -1121,12 +1118,12 @@ gemm_dl_kernel(const gemm_args g) {
   tile_epilogue<MB, NB, MODE_NT, NW>(g, acc, smem, m0, n0, wm0, wn0, 0);
 }
 
-template <int BM, int BN, int WMS, int WNS, int BK, int STAGES, bool REFILL = true>
+template <int BM, int BN, int WMS, int WNS, int BK, int STAGES>
 int launch_dl(gp_ctx* ctx, gemm_args& g) {
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
   static char name[48];
-  if (!name[0]) snprintf(name, sizeof(name), "gemm_bf16_dl_nt_%dx%d%s", BM, BN, REFILL ? "" : "_shortk");
+  if (!name[0]) snprintf(name, sizeof(name), "gemm_bf16_dl_nt_%dx%d", BM, BN);
   const double mnk = (double)g.M * g.N * g.K;
   gp_prof_scope prof(ctx, name, 2.0 * mnk,
                      2.0 * (double)g.M * g.K + 2.0 * (double)g.K * g.N + ((g.epi.bf16 & EPI_BF_OUT) ? 2.0 : 4.0) * (double)g.M * g.N);
@@ -1139,13 +1136,12 @@ int launch_dl(gp_ctx* ctx, gemm_args& g) {
     return gp_fail(ctx, GP_BAD_ARG, "gemm: low-rank epilogue factor needs rank 1..16 and 16-byte aligned epilogue matrices");
   static bool raised = false;
   if (!raised && lds > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dl_kernel<BM, BN, WMS, WNS, BK, STAGES, REFILL>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_dl_kernel<BM, BN, WMS, WNS, BK, STAGES>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
     raised = true;
   }
-  if (!REFILL && g.K > BK * STAGES) return gp_fail(ctx, GP_BAD_ARG, "gemm: contraction longer than the ring of the no-refill kernel");
-  gemm_dl_kernel<BM, BN, WMS, WNS, BK, STAGES, REFILL><<<dim3((unsigned)tiles), 64 * NW, lds, ctx->stream>>>(g);
+  gemm_dl_kernel<BM, BN, WMS, WNS, BK, STAGES><<<dim3((unsigned)tiles), 64 * NW, lds, ctx->stream>>>(g);
   GP_LAUNCH_CHECK(ctx, "gemm_dl_kernel");
   return GP_OK;
 }
@@ -1403,15 +1399,35 @@ int dispatch(gp_ctx* ctx, gemm_args& g, int splits) {
     if (g.vecA && g.vecB) return launch_v<BM, BN, WMS, WNS, MODE, true>(ctx, g, splits);                            \
     return launch_v<BM, BN, WMS, WNS, MODE, false>(ctx, g, splits);                                                 \
   } while (0)
-  // tall activations times a wide weight matrix, both bf16 and k-contiguous: global->LDS loads, 256x256 tiles
-  if (MODE == MODE_NT && g.a_bf16 && g.b_bf16 && g.M >= 8192 && g.N > 128 && g.K % 64 == 0 && g.K >= 128 &&
-      g.lda % 8 == 0 && g.ldb % 8 == 0 && (!g.A2 || g.K % 128 == 0))
-    return g.K <= 128 ? launch_dl<256, 256, 2, 4, 64, 2, false>(ctx, g) : launch_dl<256, 256, 2, 4, 64, 2>(ctx, g);
+  // tall activations times a wide weight matrix, both bf16 and k-contiguous: global->LDS loads, 256x256 tiles, one per compute
+  // unit.  A contraction of 128 is all prologue and epilogue and runs in the smaller tiles below (20000 x 1024 x 128: 24.6 -> 18.2
+  // us, 300636: 220 -> 215).
+  if (MODE == MODE_NT && g.a_bf16 && g.b_bf16 && g.M >= 8192 && g.N > 128 && g.K % 64 == 0 && g.K > 128 &&
+      g.lda % 8 == 0 && g.ldb % 8 == 0 && (!g.A2 || g.K % 128 == 0)) {
+    // Smaller tiles where those leave more than half of the chip idle or end in a round that is mostly empty (us; the three
+    // products of a block: low-rank gate / SiLU / two operand pairs): 12700 x 512, 100 tiles, 34 / 24 / 32, in 128x256 tiles 21 / 17 /
+    // 22; 9000 x 256, 36 tiles, 27 / 18 / 21, in 128x128 12 / 9 / 11; 20000 x 1024, 316 tiles, 87 / 71 / 115 and 72 / 60 / 100; 30000 x
+    // 768, 354 tiles, 78 / 63 / 96 and 71 / 58 / 94.  Not so: 40000 x 256, 157 tiles, 28 / 19 / 24 and 26 / 20 / 27; 63420 x 512, 496
+    // tiles, 74 / 57 / 85 and 79 / 67 / 93; 300636 x 1024 909 / 787 / 1252 and 1163 / 1065 / 1719; 35500 x 1024, 556 tiles (0.72 of three
+    // rounds), 135 / 109 / 179 and 123 / 109 / 179 one after the other but 1.5 % slower within a forward pass.
+    const int64_t tm = (g.M + 255) / 256, tiles = tm * ((g.N + 255) / 256), rounds = (tiles + 255) / 256;
+    if (tiles <= 128 || (rounds > 1 && 10 * tiles < 7 * 256 * rounds)) {
+      const int64_t half = (g.M + 127) / 128 * ((g.N + 255) / 256);
+      if (half > 128 && half <= 256) return launch_dl<128, 256, 2, 4, 64, 2>(ctx, g);   // one round of them
+      return launch_dl<128, 128, 2, 2, 64, 2>(ctx, g);
+    }
+    return launch_dl<256, 256, 2, 4, 64, 2>(ctx, g);
+  }
   // ... times a narrow one (a long contraction into 33..128 columns): the same kernel streams the activations, which is all
-  // that bounds these products, through a deeper ring; 8 wavefronts of 64x64 or 32x64
+  // that bounds these products, through a deeper ring; 8 wavefronts of 64x64 or 32x64.  Up to 32768 rows 256 of them a tile leave
+  // half of the chip without work: 12700 x 64, K = 512 11.3 us, in 64x64 tiles 6.4, K = 1024 15.6 and 8.1; 20000 x 64, K = 1024 14.6,
+  // in 128x64 tiles 11.2 (64x64: 12.0), 30000 x 64, K = 768 13.5 and 12.3; 20000 x 128, K = 1024 20.0, in 128x128 tiles 13.7; 35500 x
+  // 128, K = 1024 22.0 and 26.4.
   if (MODE == MODE_NT && g.a_bf16 && g.b_bf16 && g.M >= 8192 && g.N > 32 && g.N <= 128 && g.K % 64 == 0 && g.K >= 256 &&
       g.lda % 8 == 0 && g.ldb % 8 == 0 && !g.A2 && !g.epi.lr_a) {
-    if (g.N > 64) return launch_dl<256, 128, 4, 2, 64, 3>(ctx, g);
+    if (g.N > 64) return g.M <= 32768 ? launch_dl<128, 128, 4, 2, 64, 3>(ctx, g) : launch_dl<256, 128, 4, 2, 64, 3>(ctx, g);
+    if (g.M <= 16384) return launch_dl<64, 64, 2, 2, 64, 3>(ctx, g);
+    if (g.M <= 32768) return launch_dl<128, 64, 4, 1, 64, 3>(ctx, g);
     return launch_dl<256, 64, 8, 1, 64, 3>(ctx, g);
   }
   if (g.A2) return gp_fail(ctx, GP_BAD_ARG, "gemm: a second operand pair is only taken by the global->LDS kernel");

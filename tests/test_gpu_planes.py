@@ -20,13 +20,6 @@ SHAPES = [
 
 
 @pytest.fixture(scope="module")
-def lib():
-    import paper_2203_09697_amd as gp
-    gp.load()
-    return gp
-
-
-@pytest.fixture(scope="module")
 def ctx(lib):
     return lib.Context(0)
 
@@ -49,7 +42,7 @@ def test_block_against_the_oracle(lib, ctx, emb, int_emb, slabs, nx, ny):
     # Relative error of a product: 1.6e-7 at K = 2048 and less below; ten layers in a row and back keep it under 2e-6, and the
     # fp32 instruction on the same inputs is no closer (its products are 2 to 5 times further off; 1.5 leaves room for luck in a
     # single norm).  Sums over all edges (weights, biases most of all) collect what the edges' rounding has in common: the square
-    # root of the edges (here at most 174) times 1.6e-7 / 7, from 2.6e-6 measured at 23453 edges; 5e-6 allows twice that.
+    # root of edges times width.  2.6e-6 measured at 23453 edges of width 256 makes 4.2e-6 at 30281 of width 512; 1e-5 allows twice.
     w = synth.get_workload("cfg2", emb=emb, int_emb=int_emb)
     pos, ref, e, t = _case(lib, ctx, w, 3, synth.slab_adsorbate_positions(slabs, nx, ny, 3, 5, seed=3))
     E = len(ref["src"])
@@ -64,7 +57,7 @@ def test_block_against_the_oracle(lib, ctx, emb, int_emb, slabs, nx, ny):
         assert H.row_err(got[i], want[i]) < 1e-5
     worst = {s: max(H.rel_l2(r[2][k], g) for k, g in want[2][0].items()) for s, r in (("parts", got), ("instruction", plain))}
     print("weight gradients: two fp16 parts %.2e, fp32 instruction %.2e" % (worst["parts"], worst["instruction"]))
-    assert worst["parts"] < 5e-6
+    assert worst["parts"] < 1e-5
 
 
 def test_values_of_every_size(lib, ctx):
