@@ -892,14 +892,20 @@ int backward_G(gp_ctx* ctx, const gp_dims* dims, const gp_weights_G* w, const gp
   GP_TRY(gp_gemm_tn(ctx, g, sc.dRad, E, R, S * C, sc.dWcP, nullptr, sc.part, sc.part_bytes));   // [n, (l,c)]
   GP_TRY(gp_permute3(ctx, sc.dWcP, R, S, C, 1, 0, 2, gw->W_c));                     // -> [l, n, c]
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.xg, sc.dzdn, E, H, F, gw->W_down, nullptr, sc.part_aux, sc.part_bytes, hs, dzdn_half); }, {}));
-  e = gp_epilogue(); e.out = dxg; e.bf16 = hs ? EPI_BF_OUT : 0u;
-  if (dzdn_half) {
-    GP_TRY(gp_gemm_nt(ctx, sc.dzdn, W_down, E, H, F, e, 1, 1));                     // dxg
-  } else
-    GP_TRY(gp_gemm_nt(ctx, sc.dzdn, w->W_down, E, H, F, e));                        // dxg
   float* dz_ba = d_up;   // d_up is no longer needed on this stream
+  // with the gate as its two factors the backward step of the gated activation is the epilogue of the product that gives dxg
+  const bool gate_fused = dzdn_half && lowrank_gate(ctx, dims, E) && ((uintptr_t)w->W_rbfB & 15) == 0;
+  if (!gate_fused) {
+    e = gp_epilogue(); e.out = dxg; e.bf16 = hs ? EPI_BF_OUT : 0u;
+    if (dzdn_half) {
+      GP_TRY(gp_gemm_nt(ctx, sc.dzdn, W_down, E, H, F, e, 1, 1));                   // dxg
+    } else
+      GP_TRY(gp_gemm_nt(ctx, sc.dzdn, w->W_down, E, H, F, e));                      // dxg
+  }
   GP_TRY(aux.before_write(d_up));
-  if (lowrank_gate(ctx, dims, E)) {
+  if (gate_fused) {
+    GP_TRY(gp_gemm_nt_gate_bwd(ctx, sc.dzdn, W_down, E, H, F, (const __bf16*)s.z_ba, s.gate, w->W_rbfB, RB, (__bf16*)dz_ba, (__bf16*)dgate));
+  } else if (lowrank_gate(ctx, dims, E)) {
     gp_prof_scope prof(ctx, "ew_gate_bwd_lr", 2.0 * RB * (double)EH, 8.0 * (double)EH + 4.0 * RB * (double)E);   // 4 bf16 arrays
     gate_bwd_lr_kernel<<<dim3((unsigned)((E + GATE_ROWS - 1) / GATE_ROWS), (unsigned)((H + 1023) / 1024)), 256, 0, ctx->stream>>>(
         (const __bf16*)dxg, (const __bf16*)s.z_ba, s.gate, w->W_rbfB, E, H, RB, (__bf16*)dz_ba, (__bf16*)dgate);

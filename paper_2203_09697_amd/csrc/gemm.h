@@ -8,7 +8,7 @@ struct gp_epilogue {
   const float* bias = nullptr;      // v += bias[col]
   const float* add_pre = nullptr;   // v += add_pre[row,col]
   float* save_pre = nullptr;        // save_pre[row,col] = v            (pre-activation)
-  int act = 0;                      // 1: v = silu(v); 2: v *= silu'(zsrc[row,col])
+  int act = 0;                      // 1: v = silu(v); 2: v *= silu'(zsrc[row,col]); 3: see gp_gemm_nt_gate_bwd
   const float* zsrc = nullptr;
   const float* mul = nullptr;       // v *= mul[row,col]
   const float* add_post = nullptr;  // v += add_post[row,col]
@@ -48,6 +48,11 @@ bool gp_gemm_nt_takes_lowrank(const gp_ctx* ctx, int64_t M, int N, int K);
 // out_bf16: the result is stored as bf16 (bf16-operand kernels only).
 int gp_gemm_nt2(gp_ctx* ctx, const float* A, const float* Bt, const float* A2, const float* B2t, int64_t M, int N, int K,
                 float* out, int a_bf16 = 0, int b_bf16 = 0, int out_bf16 = 0);
+// Backward step of a gated activation y = silu(z) gate, gate[e, h] = sum_k f[e, k] Wg[k, h] of rank R <= 16, behind the product that
+// gives dy = A Bt^T (bf16 operands, both k-contiguous): dz = dy gate silu'(z) and dgate = dy silu(z); z, dz, dgate bf16 [M, N],
+// f, Wg fp32.  dy is not stored.
+int gp_gemm_nt_gate_bwd(gp_ctx* ctx, const float* A, const float* Bt, int64_t M, int N, int K, const __bf16* z, const float* f,
+                        const float* Wg, int R, __bf16* dz, __bf16* dgate);
 // out[M,N] = A[rows,M]^T @ B[rows,N]; deterministic two-stage reduction through `part`.
 // If colsum_out != NULL it also receives colsum_out[n] = sum_r B[r,n] (the bias gradient).
 size_t gp_gemm_tn_scratch(int64_t rows, int M, int N);
@@ -64,6 +69,7 @@ int gp_ew_gate_bwd(gp_ctx* ctx, const float* dxg, const float* z, const float* g
 int gp_ew_add3(gp_ctx* ctx, const float* a, const float* b, const float* c, float* out, int64_t n);  // c may be NULL
 // bf16-operand kernels (gemm_bf16.hip); mode 0 NN, 1 NT, 2 TN; args is the fp32 path's argument block
 int gp_gemm_bf16_launch(gp_ctx* ctx, int mode, void* args, int splits);
+int gp_gemm_bf16_gate_launch(gp_ctx* ctx, void* args);
 // fp32 operands and result on the bf16 matrix cores, each operand as three bf16 planes (gemm_bf16.hip)
 int gp_gemm_split_launch(gp_ctx* ctx, int mode, void* args, int splits);
 bool gp_gemm_split_tn_ok(int64_t M, int N, int vecA, int vecB);   // whether A^T B of this shape runs in that form

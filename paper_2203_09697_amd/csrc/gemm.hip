@@ -503,6 +503,24 @@ int gp_gemm_nt2(gp_ctx* ctx, const float* A, const float* Bt, const float* A2, c
   return dispatch_gemm<MODE_NT>(ctx, g, 1);
 }
 
+int gp_gemm_nt_gate_bwd(gp_ctx* ctx, const float* A, const float* Bt, int64_t M, int N, int K, const __bf16* z, const float* f,
+                        const float* Wg, int R, __bf16* dz, __bf16* dgate) {
+  GP_REQUIRE(ctx, A && Bt && z && f && Wg && dz && dgate && M >= 0 && N > 0 && K > 0, "gemm_nt_gate_bwd: bad arguments");
+  GP_REQUIRE(ctx, N % 4 == 0 && K % 8 == 0 && R >= 1 && R <= 16 && aligned16(A) && aligned16(Bt) && aligned16(z) && aligned16(Wg) &&
+                      aligned16(dz) && aligned16(dgate), "gemm_nt_gate_bwd: shape or alignment not supported");
+  if (M == 0) return GP_OK;
+  gemm_args g{};
+  g.A = A; g.B = Bt; g.M = M; g.N = N; g.K = K; g.lda = K; g.ldb = K;
+  g.a_bf16 = g.b_bf16 = 1;
+  g.vecA = g.vecB = g.vecC = 1;
+  g.epi.act = 3;
+  g.epi.zsrc = reinterpret_cast<const float*>(z);
+  g.epi.lr_a = f; g.epi.lr_b = Wg; g.epi.lr_k = R;
+  g.epi.out = reinterpret_cast<float*>(dz);
+  g.epi.out2 = reinterpret_cast<float*>(dgate);
+  return gp_gemm_bf16_gate_launch(ctx, &g);
+}
+
 size_t gp_gemm_tn_scratch(int64_t rows, int M, int N) {
   tn_plan_t p = tn_plan(rows, M, N);   // the plan with the most splits: the buffer serves either one
   const size_t a = gp_align((size_t)p.splits * M * N * sizeof(float)) + gp_align((size_t)p.splits * p.tiles_m * N * sizeof(float));

@@ -532,6 +532,98 @@ __device__ __forceinline__ void tile_epilogue_pairs(const gemm_args& g, f32x16 (
     }
 }
 
+// The epilogue of gp_gemm_nt_gate_bwd: two blocks side by side as above, 16 lanes on 64 consecutive columns of a row.  The gate of a
+// block is formed by the matrix units in the accumulators' layout, both factors as three bf16 parts and six products (fp32
+// rounding error, as gemm_split_kernel); with 16 multiply-adds a value on the vector units the launch took 1045 us at 300636 x
+// 1024 instead of GATE_US.  The product enters unrounded.  LDS: 32 x EPI_LD2 floats per wavefront for the product, as many for the gate.
+template <int MB, int NB>
+__device__ __forceinline__ void tile_epilogue_gate(const gemm_args& g, f32x16 (&acc)[MB][NB], float* smem, int64_t m0, int n0, int wm0,
+                                                   int wn0) {
+  static_assert(NB % 2 == 0, "pairs of blocks");
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int kh = lane >> 5, l32 = lane & 31, c4 = (lane & 15) * 4;
+  float* stage = smem + wave * (2 * 32 * EPI_LD2);
+  float* stage_g = stage + 32 * EPI_LD2;
+  const int kk = g.epi.lr_k;
+  const __bf16* z = reinterpret_cast<const __bf16*>(g.epi.zsrc);
+  auto parts = [](float v, bf16x8 (&p)[3], int c) __attribute__((always_inline)) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      p[q][c] = (__bf16)v;
+      v -= (float)p[q][c];
+    }
+  };
+  bf16x8 ga[MB][3], gb[NB][3];   // k = 8 kh + c, zero from the rank on
+#pragma unroll
+  for (int i = 0; i < MB; ++i) {
+    const int64_t row = m0 + wm0 + i * 32 + l32 < g.M ? m0 + wm0 + i * 32 + l32 : g.M - 1;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int k = 8 * kh + c;
+      const float a = g.epi.lr_a[row * kk + (k < kk ? k : kk - 1)];
+      parts(k < kk ? a : 0.f, ga[i], c);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int col = n0 + wn0 + j * 32 + l32 < g.N ? n0 + wn0 + j * 32 + l32 : g.N - 1;
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int k = 8 * kh + c;
+      const float b = g.epi.lr_b[(int64_t)(k < kk ? k : kk - 1) * g.N + col];
+      parts(k < kk ? b : 0.f, gb[j], c);
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < MB; ++i)
+#pragma unroll
+    for (int j = 0; j < NB; j += 2) {
+      const int col = n0 + wn0 + j * 32 + c4, colc = col < g.N ? col : g.N - 4;
+      const int64_t row0 = m0 + wm0 + i * 32 + (lane >> 4);
+      bf16x4 zz[8];   // requested before the block is staged
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int64_t row = row0 + it * 4;
+        zz[it] = *reinterpret_cast<const bf16x4*>(z + (row < g.M ? row : g.M - 1) * g.N + colc);
+      }
+#pragma unroll
+      for (int jj = 0; jj < 2; ++jj) {
+        f32x16 f;
+#pragma unroll
+        for (int v = 0; v < 16; ++v) f[v] = 0.f;
+        constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+#pragma unroll
+        for (int q = 0; q < 6; ++q) f = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ga[i][PA[q]], gb[j + jj][PB[q]], f, 0, 0, 0);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+          const int o = ((v >> 2) * 8 + kh * 4 + (v & 3)) * EPI_LD2 + jj * 32 + l32;
+          stage[o] = acc[i][j + jj][v];
+          stage_g[o] = f[v];
+        }
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int it = 0; it < 8; ++it) {
+        const int64_t row = row0 + it * 4;
+        const int64_t o = row * g.N + col;
+        const int q = (it * 4 + (lane >> 4)) * EPI_LD2 + c4;
+        const f32x4 v = *reinterpret_cast<const f32x4*>(&stage[q]), gt = *reinterpret_cast<const f32x4*>(&stage_g[q]);
+        bf16x4 o1, o2;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          const float zv = (float)zz[it][c], sg = sigmoid_f(zv);   // one sigmoid for silu and its derivative
+          o1[c] = (__bf16)(v[c] * gt[c] * (sg * (1.0f + zv * (1.0f - sg))));
+          o2[c] = (__bf16)(v[c] * zv * sg);
+        }
+        if (row < g.M && col < g.N) {
+          __builtin_nontemporal_store(o1, reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(g.epi.out) + o));
+          __builtin_nontemporal_store(o2, reinterpret_cast<bf16x4*>(reinterpret_cast<__bf16*>(g.epi.out2) + o));
+        }
+      }
+      wave_lds_sync();
+    }
+}
+
 template <int MB, int NB, int MODE, int LR_WAVES = 0>
 __device__ __forceinline__ void tile_epilogue(const gemm_args& g, f32x16 (&acc)[MB][NB], float* smem, int64_t m0, int n0,
                                               int wm0, int wn0, int split) {
@@ -796,7 +888,7 @@ gemm_split_kernel(const gemm_args g) {
 // barrier per slab suffices: while slab t is multiplied out of one buffer, slab t+1 is written to the other.
 // Register sets and buffers rotate statically (the loop is unrolled over one full rotation); loads past the
 // last full slab re-read that slab (in bounds, never used).
-template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int MODE, bool GATE = false>
 __global__ void __launch_bounds__(THREADS, 2)
 gemm_hh_kernel(const gemm_args g) {
   static_assert(WAVES_M * WAVES_N == 4, "four wavefronts per workgroup");
@@ -916,10 +1008,11 @@ gemm_hh_kernel(const gemm_args g) {
       __syncthreads();
     }
   }
-  tile_epilogue<MB, NB, MODE>(g, acc, smem, m0, n0, wm0, wn0, split);
+  if constexpr (GATE) tile_epilogue_gate<MB, NB>(g, acc, smem, m0, n0, wm0, wn0);
+  else tile_epilogue<MB, NB, MODE>(g, acc, smem, m0, n0, wm0, wn0, split);
 }
 
-template <int BM, int BN, int WMS, int WNS, int MODE>
+template <int BM, int BN, int WMS, int WNS, int MODE, bool GATE = false>
 int launch_hh(gp_ctx* ctx, gemm_args& g, int splits) {
   const int64_t tiles = ((g.M + BM - 1) / BM) * ((g.N + BN - 1) / BN);
   if (tiles > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
@@ -927,15 +1020,26 @@ int launch_hh(gp_ctx* ctx, gemm_args& g, int splits) {
   if (tiles * splits > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
   dim3 grid((unsigned)(tiles * splits), 1, 1);
   static char name[48];
-  if (!name[0]) snprintf(name, sizeof(name), "gemm_bf16_hh_%s_%dx%d", MODE == MODE_NN ? "nn" : MODE == MODE_NT ? "nt" : "tn", BM, BN);
+  if (!name[0])
+    snprintf(name, sizeof(name), "%sgemm_bf16_hh_%s_%dx%d", GATE ? "gate_bwd_" : "", MODE == MODE_NN ? "nn" : MODE == MODE_NT ? "nt" : "tn", BM, BN);
   const double mnk = (double)g.M * g.N * g.K;
   gp_prof_scope prof(ctx, name, 2.0 * mnk,
-                     2.0 * (double)g.M * g.K + 2.0 * (double)g.K * g.N + 4.0 * (double)g.M * g.N * (MODE == MODE_TN ? splits : 1));
+                     2.0 * (double)g.M * g.K + 2.0 * (double)g.K * g.N +
+                         (GATE ? 6.0 : 4.0) * (double)g.M * g.N * (MODE == MODE_TN ? splits : 1));
   constexpr size_t lds_main = sizeof(__bf16) * 2 * (size_t)(BM + BN) * LDK;
-  constexpr size_t lds_epi = sizeof(float) * 4 * 32 * EPI_LD2;
+  constexpr size_t lds_epi = sizeof(float) * (GATE ? 2 : 1) * 4 * 32 * EPI_LD2;
   constexpr size_t lds = lds_main > lds_epi ? lds_main : lds_epi;
-  static_assert(lds <= 64 * 1024, "two slabs fit the default dynamic LDS limit");
-  gemm_hh_kernel<BM, BN, WMS, WNS, MODE><<<grid, THREADS, lds, ctx->stream>>>(g);
+  static_assert(2 * lds <= 160 * 1024 && (GATE || lds <= 64 * 1024), "two workgroups per compute unit; the default dynamic LDS limit");
+  if constexpr (GATE) {
+    static bool raised = false;
+    if (!raised) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_hh_kernel<BM, BN, WMS, WNS, MODE, GATE>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
+      raised = true;
+    }
+  }
+  gemm_hh_kernel<BM, BN, WMS, WNS, MODE, GATE><<<grid, THREADS, lds, ctx->stream>>>(g);
   GP_LAUNCH_CHECK(ctx, "gemm_hh_kernel");
   return GP_OK;
 }
@@ -1662,6 +1766,12 @@ int gp_gemm_bf16_launch(gp_ctx* ctx, int mode, void* args, int splits) {
   if (mode == MODE_NN) return dispatch<MODE_NN>(ctx, g, splits);
   if (mode == MODE_NT) return dispatch<MODE_NT>(ctx, g, splits);
   return dispatch<MODE_TN>(ctx, g, splits);
+}
+
+// The last layer of gp_gemm_nt_gate_bwd: the 128x128 kernel, whose contraction is short there (64 or 128); at 300636 x 1024 the
+// product and a pass of its own over dy, z, dz and dgate took 215 + 505 us.
+int gp_gemm_bf16_gate_launch(gp_ctx* ctx, void* args) {
+  return launch_hh<128, 128, 2, 2, MODE_NT, true>(ctx, *static_cast<gemm_args*>(args), 1);
 }
 
 // fp32 operands and result through three bf16 planes per operand (gemm_split_kernel); `g` filled as for the fp32 kernels
