@@ -558,8 +558,6 @@ int forward_G(gp_ctx* ctx, const gp_dims* dims, const gp_weights_G* w, const gp_
   const float* g = basis->rbf;
   gp_epilogue e;
 
-  e = gp_epilogue(); e.out = s.Wrbf;
-  GP_TRY(gp_gemm_nn(ctx, w->W_rbfS, w->W_rbfB, R, H, RB, e));                       // W_rbf = W_rbfS W_rbfB
   const bool hs = half_storage(dims);   // gate, z_ba, xg, z_skip, t_skip, z_up live in HBM as bf16
   const bool ah = a_half(ctx, dims, graph);
   ctx->fwd_flags[saved] = ah ? 1u : 0u;   // element type of the accumulator A: the backward call must read it the same way
@@ -569,6 +567,8 @@ int forward_G(gp_ctx* ctx, const gp_dims* dims, const gp_weights_G* w, const gp_
     e = gp_epilogue(); e.out = s.gate;
     GP_TRY(gp_gemm_nn(ctx, g, w->W_rbfS, E, RB, R, e));                             // g W_rbfS [E, emb_rbf], fp32
   } else {
+    e = gp_epilogue(); e.out = s.Wrbf;
+    GP_TRY(gp_gemm_nn(ctx, w->W_rbfS, w->W_rbfB, R, H, RB, e));                     // W_rbf = W_rbfS W_rbfB
     e = gp_epilogue(); e.out = s.gate; e.bf16 = hs ? EPI_BF_OUT : 0u;
     GP_TRY(gp_gemm_nn(ctx, g, s.Wrbf, E, H, R, e));                                 // gate
   }
