@@ -372,6 +372,7 @@ inline unsigned wblk(int64_t n) { return (unsigned)((n + WPB - 1) / WPB); }
 
 struct head_saved {
   float *h, *z1, *a1, *e_atom;
+  void* planes;   // W1 as operand planes (gemm_planes.hip): scratch of the forward call, which has no other
 };
 size_t carve_head_saved(void* p, int64_t N, int H, int K, head_saved* s) {
   gp_carver c(p);
@@ -379,11 +380,13 @@ size_t carve_head_saved(void* p, int64_t N, int H, int K, head_saved* s) {
   s->z1 = c.take<float>(N * K);
   s->a1 = c.take<float>(N * K);
   s->e_atom = c.take<float>(N);
+  s->planes = c.take<char>(gp_planes_bytes(K, H));
   return c.off;
 }
 struct head_scratch {
   float *dz1, *dh, *part;
   size_t part_bytes;
+  void* planes;   // W1 for the product with its transpose
 };
 size_t carve_head_scratch(void* p, int64_t N, int H, int K, head_scratch* s) {
   gp_carver c(p);
@@ -391,6 +394,7 @@ size_t carve_head_scratch(void* p, int64_t N, int H, int K, head_scratch* s) {
   s->dh = c.take<float>(N * H);
   s->part_bytes = std::max(gp_gemm_tn_scratch(N, H, K), gp_colsum_scratch(N, K));
   s->part = (float*)c.take<char>(s->part_bytes);
+  s->planes = c.take<char>(gp_planes_bytes(H, K));
   return c.off;
 }
 struct forces_ws {
@@ -526,7 +530,10 @@ int gp_energy_forward(gp_ctx* ctx, int32_t emb, int32_t hidden, const gp_weights
   }
   gp_epilogue e;
   e.bias = w->b1; e.save_pre = s.z1; e.act = 1; e.out = s.a1;
-  GP_TRY(gp_gemm_nn(ctx, s.h, w->W1, n_atoms, hidden, emb, e));
+  gp_weight_planes wp(ctx, s.planes);
+  const void* p_W1 = wp.add(w->W1, n_atoms, hidden, emb, 1);
+  GP_TRY(wp.run());
+  GP_TRY(gp_gemm_nn_w(ctx, s.h, w->W1, p_W1, n_atoms, hidden, emb, e));
   atom_energy_kernel<<<wblk(n_atoms), 256, 0, st>>>(s.a1, w->w2, w->b2, n_atoms, hidden, s.e_atom);
   graph_energy_kernel<<<wblk(n_graphs), 256, 0, st>>>(s.e_atom, graph_ptr, n_graphs, energy);
   GP_LAUNCH_CHECK(ctx, "energy kernels");
@@ -549,7 +556,10 @@ int gp_energy_backward(gp_ctx* ctx, int32_t emb, int32_t hidden, const gp_weight
   GP_LAUNCH_CHECK(ctx, "head_dz_kernel");
   gp_epilogue e;
   e.out = sc.dh;
-  GP_TRY(gp_gemm_nt(ctx, sc.dz1, w->W1, n_atoms, emb, hidden, e));
+  gp_weight_planes wp(ctx, sc.planes);
+  const void* p_W1 = wp.add(w->W1, n_atoms, emb, hidden, 0);
+  GP_TRY(wp.run());
+  GP_TRY(gp_gemm_nt_w(ctx, sc.dz1, w->W1, p_W1, n_atoms, emb, hidden, e));
   if (n_edges > 0) {
     gp_prof_scope prof(ctx, "head_gather_rows", 0.0, 4.0 * (double)emb * ((double)n_edges + (double)n_atoms));
     if (emb % 4 == 0 && (reinterpret_cast<uintptr_t>(grad_m) & 15) == 0 && (reinterpret_cast<uintptr_t>(sc.dh) & 15) == 0)

@@ -535,7 +535,7 @@ __device__ __forceinline__ void tile_epilogue_pairs(const gemm_args& g, f32x16 (
 // The epilogue of gp_gemm_nt_gate_bwd: two blocks side by side as above, 16 lanes on 64 consecutive columns of a row.  The gate of a
 // block is formed by the matrix units in the accumulators' layout, both factors as three bf16 parts and six products (fp32
 // rounding error, as gemm_split_kernel); with 16 multiply-adds a value on the vector units the launch took 1045 us at 300636 x
-// 1024 instead of GATE_US.  The product enters unrounded.  LDS: 32 x EPI_LD2 floats per wavefront for the product, as many for the gate.
+// 1024 beside a weight gradient, so 850 (alone, the product 215 and the pass after it 505).  The product enters unrounded.  LDS: 32 x EPI_LD2 floats per wavefront for the product, as many for the gate.
 template <int MB, int NB>
 __device__ __forceinline__ void tile_epilogue_gate(const gemm_args& g, f32x16 (&acc)[MB][NB], float* smem, int64_t m0, int n0, int wm0,
                                                    int wn0) {

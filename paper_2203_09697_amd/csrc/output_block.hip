@@ -69,16 +69,24 @@ out_graph_sum_kernel(const float* __restrict__ p, const int32_t* __restrict__ gr
   if ((threadIdx.x & 63) == 0) energy[g] = accumulate ? energy[g] + s : s;
 }
 
-// ga[i] = grad_energy[structure of atom i];  du[i, k] = ga[i] w[k]; one wavefront per structure walks its atoms
+// ga[i] = grad_energy[structure of atom i];  du[i, k] = ga[i] w[k] silu'(z[i, k]) (z NULL: without it); a wavefront per atom, which
+// looks its structure up (one per structure walked its atoms one after the other: 52 us at 62 atoms each, 4 us so)
 __global__ void __launch_bounds__(256)
-out_seed_kernel(const float* __restrict__ grad_energy, const int32_t* __restrict__ graph_ptr, int n_graphs,
-                const float* __restrict__ w, int K, float* __restrict__ ga, float* __restrict__ du) {
-  const int g = blockIdx.x * WPB + (threadIdx.x >> 6);
-  if (g >= n_graphs) return;
-  const float ge = grad_energy[g];
-  for (int i = graph_ptr[g]; i < graph_ptr[g + 1]; ++i) {
-    if ((threadIdx.x & 63) == 0) ga[i] = ge;
-    for (int k = threadIdx.x & 63; k < K; k += 64) du[(int64_t)i * K + k] = ge * w[k];
+out_seed_kernel(const float* __restrict__ grad_energy, const int32_t* __restrict__ graph_ptr, int n_graphs, int64_t n_atoms,
+                const float* __restrict__ w, const float* __restrict__ z, int K, float* __restrict__ ga, float* __restrict__ du) {
+  const int64_t i = (int64_t)blockIdx.x * WPB + (threadIdx.x >> 6);
+  if (i >= n_atoms) return;
+  int lo = 0, hi = n_graphs;   // graph_ptr[lo] <= i < graph_ptr[hi]
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (graph_ptr[mid] <= i) lo = mid;
+    else hi = mid;
+  }
+  const float ge = grad_energy[lo];
+  if ((threadIdx.x & 63) == 0) ga[i] = ge;
+  for (int k = threadIdx.x & 63; k < K; k += 64) {
+    const float v = ge * w[k];
+    du[i * K + k] = z ? v * dsilu_f(z[i * K + k]) : v;
   }
 }
 
@@ -122,8 +130,9 @@ struct out_scratch {
   float *dh;          // [N, H]
   float* part;
   size_t part_bytes;
+  void* planes;       // the weights of a call as operand planes (gemm_planes.hip)
 };
-size_t carve_out_scratch(void* p, int64_t N, int64_t E, int H, int D, int R, out_scratch* s) {
+size_t carve_out_scratch(void* p, int64_t N, int64_t E, int H, int D, int R, int L, out_scratch* s) {
   gp_carver c(p);
   s->tE = c.take<float>(E * H);
   s->p = c.take<float>(N);
@@ -137,6 +146,7 @@ size_t carve_out_scratch(void* p, int64_t N, int64_t E, int H, int D, int R, out
   m = std::max(m, gp_gemm_tn_scratch(N, D, 1));
   s->part_bytes = m;
   s->part = (float*)c.take<char>(m);
+  s->planes = c.take<char>((size_t)L * gp_align(gp_planes_bytes(D, D)) + gp_align(std::max(gp_planes_bytes(D, H), gp_planes_bytes(H, D))));
   return c.off;
 }
 
@@ -163,7 +173,7 @@ int gp_output_workspace(int32_t emb, int32_t out_emb, int32_t num_radial, int32_
   out_saved s;
   out_scratch sc;
   *saved_bytes = carve_out_saved(nullptr, n_atoms, emb, out_emb, n_layers, &s);
-  *scratch_bytes = carve_out_scratch(nullptr, n_atoms, n_edges, emb, out_emb, num_radial, &sc);
+  *scratch_bytes = carve_out_scratch(nullptr, n_atoms, n_edges, emb, out_emb, num_radial, n_layers, &sc);
   return GP_OK;
 }
 
@@ -181,7 +191,7 @@ int gp_output_forward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_rad
   out_saved s;
   out_scratch sc;
   if (saved_bytes < carve_out_saved(saved, n_atoms, H, D, L, &s)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_forward: saved buffer too small");
-  if (scratch_bytes < carve_out_scratch(scratch, n_atoms, n_edges, H, D, R, &sc)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_forward: scratch too small");
+  if (scratch_bytes < carve_out_scratch(scratch, n_atoms, n_edges, H, D, R, L, &sc)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_forward: scratch too small");
   GP_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   gp_epilogue e;
@@ -194,12 +204,17 @@ int gp_output_forward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_rad
     out_atom_sum_kernel<<<wblk(n_atoms * ((H + 63) / 64)), 256, 0, st>>>(sc.tE, row_ptr, n_atoms, H, s.h);
     GP_LAUNCH_CHECK(ctx, "out_atom_sum_kernel");
   }
+  gp_weight_planes wp(ctx, sc.planes);
+  const void* p_up = wp.add(w->W_up, n_atoms, D, H, 1);
+  const void* p_layer[GP_MAX_OUT_LAYERS] = {};
+  for (int k = 0; k < L; ++k) p_layer[k] = wp.add(w->W[k], n_atoms, D, D, 1);
+  GP_TRY(wp.run());
   e = gp_epilogue(); e.out = s.u0;
-  GP_TRY(gp_gemm_nn(ctx, s.h, w->W_up, n_atoms, D, H, e));
+  GP_TRY(gp_gemm_nn_w(ctx, s.h, w->W_up, p_up, n_atoms, D, H, e));
   const float* u = s.u0;
   for (int k = 0; k < L; ++k) {
     e = gp_epilogue(); e.bias = w->b[k]; e.save_pre = s.z[k]; e.act = 1; e.out = s.u[k];
-    GP_TRY(gp_gemm_nn(ctx, u, w->W[k], n_atoms, D, D, e));
+    GP_TRY(gp_gemm_nn_w(ctx, u, w->W[k], p_layer[k], n_atoms, D, D, e));
     u = s.u[k];
   }
   out_atom_dot_kernel<<<wblk(n_atoms), 256, 0, st>>>(u, w->w_final, n_atoms, D, sc.p);
@@ -225,27 +240,33 @@ int gp_output_backward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_ra
   out_saved s;
   out_scratch sc;
   if (saved_bytes < carve_out_saved(const_cast<void*>(saved), n_atoms, H, D, L, &s)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_backward: saved buffer too small");
-  if (scratch_bytes < carve_out_scratch(scratch, n_atoms, n_edges, H, D, R, &sc)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_backward: scratch too small");
+  if (scratch_bytes < carve_out_scratch(scratch, n_atoms, n_edges, H, D, R, L, &sc)) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gp_output_backward: scratch too small");
   GP_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   gp_epilogue e;
   float* du = sc.du[0];
   float* other = sc.du[1];
-  out_seed_kernel<<<wblk(n_graphs), 256, 0, st>>>(grad_energy, graph_ptr, n_graphs, w->w_final, D, sc.ga, du);
+  out_seed_kernel<<<wblk(n_atoms), 256, 0, st>>>(grad_energy, graph_ptr, n_graphs, n_atoms, w->w_final, L > 0 ? s.z[L - 1] : nullptr, D,
+                                                 sc.ga, du);                              // du = dz_{L-1}
   GP_LAUNCH_CHECK(ctx, "out_seed_kernel");
+  gp_weight_planes wp(ctx, sc.planes);
+  const void* p_up = wp.add(w->W_up, n_atoms, H, D, 0);
+  const void* p_layer[GP_MAX_OUT_LAYERS] = {};
+  for (int k = 0; k < L; ++k) p_layer[k] = wp.add(w->W[k], n_atoms, D, D, 0);
+  GP_TRY(wp.run());
   const float* u_last = L > 0 ? s.u[L - 1] : s.u0;
   if (grad_w) GP_TRY(gp_gemm_tn(ctx, u_last, sc.ga, n_atoms, D, 1, grad_w->w_final, nullptr, sc.part, sc.part_bytes));
   for (int k = L - 1; k >= 0; --k) {
-    GP_TRY(gp_ew_dsilu_mul(ctx, du, s.z[k], du, n_atoms * D));                          // dz_k (in place)
     const float* u_in = k > 0 ? s.u[k - 1] : s.u0;
     if (grad_w) GP_TRY(gp_gemm_tn(ctx, u_in, du, n_atoms, D, D, grad_w->W[k], grad_w->b[k], sc.part, sc.part_bytes));
     e = gp_epilogue(); e.out = other;
-    GP_TRY(gp_gemm_nt(ctx, du, w->W[k], n_atoms, D, D, e));                             // du_{k-1}
+    if (k > 0) e.act = 2, e.zsrc = s.z[k - 1];
+    GP_TRY(gp_gemm_nt_w(ctx, du, w->W[k], p_layer[k], n_atoms, D, D, e));               // dz_{k-1}, du_{-1} = du0
     std::swap(du, other);
   }
   if (grad_w) GP_TRY(gp_gemm_tn(ctx, s.h, du, n_atoms, H, D, grad_w->W_up, nullptr, sc.part, sc.part_bytes));
   e = gp_epilogue(); e.out = sc.dh;
-  GP_TRY(gp_gemm_nt(ctx, du, w->W_up, n_atoms, H, D, e));                               // dh
+  GP_TRY(gp_gemm_nt_w(ctx, du, w->W_up, p_up, n_atoms, H, D, e));                       // dh
   if (n_edges > 0) {
     {
       gp_prof_scope prof(ctx, "out_gather_rows", 0.0, 4.0 * ((double)n_edges * H + (double)n_atoms * H));
