@@ -465,13 +465,17 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   }
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.xg, sc.dF2, E, H, F, gw->W_down, nullptr, sc.part_aux, sc.part_bytes); },
                     {sc.dF2}));
-  {
+  if (p_down) {   // dxg = dF2 W_down^T is not stored: its epilogue takes the gate apart (two launches: 26 + 48 us at 43380 x 256)
+    GP_TRY(aux.before_write(dz_kj));
+    gp_epilogue e; e.act = 3; e.zsrc = s.z_kj; e.mul = s.gate; e.out = dz_kj; e.out2 = dgate;
+    GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                        // dz_kj, dgate
+  } else {
     GP_TRY(aux.before_write(T2));
     gp_epilogue e; e.out = T2;
-    GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                                  // dxg
+    GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));                                  // dxg
+    GP_TRY(aux.before_write(dz_kj));
+    GP_TRY(gp_ew_gate_bwd(ctx, T2, s.z_kj, s.gate, dz_kj, dgate, EH));                       // dz_kj, dgate
   }
-  GP_TRY(aux.before_write(dz_kj));
-  GP_TRY(gp_ew_gate_bwd(ctx, T2, s.z_kj, s.gate, dz_kj, dgate, EH));                         // dz_kj, dgate
   GP_TRY(gp_gemm_tn(ctx, basis->rbf, dgate, E, R, H, sc.dWrbf, nullptr, sc.part, sc.part_bytes));
   if (grad_rbf) {   // dL/drbf = dgate W_rbf^T
     gp_epilogue e; e.out = grad_rbf;

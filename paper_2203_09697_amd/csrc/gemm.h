@@ -8,7 +8,7 @@ struct gp_epilogue {
   const float* bias = nullptr;      // v += bias[col]
   const float* add_pre = nullptr;   // v += add_pre[row,col]
   float* save_pre = nullptr;        // save_pre[row,col] = v            (pre-activation)
-  int act = 0;                      // 1: v = silu(v); 2: v *= silu'(zsrc[row,col]); 3: see gp_gemm_nt_gate_bwd
+  int act = 0;                      // 1: v = silu(v); 2: v *= silu'(zsrc[row,col]); 3: see gp_gemm_nt_gate_bwd and gp_gemm_nt_w
   const float* zsrc = nullptr;
   const float* mul = nullptr;       // v *= mul[row,col]
   const float* add_post = nullptr;  // v += add_post[row,col]
@@ -119,6 +119,8 @@ struct gp_weight_planes {
 };
 // gp_gemm_nn / gp_gemm_nt with the planes of the weight matrix at hand (NULL: the general kernels)
 int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
+// gp_gemm_nt_w also takes (planes at hand, 16-byte aligned matrices) act = 3, the backward step of y = silu(z) gate behind the product
+// dy: out = dy mul silu'(zsrc) and out2 = dy silu(zsrc), with mul the gate.
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
 // A^T B over the rows in the same form: tiles, splits of the rows, whether it is taken, launch with gp_gemm_tn's argument block
 struct gp_tn_planes_plan {

@@ -37,12 +37,12 @@ struct gemm_args {
 // fp32 kernels: the steps present as a bit mask; the kernel switches once per tile over the masks listed in
 // GP_EM_LIST (those of the variant-D block) to a loop compiled for that mask
 enum : unsigned { EM_BIAS = 1, EM_ADD_PRE = 2, EM_SAVE_PRE = 4, EM_ACT1 = 8, EM_ACT2 = 16, EM_MUL = 32, EM_ADD_POST = 64, EM_SCALE = 128,
-                  EM_OUT = 256, EM_OUT2 = 512 };
+                  EM_OUT = 256, EM_OUT2 = 512, EM_GATE = 1024 };
 #define GP_EM_LIST(X) X(256) X(269) X(333) X(272) X(320) X(832) X(301) X(268) X(332) X(768) X(322)
 inline unsigned gp_epilogue_mask(const gp_epilogue& e, int vecC) {
   if (!vecC || e.bf16 || e.lr_a) return 0;
   return (e.bias ? EM_BIAS : 0u) | (e.add_pre ? EM_ADD_PRE : 0u) | (e.save_pre ? EM_SAVE_PRE : 0u) | (e.act == 1 ? EM_ACT1 : 0u) |
-         (e.act == 2 ? EM_ACT2 : 0u) | (e.mul ? EM_MUL : 0u) | (e.add_post ? EM_ADD_POST : 0u) | (e.scale != 1.0f ? EM_SCALE : 0u) |
+         (e.act == 2 ? EM_ACT2 : 0u) | (e.act == 3 ? EM_GATE : 0u) | (e.mul ? EM_MUL : 0u) | (e.add_post ? EM_ADD_POST : 0u) | (e.scale != 1.0f ? EM_SCALE : 0u) |
          (e.out ? EM_OUT : 0u) | (e.out2 ? EM_OUT2 : 0u);
 }
 

@@ -160,10 +160,10 @@ struct epi_in {
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
       if constexpr ((M & EM_ADD_PRE) != 0) pre[it] = ld4(e.add_pre + o[it]);
-      if constexpr ((M & EM_ACT2) != 0) z[it] = ld4(e.zsrc + o[it]);
+      if constexpr ((M & (EM_ACT2 | EM_GATE)) != 0) z[it] = ld4(e.zsrc + o[it]);
       if constexpr ((M & EM_MUL) != 0) mul[it] = ld4(e.mul + o[it]);
       if constexpr ((M & EM_ADD_POST) != 0) post[it] = ld4(e.add_post + o[it]);
-      if constexpr ((M & EM_OUT2) != 0) z2[it] = ld4(e.z2src + o[it]);
+      if constexpr ((M & EM_OUT2) != 0 && (M & EM_GATE) == 0) z2[it] = ld4(e.z2src + o[it]);
     }
   }
 };
@@ -222,6 +222,19 @@ __device__ __forceinline__ void epilogue_blocks(const gemm_args& g, f32x16 (&acc
 #pragma unroll
         for (int c = 0; c < 4; ++c) v[c] *= dsilu_f(q.z[it][c]);
       }
+      if constexpr ((M & EM_GATE) != 0) {
+        f32x4 dz, dg;
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          dz[c] = v[c] * q.mul[it][c] * dsilu_f(q.z[it][c]);
+          dg[c] = v[c] * silu_f(q.z[it][c]);
+        }
+        if (in_m) {
+          st4(g.epi.out + o[it], dz);
+          st4(g.epi.out2 + o[it], dg);
+        }
+        continue;
+      }
       if constexpr ((M & EM_MUL) != 0) v *= q.mul[it];
       if constexpr ((M & EM_ADD_POST) != 0) v += q.post[it];
       if constexpr ((M & EM_OUT) != 0) {
@@ -237,10 +250,13 @@ __device__ __forceinline__ void epilogue_blocks(const gemm_args& g, f32x16 (&acc
   }
 }
 
+// the combinations of gemm_common.h and the gate's backward step
+#define GP_EM_LIST_PLANES(X) GP_EM_LIST(X) X(1824)
+static_assert((EM_GATE | EM_MUL | EM_OUT | EM_OUT2) == 1824, "listed above");
 bool epilogue_listed(unsigned mask) {
   switch (mask) {
 #define GP_EM_CASE(M) case M:
-    GP_EM_LIST(GP_EM_CASE)
+    GP_EM_LIST_PLANES(GP_EM_CASE)
 #undef GP_EM_CASE
     return true;
     default: return false;
@@ -417,7 +433,7 @@ gemm_planes_kernel(const gemm_args g) {
   const float* inv_n = reinterpret_cast<const float*>(reinterpret_cast<const char*>(g.B) + (int64_t)nb * n_st * GROUP_B);
   switch (g.epi_mask) {   // uniform
 #define GP_EM_CASE(M) case M: epilogue_blocks<MB, NB, M>(g, acc, stage, m0 + wm0, n0, inv_n); break;
-    GP_EM_LIST(GP_EM_CASE)
+    GP_EM_LIST_PLANES(GP_EM_CASE)
 #undef GP_EM_CASE
     default: break;   // not launched with any other mask
   }
@@ -682,11 +698,11 @@ size_t gp_planes_bytes(int N, int K) {
 }
 
 // From K = 64 on the error is the smaller one (above).  At K = 64 a short product is launch and epilogue, which both forms have
-// (13323 x 256 x 64: 10.7 us, three bf16 parts 10.0; 43380 x 256 x 64, A W^T: 19.7, 25.4); the conversion of all weights of a call
-// is one launch of 4 to 5 us.
+// (13323 x 256 x 64: 10.7 us, three bf16 parts 10.0; 43380 x 256 x 64, A W^T: 19.7, 25.4; 5000 x 64 x 64: 7.1, 6.4); the conversion of all
+// weights of a call is one launch of 4 to 5 us.
 bool gp_planes_take(const gp_ctx* ctx, int64_t M, int N, int K) {
   return ctx->f32_split && !ctx->gemm_bf16 && K % 16 == 0 && N % 4 == 0 && N >= 64 && N <= 8192 && K <= 8192 &&
-         (K >= 128 || (K >= 64 && M >= 16384));
+         (K >= 128 || (K >= 64 && M >= 8192));
 }
 
 int gp_weight_planes::run() {
@@ -716,7 +732,7 @@ int gemm_planes(gp_ctx* ctx, const float* A, const void* planes, int64_t M, int 
            al16(epi.out) && al16(epi.out2) && al16(epi.z2src);
   g.epi_mask = gp_epilogue_mask(g.epi, g.vecC);
   if (!planes || !al16(A) || !epilogue_listed(g.epi_mask)) return 1;
-  GP_REQUIRE(ctx, M >= 0 && gp_planes_take(ctx, 16384, N, K), "gemm: planes of a shape that has none");
+  GP_REQUIRE(ctx, M >= 0 && gp_planes_take(ctx, 8192, N, K), "gemm: planes of a shape that has none");
   if (M == 0) return GP_OK;
   // Tiles: 128 x 256 where there are enough of them for several rounds of two per compute unit (43380 x 2048 x 2048: 1.41 ms, with
   // 128 x 128 1.57; 13323 x 1024 x 1024: 0.124, 0.139; 22000 x 512 x 512, 344 tiles: 0.060, 0.055); 64 x 64 where a launch of 128 x
