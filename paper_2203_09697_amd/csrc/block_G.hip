@@ -184,6 +184,67 @@ __global__ void iota_kernel(int32_t* __restrict__ out, int64_t n) {
   if (i < n) out[i] = (int32_t)i;
 }
 
+// Radt[p, e] = sum_n WcT[p, n] g[e, n] for p < P <= 128 (the table of every (l, c) over the edges), operands rounded to bf16, fp32
+// accumulation, 16 n at a time: what the general kernel computes, bit for bit.  There the edges are the columns of the
+// result: a tile of 128 of them per workgroup, and value by value through the general epilogue where their number is no
+// multiple of 4 (12.7 k edges x 112 x 128 28 us, 35.5 k 33 us; bound by neither bytes nor products).  Here a wavefront takes 32
+// edges, their n straight from memory in operand order, and stores each of its 64 rows as they come from the matrix
+// units, 128 bytes of neighbouring edges at a time.
+typedef __bf16 h8 __attribute__((ext_vector_type(8)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+constexpr int RT_K = 128;   // n per pass through LDS
+__global__ void __launch_bounds__(256)
+radial_table_kernel(const float* __restrict__ WcT, int P, const float* __restrict__ g, int64_t E, int R, float* __restrict__ Radt) {
+  __shared__ h8 frag[4 * (RT_K / 16) * 64];   // [block of 32 p][step][lane]
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, kh = lane >> 5, l32 = lane & 31;
+  const int64_t e = (int64_t)blockIdx.x * 128 + wave * 32 + l32;
+  const float* ge = g + (e < E ? e : E - 1) * R + kh * 8;
+  auto round8 = [](f4v a, f4v b) __attribute__((always_inline)) {
+    return h8{(__bf16)a[0], (__bf16)a[1], (__bf16)a[2], (__bf16)a[3], (__bf16)b[0], (__bf16)b[1], (__bf16)b[2], (__bf16)b[3]};
+  };
+  f16v acc[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+  for (int k0 = 0; k0 < R; k0 += RT_K) {
+    f4v r[RT_K / 16][2];
+#pragma unroll
+    for (int ks = 0; ks < RT_K / 16; ++ks)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = k0 + ks * 16 + kh * 8;   // R is a multiple of 8
+        r[ks][h] = k < R ? *reinterpret_cast<const f4v*>(ge + k0 + ks * 16 + 4 * h) : f4v{0.f, 0.f, 0.f, 0.f};
+      }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 4 * (RT_K / 16) * 64; i += 256) {
+      const int p = i / (RT_K / 16 * 64) * 32 + (i & 31), k = k0 + (i / 64) % (RT_K / 16) * 16 + ((i >> 5) & 1) * 8;
+      f4v a = {0.f, 0.f, 0.f, 0.f}, b = a;
+      if (p < P && k < R) {
+        a = *reinterpret_cast<const f4v*>(WcT + (int64_t)p * R + k);
+        b = *reinterpret_cast<const f4v*>(WcT + (int64_t)p * R + k + 4);
+      }
+      frag[i] = round8(a, b);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int ks = 0; ks < RT_K / 16; ++ks) {
+      const h8 gb = round8(r[ks][0], r[ks][1]);
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag[(b * (RT_K / 16) + ks) * 64 + lane], gb, acc[b], 0, 0, 0);
+    }
+  }
+  if (e >= E) return;
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+      const int p = b * 32 + (v >> 2) * 8 + kh * 4 + (v & 3);
+      if (p < P) Radt[(int64_t)p * E + e] = acc[b][v];
+    }
+}
+
 typedef __bf16 h4 __attribute__((ext_vector_type(4)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 // four consecutive elements of an fp32 or bf16 array (index a multiple of 4, base 16- / 8-byte aligned)
@@ -611,8 +672,14 @@ int forward_G(gp_ctx* ctx, const gp_dims* dims, const gp_weights_G* w, const gp_
   if (down_T) GP_TRY(gp_gemm_nt(ctx, s.xg, W_down, E, F, H, e, 1, 1));              // x
   else GP_TRY(gp_gemm_nn(ctx, s.xg, W_down, E, F, H, e, hs, wh));
   GP_TRY(gp_permute3(ctx, w->W_c, S, R, C, 0, 2, 1, s.WcT));                        // WcT[(l,c), n]
-  e = gp_epilogue(); e.out = s.Radt;
-  GP_TRY(gp_gemm_nt(ctx, s.WcT, g, S * C, (int)E, R, e));                           // Radt[(l,c), e]
+  if (ctx->gemm_bf16 && R % 8 == 0 && ((uintptr_t)g & 15) == 0) {                   // S C <= 128 (check_dims_G)
+    gp_prof_scope prof(ctx, "tripG_radial_table", 2.0 * S * C * (double)E * R, 4.0 * ((double)E * R + (double)S * C * E));
+    radial_table_kernel<<<(unsigned)((E + 127) / 128), 256, 0, ctx->stream>>>(s.WcT, S * C, g, E, R, s.Radt);
+    GP_LAUNCH_CHECK(ctx, "radial_table_kernel");
+  } else {
+    e = gp_epilogue(); e.out = s.Radt;
+    GP_TRY(gp_gemm_nt(ctx, s.WcT, g, S * C, (int)E, R, e));                         // Radt[(l,c), e]
+  }
   if (dims->radial_at_target) {
     // A_e = Rad_e^T B1_e,  B1[e,l,f] = sum_{t in seg(e)} Y_l(t) x[kj(t),f]: the radial factor has left the sum
     GP_REQUIRE(ctx, graph->seg_ptr_kj && (graph->n_triplets == 0 || graph->idx_ji_kj), "gp_block_forward_G: kj-major view missing");

@@ -27,9 +27,19 @@ def ctx(lib):
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("emb,trip,slabs,nx,ny,symmetric", SHAPES, ids=["%d_%d_%d" % s[:3] for s in SHAPES])
 def test_bf16_block_near_fp32_block(lib, ctx, emb, trip, slabs, nx, ny, symmetric):
+    _near_fp32(lib, ctx, slabs, nx, ny, dict(emb=emb, int_emb=trip, symmetric=symmetric))
+
+
+@pytest.mark.parametrize("num_radial,num_spherical,emb_cbf", [(8, 3, 5), (40, 7, 16), (136, 8, 16), (128, 7, 16)])
+def test_radial_table_widths(lib, ctx, num_radial, num_spherical, emb_cbf):
+    # contractions that end inside a step of 16 and inside the second pass of 128, 15 to 128 rows of the table
+    _near_fp32(lib, ctx, 1, 2, 2, dict(emb=64, int_emb=32, num_radial=num_radial, num_spherical=num_spherical, emb_cbf=emb_cbf))
+
+
+def _near_fp32(lib, ctx, slabs, nx, ny, widths):
     from paper_2203_09697_amd.binding_g import StackG
-    w = synth.get_workload("cfg3", emb=emb, int_emb=trip, symmetric=symmetric)
-    dims = w.dims
+    w = synth.get_workload("cfg3", **widths)
+    dims, emb = w.dims, widths["emb"]
     pos, gptr = synth.slab_adsorbate_positions(slabs, nx, ny, 3, 5, seed=3)
     e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), dims.cutoff, w.max_neighbors)
     basis = lib.gp_basis_forward(ctx, dims, e, t)
