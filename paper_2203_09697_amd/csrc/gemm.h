@@ -122,12 +122,12 @@ int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 // gp_gemm_nt_w also takes (planes at hand, 16-byte aligned matrices) act = 3, the backward step of y = silu(z) gate behind the product
 // dy: out = dy mul silu'(zsrc) and out2 = dy silu(zsrc), with mul the gate.
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
-// A^T B over the rows in the same form: tiles, splits of the rows, whether it is taken, launch with gp_gemm_tn's argument block
-struct gp_tn_planes_plan {
+// A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, whether it is taken, launch with gp_gemm_tn's argument block
+struct gp_tn_parts_plan {
   bool big;       // 256 x 256 tiles instead of 128 x 128
   int tiles_m, splits;
   int64_t per;    // rows of a split
 };
-gp_tn_planes_plan gp_planes_tn_plan(int64_t rows, int M, int N);
-bool gp_planes_tn_take(const gp_ctx* ctx, int64_t rows);
-int gp_planes_tn_launch(gp_ctx* ctx, void* args, const gp_tn_planes_plan& plan);
+gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N);
+bool gp_parts_tn_take(const gp_ctx* ctx);
+int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& plan);

@@ -553,7 +553,7 @@ size_t gp_gemm_tn_scratch(int64_t rows, int M, int N) {
   tn_plan_t p = tn_plan(rows, M, N);   // the plan with the most splits: the buffer serves either one
   const size_t a = gp_align((size_t)p.splits * M * N * sizeof(float)) + gp_align((size_t)p.splits * p.tiles_m * N * sizeof(float));
   const size_t b = gp_align((size_t)gp_gemm_bf16_tn_dl_splits(rows, M, N) * M * N * sizeof(float));   // the bf16 kernel with its own plan
-  const gp_tn_planes_plan q = gp_planes_tn_plan(rows > 0 ? rows : 1, M, N);                          // and the one with two fp16 parts
+  const gp_tn_parts_plan q = gp_parts_tn_plan(rows > 0 ? rows : 1, M, N);                          // and that of the fp32 blocks
   const size_t c = gp_align((size_t)q.splits * M * N * sizeof(float)) + gp_align((size_t)q.splits * q.tiles_m * N * sizeof(float));
   return std::max(a, std::max(b, c));
 }
@@ -591,12 +591,12 @@ int gp_gemm_tn(gp_ctx* ctx, const float* A, const float* B, int64_t rows, int M,
       return launch_reduce(ctx, part, s_dl, (int64_t)M * N, out, nullptr, 0, 0, nullptr);
     }
   }
-  if (gp_planes_tn_take(ctx, rows) && !a_bf16 && !b_bf16) {
-    const gp_tn_planes_plan q = gp_planes_tn_plan(rows, M, N);
+  if (gp_parts_tn_take(ctx) && !a_bf16 && !b_bf16) {
+    const gp_tn_parts_plan q = gp_parts_tn_plan(rows, M, N);
     float* cpart = (float*)((char*)part + gp_align((size_t)q.splits * M * N * sizeof(float)));
     g.colsum_part = colsum_out ? cpart : nullptr;
     g.k_per_split = q.per;
-    GP_TRY(gp_planes_tn_launch(ctx, &g, q));
+    GP_TRY(gp_parts_tn_launch(ctx, &g, q));
     return launch_reduce(ctx, part, q.splits, (int64_t)M * N, out, cpart, q.splits * q.tiles_m, colsum_out ? N : 0, colsum_out);
   }
   float* cpart = (float*)((char*)part + gp_align((size_t)p.splits * M * N * sizeof(float)));

@@ -1,5 +1,6 @@
-// fp32 products A W, A W^T (edge and atom rows times a weight matrix) and A^T B (their sums over the rows: weight gradients) on
-// the fp16 matrix cores: every element enters as
+// fp32 products A W, A W^T (edge and atom rows times a weight matrix) on the fp16 matrix cores, and A^T B (sums over the rows:
+// weight gradients), which has a form of its own below.
+// In A W and A W^T every element enters as
 // the sum of two fp16 numbers, v 2^k = hi + lo (22 to 23 significant bits), and three of the four products of the parts are
 // formed (lo.lo is below 2^-22 of the product).  The power of two is chosen so that the largest of the values that share it
 // lies in [2^14, 2^15): the values of a row of A over 32 consecutive k, and a column of W.  Smaller values of the group keep
@@ -24,6 +25,7 @@
 namespace {
 
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __attribute__((address_space(3))) void* lds_void_ptr;
 typedef const __attribute__((address_space(1))) void* global_void_ptr;
 
@@ -37,6 +39,19 @@ __device__ __forceinline__ void split8(const float* v, f16x8& hi, f16x8& lo) {
   for (int c = 0; c < 8; ++c) hi[c] = (_Float16)v[c];
 #pragma unroll
   for (int c = 0; c < 8; ++c) lo[c] = (_Float16)(v[c] - (float)hi[c]);
+}
+
+// v = p[0] + p[1] + p[2], every part with its own exponent
+__device__ __forceinline__ void parts8(const float* v, bf16x8 (&p)[3]) {
+#pragma unroll
+  for (int c = 0; c < 8; ++c) {
+    float r = v[c];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      p[q][c] = (__bf16)r;
+      r -= (float)p[q][c];
+    }
+  }
 }
 
 // The power of two 2^k that brings the largest of some values into [2^14, 2^15), for the bits of its absolute value: k = 0 where
@@ -53,24 +68,13 @@ __device__ __forceinline__ float pow2(int k) { return __int_as_float((k + 127) <
 // width 256 over 23453 edges are 3e-7 off, with none 5.1e-6, three bf16 parts 3.9e-6, the fp32 instruction 9e-7.  In A W and A W^T a
 // quarter is turned where K < 1024 and none above, where the 32 k of a sum leave less than the running sums of that form
 // (K = 1024 3.5e-6 and 4.9e-6): closer than before at every width, and results that differ from those of the other forms, whose
-// error this is, by half as much as with all of it taken out.  In A^T B, whose sums nothing adds up, half.
+// error this is, by half as much as with all of it taken out.
 __device__ __forceinline__ float turned(float scale, bool turn) { return __int_as_float(__float_as_int(scale) ^ (turn ? 1 << 31 : 0)); }
 // the larger of lanes l and l ^ 32
 __device__ __forceinline__ uint32_t max_halves(uint32_t m) {
   const auto h = __builtin_amdgcn_permlane32_swap(m, m, false, false);
   return h[0] > h[1] ? h[0] : h[1];
 }
-// the largest of 32 lanes (either half of the wavefront by itself)
-__device__ __forceinline__ uint32_t max_of_32(uint32_t m) {
-  auto up = [&](uint32_t o) { m = o > m ? o : m; };
-  up(__builtin_amdgcn_mov_dpp(m, 0x128, 0xF, 0xF, true));   // rotations within rows of 16 lanes by 8, 4, 2, 1
-  up(__builtin_amdgcn_mov_dpp(m, 0x124, 0xF, 0xF, true));
-  up(__builtin_amdgcn_mov_dpp(m, 0x122, 0xF, 0xF, true));
-  up(__builtin_amdgcn_mov_dpp(m, 0x121, 0xF, 0xF, true));
-  const auto h = __builtin_amdgcn_permlane16_swap(m, m, false, false);
-  return h[0] > h[1] ? h[0] : h[1];
-}
-
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_lgkmcnt0() {
   static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit counter");
@@ -439,27 +443,29 @@ gemm_planes_kernel(const gemm_args g) {
   }
 }
 
-// C = A^T B, the contraction running over the rows of both (the weight gradients: rows = edges), in the same form.  A chunk is 32
-// rows.  The loads are those of an operand: lane (kh, x) takes 8 consecutive rows of column x, one value a load (256 bytes of
-// two rows per instruction), so the parts are written to LDS as fragments and nothing is transposed.  A wavefront loads
-// LA + LB blocks of 32 columns a chunk ahead and splits them once for the whole workgroup.  Scales: B's per column, a lane's in
-// the result; A's per block of 32 columns x 32 rows (its columns are the result's rows, which lie in different registers; a
-// column 2^-17 of the block's largest value begins to lose low bits).  The chunk's sums take both factors back at once.
+// C = A^T B, the contraction running over the rows of both (the weight gradients: rows = edges).  Every value enters as the sum of three
+// bf16 numbers, each with its own exponent (24 bits), and the six of the nine products that are not below 2^-24 of the whole are
+// formed: a column of A becomes a row of the result, next to columns of any other size, and rows of any size meet in a sum, so
+// there is no scale that could be shared.
+// A chunk is 16 rows.  The loads are those of an operand: lane (kh, x) takes 8 consecutive rows of column x, one value a load (256
+// bytes of two rows per instruction), so the parts are written to LDS as fragments and nothing is transposed.  A wavefront loads
+// LA + LB blocks of 32 columns a chunk ahead and splits them once for the whole workgroup.
 // Two buffers, one barrier a chunk.  Workgroup = (tile, split of the rows); partial sums and column sums of B (bias gradients,
 // from the fp32 values, each chunk by one of the tiles that share it) as gp_gemm_tn lays them out.
 // 256 x 256 with 8 wavefronts of 128 x 64 where that many columns exist, else 128 x 128 with 4 of 64 x 64 (two workgroups per
-// compute unit).
+// compute unit).  43380 rows, 2048 x 2048 1.91 ms, 256 x 256 42 us, 6 x 256 25; 13230, 256 x 256 19; 434, 256 x 256 7.7; 336, 32 x 32 6.1.  Two fp16
+// parts under shared scales take 1.38 ms, 39, 32, 19, 7.3 and 6.5, and lose what is 2^17 smaller than its neighbours; with every such
+// value sought out and added in fp32 they took 1.7 ms, 46, - and 27.
+constexpr int TN_ROWS = 16, TN_BLOCK_B = 3 * FRAG_B;   // rows of a chunk, bytes of its three parts for 32 columns
 template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, OCC)
-gemm_planes_tn_kernel(const gemm_args g) {
+gemm_parts_tn_kernel(const gemm_args g) {
   constexpr int NW = WAVES_M * WAVES_N, BA = MB * WAVES_M, BB = NB * WAVES_N;   // 32-wide blocks of the operands
   constexpr int LA = BA / NW, LB = BB / NW;                                     // ... a wavefront loads
   static_assert(BA % NW == 0 && BB % NW == 0, "blocks are dealt evenly");
-  constexpr int BLOCK_B = 2 * GROUP_B, BUF_B = (BA + BB) * BLOCK_B;
+  constexpr int BUF_B = (BA + BB) * TN_BLOCK_B;
   extern __shared__ __attribute__((aligned(16))) float smem[];
   char* lds = reinterpret_cast<char*>(smem);
-  float* inv_lds = reinterpret_cast<float*>(lds + 2 * BUF_B);                   // [2][BA] factors of A's blocks, then [2][32 BB] of B's columns
-  float* invB_lds = inv_lds + 2 * BA;
 
   const int tiles_n = (g.N + 32 * BB - 1) / (32 * BB);
   const int tiles_m = (int)((g.M + 32 * BA - 1) / (32 * BA));
@@ -473,10 +479,9 @@ gemm_planes_tn_kernel(const gemm_args g) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WAVES_N) * MB, wn = (wave % WAVES_N) * NB;             // first blocks of the wavefront's products
   const int kh = lane >> 5, l32 = lane & 31;
-  const int n_ch = (int)((k_end - k_begin + 31) / 32);
+  const int n_ch = (int)((k_end - k_begin + TN_ROWS - 1) / TN_ROWS);
 
-  // loads: lane (kh, x) takes column x of a block, rows 8 kh .. + 7 of either 16-row step: a uniform address that moves with
-  // the rows plus the lane's offset
+  // loads: lane (kh, x) takes column x of a block, rows 8 kh .. + 7: a uniform address that moves with the rows plus the lane's offset
   constexpr int NL = LA + LB;
   const char* base[NL];
   int64_t ldb[NL];       // bytes per row
@@ -490,30 +495,26 @@ gemm_planes_tn_kernel(const gemm_args g) {
     base[b] = reinterpret_cast<const char*>((is_a ? g.A : g.B) + xb);
     off[b] = (uint32_t)(8 * kh * ldb[b]) + 4u * (uint32_t)(xb + l32 < width ? l32 : width - 1 - xb);
   }
-  float raw[NL][2][8];
+  float raw[NL][8];
   auto fetch = [&](int c) __attribute__((always_inline)) {
     c = c < n_ch ? c : n_ch - 1;
-    const int64_t k0 = k_begin + (int64_t)c * 32;
-    if (k0 + 32 <= k_end) {
+    const int64_t k0 = k_begin + (int64_t)c * TN_ROWS;
+    if (k0 + TN_ROWS <= k_end) {
 #pragma unroll
       for (int b = 0; b < NL; ++b) {
         const char* p = base[b] + k0 * ldb[b];
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int r = 0; r < 8; ++r) raw[b][ks][r] = *reinterpret_cast<const float*>(p + (16 * ks + r) * ldb[b] + off[b]);
+        for (int r = 0; r < 8; ++r) raw[b][r] = *reinterpret_cast<const float*>(p + r * ldb[b] + off[b]);
       }
     } else {   // the last rows of the split: a valid row in the place of those past the end, then zero
 #pragma unroll
       for (int b = 0; b < NL; ++b)
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int r = 0; r < 8; ++r) {
-            const int64_t k = k0 + 16 * ks + 8 * kh + r;
-            const float v = *reinterpret_cast<const float*>(base[b] + ((k < k_end ? k : k_end - 1) - 8 * kh) * ldb[b] + off[b]);
-            raw[b][ks][r] = k < k_end ? v : 0.f;
-          }
+        for (int r = 0; r < 8; ++r) {
+          const int64_t k = k0 + 8 * kh + r;
+          const float v = *reinterpret_cast<const float*>(base[b] + ((k < k_end ? k : k_end - 1) - 8 * kh) * ldb[b] + off[b]);
+          raw[b][r] = k < k_end ? v : 0.f;
+        }
     }
   };
   float cs[LB];
@@ -525,40 +526,16 @@ gemm_planes_tn_kernel(const gemm_args g) {
     const bool mine = want_cs && c % tiles_m == tile_m;
 #pragma unroll
     for (int b = 0; b < NL; ++b) {
-      const bool is_a = b < LA;
-      const int blk = is_a ? wave * LA + b : BA + wave * LB + b - LA;
-      uint32_t m = 0;
+      const int blk = b < LA ? wave * LA + b : BA + wave * LB + b - LA;
+      bf16x8 part[3];
+      parts8(raw[b], part);
+      char* dst = lds + u * BUF_B + blk * TN_BLOCK_B + lane * 16;
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int r = 0; r < 8; ++r) {
-          const uint32_t w = __float_as_uint(raw[b][ks][r]) & 0x7FFFFFFFu;
-          m = w > m ? w : m;
-        }
-      m = max_halves(m);
-      if (is_a) m = max_of_32(m);   // one factor for the block
-      const int se = scale_exp(m);
-      const float sc = is_a ? pow2(se) : turned(pow2(se), ((c ^ l32) & 1) != 0);
-      if (is_a) {
-        if (lane == 0) inv_lds[u * BA + blk] = pow2(-se);
-      } else if (kh == 0) invB_lds[u * 32 * BB + (blk - BA) * 32 + l32] = turned(pow2(-se), ((c ^ l32) & 1) != 0);
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        float v[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) v[r] = raw[b][ks][r] * sc;
-        f16x8 hi, lo;
-        split8(v, hi, lo);
-        char* dst = lds + u * BUF_B + blk * BLOCK_B + ks * GROUP_B + lane * 16;
-        *reinterpret_cast<f16x8*>(dst) = hi;
-        *reinterpret_cast<f16x8*>(dst + FRAG_B) = lo;
-      }
-      if (!is_a && mine) {
+      for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(dst + p * FRAG_B) = part[p];
+      if (b >= LA && mine) {
         float t = 0.f;
 #pragma unroll
-        for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-          for (int r = 0; r < 8; ++r) t += raw[b][ks][r];
+        for (int r = 0; r < 8; ++r) t += raw[b][r];
         cs[b - LA < 0 ? 0 : b - LA] += t;
       }
     }
@@ -572,44 +549,23 @@ gemm_planes_tn_kernel(const gemm_args g) {
 #pragma unroll
       for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
   auto multiply = [&](int u) __attribute__((always_inline)) {
-    const char* sa = lds + u * BUF_B + wm * BLOCK_B + lane * 16;
-    const char* sb = lds + u * BUF_B + (BA + wn) * BLOCK_B + lane * 16;
-    f16x8 b[NB][2][PL];
-    float fb[NB];
+    const char* sa = lds + u * BUF_B + wm * TN_BLOCK_B + lane * 16;
+    const char* sb = lds + u * BUF_B + (BA + wn) * TN_BLOCK_B + lane * 16;
+    bf16x8 b[NB][3];
 #pragma unroll
-    for (int j = 0; j < NB; ++j) {
-      fb[j] = invB_lds[u * 32 * BB + (wn + j) * 32 + l32];
+    for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int p = 0; p < PL; ++p) b[j][ks][p] = *reinterpret_cast<const f16x8*>(sb + j * BLOCK_B + ks * GROUP_B + p * FRAG_B);
-    }
+      for (int p = 0; p < 3; ++p) b[j][p] = *reinterpret_cast<const bf16x8*>(sb + j * TN_BLOCK_B + p * FRAG_B);
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      f16x8 a[2][PL];
+      bf16x8 a[3];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
+      for (int p = 0; p < 3; ++p) a[p] = *reinterpret_cast<const bf16x8*>(sa + i * TN_BLOCK_B + p * FRAG_B);
+      constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // the smallest first
 #pragma unroll
-        for (int p = 0; p < PL; ++p) a[ks][p] = *reinterpret_cast<const f16x8*>(sa + i * BLOCK_B + ks * GROUP_B + p * FRAG_B);
-      const float fa = inv_lds[u * BA + wm + i];
-      __builtin_amdgcn_sched_barrier(0);
-      f32x16 t[NB];
+      for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int j = 0; j < NB; ++j)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) t[j][v] = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-        for (int x = 0; x < 3; ++x)
-#pragma unroll
-          for (int j = 0; j < NB; ++j) t[j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ks][x == 0], b[j][ks][x == 1], t[j], 0, 0, 0);
-#pragma unroll
-      for (int j = 0; j < NB; ++j) {
-        const float f = fa * fb[j];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[i][j][v] = __builtin_fmaf(t[j][v], f, acc[i][j][v]);
-      }
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]], b[j][PB[q]], acc[i][j], 0, 0, 0);
     }
   };
 
@@ -641,26 +597,26 @@ gemm_planes_tn_kernel(const gemm_args g) {
 }
 
 template <int MB, int NB, int WMS, int WNS, int OCC>
-int launch_planes_tn(gp_ctx* ctx, gemm_args& g, int splits) {
+int launch_parts_tn(gp_ctx* ctx, gemm_args& g, int splits) {
   constexpr int BA = MB * WMS, BB = NB * WNS, NW = WMS * WNS;
   const int64_t tiles = (g.M + 32 * BA - 1) / (32 * BA) * ((g.N + 32 * BB - 1) / (32 * BB));
   if (tiles * splits > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
   static char name[48];
-  if (!name[0]) snprintf(name, sizeof(name), "gemm_f32x2_tn_%dx%d", 32 * BA, 32 * BB);
+  if (!name[0]) snprintf(name, sizeof(name), "gemm_f32x3_tn_%dx%d", 32 * BA, 32 * BB);
   gp_prof_scope prof(ctx, name, 2.0 * (double)g.M * g.N * g.K,
                      4.0 * ((double)g.M * g.K + (double)g.K * g.N + (double)g.M * g.N * splits));
-  constexpr size_t lds_main = 2 * (size_t)(BA + BB) * 2 * GROUP_B + 2 * (BA + 32 * BB) * sizeof(float);
+  constexpr size_t lds_main = 2 * (size_t)(BA + BB) * TN_BLOCK_B;
   constexpr size_t lds_epi = sizeof(float) * NW * 32 * EPI_LD;
   constexpr size_t lds = lds_main > lds_epi ? lds_main : lds_epi;
   static bool raised = false;
   if (!raised && lds > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_planes_tn_kernel<MB, NB, WMS, WNS, OCC>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
     raised = true;
   }
-  gemm_planes_tn_kernel<MB, NB, WMS, WNS, OCC><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(g);
-  GP_LAUNCH_CHECK(ctx, "gemm_planes_tn_kernel");
+  gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(g);
+  GP_LAUNCH_CHECK(ctx, "gemm_parts_tn_kernel");
   return GP_OK;
 }
 
@@ -755,12 +711,10 @@ int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
   return rc == 1 ? gp_gemm_nt(ctx, A, W, M, N, K, epi) : rc;
 }
 
-// Tiles and splits.  Against 128 x 128, 256 x 256 takes 1.42 / 1.91 ms at 43380 rows and 2048 x 2048, 178 / 232 us at 22000 and 1024 x
-// 1024, 63 / 67 at 22000 and 512 x 512 (three bf16 parts: 2.27 ms, 306, 78 us).  About one or two workgroups per compute unit; few
-// rows are cut into short runs, since a workgroup spends 2 us on a chunk by itself (336 rows, 64 x 64: 32 rows a split 9 us, 128
-// 16, three bf16 parts 17; 3000 rows, 256 x 256: 64 rows 16 us, 256 22).
-gp_tn_planes_plan gp_planes_tn_plan(int64_t rows, int M, int N) {
-  gp_tn_planes_plan p;
+// Tiles and splits.  About one or two workgroups per compute unit; few rows are cut into short runs, since a workgroup spends 1 us
+// on a chunk by itself.
+gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
+  gp_tn_parts_plan p;
   p.big = (int64_t)(M / 256) * (N / 256) >= 4;
   const int T = p.big ? 256 : 128;
   p.tiles_m = (M + T - 1) / T;
@@ -773,11 +727,10 @@ gp_tn_planes_plan gp_planes_tn_plan(int64_t rows, int M, int N) {
   return p;
 }
 
-// From 32 rows on the error is no larger than that of three bf16 parts.
-bool gp_planes_tn_take(const gp_ctx* ctx, int64_t rows) { return ctx->f32_split && !ctx->gemm_bf16 && rows >= 32; }
+bool gp_parts_tn_take(const gp_ctx* ctx) { return ctx->f32_split && !ctx->gemm_bf16; }
 
-int gp_planes_tn_launch(gp_ctx* ctx, void* args, const gp_tn_planes_plan& p) {
+int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& p) {
   gemm_args& g = *static_cast<gemm_args*>(args);
-  if (p.big) return launch_planes_tn<4, 2, 2, 4, 2>(ctx, g, p.splits);
-  return launch_planes_tn<2, 2, 2, 2, 2>(ctx, g, p.splits);
+  if (p.big) return launch_parts_tn<4, 2, 2, 4, 2>(ctx, g, p.splits);
+  return launch_parts_tn<2, 2, 2, 2, 2>(ctx, g, p.splits);
 }

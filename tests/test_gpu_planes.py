@@ -1,4 +1,6 @@
-"""fp32 products with operands as two fp16 parts (csrc/gemm_planes.hip), through the Hadamard block whose dense layers they are."""
+"""fp32 products with operands as two fp16 parts (csrc/gemm_planes.hip), through the Hadamard block whose dense layers they are, and
+the fp32 weight gradients of both blocks (three bf16 parts)."""
+import numpy as np
 import pytest
 import torch
 
@@ -107,3 +109,68 @@ def test_weight_gradient_columns_of_every_size(lib, ctx):
     assert float(err.max()) < 1e-6, err.max()
     want_b = 0.25 * (gup.double() @ W_lin.double().t()).sum(0)
     assert H.rel_l2(gw["b_ji"], want_b.numpy()) < 1e-6
+
+
+def _weight_gradient(lib, ctx, emb, seed, m_scale, gup_scale):
+    """W_ji's gradient and m^T dz in 64 bits, column by column of m: with W_ji = 0, dz = (gup / 2) W_lin^T / 2 for any m."""
+    w = synth.get_workload("cfg2", emb=emb, int_emb=64, n_res_before=0, n_res_after=0)
+    pos, ref, e, t = _case(lib, ctx, w, 4, synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4))
+    E = len(ref["src"])
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(seed)
+    W_lin = torch.eye(emb)      # one product per value: dz is gup / 4 to the last bit
+    W["W_lin"] = W_lin.numpy()
+    m = torch.randn(E, emb, generator=rng) * m_scale(E, emb, rng)
+    gup = torch.randn(E, emb, generator=rng) * gup_scale(E, emb, rng)
+    _, _, gw = _block(lib, ctx, w, t, e, W, m.numpy(), gup.numpy(), 1)
+    want = 0.25 * m.double().t() @ gup.double()
+    size = 0.25 * m.double().abs().t() @ gup.double().abs()     # what the terms of a sum add up to
+    return torch.as_tensor(gw["W_ji"]).double(), want, size
+
+
+@pytest.mark.parametrize("emb", [128, 512])      # the two tiles
+@pytest.mark.parametrize("far", [24, 32, 40])
+def test_weight_gradient_of_a_column_far_below_its_neighbours(lib, ctx, emb, far):
+    # Features 2^-far of the size of those next to them: every value has three bf16 parts of its own (24 bits), so a row of the
+    # gradient is as exact as any other.  Bound: terms off by 3 2^-24 and 394 additions in fp32, 2^-24 of the running sum each, whose
+    # signs are random: 20 2^-24; 2e-6 is some 30 of them.
+    def some_small(E, emb, rng):
+        return torch.where(torch.arange(emb) % 8 == 5, 2.0 ** -far, 1.0)[None, :]
+    got, want, _ = _weight_gradient(lib, ctx, emb, 3, some_small, lambda E, emb, rng: 1.0)
+    err = (got - want).norm(dim=1) / want.norm(dim=1)
+    assert float(err.max()) < 2e-6, err.max()
+
+
+def test_weight_gradient_of_rows_of_every_size(lib, ctx):
+    # Edges whose messages are 2^-40 to 2^40 of each other's size and whose gradients are as much the other way: all count alike.
+    # Bound as above, against the sum of the terms' absolute values.
+    rows = torch.exp2(torch.randint(-40, 41, (4096, 1), generator=torch.Generator().manual_seed(6)).float())
+    got, want, size = _weight_gradient(lib, ctx, 128, 4, lambda E, emb, rng: rows[:E], lambda E, emb, rng: 1.0 / rows[:E])
+    assert float(((got - want).abs() / size).max()) < 2e-6
+
+
+def test_bilinear_weight_gradients_row_by_row(lib, ctx):
+    # The fp32 bilinear block: its Gaussians are 1 to 1e-28 and less of each other's size over the edges of a graph, and the gradients of the
+    # weights that meet them lie in rows of such sizes.  The sum over the edges of W_rbfS's and W_c's gradients is exact to fp32 in every
+    # row (the block's own rounding, some 1e-6, comes on top: 1e-5).
+    from paper_2203_09697_amd.binding_g import StackG
+    w = synth.get_workload("cfg3", emb=64, int_emb=32, num_radial=128, dtype="f32")
+    pos, gptr = synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4)
+    ref = H.oracle_graph(pos, gptr, w.dims.cutoff, w.max_neighbors)
+    e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+    W = synth.weights_G(w.dims, seed=5)
+    m, gup = synth.edge_embeddings(len(ref["src"]), 64, seed=6)
+    basis = lib.gp_basis_forward(ctx, w.dims, e, t)
+    st = StackG(ctx, w.dims, [lib.weights_to_device(W)], t, basis)
+    st.forward(H.to_dev(m, torch.float32))
+    _, gw = st.backward(H.to_dev(gup, torch.float32))
+    ob = H.oracle_basis_G(pos, ref, w.dims)
+    ob["rbf"] = basis["rbf"].cpu().double()       # the same Gaussians, however small
+    want = H.oracle_stack_G(ref, ob, w.dims, [W], m, gup)[2][0]
+    for name, rows in (("W_rbfS", (128,)), ("W_c", (w.dims.num_spherical, 128))):
+        got, ref_rows = (np.asarray(x, np.float64).reshape(-1, want[name].shape[-1]) for x in (gw[0][name].cpu(), want[name]))
+        size = np.linalg.norm(ref_rows, axis=1)
+        seen = size > 1e-26                         # below: parts of the values are no normal numbers any more
+        err = np.linalg.norm(got - ref_rows, axis=1)[seen] / size[seen]
+        print("%s: rows of size %.1e to %.1e, worst %.1e" % (name, size[seen].min(), size.max(), err.max()))
+        assert size[seen].min() < 1e-9 * size.max() and err.max() < 1e-5
