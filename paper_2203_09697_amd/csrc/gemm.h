@@ -70,9 +70,8 @@ int gp_ew_add3(gp_ctx* ctx, const float* a, const float* b, const float* c, floa
 // bf16-operand kernels (gemm_bf16.hip); mode 0 NN, 1 NT, 2 TN; args is the fp32 path's argument block
 int gp_gemm_bf16_launch(gp_ctx* ctx, int mode, void* args, int splits);
 int gp_gemm_bf16_gate_launch(gp_ctx* ctx, void* args);
-// fp32 operands and result on the bf16 matrix cores, each operand as three bf16 planes (gemm_bf16.hip)
+// fp32 operands and result on the bf16 matrix cores, each operand as three bf16 planes (gemm_bf16.hip); mode 0 NN, 1 NT
 int gp_gemm_split_launch(gp_ctx* ctx, int mode, void* args, int splits);
-bool gp_gemm_split_tn_ok(int64_t M, int N, int vecA, int vecB);   // whether A^T B of this shape runs in that form
 // A^T B with both operands bf16 through global->LDS loads and LDS transpose reads: number of splits of its plan (0: the
 // shape is not taken), whether the filled argument block qualifies, launch
 int gp_gemm_bf16_tn_dl_splits(int64_t rows, int M, int N);
@@ -122,12 +121,11 @@ int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 // gp_gemm_nt_w also takes (planes at hand, 16-byte aligned matrices) act = 3, the backward step of y = silu(z) gate behind the product
 // dy: out = dy mul silu'(zsrc) and out2 = dy silu(zsrc), with mul the gate.
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
-// A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, whether it is taken, launch with gp_gemm_tn's argument block
+// A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, launch with gp_gemm_tn's argument block
 struct gp_tn_parts_plan {
   bool big;       // 256 x 256 tiles instead of 128 x 128
   int tiles_m, splits;
   int64_t per;    // rows of a split
 };
 gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N);
-bool gp_parts_tn_take(const gp_ctx* ctx);
 int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& plan);

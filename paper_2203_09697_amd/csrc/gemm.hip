@@ -395,8 +395,7 @@ int dispatch_gemm(gp_ctx* ctx, gemm_args& g, int splits) {
   if (g.a_bf16 || g.b_bf16 || g.epi.bf16)
     return gp_fail(ctx, GP_BAD_ARG, "gemm: bf16 storage is only handled by the bf16-operand kernels");
   if (g.epi.lr_a) return gp_fail(ctx, GP_BAD_ARG, "gemm: a low-rank epilogue factor is only taken by the global->LDS bf16 kernel");
-  // the reduction over rows in that form has one tile shape (128 x 128) and wants 16-byte aligned rows
-  if (ctx->f32_split && (MODE != MODE_TN || gp_gemm_split_tn_ok(g.M, g.N, g.vecA, g.vecB))) return gp_gemm_split_launch(ctx, MODE, &g, splits);
+  if (ctx->f32_split && MODE != MODE_TN) return gp_gemm_split_launch(ctx, MODE, &g, splits);
   if (MODE == MODE_TN) {   // tile widths the split plan (tn_plan / tile_bn) was made for
     if (g.N > 64) return launch_gemm<TILE_BM, 128, 2, 2, MODE>(ctx, g, splits);
     if (g.N > 32) return launch_gemm<TILE_BM, 64, 2, 2, MODE>(ctx, g, splits);
@@ -428,15 +427,12 @@ struct tn_plan_t {
 
 // Split the reduction so that about three workgroups per CU exist (what the register file holds), each
 // reducing >= 256 rows.
-// `light`: the three-plane kernel multiplies 2.7 times faster, so what its workgroups wait for is the partial sums they
-// write (as many bytes as the operands at 169 splits of 43 372 rows): two workgroups per CU instead of three, a third fewer
-// partial sums (configuration 2: 44 -> 41 us per weight gradient, 10 -> 9 us per reduction)
-tn_plan_t tn_plan(int64_t rows, int M, int N, bool light = false) {
+tn_plan_t tn_plan(int64_t rows, int M, int N) {
   tn_plan_t p;
   p.tiles_m = (M + TILE_BM - 1) / TILE_BM;
   p.tiles_n = (N + tile_bn(N) - 1) / tile_bn(N);
   const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-  int64_t s = ((light ? 512 : 768) + tiles - 1) / tiles;
+  int64_t s = (768 + tiles - 1) / tiles;
   const int64_t max_s = (rows + 255) / 256;
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
@@ -550,7 +546,7 @@ int gp_gemm_nt_gate_bwd(gp_ctx* ctx, const float* A, const float* Bt, int64_t M,
 }
 
 size_t gp_gemm_tn_scratch(int64_t rows, int M, int N) {
-  tn_plan_t p = tn_plan(rows, M, N);   // the plan with the most splits: the buffer serves either one
+  tn_plan_t p = tn_plan(rows, M, N);
   const size_t a = gp_align((size_t)p.splits * M * N * sizeof(float)) + gp_align((size_t)p.splits * p.tiles_m * N * sizeof(float));
   const size_t b = gp_align((size_t)gp_gemm_bf16_tn_dl_splits(rows, M, N) * M * N * sizeof(float));   // the bf16 kernel with its own plan
   const gp_tn_parts_plan q = gp_parts_tn_plan(rows > 0 ? rows : 1, M, N);                          // and that of the fp32 blocks
@@ -570,8 +566,7 @@ int gp_gemm_tn(gp_ctx* ctx, const float* A, const float* B, int64_t rows, int M,
   if (rows > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gemm_tn: too many rows");
   const bool vA = a_bf16 ? (M % 2 == 0 && ((uintptr_t)A & 3) == 0) : (M % 4 == 0) && aligned16(A);
   const bool vB = b_bf16 ? (N % 2 == 0 && ((uintptr_t)B & 3) == 0) : (N % 4 == 0) && aligned16(B);
-  const bool light = !ctx->gemm_bf16 && ctx->f32_split && !a_bf16 && !b_bf16 && gp_gemm_split_tn_ok(M, N, vA, vB);
-  const tn_plan_t p = tn_plan(rows, M, N, light);
+  const tn_plan_t p = tn_plan(rows, M, N);
   const size_t need = gp_gemm_tn_scratch(rows, M, N);
   if (!part || part_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gemm_tn: scratch %zu < %zu", part_bytes, need);
   gemm_args g{};
@@ -591,7 +586,8 @@ int gp_gemm_tn(gp_ctx* ctx, const float* A, const float* B, int64_t rows, int M,
       return launch_reduce(ctx, part, s_dl, (int64_t)M * N, out, nullptr, 0, 0, nullptr);
     }
   }
-  if (gp_parts_tn_take(ctx) && !a_bf16 && !b_bf16) {
+  // fp32 operands; column sums exist in the fp32 kernels only
+  if (ctx->f32_split && (!ctx->gemm_bf16 || colsum_out) && !a_bf16 && !b_bf16) {
     const gp_tn_parts_plan q = gp_parts_tn_plan(rows, M, N);
     float* cpart = (float*)((char*)part + gp_align((size_t)q.splits * M * N * sizeof(float)));
     g.colsum_part = colsum_out ? cpart : nullptr;

@@ -727,8 +727,6 @@ gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
   return p;
 }
 
-bool gp_parts_tn_take(const gp_ctx* ctx) { return ctx->f32_split && !ctx->gemm_bf16; }
-
 int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& p) {
   gemm_args& g = *static_cast<gemm_args*>(args);
   if (p.big) return launch_parts_tn<4, 2, 2, 4, 2>(ctx, g, p.splits);
