@@ -73,8 +73,9 @@ int gp_gemm_bf16_gate_launch(gp_ctx* ctx, void* args);
 // fp32 operands and result on the bf16 matrix cores, each operand as three bf16 planes (gemm_bf16.hip); mode 0 NN, 1 NT
 int gp_gemm_split_launch(gp_ctx* ctx, int mode, void* args, int splits);
 // A^T B with both operands bf16 through global->LDS loads and LDS transpose reads: number of splits of its plan (0: the
-// shape is not taken), whether the filled argument block qualifies, launch
+// shape is not taken) and a bound on it that is no smaller for more rows, whether the filled argument block qualifies, launch
 int gp_gemm_bf16_tn_dl_splits(int64_t rows, int M, int N);
+int gp_gemm_bf16_tn_dl_most(int64_t rows, int M, int N);
 bool gp_gemm_bf16_tn_dl_ok(const void* args);
 int gp_gemm_bf16_tn_dl(gp_ctx* ctx, void* args, int splits);
 // While alive, GEMMs issued on the context round their operands to bf16 if `on`.
@@ -124,7 +125,7 @@ int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 // A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, launch with gp_gemm_tn's argument block
 struct gp_tn_parts_plan {
   bool big;       // 256 x 256 tiles instead of 128 x 128
-  int tiles_m, splits;
+  int tiles_m, splits, most;   // most: no smaller for more rows, and at least `splits`
   int64_t per;    // rows of a split
 };
 gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N);

@@ -421,7 +421,7 @@ bool epi_vec_ok(const gp_epilogue& e, int N) {
 }
 
 struct tn_plan_t {
-  int splits, tiles_m, tiles_n;
+  int splits, tiles_m, tiles_n, most;   // most: no smaller for more rows, and at least `splits`
   int64_t per;
 };
 
@@ -436,6 +436,7 @@ tn_plan_t tn_plan(int64_t rows, int M, int N) {
   const int64_t max_s = (rows + 255) / 256;
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
+  p.most = (int)s;
   int64_t per = (rows + s - 1) / s;
   per = (per + BK - 1) / BK * BK;
   s = (rows + per - 1) / per;
@@ -546,11 +547,11 @@ int gp_gemm_nt_gate_bwd(gp_ctx* ctx, const float* A, const float* Bt, int64_t M,
 }
 
 size_t gp_gemm_tn_scratch(int64_t rows, int M, int N) {
-  tn_plan_t p = tn_plan(rows, M, N);
-  const size_t a = gp_align((size_t)p.splits * M * N * sizeof(float)) + gp_align((size_t)p.splits * p.tiles_m * N * sizeof(float));
-  const size_t b = gp_align((size_t)gp_gemm_bf16_tn_dl_splits(rows, M, N) * M * N * sizeof(float));   // the bf16 kernel with its own plan
-  const gp_tn_parts_plan q = gp_parts_tn_plan(rows > 0 ? rows : 1, M, N);                          // and that of the fp32 blocks
-  const size_t c = gp_align((size_t)q.splits * M * N * sizeof(float)) + gp_align((size_t)q.splits * q.tiles_m * N * sizeof(float));
+  const tn_plan_t p = tn_plan(rows, M, N);
+  const size_t a = gp_align((size_t)p.most * M * N * sizeof(float)) + gp_align((size_t)p.most * p.tiles_m * N * sizeof(float));
+  const size_t b = gp_align((size_t)gp_gemm_bf16_tn_dl_most(rows, M, N) * M * N * sizeof(float));   // the bf16 kernel with its own plan
+  const gp_tn_parts_plan q = gp_parts_tn_plan(rows > 0 ? rows : 1, M, N);                           // and that of the fp32 blocks
+  const size_t c = gp_align((size_t)q.most * M * N * sizeof(float)) + gp_align((size_t)q.most * q.tiles_m * N * sizeof(float));
   return std::max(a, std::max(b, c));
 }
 

@@ -1579,12 +1579,16 @@ int dispatch_split(gp_ctx* ctx, gemm_args& g, int splits) {
 
 // The transposed global->LDS kernel: whether it takes the shape, how it splits the rows (about one workgroup per compute
 // unit: tiles x splits), and its launch.  gp_gemm_tn sizes its partial sums with the same plan.
-int gp_gemm_bf16_tn_dl_splits(int64_t rows, int M, int N) {
+int gp_gemm_bf16_tn_dl_most(int64_t rows, int M, int N) {
   if (M % 256 || N % 256 || M > 4096 || N > 4096 || rows < 8192) return 0;
   const int tiles = (M / 256) * (N / 256);
+  const int64_t slabs = (rows + TN_DL_BK - 1) / TN_DL_BK, s = tiles >= 256 ? 1 : 256 / tiles;
+  return (int)(s > slabs ? slabs : s);
+}
+int gp_gemm_bf16_tn_dl_splits(int64_t rows, int M, int N) {
+  const int64_t s = gp_gemm_bf16_tn_dl_most(rows, M, N);
+  if (s == 0) return 0;
   const int64_t slabs = (rows + TN_DL_BK - 1) / TN_DL_BK;
-  int64_t s = tiles >= 256 ? 1 : 256 / tiles;
-  if (s > slabs) s = slabs;
   const int64_t per = (slabs + s - 1) / s;
   return (int)((slabs + per - 1) / per);
 }

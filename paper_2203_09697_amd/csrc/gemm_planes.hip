@@ -712,16 +712,17 @@ int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 }
 
 // Tiles and splits.  About one or two workgroups per compute unit; few rows are cut into short runs, since a workgroup spends 1 us
-// on a chunk by itself.
+// on a chunk by itself: of 32 rows up to 1024 rows, then 32 runs up to 2048, then of 64 rows.  `most` grows with the rows, `splits` (rounded
+// to whole chunks) need not: scratch is sized by the former, so that what serves a graph serves every smaller one.
 gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
   gp_tn_parts_plan p;
   p.big = (int64_t)(M / 256) * (N / 256) >= 4;
   const int T = p.big ? 256 : 128;
   p.tiles_m = (M + T - 1) / T;
   const int64_t tiles = (int64_t)p.tiles_m * ((N + T - 1) / T);
-  const int64_t least = p.big ? 256 : rows < 2048 ? 32 : 64;
-  int64_t s = std::min((p.big ? 256 : 512) / tiles, (rows + least - 1) / least);
-  s = std::max<int64_t>(s, 1);
+  const int64_t runs = p.big ? (rows + 255) / 256 : std::max(std::min<int64_t>((rows + 31) / 32, 32), (rows + 63) / 64);
+  const int64_t s = std::max<int64_t>(std::min((p.big ? 256 : 512) / tiles, runs), 1);
+  p.most = (int)s;
   p.per = ((rows + s - 1) / s + 31) / 32 * 32;
   p.splits = (int)((rows + p.per - 1) / p.per);
   return p;

@@ -56,3 +56,29 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(B, "_HERE", str(tmp_path))
     with pytest.raises(ImportError):
         B.load()
+
+
+@pytest.mark.parametrize("name,widths", [("cfg2", {}), ("cfg2", dict(emb=64, int_emb=32)), ("cfg2", dict(emb=2048, int_emb=256)),
+                                         ("cfg3", {}), ("cfg3", dict(dtype="f32")), ("cfg3", dict(emb=512))])
+def test_workspaces_do_not_shrink_as_the_graph_grows(cdll, name, widths):
+    # a buffer sized for a program's largest graph serves every smaller one
+    import synth
+    from paper_2203_09697_amd import binding as B
+    dims = synth.get_workload(name, **widths).dims
+    last = (0, 0)
+    for E in list(range(1, 9000, 7)) + list(range(9000, 400000, 997)):
+        size = B.gp_block_workspace(dims, E, E * 40, E // 40 + 1)
+        assert size[0] >= last[0] and size[1] >= last[1], (E, last, size)
+        last = size
+
+
+def test_output_and_head_workspaces_do_not_shrink_as_the_graph_grows(cdll):
+    from paper_2203_09697_amd.binding_e import gp_energy_workspace
+    from paper_2203_09697_amd.binding_o import gp_output_workspace
+    for emb in (64, 256, 1024):
+        last = [(0, 0), (0, 0)]
+        for N in list(range(1, 5000, 7)) + list(range(5000, 40000, 503)):
+            now = [gp_output_workspace(emb, 256, 6, 3, N, 30 * N), gp_energy_workspace(emb, 256, N)]
+            for a, b in zip(now, last):
+                assert a[0] >= b[0] and a[1] >= b[1], (emb, N)
+            last = now
