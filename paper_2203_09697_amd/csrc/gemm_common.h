@@ -29,6 +29,9 @@ struct gemm_args {
   // taken by the global->LDS kernel, which walks the second pair's slabs after the first's
   const float* A2 = nullptr;
   const float* B2 = nullptr;
+  // a weight matrix whose operand planes are B: the matrix itself, [K, N] (w_k_rows) or [N, K]
+  const float* W = nullptr;
+  int w_k_rows = 0;
   gp_epilogue epi;
   int epi_kind = 0;        // EK_*: which fixed sequence of epilogue steps `epi` amounts to (set by gp_epilogue_kind on the host)
   unsigned epi_mask = 0;   // EM_*: the steps present when every matrix is fp32 (0: take the general loop); fp32 kernels

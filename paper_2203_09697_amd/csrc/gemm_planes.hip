@@ -1,11 +1,11 @@
 // fp32 products A W, A W^T (edge and atom rows times a weight matrix) on the fp16 matrix cores, and A^T B (sums over the rows:
 // weight gradients), which has a form of its own below.
-// In A W and A W^T every element enters as
-// the sum of two fp16 numbers, v 2^k = hi + lo (22 to 23 significant bits), and three of the four products of the parts are
-// formed (lo.lo is below 2^-22 of the product).  The power of two is chosen so that the largest of the values that share it
-// lies in [2^14, 2^15): the values of a row of A over 32 consecutive k, and a column of W.  Smaller values of the group keep
-// all their bits down to 2^-17 of the largest and lose at most 2^-40 of the largest below that: nothing overflows, fp16's
-// exponents do not matter, and subnormal parts count (this target's matrix instruction takes them).
+// In A W and A W^T every element enters as the sum of two fp16 numbers, v 2^k = hi + lo, and three of the four products of the parts
+// are formed (lo.lo is below 2^-22 of the product).  The power of two is chosen so that the largest of the values that share it
+// lies in [2^15, 2^16): the values of a row of A over 32 consecutive k, and a column of W.  fp16's last place is 2^-24, so a value
+// keeps 23 bits down to 2^-17 of the largest, 21 at 2^-19 (SPAN) and would lose one more with every power of two below that.  Values of A that
+// are smaller still get a pass over the same k of their own, with a scale of their own, and so on until none is left; of W the 16 k of 32
+// columns that hold one are left out and added from the matrix itself, in fp32.  So no value loses bits for what stands beside it.
 // The 32 k are summed from zero and enter the result with their scale taken back: K / 32 additions into the fp32 sum.
 //
 // Against the form with three bf16 parts and six products (gemm_split_kernel: 24 bits, 6 K / 16 additions) that is half the
@@ -40,7 +40,6 @@ __device__ __forceinline__ void split8(const float* v, f16x8& hi, f16x8& lo) {
 #pragma unroll
   for (int c = 0; c < 8; ++c) lo[c] = (_Float16)(v[c] - (float)hi[c]);
 }
-
 // v = p[0] + p[1] + p[2], every part with its own exponent
 __device__ __forceinline__ void parts8(const float* v, bf16x8 (&p)[3]) {
 #pragma unroll
@@ -54,12 +53,38 @@ __device__ __forceinline__ void parts8(const float* v, bf16x8 (&p)[3]) {
   }
 }
 
-// The power of two 2^k that brings the largest of some values into [2^14, 2^15), for the bits of its absolute value: k = 0 where
-// that is 0, an infinity or a NaN, and at most 112 (below 2^-98 not all of the way), so that the factors back are normal numbers.
+// Of the values that share a scale: the largest absolute value, and twice the bits of the smallest that is not zero, less one
+struct value_range {
+  float top = 0.f;
+  uint32_t least = ~0u;
+  __device__ __forceinline__ void add(float a, float b) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(a), "v"(b));
+    add_least(a);
+    add_least(b);
+  }
+  __device__ __forceinline__ void add_least(float v) {
+    const uint32_t d = (__float_as_uint(v) << 1) - 1u;
+    least = d < least ? d : least;
+  }
+  __device__ __forceinline__ uint32_t most() const { return __float_as_uint(top); }
+};
+__device__ __forceinline__ bool any_below(const value_range& r, uint32_t from) {   // zeros are not
+  return r.least < (from ? 2u * from - 1u : 0u);
+}
+// The biased exponent by which some values are scaled, for the bits of the largest absolute one: the next where fp16 would round it up to 2^16
+__device__ __forceinline__ int top_exp(uint32_t bits) { return (int)((bits + 0x1000u) >> 23); }
+// The bits of the smallest absolute value that keeps 21 bits beside that one: hi is at least 2^-4, lo at most 2^-25 off
+constexpr int SPAN = 19;
+__device__ __forceinline__ uint32_t keeps_from(uint32_t most) {
+  const int e = top_exp(most) - SPAN;
+  return (most >> 23) != 255u && e > 0 ? (uint32_t)e << 23 : 0u;
+}
+
+// The power of two 2^k that brings the largest of some values into [2^15, 2^16): k = 0 where that is 0, an infinity or a NaN, and
+// at most 112 (below 2^-97 not all of the way), so that the factors back are normal numbers.
 __device__ __forceinline__ int scale_exp(uint32_t bits) {
-  const int e = (int)(bits >> 23);   // biased exponent
-  const int k = 141 - e;
-  return e == 255 || bits == 0u ? 0 : k < 112 ? k : 112;
+  const int k = 142 - top_exp(bits);
+  return bits >= 0x7F800000u || bits == 0u ? 0 : k < 112 ? k : 112;
 }
 __device__ __forceinline__ float pow2(int k) { return __int_as_float((k + 127) << 23); }   // -126 <= k <= 127
 // The matrix instruction's sums come out low on average, by a part of the last place of their largest term and whatever their
@@ -86,15 +111,18 @@ struct plane_jobs {
 };
 
 // One workgroup per 32 columns n: the scales of the columns first (largest |w| over all k), then the planes, a wavefront per
-// 16 k: lane (kh, n) takes 8 consecutive k of column n.  Behind the planes: the columns' factors back, 2^14 / scale.
+// 16 k: lane (kh, n) takes 8 consecutive k of column n.  Behind the planes: the columns' factors back, 2^14 / scale; a word per block
+// of 32 columns, whether one of its 16-k pieces holds a value that would lose bits; a word per piece, whether this one does.  The
+// planes of such a piece are zero and the products take it from the matrix itself.
 constexpr int PREP_WAVES = 16, PREP_KEEP = 8;   // 16-k pieces a wavefront keeps in registers between the two passes
 __global__ void __launch_bounds__(64 * PREP_WAVES) make_planes_kernel(const plane_jobs jobs) {
   const gp_plane_job& q = jobs.j[blockIdx.y];
   const int k16 = (q.K + 31) / 32 * 2, nb = (q.N + 31) / 32;
   const int blk = blockIdx.x;
   if (blk >= nb) return;
-  __shared__ uint32_t big[32];
+  __shared__ uint32_t big[32], some;
   if (threadIdx.x < 32) big[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) some = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int n = blk * 32 + (lane & 31);
@@ -133,11 +161,25 @@ __global__ void __launch_bounds__(64 * PREP_WAVES) make_planes_kernel(const plan
   __syncthreads();
   const int se = scale_exp(big[lane & 31]);
   const float s = pow2(se);
-  auto put = [&](int u, float* v) __attribute__((always_inline)) {
+  const uint32_t from = keeps_from(big[lane & 31]);
+  char* tail = static_cast<char*>(q.dst) + (int64_t)nb * k16 * GROUP_B;
+  uint32_t* uneven = reinterpret_cast<uint32_t*>(tail + (int64_t)nb * 32 * sizeof(float));
+  auto put = [&](int u, const float* v) __attribute__((always_inline)) {
+    value_range r;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] *= s;
-    f16x8 hi, lo;
-    split8(v, hi, lo);
+    for (int c = 0; c < 8; ++c) r.add_least(v[c]);
+    const bool out = __any(any_below(r, from));
+    if (lane == 0) {
+      uneven[nb + (int64_t)blk * k16 + u] = out;
+      if (out) some = 1u;
+    }
+    f16x8 hi = {}, lo = {};
+    if (!out) {
+      float t[8];
+#pragma unroll
+      for (int c = 0; c < 8; ++c) t[c] = v[c] * s;
+      split8(t, hi, lo);
+    }
     char* dst = static_cast<char*>(q.dst) + ((int64_t)blk * k16 + u) * GROUP_B + lane * 16;
     *reinterpret_cast<f16x8*>(dst) = hi;
     *reinterpret_cast<f16x8*>(dst + FRAG_B) = lo;
@@ -150,7 +192,9 @@ __global__ void __launch_bounds__(64 * PREP_WAVES) make_planes_kernel(const plan
     load(u, v);
     put(u, v);
   }
-  if (threadIdx.x < 32) reinterpret_cast<float*>(static_cast<char*>(q.dst) + (int64_t)nb * k16 * GROUP_B)[n] = pow2(14 - se);
+  if (threadIdx.x < 32) reinterpret_cast<float*>(tail)[n] = pow2(14 - se);
+  __syncthreads();
+  if (threadIdx.x == 0) uneven[blk] = some;
 }
 
 // Epilogue of a wavefront's MB x NB blocks for the steps EMASK names (see tile_epilogue_f32 for the register layout and the
@@ -272,6 +316,9 @@ bool epilogue_listed(unsigned mask) {
 // same values by another wavefront of the workgroup.  The planes of W, 4 KB per 32 columns and 32 k, come through LDS by
 // global->LDS loads, NBUF chunks of them, and are read once per wavefront.  JB column blocks are multiplied together; TD and
 // WD: whether the sums of a group (added to the result while the next group is multiplied) and its planes are double.
+// Rows with values of their own pass (SPAN) take the chunk again: they are read once more (cached), the planes are still in LDS.  Of gradients,
+// which are products, one 32 x 32 in 30 has such a value, of activations one in 300; looking for them costs 1 to 3 %, the passes as much
+// again at 43380 x 2048 x 2048 (1.17 -> 1.25 ms, gradients 1.49 -> 1.66); 13230 x 256 x 256 20 -> 23 us.
 // The activations of the next chunk are requested as soon as this one's are split.  (Splitting the next chunk beside the
 // products of this one, or wavefronts of 64 x 128, ran out of registers: 1.41 -> 1.8 ms at 43380 x 2048 x 2048.)
 template <int MB, int NB, int WAVES, int NBUF, int OCC, int JB, int TD, int WD>
@@ -295,11 +342,12 @@ gemm_planes_kernel(const gemm_args g) {
   const int kh = lane >> 5, l32 = lane & 31;
   const int n_ch = (g.K + 31) / 32, n_st = 2 * n_ch;   // the planes of a K that is no multiple of 32 end in zeros
 
-  const char* srcA[MB];
+  const char* baseA = reinterpret_cast<const char*>(g.A + m0 * g.lda);   // uniform, and a lane's offset
+  uint32_t offA[MB];
 #pragma unroll
   for (int i = 0; i < MB; ++i) {
-    const int64_t row = m0 + wm0 + i * 32 + l32;
-    srcA[i] = reinterpret_cast<const char*>(g.A + (row < g.M ? row : g.M - 1) * g.lda + kh * 8);
+    const int row = wm0 + i * 32 + l32;
+    offA[i] = (uint32_t)(m0 + row < g.M ? row : (int)(g.M - 1 - m0)) * (uint32_t)(g.lda * 4) + kh * 32u;
   }
   f32x4 ra[2][MB][2];   // [step][block][half]: a chunk on its way
   auto fetchA = [&](int c) __attribute__((always_inline)) {
@@ -310,19 +358,19 @@ gemm_planes_kernel(const gemm_args g) {
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) ra[ks][i][h] = *reinterpret_cast<const f32x4*>(srcA[i] + (int64_t)k * 4 + h * 16);
+        for (int h = 0; h < 2; ++h) ra[ks][i][h] = *reinterpret_cast<const f32x4*>(baseA + (int64_t)k * 4 + h * 16 + offA[i]);
     }
   };
   // KB q of a chunk: column block q / 4, step (q % 4) / 2, plane q % 2
   const int nb = (g.N + 31) / 32;                       // column blocks of the planes; past the last: that one again, never stored
-  const char* srcB = reinterpret_cast<const char*>(g.B) + lane * 16;
+  const char* srcB = reinterpret_cast<const char*>(g.B);
   auto issueB = [&](int c, int buf) __attribute__((always_inline)) {
     c = c < n_ch ? c : n_ch - 1;
 #pragma unroll
     for (int i = 0; i < PB; ++i) {
       const int q = wave * PB + i;
       const int blk = n0 / 32 + q / 4 < nb ? n0 / 32 + q / 4 : nb - 1;
-      __builtin_amdgcn_global_load_lds((global_void_ptr)(srcB + ((int64_t)blk * n_st + 2 * c) * GROUP_B + (q % 4) * FRAG_B),
+      __builtin_amdgcn_global_load_lds((global_void_ptr)(srcB + (((int64_t)blk * n_st + 2 * c) * GROUP_B + (q % 4) * FRAG_B) + (uint32_t)lane * 16u),
                                        (lds_void_ptr)(lds + buf * CHUNK_B + q * 1024), 16, 0, 0);
     }
   };
@@ -330,21 +378,39 @@ gemm_planes_kernel(const gemm_args g) {
   // W takes the place of the first operand, so a lane's column of the result is one row of A, whose scale is then a lane's
   f16x8 hi[2][MB], lo[2][MB];   // [step][block]
   float inv[MB];
-  auto splitA = [&](int c) __attribute__((always_inline)) {
+  uint32_t from[MB];   // smaller values of the row wait for a pass of their own
+  auto splitA = [&](int c) __attribute__((always_inline)) {   // returns whether there are any
+    bool below = false;
+    uint32_t most[MB];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-      uint32_t m = 0;
+      value_range r;
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const uint32_t b = __float_as_uint(ra[ks][i][h][q]) & 0x7FFFFFFFu;
-            m = b > m ? b : m;
-          }
-      m = max_halves(m);   // the other 8 k of the row's steps
-      const int se = scale_exp(m);
+          for (int q = 0; q < 4; q += 2) r.add(ra[ks][i][h][q], ra[ks][i][h][q + 1]);
+      most[i] = max_halves(r.most());   // the other 8 k of the row's steps
+      from[i] = keeps_from(most[i]);
+      below |= any_below(r, from[i]);
+    }
+    const bool more = __any(below);
+    if (more) {
+      asm volatile("");   // a branch, which is rarely taken
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+          for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              if ((__float_as_uint(ra[ks][i][h][q]) & 0x7FFFFFFFu) < from[i]) ra[ks][i][h][q] = 0.f;
+    }
+#pragma unroll
+    for (int i = 0; i < MB; ++i) {
+      const int se = scale_exp(most[i]);
       const bool turn = g.K < 1024 && ((c ^ l32) & 3) == 0;
       const float sc = turned(pow2(se), turn);
       inv[i] = turned(pow2(-14 - se), turn);   // the columns' factors carry 2^14 back: the sums stay where the products of the fp32 values are
@@ -356,6 +422,19 @@ gemm_planes_kernel(const gemm_args g) {
         split8(v, hi[ks][i], lo[ks][i]);
       }
     }
+    return more;
+  };
+  auto restA = [&](int c) __attribute__((always_inline)) {   // the values that wait
+    fetchA(c);
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if ((__float_as_uint(ra[ks][i][h][q]) & 0x7FFFFFFFu) >= from[i]) ra[ks][i][h][q] = 0.f;
   };
 
   f32x16 acc[MB][NB], t[TD][MB][JB];
@@ -402,39 +481,83 @@ gemm_planes_kernel(const gemm_args g) {
         for (int v = 0; v < 16; ++v) acc[i][q * JB + jj][v] = __builtin_fmaf(t[q % TD][i][jj][v], inv[i], acc[i][q * JB + jj][v]);
   };
 
+  const float* inv_n = reinterpret_cast<const float*>(reinterpret_cast<const char*>(g.B) + (int64_t)nb * n_st * GROUP_B);
+  const uint32_t* out = reinterpret_cast<const uint32_t*>(inv_n + nb * 32);
+  const uint32_t out_l = lane < NB && n0 / 32 + lane < nb ? out[n0 / 32 + lane] : 0u;   // asked for here, looked at below
 #pragma unroll
   for (int c = 0; c < NBUF - 1; ++c) issueB(c, c);
   __builtin_amdgcn_sched_barrier(0);
   fetchA(0);
   __builtin_amdgcn_sched_barrier(0);
   wait_vmcnt_lgkmcnt0<4 * MB>();
+  const uint32_t cols_out = (uint32_t)__ballot(out_l != 0u);
   __syncthreads();
   int bb = 0;
   for (int c = 0; c < n_ch; ++c) {
     readW(bb, 0);
-    splitA(c);
+    bool more = splitA(c);
     issueB(c + NBUF - 1, bb == 0 ? NBUF - 1 : bb - 1);
-    __builtin_amdgcn_sched_barrier(0);   // the wait at the end counts on this order of the loads
-    fetchA(c + 1);
+    for (;;) {
+      __builtin_amdgcn_sched_barrier(0);   // the wait at the end counts on this order of the loads
+      fetchA(c + 1);
 #pragma unroll
-    for (int q = 0; q < NG; ++q) {
-      if (WD == 2 && q + 1 < NG) readW(bb, q + 1);
-      __builtin_amdgcn_sched_barrier(0);
-      products(q);
-      if (WD == 1 && q + 1 < NG) readW(bb, q + 1);
-      if (TD == 2 && q > 0) add(q - 1);   // while this group's products run
-      if (TD == 1) add(q);
-      __builtin_amdgcn_sched_barrier(0);
+      for (int q = 0; q < NG; ++q) {
+        if (WD == 2 && q + 1 < NG) readW(bb, q + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        products(q);
+        if (WD == 1 && q + 1 < NG) readW(bb, q + 1);
+        if (TD == 2 && q > 0) add(q - 1);   // while this group's products run
+        if (TD == 1) add(q);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (TD == 2) add(NG - 1);
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j) asm volatile("" : "+v"(acc[i][j]));   // the additions stay on this side of the branch
+      if (!more) break;
+      restA(c);   // every pass takes the largest of what is left, and SPAN powers of two below it
+      readW(bb, 0);
+      more = splitA(c);
     }
-    if (TD == 2) add(NG - 1);
     wait_vmcnt_lgkmcnt0<4 * MB + (NBUF - 2) * (PB + 4 * MB)>();
     __syncthreads();
     bb = bb == NBUF - 1 ? 0 : bb + 1;
   }
   wait_vmcnt_lgkmcnt0<0>();
+
+  // The 16 k that W's planes leave out: these rows of W times A's values, both from memory, two k an instruction (fp32).  The sums are in
+  // units of the columns' factors.
+#pragma unroll
+  for (int j = 0; j < NB; ++j) {
+    const int blk = n0 / 32 + j;
+    if (!(cols_out >> j & 1u)) continue;
+    const int n = blk * 32 + l32 < g.N ? blk * 32 + l32 : g.N - 1;
+    const int back = (int)(__float_as_uint(inv_n[n]) >> 23) - 127;
+    const int64_t w_k = g.w_k_rows ? g.N : 1;
+    const float* wn = g.W + n * (int64_t)(g.w_k_rows ? 1 : g.K) + 8 * kh * w_k;
+#pragma unroll 1
+    for (int s0 = 0; s0 < n_st; s0 += 64) {
+      uint64_t steps = __ballot(s0 + lane < n_st && out[nb + (int64_t)blk * n_st + s0 + lane] != 0u);   // none past K
+#pragma unroll 1
+      for (; steps; steps &= steps - 1) {
+        const int k = (s0 + __builtin_ctzll(steps)) * 16;
+        float w[8], a[MB][8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          w[q] = __builtin_ldexpf(wn[(k + q) * w_k], -back);
+#pragma unroll
+          for (int i = 0; i < MB; ++i) a[i][q] = *reinterpret_cast<const float*>(baseA + (int64_t)(k + q) * 4 + offA[i]);
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int i = 0; i < MB; ++i) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[q], a[i][q], acc[i][j], 0, 0, 0);
+      }
+    }
+  }
   __syncthreads();
   float* stage = smem + wave * (32 * EPI_LD);
-  const float* inv_n = reinterpret_cast<const float*>(reinterpret_cast<const char*>(g.B) + (int64_t)nb * n_st * GROUP_B);
   switch (g.epi_mask) {   // uniform
 #define GP_EM_CASE(M) case M: epilogue_blocks<MB, NB, M>(g, acc, stage, m0 + wm0, n0, inv_n); break;
     GP_EM_LIST_PLANES(GP_EM_CASE)
@@ -649,8 +772,8 @@ inline bool al16(const void* p) { return ((uintptr_t)p & 15) == 0; }
 }  // namespace
 
 size_t gp_planes_bytes(int N, int K) {
-  const size_t nb = (size_t)(N + 31) / 32;
-  return nb * (size_t)((K + 31) / 32 * 2) * GROUP_B + nb * 32 * sizeof(float);
+  const size_t nb = (size_t)(N + 31) / 32, k16 = (size_t)((K + 31) / 32 * 2);
+  return nb * k16 * GROUP_B + nb * (32 + 1 + k16) * sizeof(float);
 }
 
 // From K = 64 on the error is the smaller one (above).  At K = 64 a short product is launch and epilogue, which both forms have
@@ -680,8 +803,9 @@ int gp_weight_planes::run() {
 namespace {
 
 // GP_OK, an error, or 1: not taken
-int gemm_planes(gp_ctx* ctx, const float* A, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
+int gemm_planes(gp_ctx* ctx, const float* A, const float* W, int k_rows, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
   gemm_args g{};
+  g.W = W; g.w_k_rows = k_rows;
   g.A = A; g.B = static_cast<const float*>(planes); g.M = M; g.N = N; g.K = K; g.lda = K;
   g.epi = epi;
   g.vecC = al16(epi.bias) && al16(epi.add_pre) && al16(epi.save_pre) && al16(epi.zsrc) && al16(epi.mul) && al16(epi.add_post) &&
@@ -695,7 +819,7 @@ int gemm_planes(gp_ctx* ctx, const float* A, const void* planes, int64_t M, int 
   // 128 leaves compute units idle or the matrix has 64 columns (3000 x 256 x 256: 10.0 us, 128 x 128 14.1; 20000 x 128 x 128: 9.8,
   // 11.0; 13323 x 256 x 256, 210 tiles: 16.2, 15.3).  The values of the result do not depend on the choice.
   const int64_t rows = (M + 127) / 128;
-  if (N >= 512 && rows * ((N + 255) / 256) >= 400) return launch_planes<1, 8, 4, 2, 2, 1, 2, 2>(ctx, g);
+  if (N >= 512 && rows * ((N + 255) / 256) >= 400) return launch_planes<1, 8, 4, 2, 2, 1, 2, 1>(ctx, g);
   if (N > 64 && rows * ((N + 127) / 128) >= 192) return launch_planes<1, 4, 4, 2, 3, 1, 1, 1>(ctx, g);
   return launch_planes<1, 2, 2, 3, 3, 1, 2, 2>(ctx, g);
 }
@@ -703,11 +827,11 @@ int gemm_planes(gp_ctx* ctx, const float* A, const void* planes, int64_t M, int 
 }  // namespace
 
 int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
-  const int rc = gemm_planes(ctx, A, planes, M, N, K, epi);
+  const int rc = gemm_planes(ctx, A, W, 1, planes, M, N, K, epi);
   return rc == 1 ? gp_gemm_nn(ctx, A, W, M, N, K, epi) : rc;
 }
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
-  const int rc = gemm_planes(ctx, A, planes, M, N, K, epi);
+  const int rc = gemm_planes(ctx, A, W, 0, planes, M, N, K, epi);
   return rc == 1 ? gp_gemm_nt(ctx, A, W, M, N, K, epi) : rc;
 }
 

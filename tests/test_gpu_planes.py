@@ -174,3 +174,74 @@ def test_bilinear_weight_gradients_row_by_row(lib, ctx):
         err = np.linalg.norm(got - ref_rows, axis=1)[seen] / size[seen]
         print("%s: rows of size %.1e to %.1e, worst %.1e" % (name, size[seen].min(), size.max(), err.max()))
         assert size[seen].min() < 1e-9 * size.max() and err.max() < 1e-5
+
+
+# (emb, slabs, nx, ny): the three tiles of the products with planes; 272: the last 32 k are half past the end
+@pytest.mark.parametrize("emb,slabs,nx,ny", [(128, 1, 2, 2), (272, 1, 2, 2), (192, 12, 4, 3), (512, 16, 5, 4)])
+@pytest.mark.parametrize("far", [22, 40])
+def test_features_and_weights_far_below_their_neighbours(lib, ctx, emb, slabs, nx, ny, far):
+    # Features of a row 2^-far to 2^far of each other's size meet weights that are as much the other way, so that all terms of a sum count
+    # alike; a weight of 2^60 meets a feature that is zero.  A value keeps 21 bits at least whatever stands beside it, the dropped products
+    # are below 2^-22 of theirs: terms 2^-21 + 2^-21 + 2^-22 off at most, 1.2e-6, mostly a quarter of it, and of random sign; the additions
+    # of some 20 partial sums in fp32 add 2^-24 each.  1e-6 of the sum of the terms' sizes: half of the largest sum.
+    w = synth.get_workload("cfg2", emb=emb, int_emb=64, n_res_before=0, n_res_after=0)
+    pos, gptr = synth.slab_adsorbate_positions(slabs, nx, ny, 3, 4, seed=4)
+    e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+    E = e["n_edges"]
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(far)
+    size = torch.exp2(torch.randint(-far, far + 1, (1, emb), generator=rng).float())
+    half = emb // 2
+    size[:, half:] = 2.0 ** -far        # the columns that are looked at: the gradient that goes past the block is nothing there
+    W_lin = torch.randn(emb, emb, generator=rng) / size
+    gup = torch.randn(E, emb, generator=rng) * size
+    gup[:, 3], W_lin[:, 3] = 0.0, 2.0 ** 60
+    W["W_lin"], W["W_ji"] = W_lin.numpy(), torch.eye(emb).numpy()
+    _, gm, _ = _block(lib, ctx, w, t, e, W, torch.zeros(E, emb).numpy(), gup.numpy(), 1)
+    g, lin = gup.double(), W_lin.double()
+    want, terms = g + 0.25 * g @ lin.t(), g.abs() + 0.25 * g.abs() @ lin.abs().t()
+    err = ((torch.as_tensor(gm).double() - want).abs() / terms)[:, half:]
+    print("E = %d: %.2e" % (E, err.max()))
+    assert float(err.max()) < 1e-6
+
+
+def test_weights_far_below_their_column(lib, ctx):
+    # The forward product (weights [K, N]): in every column one weight of 2^30, which meets a feature that is zero.
+    w = synth.get_workload("cfg2", emb=128, int_emb=64, n_res_before=0, n_res_after=0)
+    pos, gptr = synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4)
+    e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+    E = e["n_edges"]
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(8)
+    W_ji = torch.randn(128, 128, generator=rng)
+    W_ji[9] = 2.0 ** 30
+    m = torch.randn(E, 128, generator=rng)
+    m[:, 9] = 0.0
+    W["W_ji"], W["W_lin"] = W_ji.numpy(), torch.eye(128).numpy()
+    out, _, _ = _block(lib, ctx, w, t, e, W, m.numpy(), m.numpy(), 1)
+    act = lambda v: v * torch.sigmoid(v)
+    want = act(act(m.double() @ W_ji.double())) + m.double()
+    assert H.rel_l2(out, want.numpy()) < 1e-6
+
+
+def test_an_infinity_stays_in_its_row(lib, ctx):
+    # pairs of atoms by themselves: without triplets no edge sees another
+    w = synth.get_workload("cfg2", emb=128, int_emb=64, n_res_before=0, n_res_after=0)
+    pos = np.arange(80, dtype=np.float32)[:, None] * np.float32([100.0, 0.0, 0.0])
+    pos = np.stack([pos, pos + np.float32([1.5, 0.0, 0.0])], 1).reshape(-1, 3)
+    gptr = np.asarray([0, len(pos)], np.int32)
+    e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+    E = e["n_edges"]
+    W = {k: v * 0 for k, v in synth.weights_D(w.dims, seed=5, bias_scale=0.0).items()}
+    rng = torch.Generator().manual_seed(9)
+    W["W_ji"], W["W_lin"] = torch.randn(128, 128, generator=rng).numpy(), torch.randn(128, 128, generator=rng).numpy()
+    gup = torch.randn(E, 128, generator=rng)
+    got = []
+    for value in (None, float("inf"), float("nan")):
+        g = gup.clone()
+        if value is not None:
+            g[17, 40] = value
+        got.append(torch.as_tensor(_block(lib, ctx, w, t, e, W, torch.zeros(E, 128).numpy(), g.numpy(), 1)[1]))
+    keep = torch.arange(E) != 17
+    for bad in got[1:]:
+        assert not bool(torch.isfinite(bad[17]).any()) and torch.equal(bad[keep], got[0][keep])
