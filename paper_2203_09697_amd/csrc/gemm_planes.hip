@@ -88,12 +88,9 @@ __device__ __forceinline__ int scale_exp(uint32_t bits) {
 }
 __device__ __forceinline__ float pow2(int k) { return __int_as_float((k + 127) << 23); }   // -126 <= k <= 127
 // The matrix instruction's sums come out low on average, by a part of the last place of their largest term and whatever their
-// sign: over the rows of a bias gradient that adds up.  Some of the sums are therefore formed with the sign of one operand
-// turned round (its scale is negative, and so is the factor back).  With half of them turned the bias gradients of a block of
-// width 256 over 23453 edges are 3e-7 off, with none 5.1e-6, three bf16 parts 3.9e-6, the fp32 instruction 9e-7.  In A W and A W^T a
-// quarter is turned where K < 1024 and none above, where the 32 k of a sum leave less than the running sums of that form
-// (K = 1024 3.5e-6 and 4.9e-6): closer than before at every width, and results that differ from those of the other forms, whose
-// error this is, by half as much as with all of it taken out.
+// sign: over the rows of a bias gradient that adds up.  Half of the sums are therefore formed with the sign of one operand turned round
+// (its scale is negative, and so is the factor back): four blocks of width 256 over 43380 edges 6e-7 off (a quarter turned 2.2e-5,
+// three bf16 parts, whose sums run on, 3.4e-5), one of width 2048 4.3e-7 (none turned 2.3e-5, three bf16 parts 4.0e-5).
 __device__ __forceinline__ float turned(float scale, bool turn) { return __int_as_float(__float_as_int(scale) ^ (turn ? 1 << 31 : 0)); }
 // the larger of lanes l and l ^ 32
 __device__ __forceinline__ uint32_t max_halves(uint32_t m) {
@@ -411,7 +408,7 @@ gemm_planes_kernel(const gemm_args g) {
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
       const int se = scale_exp(most[i]);
-      const bool turn = g.K < 1024 && ((c ^ l32) & 3) == 0;
+      const bool turn = ((c ^ l32) & 1) == 0;
       const float sc = turned(pow2(se), turn);
       inv[i] = turned(pow2(-14 - se), turn);   // the columns' factors carry 2^14 back: the sums stay where the products of the fp32 values are
 #pragma unroll

@@ -245,3 +245,21 @@ def test_an_infinity_stays_in_its_row(lib, ctx):
     keep = torch.arange(E) != 17
     for bad in got[1:]:
         assert not bool(torch.isfinite(bad[17]).any()) and torch.equal(bad[keep], got[0][keep])
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("emb,slabs", [(256, 12), (1024, 3)])
+def test_bias_gradients_collect_no_rounding_of_one_sign(lib, ctx, emb, slabs):
+    # A bias gradient sums a value of every edge: what the products' rounding has in common on all of them adds up, what has none grows
+    # as the root of their number.  The fp32 instruction's own sums come out low; the products in two fp16 parts are no further off.
+    w = synth.get_workload("cfg2", emb=emb, int_emb=64)
+    pos, ref, e, t = _case(lib, ctx, w, 3, synth.slab_adsorbate_positions(slabs, 4, 4, 3, 5, seed=3))
+    W = synth.weights_D(w.dims, seed=5, bias_scale=0.1)
+    m, gup = synth.edge_embeddings(len(ref["src"]), emb, seed=6)
+    want = H.oracle_stack_D(ref, H.oracle_basis_D(pos, ref, w.dims), w.dims, [W], m, gup)[2][0]
+    err = {}
+    for split in (1, 0):
+        got = _block(lib, ctx, w, t, e, W, m, gup, split)[2]
+        err[split] = max(H.rel_l2(got[k], want[k]) for k in want if k[0] == "b")
+    print("E=%d: two fp16 parts %.2e, fp32 instruction %.2e" % (len(ref["src"]), err[1], err[0]))
+    assert err[1] < err[0]
