@@ -465,7 +465,12 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   }
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.xg, sc.dF2, E, H, F, gw->W_down, nullptr, sc.part_aux, sc.part_bytes); },
                     {sc.dF2}));
-  if (p_down) {   // dxg = dF2 W_down^T is not stored: its epilogue takes the gate apart (two launches: 26 + 48 us at 43380 x 256)
+  // dxg = dF2 W_down^T is not stored where its epilogue can take the gate apart (two launches: 26 + 48 us at 43380 x 256): planes, and
+  // buffers that start on 16 bytes
+  bool gate_fused = p_down != nullptr;
+  for (const void* p : {(const void*)sc.dF2, (const void*)s.z_kj, (const void*)s.gate, (const void*)dz_kj, (const void*)dgate})
+    gate_fused = gate_fused && ((uintptr_t)p & 15) == 0;
+  if (gate_fused) {
     GP_TRY(aux.before_write(dz_kj));
     gp_epilogue e; e.act = 3; e.zsrc = s.z_kj; e.mul = s.gate; e.out = dz_kj; e.out2 = dgate;
     GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                        // dz_kj, dgate

@@ -961,7 +961,9 @@ int backward_G(gp_ctx* ctx, const gp_dims* dims, const gp_weights_G* w, const gp
   GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.xg, sc.dzdn, E, H, F, gw->W_down, nullptr, sc.part_aux, sc.part_bytes, hs, dzdn_half); }, {}));
   float* dz_ba = d_up;   // d_up is no longer needed on this stream
   // with the gate as its two factors the backward step of the gated activation is the epilogue of the product that gives dxg
-  const bool gate_fused = dzdn_half && lowrank_gate(ctx, dims, E) && ((uintptr_t)w->W_rbfB & 15) == 0;
+  bool gate_fused = dzdn_half && lowrank_gate(ctx, dims, E);
+  for (const void* p : {(const void*)w->W_rbfB, (const void*)sc.dzdn, (const void*)W_down, (const void*)s.z_ba, (const void*)dz_ba, (const void*)dgate})
+    gate_fused = gate_fused && ((uintptr_t)p & 15) == 0;
   if (!gate_fused) {
     e = gp_epilogue(); e.out = dxg; e.bf16 = hs ? EPI_BF_OUT : 0u;
     if (dzdn_half) {

@@ -107,9 +107,9 @@ struct gp_weight_planes {
   gp_plane_job jobs[GP_PLANE_JOBS_MAX];
   int n = 0;
   gp_weight_planes(gp_ctx* c, void* room) : ctx(c), next(static_cast<char*>(room)) {}
-  // planes of W for products with M rows (NULL where the general kernels take them)
+  // planes of W for products with M rows (NULL where the general kernels take them, as they do where the room is not 16-byte aligned)
   const void* add(const float* W, int64_t M, int N, int K, int k_rows) {
-    if (n == GP_PLANE_JOBS_MAX || !gp_planes_take(ctx, M, N, K)) return nullptr;
+    if (n == GP_PLANE_JOBS_MAX || ((uintptr_t)next & 15) != 0 || !gp_planes_take(ctx, M, N, K)) return nullptr;
     jobs[n++] = gp_plane_job{W, next, N, K, k_rows};
     void* p = next;
     next += gp_align(gp_planes_bytes(N, K));
@@ -119,8 +119,8 @@ struct gp_weight_planes {
 };
 // gp_gemm_nn / gp_gemm_nt with the planes of the weight matrix at hand (NULL: the general kernels)
 int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
-// gp_gemm_nt_w also takes (planes at hand, 16-byte aligned matrices) act = 3, the backward step of y = silu(z) gate behind the product
-// dy: out = dy mul silu'(zsrc) and out2 = dy silu(zsrc), with mul the gate.
+// gp_gemm_nt_w also takes act = 3, the backward step of y = silu(z) gate behind the product dy: out = dy mul silu'(zsrc) and
+// out2 = dy silu(zsrc), with mul the gate; only with planes at hand and every matrix 16-byte aligned, which the caller looks at.
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
 // A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, launch with gp_gemm_tn's argument block
 struct gp_tn_parts_plan {

@@ -829,6 +829,7 @@ int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 }
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi) {
   const int rc = gemm_planes(ctx, A, W, 0, planes, M, N, K, epi);
+  GP_REQUIRE(ctx, rc != 1 || epi.act != 3, "gemm: the gate's step needs planes and 16-byte aligned matrices");
   return rc == 1 ? gp_gemm_nt(ctx, A, W, M, N, K, epi) : rc;
 }
 

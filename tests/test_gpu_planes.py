@@ -263,3 +263,26 @@ def test_bias_gradients_collect_no_rounding_of_one_sign(lib, ctx, emb, slabs):
         err[split] = max(H.rel_l2(got[k], want[k]) for k in want if k[0] == "b")
     print("E=%d: two fp16 parts %.2e, fp32 instruction %.2e" % (len(ref["src"]), err[1], err[0]))
     assert err[1] < err[0]
+
+
+@pytest.mark.parametrize("saved_at,scratch_at", [(8, 0), (0, 8), (8, 8)])
+def test_buffers_that_do_not_start_on_16_bytes(lib, ctx, saved_at, scratch_at):
+    # saved and scratch may start anywhere: the same results by the kernels that do not need more
+    from paper_2203_09697_amd.stack import StackD
+    w = synth.get_workload("cfg2", emb=128, int_emb=128)
+    pos, gptr = synth.slab_adsorbate_positions(1, 2, 2, 3, 4, seed=4)
+    e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+    W = lib.weights_to_device(synth.weights_D(w.dims, seed=5, bias_scale=0.1))
+    m, gup = (H.to_dev(x, torch.float32) for x in synth.edge_embeddings(e["n_edges"], 128, seed=6))
+    basis = lib.gp_basis_forward(ctx, w.dims, e, t)
+    got = []
+    for at in ((0, 0), (saved_at, scratch_at)):
+        st = StackD(ctx, w.dims, [W], t, basis)
+        room = [torch.empty(b.numel() + 8, dtype=torch.uint8, device="cuda:0") for b in (st.saved[0], st.scratch)]
+        st.saved[0], st.scratch = room[0][at[0]:at[0] + st.saved[0].numel()], room[1][at[1]:at[1] + st.scratch.numel()]
+        assert st.saved[0].data_ptr() % 16 == at[0] and st.scratch.data_ptr() % 16 == at[1]
+        out = st.forward(m).cpu().numpy()
+        gm, gw = st.backward(gup)
+        got.append([out, gm.cpu().numpy()] + [gw[0][k].cpu().numpy() for k in sorted(gw[0])])
+    for a, b in zip(*got):
+        assert H.rel_l2(b, a) < 5e-6      # fp32 sums in another order, and those of two forms against each other
