@@ -23,6 +23,21 @@ PEAK = {"hbm": (8000.0, "GB/s"), "mfma_f32": (157.3, "TFLOP/s"), "mfma_bf16": (2
 ALU_KERNELS = ("tripD_fwd", "tripD_bwd", "tripG_fwd", "trip_bwd_H", "tripG_grad_cos", "tripG_edge")
 
 
+def peak_key(kernel):
+    """The entry of PEAK (and of measured_rates) that bounds a kernel."""
+    for prefix, key in (("gemm_f32x2", "mfma_f32x2"), ("gemm_f32x3", "mfma_f32x3"), (("gemm_f32", "tripD_mfma"), "mfma_f32"),
+                        (("gemm_bf16", "tripG_mfma"), "mfma_bf16"), (ALU_KERNELS, "alu_f32")):
+        if kernel.startswith(prefix):
+            return key
+    return "hbm"
+
+
+def measured_rates(mp):
+    """The same ceilings from the rates that gp_measure_peaks finds on the card (none for the vector units)."""
+    return {"hbm": mp["copy_GBps"], "mfma_f32": mp["mfma_f32_TFLOPs"], "mfma_bf16": mp["mfma_bf16_TFLOPs"],
+            "mfma_f32x3": mp["mfma_bf16_TFLOPs"] / 6.0, "mfma_f32x2": mp["mfma_bf16_TFLOPs"] / 3.0}
+
+
 def measured_traffic(workload, modified):
     """HBM bytes per launch from the committed rocprofv3 --pmc summary of this workload, if any
     (profiles/block_<variant>_<workload>_hbm_traffic.md; counters cannot be read from inside the run).
@@ -264,30 +279,19 @@ def main():
     kernels = []
     for name, d in sorted(prof.items(), key=lambda kv: -kv[1]["ms"]):
         per_launch_ms = d["ms"] / d["launches"]
-        if name.startswith("gemm_f32x2"):
-            ach, (peak, unit), bound = d["flops"] / (d["ms"] * 1e-3) / 1e12, PEAK["mfma_f32x2"], "mfma"
-        elif name.startswith("gemm_f32x3"):
-            ach, (peak, unit), bound = d["flops"] / (d["ms"] * 1e-3) / 1e12, PEAK["mfma_f32x3"], "mfma"
-        elif name.startswith(("gemm_f32", "tripD_mfma")):
-            ach, (peak, unit), bound = d["flops"] / (d["ms"] * 1e-3) / 1e12, PEAK["mfma_f32"], "mfma"
-        elif name.startswith(("gemm_bf16", "tripG_mfma")):
-            ach, (peak, unit), bound = d["flops"] / (d["ms"] * 1e-3) / 1e12, PEAK["mfma_bf16"], "mfma"
-        elif name.startswith(ALU_KERNELS):
-            ach, (peak, unit), bound = d["flops"] / (d["ms"] * 1e-3) / 1e12, PEAK["alu_f32"], "alu"
-        else:
-            ach, (peak, unit), bound = d["bytes"] / (d["ms"] * 1e-3) / 1e9, PEAK["hbm"], "hbm"
+        key = peak_key(name)
+        peak, unit = PEAK[key]
+        bound = "mfma" if key.startswith("mfma") else "alu" if key == "alu_f32" else key
+        ach = d["bytes"] / (d["ms"] * 1e-3) / 1e9 if key == "hbm" else d["flops"] / (d["ms"] * 1e-3) / 1e12
         kernels.append({"kernel": name, "launches_per_step": d["launches"] / prof_steps, "avg_ms": round(per_launch_ms, 5),
                         "ms_per_step": round(d["ms"] / prof_steps, 4), "bound": bound, "achieved": round(ach, 3),
                         "peak": peak, "unit": unit, "frac": round(ach / peak, 4)})
     # the same fractions against rates measured on this GPU (copy kernel, register-resident MFMA chains)
     mp = gp.gp_measure_peaks(ctx)
-    measured = {"hbm": mp["copy_GBps"], "mfma_f32": mp["mfma_f32_TFLOPs"], "mfma_bf16": mp["mfma_bf16_TFLOPs"],
-                "mfma_f32x3": mp["mfma_bf16_TFLOPs"] / 6.0, "mfma_f32x2": mp["mfma_bf16_TFLOPs"] / 3.0}
+    measured = measured_rates(mp)
     for k in kernels:
-        key = "hbm" if k["bound"] == "hbm" else ("mfma_bf16" if k["peak"] == PEAK["mfma_bf16"][0] else
-                                                  "mfma_f32x3" if k["peak"] == PEAK["mfma_f32x3"][0] else
-                                                  "mfma_f32" if k["bound"] == "mfma" else None)
-        k["frac_of_measured"] = round(k["achieved"] / measured[key], 4) if key else None
+        rate = measured.get(peak_key(k["kernel"]))
+        k["frac_of_measured"] = round(k["achieved"] / rate, 4) if rate else None
     top = kernels[0]
     traffic = measured_traffic(w, bool(opts) or a.output_blocks or a.trip_mode >= 0 or a.no_side_stream or a.f32_gemm != "split")
     for k in kernels:
