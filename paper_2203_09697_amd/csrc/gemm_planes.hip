@@ -10,9 +10,9 @@
 //
 // Against the form with three bf16 parts and six products (gemm_split_kernel: 24 bits, 6 K / 16 additions) that is half the
 // matrix instructions and a smaller error, because the additions are what that form's error is made of.  Relative error
-// against 64 bits, operands uniform in +-1 (three bf16 parts / two fp16 parts / fp32 matrix instruction): K = 32 6.9e-8 / 6.3e-8 /
-// 1.0e-7, K = 64 1.1e-7 / 7.1e-8 / 1.4e-7, K = 256 2.3e-7 / 8.8e-8 / 2.9e-7, K = 2048 7.0e-7 / 1.6e-7 / 8.1e-7.  At K = 16 it is
-// the larger one (3.3e-8 / 4.7e-8 / 7.4e-8): shapes with K < 64 stay with the other kernels.
+// against 64 bits, operands uniform in +-1 (three bf16 parts / two fp16 parts / fp32 matrix instruction): K = 64 1.1e-7 / 8.3e-8 /
+// 1.5e-7, K = 128 1.6e-7 / 8.9e-8 / 2.0e-7, K = 256 2.4e-7 / 9.8e-8 / 2.9e-7, K = 1024 4.8e-7 / 1.3e-7 / 5.7e-7, K = 2048 6.9e-7 /
+// 1.7e-7 / 8.1e-7.  Shorter contractions, where the two forms meet, stay with the other kernels (gp_planes_take).
 //
 // What bounds these products is power as much as anything: with random operands the matrix units of the whole chip sustain 1.87
 // PFLOP/s in bf16 and 1.72 in fp16 from registers alone (2.47 with zeros), so fewer matrix instructions is what helps.

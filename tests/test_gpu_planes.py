@@ -286,3 +286,28 @@ def test_buffers_that_do_not_start_on_16_bytes(lib, ctx, saved_at, scratch_at):
         got.append([out, gm.cpu().numpy()] + [gw[0][k].cpu().numpy() for k in sorted(gw[0])])
     for a, b in zip(*got):
         assert H.rel_l2(b, a) < 5e-6      # fp32 sums in another order, and those of two forms against each other
+
+
+@pytest.mark.parametrize("emb,many", [(128, 20), (512, 20)])     # 64 x 64 tiles of one slab; 128 x 128 and 128 x 256 of many
+def test_values_do_not_depend_on_the_tile(lib, ctx, emb, many):
+    # the same slab by itself and as the first of many: other tiles, the same values.  No triplets: their kernels go by the graph.
+    from paper_2203_09697_amd.stack import StackD
+    w = synth.get_workload("cfg2", emb=emb, int_emb=64)
+    one, _ = synth.slab_adsorbate_positions(1, 4, 3, 3, 5, seed=3)
+    W = synth.weights_D(w.dims, seed=5, bias_scale=0.1)
+    for k in ("W_down", "W_up", "W_sbf1", "W_sbf2"):
+        W[k] = W[k] * 0
+    W = lib.weights_to_device(W)
+    got = []
+    for n in (1, many):
+        pos, gptr = np.tile(one, (n, 1)), np.arange(n + 1, dtype=np.int32) * len(one)
+        e, t = lib.build_graph(ctx, H.to_dev(pos, torch.float32), H.to_dev(gptr, torch.int32), w.dims.cutoff, w.max_neighbors)
+        E = e["n_edges"] // n
+        m, gup = (H.to_dev(np.tile(x, (n, 1)), torch.float32) for x in synth.edge_embeddings(E, emb, seed=6))
+        st = StackD(ctx, w.dims, [W], t, lib.gp_basis_forward(ctx, w.dims, e, t))
+        out = st.forward(m).cpu()
+        got.append((out[:E], st.backward(gup)[0].cpu()[:E]))
+        for first in got[-1]:
+            assert bool(torch.isfinite(first).all())
+    print("E = %d and %d" % (E, E * many))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
