@@ -67,11 +67,17 @@ int gp_set_side_stream(gp_ctx* ctx, int on);
 int gp_set_triplet_mfma(gp_ctx* ctx, int mode);
 
 /* GEMMs with fp32 operands and results (the fp32 blocks, Sec. 3.3; the energy head).  split = 1 (default): on the 16-bit
- * matrix cores with fp32 accumulation, in one of two forms, chosen by shape.  Products of edge rows with the wide weights: every
- * operand element as two fp16 numbers under a power-of-two scale (per row and 32 contraction indices; per column of the
- * weights), three products.  The others: every element as three bf16 numbers whose sum is the fp32 value (24 significant
- * bits), six of the nine products, the dropped ones below 2^-24.  Either agrees with 64-bit results at least as closely as
- * the fp32 instruction does, at 2.7 to 5 times its rate.
+ * matrix cores with fp32 accumulation, in one of two forms:
+ *  - two fp16 numbers per element, three products: A W and A W^T of the dense layers of the Hadamard block, the output
+ *    blocks and the energy head, for contractions of 128 and more (64 and more from 8192 rows on) that are multiples of 16 and
+ *    matrices of 64 columns and more, a multiple of 4, both up to 8192; buffers that start on 16 bytes.  Elements share a power of
+ *    two: a row of A over 32 contraction indices, a column of W.  Those from 2^-17 of the largest that shares it keep 23
+ *    bits, to 2^-19 21; smaller ones enter by themselves, with a scale of their own (A) or in fp32 (W).  Dropped: below 2^-22 of a product.
+ *  - three bf16 numbers per element, each with its own exponent, whose sum is the fp32 value (24 bits), six of the nine products, the
+ *    dropped ones below 2^-24: all sums over rows A^T B (weight gradients) and every other product, the fp32 bilinear block's among them.
+ * Relative error of a product against 64 bits, uniform operands, two fp16 / three bf16 / split = 0: contraction of 64 8e-8 /
+ * 1.1e-7 / 1.5e-7, 256 1.0e-7 / 2.4e-7 / 2.9e-7, 2048 1.7e-7 / 6.9e-7 / 8.1e-7.  The matrix cores' fp32-equivalent rate is 5.3 (two
+ * fp16) or 2.7 times (three bf16) that of the fp32 instruction.
  * split = 0: the fp32-operand matrix-core instruction.  GP_F32_GEMM=0/1 in the environment sets it at gp_create. */
 int gp_set_f32_gemm(gp_ctx* ctx, int split);
 

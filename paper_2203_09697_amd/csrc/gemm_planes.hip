@@ -774,8 +774,8 @@ size_t gp_planes_bytes(int N, int K) {
 }
 
 // From K = 64 on the error is the smaller one (above).  At K = 64 a short product is launch and epilogue, which both forms have
-// (13323 x 256 x 64: 10.7 us, three bf16 parts 10.0; 43380 x 256 x 64, A W^T: 19.7, 25.4; 5000 x 64 x 64: 7.1, 6.4); the conversion of all
-// weights of a call is one launch of 4 to 5 us.
+// (13505 x 256 x 64: 14.9 us in 64 x 64 tiles, 17.2 in 128 x 128, three bf16 parts 16.2; 43045 x 256 x 64: 39.8, three bf16 parts 45.8;
+// 5448 x 64 x 64: 7.7, 7.5; 5448 x 256 x 64: 10.1, 13.0); the conversion of all weights of a call is one launch (6.5 us at width 256, 88 at 2048).
 bool gp_planes_take(const gp_ctx* ctx, int64_t M, int N, int K) {
   return ctx->f32_split && !ctx->gemm_bf16 && K % 16 == 0 && N % 4 == 0 && N >= 64 && N <= 8192 && K <= 8192 &&
          (K >= 128 || (K >= 64 && M >= 8192));
@@ -811,10 +811,13 @@ int gemm_planes(gp_ctx* ctx, const float* A, const float* W, int k_rows, const v
   if (!planes || !al16(A) || !epilogue_listed(g.epi_mask)) return 1;
   GP_REQUIRE(ctx, M >= 0 && gp_planes_take(ctx, 8192, N, K), "gemm: planes of a shape that has none");
   if (M == 0) return GP_OK;
-  // Tiles: 128 x 256 where there are enough of them for several rounds of two per compute unit (43380 x 2048 x 2048: 1.41 ms, with
-  // 128 x 128 1.57; 13323 x 1024 x 1024: 0.124, 0.139; 22000 x 512 x 512, 344 tiles: 0.060, 0.055); 64 x 64 where a launch of 128 x
-  // 128 leaves compute units idle or the matrix has 64 columns (3000 x 256 x 256: 10.0 us, 128 x 128 14.1; 20000 x 128 x 128: 9.8,
-  // 11.0; 13323 x 256 x 256, 210 tiles: 16.2, 15.3).  The values of the result do not depend on the choice.
+  // Tiles: 128 x 256 where there are enough of them for several rounds of two per compute unit (43045 x 2048 x 2048: 1.24 ms, with
+  // 128 x 128 1.37; 13505 x 1024 x 1024, 424 tiles: 0.128, 0.150; 21612 x 512 x 512, 338: 0.074, 0.069; 8131 x 1024 x 1024, 256: 0.085,
+  // 0.080); 64 x 64 where a launch of 128 x 128 leaves compute units idle or the matrix has 64 columns (2667 x 256 x 256: 14.7 us,
+  // 128 x 128 20.5; 18844 x 128 x 128, 148 tiles: 14.1, 16.8; 27036 x 256 x 256, 424: 43.5, 31.0; 10790 x 512 x 512, 340: 47, 43).  The two
+  // meet between 250 and 340 tiles (13505 x 256 x 256, 212: 20.6, 22.5; 16180, 254: 22.5, 23.8; 21612, 338: 29.6, 30.2; 8131 x 512 x 512,
+  // 256: 34.5, 35.5): the line stands where it was drawn for products without passes over small values (210 tiles: 16.2, 15.3).
+  // The values of the result do not depend on the choice.
   const int64_t rows = (M + 127) / 128;
   if (N >= 512 && rows * ((N + 255) / 256) >= 400) return launch_planes<1, 8, 4, 2, 2, 1, 2, 1>(ctx, g);
   if (N > 64 && rows * ((N + 127) / 128) >= 192) return launch_planes<1, 4, 4, 2, 3, 1, 1, 1>(ctx, g);

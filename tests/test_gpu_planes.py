@@ -58,7 +58,7 @@ def test_block_against_the_oracle(lib, ctx, emb, int_emb, slabs, nx, ny):
         assert err < 2e-6 and err < 1.5 * H.rel_l2(plain[i], want[i])
         assert H.row_err(got[i], want[i]) < 1e-5
     worst = {s: max(H.rel_l2(r[2][k], g) for k, g in want[2][0].items()) for s, r in (("parts", got), ("instruction", plain))}
-    print("weight gradients: two fp16 parts %.2e, fp32 instruction %.2e" % (worst["parts"], worst["instruction"]))
+    print("weight gradients: 16-bit parts %.2e, fp32 instruction %.2e" % (worst["parts"], worst["instruction"]))
     assert worst["parts"] < 1e-5
 
 
