@@ -12,34 +12,30 @@ constexpr int MAX_S = 8;
 constexpr int MAX_R_BESSEL = 16;
 
 struct bessel_table {
-  double z[MAX_S * MAX_R_BESSEL];     // z[l*R + n]  zeros of j_l
-  double norm[MAX_S * MAX_R_BESSEL];  // sqrt(2 / (c^3 j_{l+1}(z)^2))
+  double z[MAX_S * MAX_R_BESSEL];      // z[l*R + n]  zeros of j_l
+  double inv_z[MAX_S * MAX_R_BESSEL];  // 1 / z
+  double norm[MAX_S * MAX_R_BESSEL];   // sqrt(2 / (c^3 j_{l+1}(z)^2))
+  double inv_cutoff, root;             // 1 / c, sqrt(2 / c)
 };
 
-// j_{l-1}(x) and j_l(x) (the former only for l >= 1), x > 0: ascending series below the turning point, upward recurrence
-// above it.  The series stops when its terms no longer reach the sum.
-__host__ __device__ inline double bessel_series(int l, double x) {
-  const double q = -0.5 * x * x;
-  double term = 1.0, sum = 1.0;
-  for (int k = 1; k <= 40 && fabs(term) > 1e-18 * fabs(sum); ++k) {
-    term *= q / ((double)k * (double)(2 * l + 2 * k + 1));
-    sum += term;
-  }
-  double num = 1.0, den = 1.0;   // x^l / (2l+1)!!
-  for (int k = 1; k <= l; ++k) {
-    num *= x;
-    den *= (double)(2 * k + 1);
-  }
-  return num / den * sum;
-}
-__host__ __device__ inline double sph_bessel_pair(int l, double x, double* below) {
+// j_l(x) on the host, where the zeros are found: ascending series below the turning point, upward recurrence above it.  The series
+// stops when its terms no longer reach the sum.
+inline double sph_bessel(int l, double x) {
   if (x < (double)l + 1.0 && l >= 2) {
-    if (below) *below = bessel_series(l - 1, x);
-    return bessel_series(l, x);
+    const double q = -0.5 * x * x;
+    double term = 1.0, sum = 1.0;
+    for (int k = 1; k <= 40 && fabs(term) > 1e-18 * fabs(sum); ++k) {
+      term *= q / ((double)k * (double)(2 * l + 2 * k + 1));
+      sum += term;
+    }
+    double num = 1.0, den = 1.0;   // x^l / (2l+1)!!
+    for (int k = 1; k <= l; ++k) {
+      num *= x;
+      den *= (double)(2 * k + 1);
+    }
+    return num / den * sum;
   }
-  double s, c;
-  sincos(x, &s, &c);
-  const double inv = 1.0 / x;
+  const double s = sin(x), c = cos(x), inv = 1.0 / x;
   double j0 = s * inv;
   if (l == 0) return j0;
   double j1 = (s * inv - c) * inv;
@@ -48,10 +44,86 @@ __host__ __device__ inline double sph_bessel_pair(int l, double x, double* below
     j0 = j1;
     j1 = j2;
   }
-  if (below) *below = j0;
   return j1;
 }
-__host__ __device__ inline double sph_bessel(int l, double x) { return sph_bessel_pair(l, x, nullptr); }
+
+// sin and cos of the arguments of the Bessel functions: the multiple of pi/2 taken off (pi/2 as the double next to it, whose
+// multiple leaves y without rounding, since both end at 2^-52 and what is left is below 1, and the rest of it), then the Taylor sums over [-pi/4, pi/4] to r^17 and r^16 (what follows is below 1e-19 and 2e-18).  About 30
+// instructions, a third of the library's sincos, which takes the arguments that are larger, infinite or no number.
+__device__ __forceinline__ void sincos_small(double y, double* s, double* c) {
+  if (!(fabs(y) < 1e5)) {
+    sincos(y, s, c);
+    return;
+  }
+  const double n = rint(y * M_2_PI);
+  const int q = (int)n;
+  const double r = fma(-n, 6.123233995736766e-17, fma(-n, M_PI_2, y));
+  const double r2 = r * r;
+  double a = 1.0 / 355687428096000.0, b = 1.0 / 20922789888000.0;
+  a = fma(a, r2, -1.0 / 1307674368000.0);
+  b = fma(b, r2, -1.0 / 87178291200.0);
+  a = fma(a, r2, 1.0 / 6227020800.0);
+  b = fma(b, r2, 1.0 / 479001600.0);
+  a = fma(a, r2, -1.0 / 39916800.0);
+  b = fma(b, r2, -1.0 / 3628800.0);
+  a = fma(a, r2, 1.0 / 362880.0);
+  b = fma(b, r2, 1.0 / 40320.0);
+  a = fma(a, r2, -1.0 / 5040.0);
+  b = fma(b, r2, -1.0 / 720.0);
+  a = fma(a, r2, 1.0 / 120.0);
+  b = fma(b, r2, 1.0 / 24.0);
+  a = fma(a, r2, -1.0 / 6.0);
+  b = fma(b, r2, -0.5);
+  const double sr = fma(a * r2, r, r), cr = fma(b, r2, 1.0);
+  const double s0 = q & 1 ? cr : sr, c0 = q & 1 ? sr : cr;
+  *s = q & 2 ? -s0 : s0;
+  *c = (q + 1) & 2 ? -c0 : c0;
+}
+
+// x^l / (2l+1)!! times 1 + q a[l][0] (1 + q a[l][1] (1 + ...)), q = -x^2 / 2: the ascending series of j_l, 14 terms of it for x < 0.6 (l + 2)
+constexpr int SERIES_TERMS = 14;
+struct series_table {
+  double a[MAX_S][SERIES_TERMS], lead[MAX_S];
+  constexpr series_table() : a(), lead() {
+    double f = 1.0;
+    for (int l = 0; l < MAX_S; ++l) {
+      f *= (double)(2 * l + 1);
+      lead[l] = 1.0 / f;
+      for (int k = 1; k <= SERIES_TERMS; ++k) a[l][k - 1] = 1.0 / ((double)k * (double)(2 * l + 2 * k + 1));
+    }
+  }
+};
+__constant__ const series_table SERIES = series_table();
+__device__ __forceinline__ double series_j(int l, double x) {
+  const double q = -0.5 * x * x;
+  double t = 1.0;
+#pragma unroll
+  for (int k = SERIES_TERMS - 1; k >= 0; --k) t = fma(q * SERIES.a[l][k], t, 1.0);
+  double p = SERIES.lead[l];
+  for (int k = 0; k < l; ++k) p *= x;
+  return p * t;
+}
+// j_l(y) and, where PAIR, j_{l-1}(y) (l >= 1), y > 0 and inv = 1/y: the series below 0.6 (l + 1), where the upward recurrence has lost three of
+// its sixteen digits, and the recurrence from there on.
+template <bool PAIR>
+__device__ __forceinline__ double sph_bessel_dev(int l, double y, double inv, double* below) {
+  if (l >= 1 && y < 0.6 * (double)(l + 1)) {
+    if (PAIR) *below = series_j(l - 1, y);
+    return series_j(l, y);
+  }
+  double s, c;
+  sincos_small(y, &s, &c);
+  double j0 = s * inv;
+  if (l == 0) return j0;
+  double j1 = (j0 - c) * inv;
+  for (int k = 1; k < l; ++k) {
+    const double j2 = fma((double)(2 * k + 1) * inv, j1, -j0);
+    j0 = j1;
+    j1 = j2;
+  }
+  if (PAIR) *below = j0;
+  return j1;
+}
 
 __host__ __device__ inline double envelope_d(double x, int p) {
   double xp = 1.0;
@@ -89,39 +161,50 @@ struct bessel_zeros {
 };
 void make_bessel_table(int S, int R, double cutoff, bessel_table* t) {
   static const bessel_zeros zeros;   // initialised once, also with several threads
+  t->inv_cutoff = 1.0 / cutoff;
+  t->root = sqrt(2.0 / cutoff);
   for (int l = 0; l < S; ++l)
     for (int n = 0; n < R; ++n) {
       const double j = zeros.j_next[l][n];
       t->z[l * R + n] = zeros.z[l][n];
+      t->inv_z[l * R + n] = 1.0 / zeros.z[l][n];
       t->norm[l * R + n] = sqrt(2.0 / (cutoff * cutoff * cutoff * j * j));
     }
 }
 
 // variant D: rbf[E,R] and rad[E,S*R].  A workgroup evaluates all R + S*R functions of EB edges, lanes over edges first: a
-// wavefront then follows one or two orders l (their loops differ) and the results leave through LDS as whole rows.
-// One thread per value: with one per (edge, l) a thread's six values came one after the other (67 us for 43 380 edges, and
-// 31 us for 336 edges; graph and bases of the former batch 0.43 -> 0.34 ms).
+// wavefront then follows one or two orders l (their loops differ) and the results leave through LDS as whole rows.  What depends on
+// the edge alone, three divisions and the envelope, is found once per edge and read from LDS.  One thread per value: with
+// one per (edge, l) a thread's six values came one after the other.  Bound by fp64 instructions, about BASIS_INSTR a value.
 template <int EB>
 __global__ void __launch_bounds__(256)
-basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p,
-                    double cutoff, bessel_table tab, float* __restrict__ rbf, float* __restrict__ rad) {
+basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p, const bessel_table tab, float* __restrict__ rbf,
+                    float* __restrict__ rad) {
   extern __shared__ float rows_s[];   // [EB][F + 1]
+  __shared__ double edge_s[3][EB];    // x = d / c, 1 / x, the envelope
   const int F = R + S * R, ld = F + 1;
   const int first = rbf ? 0 : R, last = rad ? F : R;   // the functions that are wanted
   const int64_t e0 = (int64_t)blockIdx.x * EB;
   const int ne = n_edges - e0 < EB ? (int)(n_edges - e0) : EB;
+  if ((int)threadIdx.x < ne) {
+    const double x = (double)dist[e0 + threadIdx.x] * tab.inv_cutoff;
+    edge_s[0][threadIdx.x] = x;
+    edge_s[1][threadIdx.x] = 1.0 / x;
+    edge_s[2][threadIdx.x] = envelope_d(x, p);
+  }
+  __syncthreads();
   for (int i = threadIdx.x; i < EB * (last - first); i += 256) {
     const int el = i % EB, f = first + i / EB;
     if (el >= ne) continue;
-    const double d = (double)dist[e0 + el];
-    const double x = d / cutoff;
-    const double u = envelope_d(x, p);
+    const double x = edge_s[0][el], inv_x = edge_s[1][el], u = edge_s[2][el];
     double v;
     if (f < R) {
-      v = u * sqrt(2.0 / cutoff) / d * sin((double)(f + 1) * M_PI * x);
+      double s, c;
+      sincos_small((double)(f + 1) * M_PI * x, &s, &c);
+      v = u * tab.root * (tab.inv_cutoff * inv_x) * s;
     } else {
       const int k = f - R;
-      v = u * tab.norm[k] * sph_bessel(k / R, tab.z[k] * x);
+      v = u * tab.norm[k] * sph_bessel_dev<false>(k / R, tab.z[k] * x, tab.inv_z[k] * inv_x, nullptr);
     }
     rows_s[el * ld + f] = (float)v;
   }
@@ -140,38 +223,33 @@ basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int 
 template <int LANES>
 __global__ void __launch_bounds__(256)
 grad_dist_bessel_kernel(const float* __restrict__ dist, const float* __restrict__ grad_rbf,
-                        const float* __restrict__ grad_rad, int64_t n_edges, int S, int R, int p, double cutoff,
-                        bessel_table tab, float* __restrict__ gd) {
+                        const float* __restrict__ grad_rad, int64_t n_edges, int S, int R, int p,
+                        const bessel_table tab, float* __restrict__ gd) {
   const int64_t e = (int64_t)blockIdx.x * (256 / LANES) + threadIdx.x / LANES;
   if (e >= n_edges) return;
   const int lane = threadIdx.x % LANES;
-  const double d = (double)dist[e], x = d / cutoff;
+  const double inv_c = tab.inv_cutoff, x = (double)dist[e] * inv_c, inv_x = 1.0 / x, inv_d = inv_c * inv_x;
   double xp1 = 1.0;                       // x^(p-1)
   for (int k = 0; k < p - 1; ++k) xp1 *= x;
   const double a = -0.5 * (p + 1) * (p + 2), b = (double)p * (p + 2), c = -0.5 * p * (p + 1);
   const double u = 1.0 + xp1 * x * (a + x * (b + x * c));
-  const double du = xp1 * (p * a + x * ((p + 1) * b + x * (p + 2) * c)) / cutoff;   // du/dd
+  const double du = xp1 * (p * a + x * ((p + 1) * b + x * (p + 2) * c)) * inv_c;   // du/dd
   double s = 0.0;
   for (int f = lane; f < R + S * R; f += LANES) {
     if (f < R) {
       if (grad_rbf) {
         const double k = (double)(f + 1) * M_PI;
         double sn, cs;
-        sincos(k * x, &sn, &cs);
-        s += (double)grad_rbf[e * R + f] * sqrt(2.0 / cutoff) * (du * sn / d + u * (k / cutoff * cs / d - sn / (d * d)));
+        sincos_small(k * x, &sn, &cs);
+        s += (double)grad_rbf[e * R + f] * tab.root * inv_d * (du * sn + u * (k * inv_c * cs - sn * inv_d));
       }
     } else if (grad_rad) {
       const int k = f - R, l = k / R;
-      const double z = tab.z[k], y = z * x;
-      double jl, djl;
-      if (l == 0) {
-        djl = -sph_bessel_pair(1, y, &jl);
-      } else {
-        double below;
-        jl = sph_bessel_pair(l, y, &below);
-        djl = below - (double)(l + 1) / y * jl;
-      }
-      s += (double)grad_rad[e * S * R + k] * tab.norm[k] * (du * jl + u * z / cutoff * djl);
+      const double z = tab.z[k], y = z * x, inv_y = tab.inv_z[k] * inv_x;
+      double below;
+      const double j = sph_bessel_dev<true>(l == 0 ? 1 : l, y, inv_y, &below);
+      const double jl = l == 0 ? below : j, djl = l == 0 ? -j : fma(-(double)(l + 1) * inv_y, j, below);
+      s += (double)grad_rad[e * S * R + k] * tab.norm[k] * (du * jl + u * z * inv_c * djl);
     }
   }
   for (int o = LANES / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, WAVE);
@@ -372,9 +450,9 @@ static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const 
       // 12 000, 18 / 16 at 16 000, 31 / 26 at 32 000, 241 / 175 at 300 000
       const size_t row = sizeof(float) * (R + S * R + 1);
       if (n_edges >= 16384)
-        basis_edge_D_kernel<32><<<(unsigned)((n_edges + 31) / 32), 256, 32 * row, st>>>(dist, n_edges, S, R, p, (double)dims->cutoff, tab, rbf, rad);
+        basis_edge_D_kernel<32><<<(unsigned)((n_edges + 31) / 32), 256, 32 * row, st>>>(dist, n_edges, S, R, p, tab, rbf, rad);
       else
-        basis_edge_D_kernel<4><<<(unsigned)((n_edges + 3) / 4), 256, 4 * row, st>>>(dist, n_edges, S, R, p, (double)dims->cutoff, tab, rbf, rad);
+        basis_edge_D_kernel<4><<<(unsigned)((n_edges + 3) / 4), 256, 4 * row, st>>>(dist, n_edges, S, R, p, tab, rbf, rad);
       GP_LAUNCH_CHECK(ctx, "basis_edge_D_kernel");
     } else if (dims->variant == GP_VARIANT_G) {
       GP_REQUIRE(ctx, R >= 2, "%s: Gaussian basis needs num_radial >= 2", who);
@@ -455,8 +533,8 @@ int gp_grad_dist_bessel(gp_ctx* ctx, const gp_dims* dims, const float* dist, con
   // 15 / 12 / 36 at 4000, 42 / 24 / 35 at 16 000, 138 / 77 / 75 at 64 000, 612 / 336 / 299 at 300 000.
   auto launch = [&](auto kernel, int lanes) {
     const int per = 256 / lanes;
-    kernel<<<(unsigned)((n_edges + per - 1) / per), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R, dims->envelope_p,
-                                                                           (double)dims->cutoff, tab, gd);
+    kernel<<<(unsigned)((n_edges + per - 1) / per), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R, dims->envelope_p, tab,
+                                                                           gd);
   };
   if (R + S * R < 16) launch(grad_dist_bessel_kernel<1>, 1);
   else if (n_edges < 4096) launch(grad_dist_bessel_kernel<64>, 64);
