@@ -24,7 +24,8 @@ struct gp_aux {
   int nr = 0;
   std::vector<hipEvent_t> used;
 
-  explicit gp_aux(gp_ctx* ctx) : c(ctx), main_s(ctx->stream), aux_s(ctx->use_aux ? ctx->aux_stream : nullptr) {}
+  // worth: whether the call is large enough for a second stream
+  explicit gp_aux(gp_ctx* ctx, bool worth = true) : c(ctx), main_s(ctx->stream), aux_s(worth && ctx->use_aux ? ctx->aux_stream : nullptr) {}
   ~gp_aux() {
     // an entry point that returns early (an error between on_aux and join) still leaves the main stream ordered
     // behind the side work it started

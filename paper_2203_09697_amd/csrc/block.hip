@@ -57,8 +57,18 @@ size_t carve_saved_D(void* p, const gp_dims* d, int64_t E, saved_D* s) {
   return c.off;
 }
 
+// Gradients of the pre-activations of a block, one per dense layer over the edges and one for dxg; where the weight gradients are formed
+// together they all have to last, else three are used in turn.
+constexpr int DZ_MOST = 5 + 4 * GP_MAX_RES;
+// The weight gradients of a block are formed by a few launches for all of them where a product by itself would be cut into many
+// runs of the rows (gp_gemm_tn_group), i.e. below width 512.
+bool group_D(const gp_dims* d) { return d->emb < 512; }
+int dz_buffers_D(const gp_dims* d) { return group_D(d) ? 5 + 2 * (d->n_res_before + d->n_res_after) : 3; }
+
 struct scratch_D {
-  float* buf[7];     // [E,H] each
+  float* buf[3];     // [E,H] each: gradients of the messages between layers
+  float* dgate;      // [E,H]
+  float* dz[DZ_MOST];
   float *dF1, *dF2;  // [E,F]
   float* dQ;         // [E,S*B]
   float* P;          // [E,S,F]: per-edge factor of the gradient with respect to cos(alpha) (basis gradients only)
@@ -69,7 +79,8 @@ struct scratch_D {
   void* planes;      // the weights of a call as operand planes (gemm_planes.hip)
 };
 
-size_t part_bytes_D(const gp_dims* d, int64_t E) {
+// partial sums of the reductions over the edges, one at a time
+size_t part_bytes_one_D(const gp_dims* d, int64_t E) {
   const int H = d->emb, F = d->int_emb, B = d->basis_emb, S = d->num_spherical, R = d->num_radial;
   size_t m = gp_gemm_tn_scratch(E, H, H);
   m = std::max(m, gp_gemm_tn_scratch(E, F, H));
@@ -81,6 +92,20 @@ size_t part_bytes_D(const gp_dims* d, int64_t E) {
   return m;
 }
 
+size_t part_bytes_D(const gp_dims* d, int64_t E) {
+  size_t m = part_bytes_one_D(d, E);
+  if (group_D(d)) {
+    gp_tn_product all[GP_TN_JOBS_MAX];
+    int n = 0;
+    auto add = [&](int a, int b) { all[n++] = gp_tn_product{nullptr, nullptr, a, b, nullptr, nullptr}; };
+    for (int i = 0; i < 3 + 2 * (d->n_res_before + d->n_res_after); ++i) add(d->emb, d->emb);
+    add(d->int_emb, d->emb);
+    add(d->emb, d->int_emb);
+    m = std::max(m, gp_gemm_tn_group_scratch(E, all, n));
+  }
+  return m;
+}
+
 // The matrix-core backward kernel also yields the gradient of W_sbf2, so the forward pass need not keep Bacc
 // (E x basis_emb x int_emb floats).  Forward and backward must take the same decision: it depends only on the
 // context's switch, the widths and the graph.
@@ -88,7 +113,7 @@ bool bwd_mfma_D(const gp_ctx* ctx, const gp_dims* d, const gp_graph* g) {
   if (ctx->trip_mfma == 0) return false;
   const int F = d->int_emb, S = d->num_spherical, B = d->basis_emb;
   return gp_tripD_mfma_usable(g, F, S, B) && gp_tripD_mfma_bwd_usable(g, F, S, B) &&
-         gp_tripD_mfma_bwd_scratch(g, F) <= part_bytes_D(d, g->n_edges);
+         gp_tripD_mfma_bwd_scratch(g, F) <= part_bytes_one_D(d, g->n_edges);
 }
 
 // room for the planes of every weight matrix that meets the edges, for the products of either pass
@@ -101,7 +126,9 @@ size_t planes_bytes_D(const gp_dims* d) {
 size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   gp_carver c(p);
   const size_t H = d->emb, F = d->int_emb, B = d->basis_emb, S = d->num_spherical, R = d->num_radial;
-  for (int i = 0; i < 7; ++i) s->buf[i] = c.take<float>(E * H);
+  for (int i = 0; i < 3; ++i) s->buf[i] = c.take<float>(E * H);
+  s->dgate = c.take<float>(E * H);
+  for (int i = 0; i < dz_buffers_D(d); ++i) s->dz[i] = c.take<float>(E * H);
   s->dF1 = c.take<float>(E * F);
   s->dF2 = c.take<float>(E * F);
   s->dQ = c.take<float>(E * S * B);
@@ -140,6 +167,9 @@ int check_weights_D(gp_ctx* ctx, const gp_dims* d, const gp_weights_D* w, const 
   return GP_OK;
 }
 
+// Below that many edges a block's kernels take 5 us each, no longer than an event and its wait on another stream take to issue.
+constexpr int64_t SIDE_MIN_ROWS = 2048;
+
 // one residual layer forward: hout = hin + act(act(hin W1 + b1) W2 + b2); pl: the planes of W1 and W2
 int res_forward(gp_ctx* ctx, const float* hin, float* const* w, const void* const* pl, const res_saved& s, float* hout, int64_t E, int H) {
   gp_epilogue e1;
@@ -150,22 +180,54 @@ int res_forward(gp_ctx* ctx, const float* hin, float* const* w, const void* cons
   return gp_gemm_nn_w(ctx, s.y1, w[2], pl[1], E, H, H, e2);
 }
 
+// The weight gradients of a backward pass and the buffers of the gradients that enter them.
+struct wgrads_D {
+  gp_ctx* ctx;
+  gp_aux& aux;
+  scratch_D& sc;
+  int64_t E;
+  bool group;
+  int n_dz, at = 0, n = 0;
+  gp_tn_product p[GP_TN_JOBS_MAX];
+  wgrads_D(gp_ctx* c, gp_aux& a, scratch_D& s, const gp_dims* d, int64_t rows) : ctx(c), aux(a), sc(s), E(rows), group(group_D(d)), n_dz(dz_buffers_D(d)) {}
+  // room for the next gradient; with three buffers the side stream may still read what was in it
+  int take(float** dz) {
+    *dz = sc.dz[at];
+    at = at + 1 == n_dz ? 0 : at + 1;
+    return group ? GP_OK : aux.before_write(*dz);
+  }
+  // W = A^T dz, b its column sums
+  int add(const float* A, const float* dz, int M, int N, float* W, float* b) {
+    if (group) {
+      p[n++] = gp_tn_product{A, dz, M, N, W, b};
+      return GP_OK;
+    }
+    return aux.on_aux([&] { return gp_gemm_tn(ctx, A, dz, E, M, N, W, b, sc.part_aux, sc.part_bytes); }, {dz});
+  }
+  // forms what has been added, on the side stream
+  int run() {
+    if (n == 0) return GP_OK;
+    const int k = n;
+    n = 0;
+    return aux.on_aux([&] { return gp_gemm_tn_group(ctx, p, k, E, sc.part_aux, sc.part_bytes); }, {});
+  }
+};
+
 // One residual layer backward.  dz2 = dh * silu'(z2) is given (written by the producer of dh).
-// dh_out = dh + d(hin through the layer); if z_next != NULL also dz_next = dh_out * silu'(z_next).
-// The two weight-gradient GEMMs go to the side stream.
-int res_backward(gp_ctx* ctx, gp_aux& aux, const float* hin, float* const* w, const void* const* pl, float* const* gw,
-                 const res_saved& s, const float* dh, const float* dz2, float* dh_out, float* t2, const float* z_next, float* dz_next,
-                 scratch_D& sc, int64_t E, int H) {
-  GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.y1, dz2, E, H, H, gw[2], gw[3], sc.part_aux, sc.part_bytes); }, {dz2}));
+// dh_out = dh + d(hin through the layer), dz_next = dh_out * silu'(z_next).
+int res_backward(gp_ctx* ctx, wgrads_D& wg, const float* hin, float* const* w, const void* const* pl, float* const* gw,
+                 const res_saved& s, const float* dh, const float* dz2, float* dh_out, const float* z_next, float** dz_next, int64_t E, int H) {
+  GP_TRY(wg.add(s.y1, dz2, H, H, gw[2], gw[3]));
+  float* dz1;
+  GP_TRY(wg.take(&dz1));
   gp_epilogue e;
-  e.act = 2; e.zsrc = s.z1; e.out = t2;
-  GP_TRY(aux.before_write(t2));
-  GP_TRY(gp_gemm_nt_w(ctx, dz2, w[2], pl[1], E, H, H, e));                                       // dz1
-  GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, hin, t2, E, H, H, gw[0], gw[1], sc.part_aux, sc.part_bytes); }, {t2}));
+  e.act = 2; e.zsrc = s.z1; e.out = dz1;
+  GP_TRY(gp_gemm_nt_w(ctx, dz2, w[2], pl[1], E, H, H, e));
+  GP_TRY(wg.add(hin, dz1, H, H, gw[0], gw[1]));
+  GP_TRY(wg.take(dz_next));
   gp_epilogue e2;
-  e2.add_post = dh; e2.out = dh_out; e2.out2 = z_next ? dz_next : nullptr; e2.z2src = z_next;
-  if (z_next) GP_TRY(aux.before_write(dz_next));
-  return gp_gemm_nt_w(ctx, t2, w[0], pl[0], E, H, H, e2);
+  e2.add_post = dh; e2.out = dh_out; e2.out2 = *dz_next; e2.z2src = z_next;
+  return gp_gemm_nt_w(ctx, dz1, w[0], pl[0], E, H, H, e2);
 }
 
 }  // namespace
@@ -227,10 +289,9 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   // these widths is one round of workgroups whose loading, multiplying and storing phases coincide; the rows are cut
   // in two and the halves run as two chains on the two streams, out of step with each other (configuration 2:
   // 9.70 -> 9.40 ms per step; cutting the chain before the triplet sum as well: 9.51 ms).
-  constexpr int64_t SPLIT_MIN_ROWS = 2048;
-  gp_aux aux(ctx);
+  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
   const int64_t half = ((E / 2 + 127) / 128) * 128;
-  const bool split = aux.active() && E >= SPLIT_MIN_ROWS && half < E;
+  const bool split = aux.active() && half < E;
   gp_epilogue e;
   e.out = s.Wrbf;
   GP_TRY(gp_gemm_nn(ctx, w->W_rbf1, w->W_rbf2, R, H, B, e));
@@ -345,7 +406,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   GP_HIP(ctx, hipSetDevice(ctx->device));
   const int H = dims->emb, F = dims->int_emb, B = dims->basis_emb, S = dims->num_spherical, R = dims->num_radial;
   const int64_t EH = E * H;
-  float *T1 = sc.buf[3], *T2 = sc.buf[4], *T3 = sc.buf[5], *dgate = sc.buf[6];
+  float* const dgate = sc.dgate;
   // rotating buffers for dh; `keep` is a gradient that must survive (the skip into m)
   const float* dh = grad_m_out;
   const float* keep = nullptr;
@@ -364,11 +425,14 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   for (int r = 0; r < dims->n_res_after; ++r)
     for (int q = 0; q < 2; ++q) p_after[r][q] = wp.add(w->res_after[r][2 * q], E, H, H, 0);
   GP_TRY(wp.run());
-  gp_aux aux(ctx);
+  // Small graphs are launches and nothing else: one stream, all weight gradients at the end.  Otherwise they are formed on the side stream, in
+  // three groups, each as soon as what enters it is there.
+  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
+  wgrads_D wg(ctx, aux, sc, dims, E);
   // dz of the last activation in the block: the only elementwise pass that has no producer GEMM
   const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
-  float* dzcur = T1;
-  auto other_dz = [&]() -> float* { return dzcur == T1 ? T3 : T1; };
+  float *dzcur, *dznext;
+  GP_TRY(wg.take(&dzcur));
   GP_TRY(gp_ew_dsilu_mul(ctx, dh, z_first, dzcur, EH));
 
   // residual layers after the skip, last to first
@@ -376,9 +440,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     const float* hin = (r == 0) ? s.h_lin : s.after[r - 1].hout;
     const float* z_next = (r > 0) ? s.after[r - 1].z2 : s.z_lin;
     float* out = next_buf();
-    float* dznext = other_dz();
-    GP_TRY(res_backward(ctx, aux, hin, w->res_after[r], p_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, T2, z_next,
-                        dznext, sc, E, H));
+    GP_TRY(res_backward(ctx, wg, hin, w->res_after[r], p_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, z_next, &dznext, E, H));
     dh = out;
     dzcur = dznext;
   }
@@ -387,11 +449,10 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   {
     const float* hin = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].hout : s.h0;
     const float* z_next = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].z2 : s.z_up;
-    GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, hin, dzcur, E, H, H, gw->W_lin, gw->b_lin, sc.part_aux, sc.part_bytes); },
-                      {dzcur}));
+    GP_TRY(wg.add(hin, dzcur, H, H, gw->W_lin, gw->b_lin));
+    if (aux.active()) GP_TRY(wg.run());
     float* out = next_buf();
-    float* dznext = other_dz();
-    GP_TRY(aux.before_write(dznext));
+    GP_TRY(wg.take(&dznext));
     gp_epilogue e; e.out = out; e.out2 = dznext; e.z2src = z_next;
     GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_lin, p_lin, E, H, H, e));
     dh = out;
@@ -401,9 +462,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     const float* hin = (r == 0) ? s.h0 : s.before[r - 1].hout;
     const float* z_next = (r > 0) ? s.before[r - 1].z2 : s.z_up;
     float* out = next_buf();
-    float* dznext = other_dz();
-    GP_TRY(res_backward(ctx, aux, hin, w->res_before[r], p_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, T2, z_next,
-                        dznext, sc, E, H));
+    GP_TRY(res_backward(ctx, wg, hin, w->res_before[r], p_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, z_next, &dznext, E, H));
     dh = out;
     dzcur = dznext;
   }
@@ -411,19 +470,19 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   // The branch through x_ji = act(m W_ji + b_ji) needs dh0 only: all of it (dz_ji, both gradients) runs on the side
   // stream next to the chain through the triplet sum, whose kernels leave much of the chip idle; its input gradient
   // is added by the epilogue of the last GEMM below.
-  float* const dz_kj = dzcur;   // free again once the two GEMMs that read dz_up are done
-  GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.a, dzcur, E, F, H, gw->W_up, nullptr, sc.part_aux, sc.part_bytes); },
-                    {dzcur}));
-  float* const dz_ji = other_dz();   // last read by side-stream work issued earlier, and written there: no wait needed
+  GP_TRY(wg.add(s.a, dzcur, F, H, gw->W_up, nullptr));
+  float* dz_ji;
+  GP_TRY(wg.take(&dz_ji));
   float* const dm_ji = next_buf();
   GP_TRY(aux.on_aux(
       [&] {
         GP_TRY(gp_ew_dsilu_mul(ctx, dh, s.z_ji, dz_ji, EH));
-        GP_TRY(gp_gemm_tn(ctx, m_in, dz_ji, E, H, H, gw->W_ji, gw->b_ji, sc.part_aux, sc.part_bytes));
         gp_epilogue e; e.out = dm_ji;
         return gp_gemm_nt_w(ctx, dz_ji, w->W_ji, p_ji, E, H, H, e);
       },
       {dz_ji, dm_ji}));
+  GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
+  if (aux.active()) GP_TRY(wg.run());
   {
     gp_epilogue e; e.out = sc.dF1;
     GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_up, p_up, E, F, H, e));                                     // da
@@ -463,23 +522,23 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_LAUNCH_CHECK(ctx, "cos_factor_kernel");
     GP_TRY(gp_tripG_grad_cos(ctx, graph, basis->cos_alpha_kj, sc.P, sc.dF1, F, S, accumulate_basis_grads, grad_cos_kj));
   }
-  GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, s.xg, sc.dF2, E, H, F, gw->W_down, nullptr, sc.part_aux, sc.part_bytes); },
-                    {sc.dF2}));
+  GP_TRY(wg.add(s.xg, sc.dF2, H, F, gw->W_down, nullptr));
+  float* dz_kj;
+  GP_TRY(wg.take(&dz_kj));
   // dxg = dF2 W_down^T is not stored where its epilogue can take the gate apart (two launches: 26 + 48 us at 43380 x 256): planes, and
   // buffers that start on 16 bytes
   bool gate_fused = p_down != nullptr;
   for (const void* p : {(const void*)sc.dF2, (const void*)s.z_kj, (const void*)s.gate, (const void*)dz_kj, (const void*)dgate})
     gate_fused = gate_fused && ((uintptr_t)p & 15) == 0;
   if (gate_fused) {
-    GP_TRY(aux.before_write(dz_kj));
     gp_epilogue e; e.act = 3; e.zsrc = s.z_kj; e.mul = s.gate; e.out = dz_kj; e.out2 = dgate;
     GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                        // dz_kj, dgate
   } else {
-    GP_TRY(aux.before_write(T2));
-    gp_epilogue e; e.out = T2;
-    GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));                                  // dxg
-    GP_TRY(aux.before_write(dz_kj));
-    GP_TRY(gp_ew_gate_bwd(ctx, T2, s.z_kj, s.gate, dz_kj, dgate, EH));                       // dz_kj, dgate
+    float* dxg;
+    GP_TRY(wg.take(&dxg));
+    gp_epilogue e; e.out = dxg;
+    GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));
+    GP_TRY(gp_ew_gate_bwd(ctx, dxg, s.z_kj, s.gate, dz_kj, dgate, EH));                      // dz_kj, dgate
   }
   GP_TRY(gp_gemm_tn(ctx, basis->rbf, dgate, E, R, H, sc.dWrbf, nullptr, sc.part, sc.part_bytes));
   if (grad_rbf) {   // dL/drbf = dgate W_rbf^T
@@ -492,7 +551,8 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_TRY(gp_gemm_nt(ctx, sc.dWrbf, w->W_rbf2, R, B, H, e));
   }
   GP_TRY(gp_gemm_tn(ctx, w->W_rbf1, sc.dWrbf, R, B, H, gw->W_rbf2, nullptr, sc.part, sc.part_bytes));
-  GP_TRY(aux.on_aux([&] { return gp_gemm_tn(ctx, m_in, dz_kj, E, H, H, gw->W_kj, gw->b_kj, sc.part_aux, sc.part_bytes); }, {dz_kj}));
+  GP_TRY(wg.add(m_in, dz_kj, H, H, gw->W_kj, gw->b_kj));
+  GP_TRY(wg.run());
   {
     GP_TRY(aux.before_write(dm_ji));   // the side stream's input gradient of the ji path
     gp_epilogue e; e.add_pre = dm_ji; e.add_post = keep; e.out = grad_m_in;

@@ -122,11 +122,31 @@ int gp_gemm_nn_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
 // gp_gemm_nt_w also takes act = 3, the backward step of y = silu(z) gate behind the product dy: out = dy mul silu'(zsrc) and
 // out2 = dy silu(zsrc), with mul the gate; only with planes at hand and every matrix 16-byte aligned, which the caller looks at.
 int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes, int64_t M, int N, int K, const gp_epilogue& epi);
-// A^T B over the rows with three bf16 parts per value: tiles, splits of the rows, launch with gp_gemm_tn's argument block
+// A^T B over the rows with three bf16 parts per value (gemm_planes.hip): tiles and splits of the rows of one product, the splits that
+// products of 128 x 128 tiles share, launch of several products with the same rows and tile shape
+constexpr int GP_TN_JOBS_MAX = 24;
+struct gp_tn_part_job {
+  const float *A, *B;        // [rows, M], [rows, N]
+  float *part, *colsum_part; // [splits, M, N]; [splits * tiles_m, N] or NULL
+  int M, N, vec, first;      // vec: 16-byte stores to part are legal; first: set by the launch
+};
 struct gp_tn_parts_plan {
   bool big;       // 256 x 256 tiles instead of 128 x 128
   int tiles_m, splits, most;   // most: no smaller for more rows, and at least `splits`
   int64_t per;    // rows of a split
 };
 gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N);
-int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& plan);
+int gp_parts_tn_splits(int64_t rows, int64_t tiles);
+int gp_parts_tn_launch(gp_ctx* ctx, bool big, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits);
+
+// Several A^T B over the same rows (the weight gradients of a block), fp32 operands.  Alone, a product of 256 x 256 is cut into 128
+// runs of the rows to fill the chip, whose partial sums are as many bytes as its operands; together a few runs are enough, and small graphs need
+// two launches for all of them.  Products of 256 x 256 tiles and those of the other forms are run one by one.
+struct gp_tn_product {
+  const float *A, *B;   // [rows, M], [rows, N]
+  int M, N;
+  float *out, *colsum;  // [M, N]; colsum (or NULL): column sums of B
+};
+// part for any of the products, in one or several calls; no smaller for more rows
+size_t gp_gemm_tn_group_scratch(int64_t rows, const gp_tn_product* p, int n);
+int gp_gemm_tn_group(gp_ctx* ctx, const gp_tn_product* p, int n, int64_t rows, float* part, size_t part_bytes);

@@ -225,68 +225,88 @@ gemm_f32_kernel(const gemm_args g) {
     g.colsum_part[((int64_t)blockIdx.y * tiles_m + tile_m) * g.N + n0 + threadIdx.x] = colsum;
 }
 
-// out[i] = sum_z part[z*n + i] for i < n;  out2[i] = sum_z part2[z*n2 + i] for i < n2.
+// out[i] = sum_z part[z*n + i] for i < n, of several arrays in one launch (of each with a narrow second one).
 // 16 column groups x 16 split lanes per workgroup: every lane issues its (few) 16-byte loads
 // back to back, the 16 lanes of a column group are combined in a fixed order through LDS, so
-// the result is reproducible.  The second (narrow) array is handled the same way, one float
+// the result is reproducible.  The narrow arrays are handled the same way, one float
 // per column group.
 constexpr int RED_COLS = 16, RED_LANES = 16;
+struct reduce_job {
+  const float* part;
+  float* out;
+  int64_t n;
+  int splits, first;   // first workgroup
+  int vec;             // 16-byte loads and stores, four columns to a lane; else one column
+};
+struct reduce_jobs {
+  reduce_job j[2 * GP_TN_JOBS_MAX];
+  int n;
+};
 __global__ void __launch_bounds__(RED_COLS* RED_LANES)
-reduce_parts_kernel(const float* __restrict__ part, int splits, int64_t n, int vec, float* __restrict__ out,
-                    int blocks1, const float* __restrict__ part2, int splits2, int64_t n2,
-                    float* __restrict__ out2) {
+reduce_parts_kernel(const reduce_jobs q) {
   __shared__ f32x4 red[RED_LANES][RED_COLS];
+  int job = 0;
+  while (job + 1 < q.n && (int)blockIdx.x >= q.j[job + 1].first) ++job;
+  const reduce_job& r = q.j[job];
+  const int block = (int)blockIdx.x - r.first;
   const int cg = threadIdx.x % RED_COLS, sl = threadIdx.x / RED_COLS;
   f32x4 s = {0.f, 0.f, 0.f, 0.f};
-  if ((int)blockIdx.x < blocks1) {
-    const int64_t i = ((int64_t)blockIdx.x * RED_COLS + cg) * 4;
-    if (i < n) {
-      if (vec) {
+  if (r.vec) {
+    const int64_t i = ((int64_t)block * RED_COLS + cg) * 4;
+    if (i < r.n) {
 #pragma unroll 8
-        for (int z = sl; z < splits; z += RED_LANES) s += ld4(part + (int64_t)z * n + i);
-      } else {
-        for (int z = sl; z < splits; z += RED_LANES)
-          for (int c = 0; c < 4; ++c)
-            if (i + c < n) s[c] += part[(int64_t)z * n + i + c];
-      }
+      for (int z = sl; z < r.splits; z += RED_LANES) s += ld4(r.part + (int64_t)z * r.n + i);
     }
     red[sl][cg] = s;
     __syncthreads();
-    if (sl == 0 && i < n) {
+    if (sl == 0 && i < r.n) {
       f32x4 t = red[0][cg];
       for (int k = 1; k < RED_LANES; ++k) t += red[k][cg];
-      if (vec) st4(out + i, t);
-      else
-        for (int c = 0; c < 4; ++c)
-          if (i + c < n) out[i + c] = t[c];
+      st4(r.out + i, t);
     }
   } else {
-    const int64_t i = (int64_t)(blockIdx.x - blocks1) * RED_COLS + cg;
-    if (i < n2) {
+    const int64_t i = (int64_t)block * RED_COLS + cg;
+    if (i < r.n) {
 #pragma unroll 8
-      for (int z = sl; z < splits2; z += RED_LANES) s[0] += part2[(int64_t)z * n2 + i];
+      for (int z = sl; z < r.splits; z += RED_LANES) s[0] += r.part[(int64_t)z * r.n + i];
     }
     red[sl][cg] = s;
     __syncthreads();
-    if (sl == 0 && i < n2) {
+    if (sl == 0 && i < r.n) {
       float t = red[0][cg][0];
       for (int k = 1; k < RED_LANES; ++k) t += red[k][cg][0];
-      out2[i] = t;
+      r.out[i] = t;
     }
   }
 }
 
+// collects the arrays of a launch
+struct reducer {
+  reduce_jobs q;
+  int blocks = 0;
+  double bytes = 0.0;
+  reducer() { q.n = 0; }
+  void add(const float* part, int splits, int64_t n, float* out, bool narrow = false) {
+    if (n == 0) return;
+    const int vec = !narrow && n % 4 == 0 && (((uintptr_t)part | (uintptr_t)out) & 15) == 0;
+    q.j[q.n++] = reduce_job{part, out, n, splits, blocks, vec};
+    blocks += (int)((n + RED_COLS * (vec ? 4 : 1) - 1) / (RED_COLS * (vec ? 4 : 1)));
+    bytes += 4.0 * (double)(splits + 1) * n;
+  }
+  int run(gp_ctx* ctx) {
+    if (blocks == 0) return GP_OK;
+    gp_prof_scope prof(ctx, "reduce_parts", 0.0, bytes);
+    reduce_parts_kernel<<<blocks, RED_COLS * RED_LANES, 0, ctx->stream>>>(q);
+    GP_LAUNCH_CHECK(ctx, "reduce_parts_kernel");
+    return GP_OK;
+  }
+};
 int launch_reduce(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out, const float* part2, int splits2,
                   int64_t n2, float* out2) {
-  const int per_block = RED_COLS * 4;
-  const int blocks1 = (int)((n + per_block - 1) / per_block);
-  const int blocks2 = (int)((n2 + RED_COLS - 1) / RED_COLS);
-  const int vec = (n % 4 == 0) && (((uintptr_t)part | (uintptr_t)out) & 15) == 0;
-  gp_prof_scope prof(ctx, "reduce_parts", 0.0, 4.0 * ((double)(splits + 1) * n + (double)(splits2 + 1) * n2));
-  reduce_parts_kernel<<<blocks1 + blocks2, RED_COLS * RED_LANES, 0, ctx->stream>>>(part, splits, n, vec, out, blocks1,
-                                                                                  part2, splits2, n2, out2);
-  GP_LAUNCH_CHECK(ctx, "reduce_parts_kernel");
-  return GP_OK;
+  reducer r;
+  r.add(part, splits, n, out);
+  r.add(part2, splits2, n2, out2, true);
+  return r.run(ctx);
 }
 
 // part[b*N + c] = sum over the b-th slab of rows of X[r, c]
@@ -591,9 +611,8 @@ int gp_gemm_tn(gp_ctx* ctx, const float* A, const float* B, int64_t rows, int M,
   if (ctx->f32_split && (!ctx->gemm_bf16 || colsum_out) && !a_bf16 && !b_bf16) {
     const gp_tn_parts_plan q = gp_parts_tn_plan(rows, M, N);
     float* cpart = (float*)((char*)part + gp_align((size_t)q.splits * M * N * sizeof(float)));
-    g.colsum_part = colsum_out ? cpart : nullptr;
-    g.k_per_split = q.per;
-    GP_TRY(gp_parts_tn_launch(ctx, &g, q));
+    const gp_tn_part_job job{A, B, part, colsum_out ? cpart : nullptr, M, N, g.vecC, 0};
+    GP_TRY(gp_parts_tn_launch(ctx, q.big, &job, 1, rows, q.per, q.splits));
     return launch_reduce(ctx, part, q.splits, (int64_t)M * N, out, cpart, q.splits * q.tiles_m, colsum_out ? N : 0, colsum_out);
   }
   float* cpart = (float*)((char*)part + gp_align((size_t)p.splits * M * N * sizeof(float)));
@@ -601,6 +620,62 @@ int gp_gemm_tn(gp_ctx* ctx, const float* A, const float* B, int64_t rows, int M,
   GP_TRY(dispatch_gemm<MODE_TN>(ctx, g, p.splits));
   const int64_t n1 = (int64_t)M * N, n2 = colsum_out ? N : 0;
   return launch_reduce(ctx, part, p.splits, n1, out, cpart, p.splits * p.tiles_m, n2, colsum_out);
+}
+
+namespace {
+// 128 x 128 tiles of a product; 0 where it has the large ones
+int64_t small_tiles(int64_t rows, const gp_tn_product& p) {
+  if (gp_parts_tn_plan(rows > 0 ? rows : 1, p.M, p.N).big) return 0;
+  return (int64_t)((p.M + 127) / 128) * ((p.N + 127) / 128);
+}
+size_t one_run(const gp_tn_product& p) { return sizeof(float) * ((size_t)p.M * p.N + (size_t)((p.M + 127) / 128) * p.N); }
+}  // namespace
+
+size_t gp_gemm_tn_group_scratch(int64_t rows, const gp_tn_product* p, int n) {
+  size_t most = 0, run = 0, pad = 0;
+  for (int i = 0; i < n; ++i) {
+    most = std::max(most, gp_gemm_tn_scratch(rows, p[i].M, p[i].N));
+    if (small_tiles(rows, p[i]) > 0) run += one_run(p[i]), pad += 512;
+  }
+  // Splits of a launch: at most what one tile would have, and with its tiles at most 512 workgroups (more only where a single split has more).
+  // A tile's sums are at most 128 x 128 + 128 values.
+  const size_t tile = sizeof(float) * (128 * 128 + 128);
+  const size_t together = std::min((size_t)gp_parts_tn_splits(rows > 0 ? rows : 1, 1) * run, std::max(512 * tile, run));
+  return std::max(most, together + pad);
+}
+
+int gp_gemm_tn_group(gp_ctx* ctx, const gp_tn_product* p, int n, int64_t rows, float* part, size_t part_bytes) {
+  GP_REQUIRE(ctx, p && n >= 0 && n <= GP_TN_JOBS_MAX && rows >= 0, "gemm_tn: bad arguments");
+  if (rows > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gemm_tn: too many rows");
+  int64_t tiles = 0;
+  size_t need = 0;
+  bool mine[GP_TN_JOBS_MAX];
+  for (int i = 0; i < n; ++i) {
+    GP_REQUIRE(ctx, p[i].A && p[i].B && p[i].out && p[i].M > 0 && p[i].N > 0, "gemm_tn: bad arguments");
+    mine[i] = rows > 0 && ctx->f32_split && !ctx->gemm_bf16 && small_tiles(rows, p[i]) > 0;
+    if (mine[i]) tiles += small_tiles(rows, p[i]);
+    else GP_TRY(gp_gemm_tn(ctx, p[i].A, p[i].B, rows, p[i].M, p[i].N, p[i].out, p[i].colsum, part, part_bytes));
+  }
+  if (tiles == 0) return GP_OK;
+  const int64_t s = gp_parts_tn_splits(rows, tiles), per = ((rows + s - 1) / s + 31) / 32 * 32;
+  const int splits = (int)((rows + per - 1) / per);
+  gp_tn_part_job jobs[GP_TN_JOBS_MAX];
+  reducer red;
+  int k = 0;
+  for (int i = 0; i < n; ++i) {
+    if (!mine[i]) continue;
+    const int tiles_m = (p[i].M + 127) / 128;
+    float* sums = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + need);
+    need += gp_align((size_t)splits * p[i].M * p[i].N * sizeof(float));
+    float* cols = reinterpret_cast<float*>(reinterpret_cast<char*>(part) + need);
+    if (p[i].colsum) need += gp_align((size_t)splits * tiles_m * p[i].N * sizeof(float));
+    jobs[k++] = gp_tn_part_job{p[i].A, p[i].B, sums, p[i].colsum ? cols : nullptr, p[i].M, p[i].N, p[i].N % 4 == 0 && aligned16(part), 0};
+    red.add(sums, splits, (int64_t)p[i].M * p[i].N, p[i].out);
+    if (p[i].colsum) red.add(cols, splits * tiles_m, p[i].N, p[i].colsum, true);
+  }
+  if (!part || part_bytes < need) return gp_fail(ctx, GP_BUFFER_TOO_SMALL, "gemm_tn: scratch %zu < %zu", part_bytes, need);
+  GP_TRY(gp_parts_tn_launch(ctx, false, jobs, k, rows, per, splits));
+  return red.run(ctx);
 }
 
 static void colsum_plan(int64_t rows, int* blocks, int64_t* per) {

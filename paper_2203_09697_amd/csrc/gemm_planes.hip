@@ -563,23 +563,31 @@ gemm_planes_kernel(const gemm_args g) {
   }
 }
 
-// C = A^T B, the contraction running over the rows of both (the weight gradients: rows = edges).  Every value enters as the sum of three
-// bf16 numbers, each with its own exponent (24 bits), and the six of the nine products that are not below 2^-24 of the whole are
-// formed: a column of A becomes a row of the result, next to columns of any other size, and rows of any size meet in a sum, so
-// there is no scale that could be shared.
+// C = A^T B, the contraction running over the rows of both (the weight gradients: rows = edges), of several matrix pairs at once.  Every
+// value enters as the sum of three bf16 numbers, each with its own exponent (24 bits), and the six of the nine products that are not
+// below 2^-24 of the whole are formed: a column of A becomes a row of the result, next to columns of any other size, and rows of any
+// size meet in a sum, so there is no scale that could be shared.
 // A chunk is 16 rows.  The loads are those of an operand: lane (kh, x) takes 8 consecutive rows of column x, one value a load (256
 // bytes of two rows per instruction), so the parts are written to LDS as fragments and nothing is transposed.  A wavefront loads
 // LA + LB blocks of 32 columns a chunk ahead and splits them once for the whole workgroup.
-// Two buffers, one barrier a chunk.  Workgroup = (tile, split of the rows); partial sums and column sums of B (bias gradients,
-// from the fp32 values, each chunk by one of the tiles that share it) as gp_gemm_tn lays them out.
+// Two buffers, one barrier a chunk.  Workgroup = (split of the rows, product, tile); partial sums [split, M, N] of every product and column
+// sums of B (bias gradients, from the fp32 values, each chunk by one of the tiles that share it).
 // 256 x 256 with 8 wavefronts of 128 x 64 where that many columns exist, else 128 x 128 with 4 of 64 x 64 (two workgroups per
 // compute unit).  43380 rows, 2048 x 2048 1.91 ms, 256 x 256 42 us, 6 x 256 25; 13230, 256 x 256 19; 434, 256 x 256 7.7; 336, 32 x 32 6.1.  Two fp16
 // parts under shared scales take 1.38 ms, 39, 32, 19, 7.3 and 6.5, and lose what is 2^17 smaller than its neighbours; with every such
 // value sought out and added in fp32 they took 1.7 ms, 46, - and 27.
+// FOLD: every TN_FOLD chunks the sums go to a second set by fp32 additions.  The matrix instruction's sums come out low (above), so the
+// error of one run grows with its length; products that share a launch have runs of thousands of rows.
 constexpr int TN_ROWS = 16, TN_BLOCK_B = 3 * FRAG_B;   // rows of a chunk, bytes of its three parts for 32 columns
-template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC>
+constexpr int TN_FOLD = 16;
+struct tn_args {
+  gp_tn_part_job j[GP_TN_JOBS_MAX];   // tiles first, first + 1, ... of a split belong to a product
+  int n, tiles;
+  int64_t rows, per;
+};
+template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC, bool FOLD>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, OCC)
-gemm_parts_tn_kernel(const gemm_args g) {
+gemm_parts_tn_kernel(const tn_args q) {
   constexpr int NW = WAVES_M * WAVES_N, BA = MB * WAVES_M, BB = NB * WAVES_N;   // 32-wide blocks of the operands
   constexpr int LA = BA / NW, LB = BB / NW;                                     // ... a wavefront loads
   static_assert(BA % NW == 0 && BB % NW == 0, "blocks are dealt evenly");
@@ -587,14 +595,17 @@ gemm_parts_tn_kernel(const gemm_args g) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
   char* lds = reinterpret_cast<char*>(smem);
 
-  const int tiles_n = (g.N + 32 * BB - 1) / (32 * BB);
-  const int tiles_m = (int)((g.M + 32 * BA - 1) / (32 * BA));
-  const int work = xcd_remap(blockIdx.x, gridDim.x);   // the tiles of a split (same rows of both operands) side by side
-  const int tiles = tiles_m * tiles_n, split = work / tiles, tile = work % tiles;
+  const int work = xcd_remap(blockIdx.x, gridDim.x);   // the tiles of a split (same rows) side by side
+  const int split = work / q.tiles, t = work % q.tiles;
+  int job = 0;
+  while (job + 1 < q.n && t >= q.j[job + 1].first) ++job;
+  const gp_tn_part_job& jb = q.j[job];
+  const int M = jb.M, N = jb.N, tile = t - jb.first;
+  const int tiles_n = (N + 32 * BB - 1) / (32 * BB), tiles_m = (M + 32 * BA - 1) / (32 * BA);
   const int tile_m = tile / tiles_n;
   const int m0 = tile_m * 32 * BA, n0 = (tile % tiles_n) * 32 * BB;
-  const int64_t k_begin = (int64_t)split * g.k_per_split;
-  const int64_t k_end = k_begin + g.k_per_split < (int64_t)g.K ? k_begin + g.k_per_split : (int64_t)g.K;
+  const int64_t k_begin = (int64_t)split * q.per;
+  const int64_t k_end = k_begin + q.per < q.rows ? k_begin + q.per : q.rows;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = (wave / WAVES_N) * MB, wn = (wave % WAVES_N) * NB;             // first blocks of the wavefront's products
@@ -609,10 +620,10 @@ gemm_parts_tn_kernel(const gemm_args g) {
 #pragma unroll
   for (int b = 0; b < NL; ++b) {
     const bool is_a = b < LA;
-    const int x0 = is_a ? m0 + (wave * LA + b) * 32 : n0 + (wave * LB + b - LA) * 32, width = is_a ? (int)g.M : g.N;
+    const int x0 = is_a ? m0 + (wave * LA + b) * 32 : n0 + (wave * LB + b - LA) * 32, width = is_a ? M : N;
     const int xb = x0 < width ? x0 : 0;   // a block past the matrix reads its first columns and is not stored
-    ldb[b] = (is_a ? g.lda : g.ldb) * 4;
-    base[b] = reinterpret_cast<const char*>((is_a ? g.A : g.B) + xb);
+    ldb[b] = (int64_t)width * 4;
+    base[b] = reinterpret_cast<const char*>((is_a ? jb.A : jb.B) + xb);
     off[b] = (uint32_t)(8 * kh * ldb[b]) + 4u * (uint32_t)(xb + l32 < width ? l32 : width - 1 - xb);
   }
   float raw[NL][8];
@@ -640,7 +651,7 @@ gemm_parts_tn_kernel(const gemm_args g) {
   float cs[LB];
 #pragma unroll
   for (int b = 0; b < LB; ++b) cs[b] = 0.f;
-  const bool want_cs = g.colsum_part != nullptr;
+  const bool want_cs = jb.colsum_part != nullptr;
   // chunk c of the loaders' registers goes to LDS buffer u
   auto store = [&](int c, int u) __attribute__((always_inline)) {
     const bool mine = want_cs && c % tiles_m == tile_m;
@@ -653,21 +664,24 @@ gemm_parts_tn_kernel(const gemm_args g) {
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(dst + p * FRAG_B) = part[p];
       if (b >= LA && mine) {
-        float t = 0.f;
+        float sum = 0.f;
 #pragma unroll
-        for (int r = 0; r < 8; ++r) t += raw[b][r];
-        cs[b - LA < 0 ? 0 : b - LA] += t;
+        for (int r = 0; r < 8; ++r) sum += raw[b][r];
+        cs[b - LA < 0 ? 0 : b - LA] += sum;
       }
     }
   };
 
-  f32x16 acc[MB][NB];
+  f32x16 acc[MB][NB], whole[FOLD ? MB : 1][FOLD ? NB : 1];
 #pragma unroll
   for (int i = 0; i < MB; ++i)
 #pragma unroll
     for (int j = 0; j < NB; ++j)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+      for (int v = 0; v < 16; ++v) {
+        acc[i][j][v] = 0.f;
+        if constexpr (FOLD) whole[i][j][v] = 0.f;
+      }
   auto multiply = [&](int u) __attribute__((always_inline)) {
     const char* sa = lds + u * BUF_B + wm * TN_BLOCK_B + lane * 16;
     const char* sb = lds + u * BUF_B + (BA + wn) * TN_BLOCK_B + lane * 16;
@@ -683,9 +697,22 @@ gemm_parts_tn_kernel(const gemm_args g) {
       for (int p = 0; p < 3; ++p) a[p] = *reinterpret_cast<const bf16x8*>(sa + i * TN_BLOCK_B + p * FRAG_B);
       constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};   // the smallest first
 #pragma unroll
-      for (int q = 0; q < 6; ++q)
+      for (int x = 0; x < 6; ++x)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[q]], b[j][PB[q]], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[x]], b[j][PB[x]], acc[i][j], 0, 0, 0);
+    }
+  };
+  auto fold = [&]() __attribute__((always_inline)) {
+    if constexpr (FOLD) {
+#pragma unroll
+      for (int i = 0; i < MB; ++i)
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+#pragma unroll
+          for (int v = 0; v < 16; ++v) {
+            whole[i][j][v] += acc[i][j][v];
+            acc[i][j][v] = 0.f;
+          }
     }
   };
 
@@ -701,41 +728,56 @@ gemm_parts_tn_kernel(const gemm_args g) {
         fetch(c + 2);
       }
       multiply(u);
+      if (FOLD && c % TN_FOLD == TN_FOLD - 1) fold();
       __syncthreads();
     }
   }
+  fold();
   __syncthreads();
   if (want_cs) {
 #pragma unroll
     for (int b = 0; b < LB; ++b) {
-      const float t = cs[b] + __shfl_xor(cs[b], 32, 64);
+      const float sum = cs[b] + __shfl_xor(cs[b], 32, 64);
       const int n = n0 + (wave * LB + b) * 32 + l32;
-      if (kh == 0 && n < g.N) g.colsum_part[((int64_t)split * tiles_m + tile_m) * g.N + n] = t;
+      if (kh == 0 && n < N) jb.colsum_part[((int64_t)split * tiles_m + tile_m) * N + n] = sum;
     }
   }
-  tile_epilogue_f32<MB, NB, MODE_TN>(g, acc, smem, m0, n0, wm * 32, wn * 32, split);
+  gemm_args g{};
+  g.M = M; g.N = N; g.part = jb.part; g.vecC = jb.vec;
+  if constexpr (FOLD) tile_epilogue_f32<MB, NB, MODE_TN>(g, whole, smem, m0, n0, wm * 32, wn * 32, split);
+  else tile_epilogue_f32<MB, NB, MODE_TN>(g, acc, smem, m0, n0, wm * 32, wn * 32, split);
 }
 
-template <int MB, int NB, int WMS, int WNS, int OCC>
-int launch_parts_tn(gp_ctx* ctx, gemm_args& g, int splits) {
+template <int MB, int NB, int WMS, int WNS, int OCC, bool FOLD>
+int launch_parts_tn(gp_ctx* ctx, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits) {
   constexpr int BA = MB * WMS, BB = NB * WNS, NW = WMS * WNS;
-  const int64_t tiles = (g.M + 32 * BA - 1) / (32 * BA) * ((g.N + 32 * BB - 1) / (32 * BB));
+  tn_args q;
+  q.n = n; q.rows = rows; q.per = per;
+  int64_t tiles = 0;
+  double flops = 0.0, bytes = 0.0;
+  for (int i = 0; i < n; ++i) {
+    q.j[i] = jobs[i];
+    q.j[i].first = (int)tiles;
+    tiles += (int64_t)((jobs[i].M + 32 * BA - 1) / (32 * BA)) * ((jobs[i].N + 32 * BB - 1) / (32 * BB));
+    flops += 2.0 * (double)jobs[i].M * jobs[i].N * rows;
+    bytes += 4.0 * ((double)(jobs[i].M + jobs[i].N) * rows + (double)jobs[i].M * jobs[i].N * splits);
+  }
   if (tiles * splits > INT32_MAX) return gp_fail(ctx, GP_BAD_ARG, "gemm: too many tiles");
+  q.tiles = (int)tiles;
   static char name[48];
   if (!name[0]) snprintf(name, sizeof(name), "gemm_f32x3_tn_%dx%d", 32 * BA, 32 * BB);
-  gp_prof_scope prof(ctx, name, 2.0 * (double)g.M * g.N * g.K,
-                     4.0 * ((double)g.M * g.K + (double)g.K * g.N + (double)g.M * g.N * splits));
+  gp_prof_scope prof(ctx, name, flops, bytes);
   constexpr size_t lds_main = 2 * (size_t)(BA + BB) * TN_BLOCK_B;
   constexpr size_t lds_epi = sizeof(float) * NW * 32 * EPI_LD;
   constexpr size_t lds = lds_main > lds_epi ? lds_main : lds_epi;
   static bool raised = false;
   if (!raised && lds > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
     raised = true;
   }
-  gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(g);
+  gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(q);
   GP_LAUNCH_CHECK(ctx, "gemm_parts_tn_kernel");
   return GP_OK;
 }
@@ -836,6 +878,12 @@ int gp_gemm_nt_w(gp_ctx* ctx, const float* A, const float* W, const void* planes
   return rc == 1 ? gp_gemm_nt(ctx, A, W, M, N, K, epi) : rc;
 }
 
+// Products of small tiles in one launch share its splits: so many that the workgroups of all of them fill the chip once.
+int gp_parts_tn_splits(int64_t rows, int64_t tiles) {
+  const int64_t runs = std::max(std::min<int64_t>((rows + 31) / 32, 32), (rows + 63) / 64);
+  return (int)std::max<int64_t>(std::min(512 / tiles, runs), 1);
+}
+
 // Tiles and splits.  About one or two workgroups per compute unit; few rows are cut into short runs, since a workgroup spends 1 us
 // on a chunk by itself: of 32 rows up to 1024 rows, then 32 runs up to 2048, then of 64 rows.  `most` grows with the rows, `splits` (rounded
 // to whole chunks) need not: scratch is sized by the former, so that what serves a graph serves every smaller one.
@@ -845,16 +893,14 @@ gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
   const int T = p.big ? 256 : 128;
   p.tiles_m = (M + T - 1) / T;
   const int64_t tiles = (int64_t)p.tiles_m * ((N + T - 1) / T);
-  const int64_t runs = p.big ? (rows + 255) / 256 : std::max(std::min<int64_t>((rows + 31) / 32, 32), (rows + 63) / 64);
-  const int64_t s = std::max<int64_t>(std::min((p.big ? 256 : 512) / tiles, runs), 1);
+  const int64_t s = p.big ? std::max<int64_t>(std::min(256 / tiles, (rows + 255) / 256), 1) : gp_parts_tn_splits(rows, tiles);
   p.most = (int)s;
   p.per = ((rows + s - 1) / s + 31) / 32 * 32;
   p.splits = (int)((rows + p.per - 1) / p.per);
   return p;
 }
 
-int gp_parts_tn_launch(gp_ctx* ctx, void* args, const gp_tn_parts_plan& p) {
-  gemm_args& g = *static_cast<gemm_args*>(args);
-  if (p.big) return launch_parts_tn<4, 2, 2, 4, 2>(ctx, g, p.splits);
-  return launch_parts_tn<2, 2, 2, 2, 2>(ctx, g, p.splits);
+int gp_parts_tn_launch(gp_ctx* ctx, bool big, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits) {
+  if (big) return launch_parts_tn<4, 2, 2, 4, 2, false>(ctx, jobs, n, rows, per, splits);
+  return launch_parts_tn<2, 2, 2, 2, 2, true>(ctx, jobs, n, rows, per, splits);
 }
