@@ -86,7 +86,6 @@ size_t part_bytes_one_D(const gp_dims* d, int64_t E) {
   m = std::max(m, gp_gemm_tn_scratch(E, F, H));
   m = std::max(m, gp_gemm_tn_scratch(E, H, F));
   m = std::max(m, gp_gemm_tn_scratch(E, R, H));
-  m = std::max(m, gp_gemm_tn_scratch(R, B, H));
   m = std::max(m, gp_colsum_scratch(E, H));
   m = std::max(m, gp_tripD_wgrad_scratch(E, F, S, R, B));
   return m;
@@ -99,6 +98,7 @@ size_t part_bytes_D(const gp_dims* d, int64_t E) {
     int n = 0;
     auto add = [&](int a, int b) { all[n++] = gp_tn_product{nullptr, nullptr, a, b, nullptr, nullptr}; };
     for (int i = 0; i < 3 + 2 * (d->n_res_before + d->n_res_after); ++i) add(d->emb, d->emb);
+    add(d->num_radial, d->emb);
     add(d->int_emb, d->emb);
     add(d->emb, d->int_emb);
     m = std::max(m, gp_gemm_tn_group_scratch(E, all, n));
@@ -540,19 +540,15 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));
     GP_TRY(gp_ew_gate_bwd(ctx, dxg, s.z_kj, s.gate, dz_kj, dgate, EH));                      // dz_kj, dgate
   }
-  GP_TRY(gp_gemm_tn(ctx, basis->rbf, dgate, E, R, H, sc.dWrbf, nullptr, sc.part, sc.part_bytes));
+  GP_TRY(wg.add(basis->rbf, dgate, R, H, sc.dWrbf, nullptr));
   if (grad_rbf) {   // dL/drbf = dgate W_rbf^T
     gp_epilogue e; e.out = grad_rbf;
     if (accumulate_basis_grads) e.add_post = grad_rbf;
     GP_TRY(gp_gemm_nt(ctx, dgate, s.Wrbf, E, R, H, e));
   }
-  {
-    gp_epilogue e; e.out = gw->W_rbf1;
-    GP_TRY(gp_gemm_nt(ctx, sc.dWrbf, w->W_rbf2, R, B, H, e));
-  }
-  GP_TRY(gp_gemm_tn(ctx, w->W_rbf1, sc.dWrbf, R, B, H, gw->W_rbf2, nullptr, sc.part, sc.part_bytes));
   GP_TRY(wg.add(m_in, dz_kj, H, H, gw->W_kj, gw->b_kj));
   GP_TRY(wg.run());
+  GP_TRY(aux.on_aux([&] { return gp_factor_grads(ctx, sc.dWrbf, w->W_rbf1, w->W_rbf2, R, B, H, gw->W_rbf1, gw->W_rbf2); }, {}));
   {
     GP_TRY(aux.before_write(dm_ji));   // the side stream's input gradient of the ji path
     gp_epilogue e; e.add_pre = dm_ji; e.add_post = keep; e.out = grad_m_in;

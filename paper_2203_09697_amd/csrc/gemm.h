@@ -87,6 +87,10 @@ struct gp_bf16_scope {
 };
 // out[i] = sum_z part[z*n + i], z < splits
 int gp_reduce_parts(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out);
+// the same of two arrays (of either none where its n is 0)
+int gp_reduce_parts2(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out, const float* part2, int64_t n2, float* out2);
+// Gradients of the two factors of W = W1 W2, [R, B] and [B, H], from that of W: dW1 = dW W2^T, dW2 = W1^T dW
+int gp_factor_grads(gp_ctx* ctx, const float* dW, const float* W1, const float* W2, int R, int B, int H, float* dW1, float* dW2);
 
 // ---- fp32 products A W and A W^T with fp32 operands as two fp16 numbers each; the weights are converted ahead (gemm_planes.hip)
 constexpr int GP_PLANE_JOBS_MAX = 24;

@@ -381,25 +381,46 @@ int launch_gemm(gp_ctx* ctx, gemm_args& g, int splits) {
   return launch_gemm_v<BM, BN, WMS, WNS, MODE, false>(ctx, g, splits);
 }
 
+__device__ __forceinline__ float wave_dot(const float* __restrict__ a, const float* __restrict__ b, int K) {
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
+  int k = threadIdx.x & 63;
+  for (; k + 192 < K; k += 256) {
+    s0 += a[k] * b[k];
+    s1 += a[k + 64] * b[k + 64];
+    s2 += a[k + 128] * b[k + 128];
+    s3 += a[k + 192] * b[k + 192];
+  }
+  for (; k < K; k += 64) s0 += a[k] * b[k];
+  return wave_sum((s0 + s1) + (s2 + s3));
+}
+
+// Both factors' gradients of gp_factor_grads in one launch: the first R workgroups form a row of dW1, a wavefront per value at a time, the
+// others dW2, a thread per value.  (A product in tiles for each, with a reduction behind the second: three launches of 5 us.)
+__global__ void __launch_bounds__(256)
+factor_grads_kernel(const float* __restrict__ dW, const float* __restrict__ W1, const float* __restrict__ W2, int R, int B, int H,
+                    float* __restrict__ dW1, float* __restrict__ dW2) {
+  if ((int)blockIdx.x < R) {
+    for (int b = threadIdx.x >> 6; b < B; b += 4) {
+      const float s = wave_dot(dW + (int64_t)blockIdx.x * H, W2 + (int64_t)b * H, H);
+      if ((threadIdx.x & 63) == 0) dW1[blockIdx.x * B + b] = s;
+    }
+    return;
+  }
+  const int64_t i = (int64_t)(blockIdx.x - R) * 256 + threadIdx.x;
+  if (i >= (int64_t)B * H) return;
+  const int b = (int)(i / H), h = (int)(i % H);
+  double s = 0.0;
+  for (int r = 0; r < R; ++r) s += (double)W1[r * B + b] * (double)dW[(int64_t)r * H + h];
+  dW2[i] = (float)s;
+}
+
 // out = A Bt^T for a result of few values with a long contraction (the gradients of the factors of the radial gate: 128 x 16 or
 // 6 x 8 from 256 to 2048): one workgroup per row, a wavefront per value at a time, fp32.  As tiles the product is one or
 // two workgroups that walk the contraction alone: 128 x 16 x 1024 34 us, 6 x 8 x 256 19, 6 x 8 x 2048 78; so 4 to 6.
 __global__ void __launch_bounds__(256) small_nt_kernel(const float* __restrict__ A, const float* __restrict__ Bt, int N, int K, float* __restrict__ out) {
-  const int lane = threadIdx.x & 63;
-  const float* a = A + (int64_t)blockIdx.x * K;
   for (int n = threadIdx.x >> 6; n < N; n += 4) {
-    const float* b = Bt + (int64_t)n * K;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;
-    int k = lane;
-    for (; k + 192 < K; k += 256) {
-      s0 += a[k] * b[k];
-      s1 += a[k + 64] * b[k + 64];
-      s2 += a[k + 128] * b[k + 128];
-      s3 += a[k + 192] * b[k + 192];
-    }
-    for (; k < K; k += 64) s0 += a[k] * b[k];
-    const float s = wave_sum((s0 + s1) + (s2 + s3));
-    if (lane == 0) out[(int64_t)blockIdx.x * N + n] = s;
+    const float s = wave_dot(A + (int64_t)blockIdx.x * K, Bt + (int64_t)n * K, K);
+    if ((threadIdx.x & 63) == 0) out[(int64_t)blockIdx.x * N + n] = s;
   }
 }
 
@@ -710,6 +731,20 @@ int gp_colsum(gp_ctx* ctx, const float* X, int64_t rows, int N, float* out, floa
 int gp_reduce_parts(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out) {
   if (n == 0) return GP_OK;
   return launch_reduce(ctx, part, splits, n, out, nullptr, 0, 0, nullptr);
+}
+
+int gp_reduce_parts2(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out, const float* part2, int64_t n2, float* out2) {
+  reducer r;
+  r.add(part, splits, n, out);
+  r.add(part2, splits, n2, out2);
+  return r.run(ctx);
+}
+
+int gp_factor_grads(gp_ctx* ctx, const float* dW, const float* W1, const float* W2, int R, int B, int H, float* dW1, float* dW2) {
+  gp_prof_scope prof(ctx, "factor_grads", 4.0 * (double)R * B * H, 4.0 * ((double)R * H + 2.0 * B * H));
+  factor_grads_kernel<<<R + nblk((int64_t)B * H), 256, 0, ctx->stream>>>(dW, W1, W2, R, B, H, dW1, dW2);
+  GP_LAUNCH_CHECK(ctx, "factor_grads_kernel");
+  return GP_OK;
 }
 
 int gp_ew_dsilu_mul(gp_ctx* ctx, const float* g, const float* z, float* out, int64_t n) {
