@@ -9,6 +9,7 @@
 #include <stdarg.h>
 
 #include <algorithm>
+#include <initializer_list>
 
 #include "aux_stream.h"
 #include "gemm.h"
@@ -76,7 +77,8 @@ struct scratch_D {
   float* part;
   float* part_aux;   // split-K partials of the GEMMs issued on the side stream
   size_t part_bytes;
-  void* planes;      // the weights of a call as operand planes (gemm_planes.hip)
+  void* planes;      // the weights of a call as operand planes (gemm_planes.hip) or as parts for its chains
+  size_t planes_bytes;
 };
 
 // partial sums of the reductions over the edges, one at a time
@@ -120,8 +122,34 @@ bool bwd_mfma_D(const gp_ctx* ctx, const gp_dims* d, const gp_graph* g) {
 size_t planes_bytes_D(const gp_dims* d) {
   const int H = d->emb, F = d->int_emb;
   auto both = [](int a, int b) { return std::max(gp_align(gp_planes_bytes(a, b)), gp_align(gp_planes_bytes(b, a))); };
-  return (size_t)(3 + 2 * d->n_res_before + 2 * d->n_res_after) * both(H, H) + 2 * both(H, F);
+  const size_t square = 3 + 2 * d->n_res_before + 2 * d->n_res_after;
+  const size_t chain = gp_chain_takes(H, F) ? square * gp_chain_parts_bytes(H, H, H) + gp_chain_parts_bytes(H, H, F) + gp_chain_parts_bytes(H, F, H) : 0;
+  return std::max(square * both(H, H) + 2 * both(H, F), chain);
 }
+
+// Whether the layers over E edges run as chains (dense_chain.hip) with these pointers.  Training step of three blocks, layer by layer / as
+// chains (ms): width 64, 13 668 edges 1.35 / 0.93, 100 119 edges 3.53 / 3.09; 128, 1.67 / 1.25 and 5.72 / 5.12; 192, 2.27 / 1.80 and
+// 9.51 / 8.87; 256, 13 668 edges 2.55 / 2.25, 27 028 3.68 / 3.63, 32 538 4.13 / 4.03, 43 380 5.16 / 5.36, 100 119 10.54 / 11.11: at that width
+// two workgroups of 64 rows fill a compute unit, and where some would come in a second round the layers' own launches are faster.
+bool chain_D(const gp_ctx* ctx, const gp_dims* d, const gp_weights_D* w, int64_t E, std::initializer_list<const void*> more) {
+  if (!ctx->f32_split || ctx->gemm_bf16 || !group_D(d) || !gp_chain_takes(d->emb, d->int_emb) || (d->emb > 192 && E > 32768)) return false;
+  uintptr_t a = (uintptr_t)w->b_ji | (uintptr_t)w->b_kj | (uintptr_t)w->b_lin;
+  for (int r = 0; r < d->n_res_before; ++r) a |= (uintptr_t)w->res_before[r][1] | (uintptr_t)w->res_before[r][3];
+  for (int r = 0; r < d->n_res_after; ++r) a |= (uintptr_t)w->res_after[r][1] | (uintptr_t)w->res_after[r][3];
+  for (const void* p : more) a |= (uintptr_t)p;
+  return (a & 15) == 0;
+}
+
+// the steps of a call
+struct chain_list {
+  gp_chain_step s[GP_CHAIN_MAX];
+  int n = 0;
+  gp_chain_step& add(const float* W, int N, int K, int k_rows) {
+    gp_chain_step& q = s[n++];
+    q.W = W; q.N = N; q.K = K; q.k_rows = k_rows;
+    return q;
+  }
+};
 
 size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   gp_carver c(p);
@@ -137,7 +165,8 @@ size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   s->part_bytes = part_bytes_D(d, E);
   s->part = (float*)c.take<char>(s->part_bytes);
   s->part_aux = (float*)c.take<char>(s->part_bytes);
-  s->planes = c.take<char>(planes_bytes_D(d));
+  s->planes_bytes = planes_bytes_D(d);
+  s->planes = c.take<char>(s->planes_bytes);
   return c.off;
 }
 
@@ -273,7 +302,37 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   const int H = dims->emb, F = dims->int_emb, B = dims->basis_emb, S = dims->num_spherical, R = dims->num_radial;
   float* x_ji = sc.buf[0];
 
-  gp_weight_planes wp(ctx, sc.planes);
+  const bool chain = chain_D(ctx, dims, w, E, {m_in, m_out, saved, scratch});
+  chain_list ch;
+  int pre = 0;   // steps before the triplet sum
+  if (chain) {
+    gp_chain_step& ji = ch.add(w->W_ji, H, H, 1);
+    ji.load = m_in; ji.bias = w->b_ji; ji.save_pre = s.z_ji; ji.act = 1; ji.out = x_ji; ji.keep = 1;
+    gp_chain_step& kj = ch.add(w->W_kj, H, H, 1);
+    kj.bias = w->b_kj; kj.save_pre = s.z_kj; kj.act = 1; kj.mul = s.gate; kj.out = s.xg;
+    gp_chain_step& dn = ch.add(w->W_down, F, H, 1);
+    dn.save_pre = s.z_dn; dn.act = 1; dn.out = s.x_kj;
+    pre = ch.n;
+    gp_chain_step& up = ch.add(w->W_up, H, F, 1);
+    up.load = s.a; up.save_pre = s.z_up; up.act = 1; up.add = x_ji; up.out = s.h0;
+    const float* h = s.h0;
+    auto residual = [&](const float* const* wr, const res_saved& q, float* out) {
+      gp_chain_step& s1 = ch.add(wr[0], H, H, 1);
+      s1.bias = wr[1]; s1.save_pre = q.z1; s1.act = 1; s1.out = q.y1;
+      gp_chain_step& s2 = ch.add(wr[2], H, H, 1);
+      s2.bias = wr[3]; s2.save_pre = q.z2; s2.act = 1; s2.add = h; s2.out = out;
+      h = out;
+    };
+    for (int r = 0; r < dims->n_res_before; ++r) residual(w->res_before[r], s.before[r], s.before[r].hout);
+    gp_chain_step& li = ch.add(w->W_lin, H, H, 1);
+    li.bias = w->b_lin; li.save_pre = s.z_lin; li.act = 1; li.add = m_in; li.out = dims->n_res_after == 0 ? m_out : s.h_lin;
+    h = li.out;
+    for (int r = 0; r < dims->n_res_after; ++r)
+      residual(w->res_after[r], s.after[r], r == dims->n_res_after - 1 ? m_out : s.after[r].hout);
+    GP_TRY(gp_chain_prepare(ctx, H, ch.s, ch.n, sc.planes, sc.planes_bytes));
+  }
+
+  gp_weight_planes wp(ctx, chain ? nullptr : sc.planes);
   const void *p_ji = wp.add(w->W_ji, E, H, H, 1), *p_kj = wp.add(w->W_kj, E, H, H, 1), *p_down = wp.add(w->W_down, E, F, H, 1),
              *p_up = wp.add(w->W_up, E, H, F, 1), *p_lin = wp.add(w->W_lin, E, H, H, 1);
   const void *p_before[GP_MAX_RES][2] = {}, *p_after[GP_MAX_RES][2] = {};
@@ -311,8 +370,14 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
     return gp_gemm_nn_w(ctx, s.xg + o, w->W_down, p_down, n, F, H, q);
   };
   GP_TRY(aux.on_aux([&] { return project_radial(); }, {s.Q}));
-  GP_TRY(aux.on_aux([&] { return ji_rows(0, E); }, {}));
-  GP_TRY(kj_rows(0, E));
+  if (chain) {
+    gp_epilogue q; q.out = s.gate;
+    GP_TRY(gp_gemm_nn(ctx, basis->rbf, s.Wrbf, E, H, R, q));
+    GP_TRY(gp_chain_run(ctx, H, ch.s, 0, pre, E, sc.planes));
+  } else {
+    GP_TRY(aux.on_aux([&] { return ji_rows(0, E); }, {}));
+    GP_TRY(kj_rows(0, E));
+  }
   GP_TRY(aux.before_write(s.Q));   // the projected radial table, written on the side stream
   const bool fwd_mfma = ctx->trip_mfma != 0 && gp_tripD_mfma_usable(graph, F, S, B);
   const bool keep_Bacc = !(fwd_mfma && bwd_mfma_D(ctx, dims, graph));
@@ -323,6 +388,7 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   else
     GP_TRY(gp_tripD_forward(ctx, graph, basis->cos_alpha, s.x_kj, s.Q, w->W_sbf2, F, S, B, s.a, s.Bacc));
   GP_TRY(aux.join());
+  if (chain) return gp_chain_run(ctx, H, ch.s, pre, ch.n, E, sc.planes);
 
   // rows [r0, r0 + n) of the layers after the triplet sum
   auto rows_forward = [&](int64_t r0, int64_t n) -> int {
@@ -416,7 +482,17 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     return nullptr;
   };
 
-  gp_weight_planes wp(ctx, sc.planes);
+  // Small graphs are launches and nothing else: one stream, all weight gradients at the end.  Otherwise they are formed on the side stream, in
+  // groups, each as soon as what enters it is there.
+  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
+  wgrads_D wg(ctx, aux, sc, dims, E);
+  // dz of the last activation in the block
+  const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
+  const bool chain = chain_D(ctx, dims, w, E, {m_in, grad_m_out, grad_m_in, saved, scratch});
+  chain_list ch;
+  int pre = 0;   // steps before the triplet sum's gradients
+  float *dz_ji, *dz_kj, *dm_ji;
+  gp_weight_planes wp(ctx, chain ? nullptr : sc.planes);
   const void *p_ji = wp.add(w->W_ji, E, H, H, 0), *p_kj = wp.add(w->W_kj, E, H, H, 0), *p_down = wp.add(w->W_down, E, H, F, 0),
              *p_up = wp.add(w->W_up, E, F, H, 0), *p_lin = wp.add(w->W_lin, E, H, H, 0);
   const void *p_before[GP_MAX_RES][2] = {}, *p_after[GP_MAX_RES][2] = {};
@@ -425,67 +501,118 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   for (int r = 0; r < dims->n_res_after; ++r)
     for (int q = 0; q < 2; ++q) p_after[r][q] = wp.add(w->res_after[r][2 * q], E, H, H, 0);
   GP_TRY(wp.run());
-  // Small graphs are launches and nothing else: one stream, all weight gradients at the end.  Otherwise they are formed on the side stream, in
-  // three groups, each as soon as what enters it is there.
-  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
-  wgrads_D wg(ctx, aux, sc, dims, E);
-  // dz of the last activation in the block: the only elementwise pass that has no producer GEMM
-  const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
-  float *dzcur, *dznext;
-  GP_TRY(wg.take(&dzcur));
-  GP_TRY(gp_ew_dsilu_mul(ctx, dh, z_first, dzcur, EH));
-
-  // residual layers after the skip, last to first
-  for (int r = dims->n_res_after - 1; r >= 0; --r) {
-    const float* hin = (r == 0) ? s.h_lin : s.after[r - 1].hout;
-    const float* z_next = (r > 0) ? s.after[r - 1].z2 : s.z_lin;
-    float* out = next_buf();
-    GP_TRY(res_backward(ctx, wg, hin, w->res_after[r], p_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, z_next, &dznext, E, H));
-    dh = out;
-    dzcur = dznext;
-  }
-  // h_lin = act(h W_lin + b_lin) + m;  dzcur = dz_lin
-  keep = dh;
-  {
-    const float* hin = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].hout : s.h0;
-    const float* z_next = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].z2 : s.z_up;
-    GP_TRY(wg.add(hin, dzcur, H, H, gw->W_lin, gw->b_lin));
+  if (chain) {
+    float *dz, *dz_next;
+    GP_TRY(wg.take(&dz));
+    const float* z_next = nullptr;
+    // a step and the gradients that come with it; the first one's operand is made from the gradient that was handed in
+    auto step = [&](const float* W) -> gp_chain_step& {
+      gp_chain_step& q = ch.add(W, H, H, 0);
+      if (ch.n == 1) q.load = grad_m_out, q.load_z = z_first, q.load_out = dz;
+      return q;
+    };
+    auto residual = [&](const float* hin, const float* const* wr, float* const* g, const res_saved& r) -> int {
+      GP_TRY(wg.add(r.y1, dz, H, H, g[2], g[3]));
+      GP_TRY(wg.take(&dz_next));
+      gp_chain_step& s2 = step(wr[2]);
+      s2.z = r.z1; s2.out2 = dz_next;
+      dz = dz_next;
+      GP_TRY(wg.add(hin, dz, H, H, g[0], g[1]));
+      GP_TRY(wg.take(&dz_next));
+      gp_chain_step& s1 = step(wr[0]);
+      s1.add = dh; s1.out = next_buf(); s1.z = z_next; s1.out2 = dz_next;
+      dh = s1.out;
+      dz = dz_next;
+      return GP_OK;
+    };
+    for (int r = dims->n_res_after - 1; r >= 0; --r) {
+      z_next = r > 0 ? s.after[r - 1].z2 : s.z_lin;
+      GP_TRY(residual(r == 0 ? s.h_lin : s.after[r - 1].hout, w->res_after[r], gw->res_after[r], s.after[r]));
+    }
+    keep = dh;
+    GP_TRY(wg.add(dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].hout : s.h0, dz, H, H, gw->W_lin, gw->b_lin));
+    GP_TRY(wg.take(&dz_next));
+    gp_chain_step& li = step(w->W_lin);
+    li.out = next_buf(); li.z = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].z2 : s.z_up; li.out2 = dz_next;
+    dh = li.out;
+    dz = dz_next;
+    for (int r = dims->n_res_before - 1; r >= 0; --r) {
+      z_next = r > 0 ? s.before[r - 1].z2 : s.z_up;
+      GP_TRY(residual(r == 0 ? s.h0 : s.before[r - 1].hout, w->res_before[r], gw->res_before[r], s.before[r]));
+    }
+    // h0 = x_ji + act(a W_up);  dh = dh0, dz = dz_up
+    GP_TRY(wg.add(s.a, dz, F, H, gw->W_up, nullptr));
+    ch.add(w->W_up, F, H, 0).out = sc.dF1;                        // da
+    GP_TRY(wg.take(&dz_ji));
+    dm_ji = next_buf();
+    gp_chain_step& ji = ch.add(w->W_ji, H, H, 0);
+    ji.load = dh; ji.load_z = s.z_ji; ji.load_out = dz_ji; ji.out = dm_ji;
+    GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
+    pre = ch.n;
+    GP_TRY(wg.take(&dz_kj));
+    gp_chain_step& dn = ch.add(w->W_down, H, F, 0);
+    dn.load = sc.dF2; dn.gate = 1; dn.z = s.z_kj; dn.mul = s.gate; dn.out2 = dz_kj; dn.out3 = dgate;
+    gp_chain_step& kj = ch.add(w->W_kj, H, H, 0);                 // dm = kj path + ji path + skip
+    kj.add_pre = dm_ji; kj.add = keep; kj.out = grad_m_in;
+    GP_TRY(gp_chain_prepare(ctx, H, ch.s, ch.n, sc.planes, sc.planes_bytes));
+    GP_TRY(gp_chain_run(ctx, H, ch.s, 0, pre, E, sc.planes));
     if (aux.active()) GP_TRY(wg.run());
-    float* out = next_buf();
-    GP_TRY(wg.take(&dznext));
-    gp_epilogue e; e.out = out; e.out2 = dznext; e.z2src = z_next;
-    GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_lin, p_lin, E, H, H, e));
-    dh = out;
-    dzcur = dznext;
-  }
-  for (int r = dims->n_res_before - 1; r >= 0; --r) {
-    const float* hin = (r == 0) ? s.h0 : s.before[r - 1].hout;
-    const float* z_next = (r > 0) ? s.before[r - 1].z2 : s.z_up;
-    float* out = next_buf();
-    GP_TRY(res_backward(ctx, wg, hin, w->res_before[r], p_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, z_next, &dznext, E, H));
-    dh = out;
-    dzcur = dznext;
-  }
-  // h0 = x_ji + act(a W_up);  dh = dh0, dzcur = dz_up
-  // The branch through x_ji = act(m W_ji + b_ji) needs dh0 only: all of it (dz_ji, both gradients) runs on the side
-  // stream next to the chain through the triplet sum, whose kernels leave much of the chip idle; its input gradient
-  // is added by the epilogue of the last GEMM below.
-  GP_TRY(wg.add(s.a, dzcur, F, H, gw->W_up, nullptr));
-  float* dz_ji;
-  GP_TRY(wg.take(&dz_ji));
-  float* const dm_ji = next_buf();
-  GP_TRY(aux.on_aux(
-      [&] {
-        GP_TRY(gp_ew_dsilu_mul(ctx, dh, s.z_ji, dz_ji, EH));
-        gp_epilogue e; e.out = dm_ji;
-        return gp_gemm_nt_w(ctx, dz_ji, w->W_ji, p_ji, E, H, H, e);
-      },
-      {dz_ji, dm_ji}));
-  GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
-  if (aux.active()) GP_TRY(wg.run());
-  {
-    gp_epilogue e; e.out = sc.dF1;
-    GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_up, p_up, E, F, H, e));                                     // da
+  } else {
+    float *dzcur, *dznext;
+    GP_TRY(wg.take(&dzcur));
+    GP_TRY(gp_ew_dsilu_mul(ctx, dh, z_first, dzcur, EH));
+
+    // residual layers after the skip, last to first
+    for (int r = dims->n_res_after - 1; r >= 0; --r) {
+      const float* hin = (r == 0) ? s.h_lin : s.after[r - 1].hout;
+      const float* z_next = (r > 0) ? s.after[r - 1].z2 : s.z_lin;
+      float* out = next_buf();
+      GP_TRY(res_backward(ctx, wg, hin, w->res_after[r], p_after[r], gw->res_after[r], s.after[r], dh, dzcur, out, z_next, &dznext, E, H));
+      dh = out;
+      dzcur = dznext;
+    }
+    // h_lin = act(h W_lin + b_lin) + m;  dzcur = dz_lin
+    keep = dh;
+    {
+      const float* hin = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].hout : s.h0;
+      const float* z_next = dims->n_res_before > 0 ? s.before[dims->n_res_before - 1].z2 : s.z_up;
+      GP_TRY(wg.add(hin, dzcur, H, H, gw->W_lin, gw->b_lin));
+      if (aux.active()) GP_TRY(wg.run());
+      float* out = next_buf();
+      GP_TRY(wg.take(&dznext));
+      gp_epilogue e; e.out = out; e.out2 = dznext; e.z2src = z_next;
+      GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_lin, p_lin, E, H, H, e));
+      dh = out;
+      dzcur = dznext;
+    }
+    for (int r = dims->n_res_before - 1; r >= 0; --r) {
+      const float* hin = (r == 0) ? s.h0 : s.before[r - 1].hout;
+      const float* z_next = (r > 0) ? s.before[r - 1].z2 : s.z_up;
+      float* out = next_buf();
+      GP_TRY(res_backward(ctx, wg, hin, w->res_before[r], p_before[r], gw->res_before[r], s.before[r], dh, dzcur, out, z_next, &dznext, E, H));
+      dh = out;
+      dzcur = dznext;
+    }
+    // h0 = x_ji + act(a W_up);  dh = dh0, dzcur = dz_up
+    // The branch through x_ji = act(m W_ji + b_ji) needs dh0 only: all of it (dz_ji, both gradients) runs on the side
+    // stream next to the chain through the triplet sum, whose kernels leave much of the chip idle; its input gradient
+    // is added by the epilogue of the last GEMM below.
+    GP_TRY(wg.add(s.a, dzcur, F, H, gw->W_up, nullptr));
+    GP_TRY(wg.take(&dz_ji));
+    dm_ji = next_buf();
+    GP_TRY(aux.on_aux(
+        [&] {
+          GP_TRY(gp_ew_dsilu_mul(ctx, dh, s.z_ji, dz_ji, EH));
+          gp_epilogue e; e.out = dm_ji;
+          return gp_gemm_nt_w(ctx, dz_ji, w->W_ji, p_ji, E, H, H, e);
+        },
+        {dz_ji, dm_ji}));
+    GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
+    if (aux.active()) GP_TRY(wg.run());
+    {
+      gp_epilogue e; e.out = sc.dF1;
+      GP_TRY(gp_gemm_nt_w(ctx, dzcur, w->W_up, p_up, E, F, H, e));                                     // da
+    }
   }
   // triplet interaction
   const bool bwd_mfma = bwd_mfma_D(ctx, dims, graph);
@@ -523,22 +650,25 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_TRY(gp_tripG_grad_cos(ctx, graph, basis->cos_alpha_kj, sc.P, sc.dF1, F, S, accumulate_basis_grads, grad_cos_kj));
   }
   GP_TRY(wg.add(s.xg, sc.dF2, H, F, gw->W_down, nullptr));
-  float* dz_kj;
-  GP_TRY(wg.take(&dz_kj));
-  // dxg = dF2 W_down^T is not stored where its epilogue can take the gate apart (two launches: 26 + 48 us at 43380 x 256): planes, and
-  // buffers that start on 16 bytes
-  bool gate_fused = p_down != nullptr;
-  for (const void* p : {(const void*)sc.dF2, (const void*)s.z_kj, (const void*)s.gate, (const void*)dz_kj, (const void*)dgate})
-    gate_fused = gate_fused && ((uintptr_t)p & 15) == 0;
-  if (gate_fused) {
-    gp_epilogue e; e.act = 3; e.zsrc = s.z_kj; e.mul = s.gate; e.out = dz_kj; e.out2 = dgate;
-    GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                        // dz_kj, dgate
+  if (chain) {
+    GP_TRY(gp_chain_run(ctx, H, ch.s, pre, ch.n, E, sc.planes));   // dz_kj, dgate and the result
   } else {
-    float* dxg;
-    GP_TRY(wg.take(&dxg));
-    gp_epilogue e; e.out = dxg;
-    GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));
-    GP_TRY(gp_ew_gate_bwd(ctx, dxg, s.z_kj, s.gate, dz_kj, dgate, EH));                      // dz_kj, dgate
+    GP_TRY(wg.take(&dz_kj));
+    // dxg = dF2 W_down^T is not stored where its epilogue can take the gate apart (two launches: 26 + 48 us at 43380 x 256): planes, and
+    // buffers that start on 16 bytes
+    bool gate_fused = p_down != nullptr;
+    for (const void* p : {(const void*)sc.dF2, (const void*)s.z_kj, (const void*)s.gate, (const void*)dz_kj, (const void*)dgate})
+      gate_fused = gate_fused && ((uintptr_t)p & 15) == 0;
+    if (gate_fused) {
+      gp_epilogue e; e.act = 3; e.zsrc = s.z_kj; e.mul = s.gate; e.out = dz_kj; e.out2 = dgate;
+      GP_TRY(gp_gemm_nt_w(ctx, sc.dF2, w->W_down, p_down, E, H, F, e));                        // dz_kj, dgate
+    } else {
+      float* dxg;
+      GP_TRY(wg.take(&dxg));
+      gp_epilogue e; e.out = dxg;
+      GP_TRY(gp_gemm_nt(ctx, sc.dF2, w->W_down, E, H, F, e));
+      GP_TRY(gp_ew_gate_bwd(ctx, dxg, s.z_kj, s.gate, dz_kj, dgate, EH));                      // dz_kj, dgate
+    }
   }
   GP_TRY(wg.add(basis->rbf, dgate, R, H, sc.dWrbf, nullptr));
   if (grad_rbf) {   // dL/drbf = dgate W_rbf^T
@@ -549,7 +679,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   GP_TRY(wg.add(m_in, dz_kj, H, H, gw->W_kj, gw->b_kj));
   GP_TRY(wg.run());
   GP_TRY(aux.on_aux([&] { return gp_factor_grads(ctx, sc.dWrbf, w->W_rbf1, w->W_rbf2, R, B, H, gw->W_rbf1, gw->W_rbf2); }, {}));
-  {
+  if (!chain) {
     GP_TRY(aux.before_write(dm_ji));   // the side stream's input gradient of the ji path
     gp_epilogue e; e.add_pre = dm_ji; e.add_post = keep; e.out = grad_m_in;
     GP_TRY(gp_gemm_nt_w(ctx, dz_kj, w->W_kj, p_kj, E, H, H, e));                                     // dm = kj path + ji path + skip

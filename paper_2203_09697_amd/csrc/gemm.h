@@ -107,13 +107,13 @@ bool gp_planes_take(const gp_ctx* ctx, int64_t M, int N, int K);
 // The weights of a call, converted by one launch.
 struct gp_weight_planes {
   gp_ctx* ctx;
-  char* next;     // room for the planes: gp_planes_bytes of every matrix added, each rounded up to 256
+  char* next;     // room for the planes: gp_planes_bytes of every matrix added, each rounded up to 256 (NULL: no planes)
   gp_plane_job jobs[GP_PLANE_JOBS_MAX];
   int n = 0;
   gp_weight_planes(gp_ctx* c, void* room) : ctx(c), next(static_cast<char*>(room)) {}
   // planes of W for products with M rows (NULL where the general kernels take them, as they do where the room is not 16-byte aligned)
   const void* add(const float* W, int64_t M, int N, int K, int k_rows) {
-    if (n == GP_PLANE_JOBS_MAX || ((uintptr_t)next & 15) != 0 || !gp_planes_take(ctx, M, N, K)) return nullptr;
+    if (!next || n == GP_PLANE_JOBS_MAX || ((uintptr_t)next & 15) != 0 || !gp_planes_take(ctx, M, N, K)) return nullptr;
     jobs[n++] = gp_plane_job{W, next, N, K, k_rows};
     void* p = next;
     next += gp_align(gp_planes_bytes(N, K));
@@ -154,3 +154,33 @@ struct gp_tn_product {
 // part for any of the products, in one or several calls; no smaller for more rows
 size_t gp_gemm_tn_group_scratch(int64_t rows, const gp_tn_product* p, int n);
 int gp_gemm_tn_group(gp_ctx* ctx, const gp_tn_product* p, int n, int64_t rows, float* part, size_t part_bytes);
+
+// ---- chains of dense layers over the rows in one launch (dense_chain.hip), fp32, all pointers 16-byte aligned
+constexpr int GP_CHAIN_MAX = 24;
+struct gp_chain_step {
+  const float* W = nullptr;         // [K, N] (k_rows) or [N, K]
+  int N = 0, K = 0, k_rows = 0;     // multiples of 16, at most the width H of the chain
+  // operand x [rows, K]: the value of the step before, or load, then times silu'(load_z) and stored to load_out where those are given
+  const float *load = nullptr, *load_z = nullptr;
+  float* load_out = nullptr;
+  // v = x W; in this order, NULL pointers skip a step
+  const float* bias = nullptr;      // v += bias[col]
+  const float* add_pre = nullptr;   // v += add_pre
+  float* save_pre = nullptr;        // save_pre = v
+  int act = 0;                      // v = silu(v)
+  // gate: out2 = v mul silu'(z), out3 = v silu(z), v = out2; in place of what follows
+  int gate = 0;
+  const float* mul = nullptr;       // v *= mul
+  const float* add = nullptr;       // v += add
+  float* out = nullptr;             // out = v
+  const float* z = nullptr;         // v *= silu'(z), out2 = v
+  float *out2 = nullptr, *out3 = nullptr;
+  int keep = 0;                     // the next step takes this one's operand, not its value
+};
+// whether there is a chain for layers of width H that meet widths F (multiple of 16)
+bool gp_chain_takes(int H, int F);
+// room for the weights of a step
+size_t gp_chain_parts_bytes(int H, int N, int K);
+// converts the weights of all steps; then runs of consecutive steps, each beginning with a load
+int gp_chain_prepare(gp_ctx* ctx, int H, const gp_chain_step* steps, int n, void* parts, size_t parts_bytes);
+int gp_chain_run(gp_ctx* ctx, int H, const gp_chain_step* steps, int from, int to, int64_t rows, const void* parts);

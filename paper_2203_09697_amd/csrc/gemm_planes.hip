@@ -576,7 +576,7 @@ gemm_planes_kernel(const gemm_args g) {
 // compute unit).  43380 rows, 2048 x 2048 1.91 ms, 256 x 256 42 us, 6 x 256 25; 13230, 256 x 256 19; 434, 256 x 256 7.7; 336, 32 x 32 6.1.  Two fp16
 // parts under shared scales take 1.38 ms, 39, 32, 19, 7.3 and 6.5, and lose what is 2^17 smaller than its neighbours; with every such
 // value sought out and added in fp32 they took 1.7 ms, 46, - and 27.
-// FOLD: every TN_FOLD chunks the sums go to a second set by fp32 additions.  The matrix instruction's sums come out low (above), so the
+// Every TN_FOLD chunks the sums, and those of the columns, go to a second set by fp32 additions (FOLD: not for lack of registers).  The matrix instruction's sums come out low (above), so the
 // error of one run grows with its length; products that share a launch have runs of thousands of rows.
 constexpr int TN_ROWS = 16, TN_BLOCK_B = 3 * FRAG_B;   // rows of a chunk, bytes of its three parts for 32 columns
 constexpr int TN_FOLD = 16;
@@ -648,9 +648,9 @@ gemm_parts_tn_kernel(const tn_args q) {
         }
     }
   };
-  float cs[LB];
+  float cs[LB], cs_whole[LB];
 #pragma unroll
-  for (int b = 0; b < LB; ++b) cs[b] = 0.f;
+  for (int b = 0; b < LB; ++b) cs[b] = cs_whole[b] = 0.f;
   const bool want_cs = jb.colsum_part != nullptr;
   // chunk c of the loaders' registers goes to LDS buffer u
   auto store = [&](int c, int u) __attribute__((always_inline)) {
@@ -714,6 +714,8 @@ gemm_parts_tn_kernel(const tn_args q) {
             acc[i][j][v] = 0.f;
           }
     }
+#pragma unroll
+    for (int b = 0; b < LB; ++b) cs_whole[b] += cs[b], cs[b] = 0.f;
   };
 
   if (n_ch > 0) {
@@ -728,7 +730,7 @@ gemm_parts_tn_kernel(const tn_args q) {
         fetch(c + 2);
       }
       multiply(u);
-      if (FOLD && c % TN_FOLD == TN_FOLD - 1) fold();
+      if (c % TN_FOLD == TN_FOLD - 1) fold();
       __syncthreads();
     }
   }
@@ -737,7 +739,7 @@ gemm_parts_tn_kernel(const tn_args q) {
   if (want_cs) {
 #pragma unroll
     for (int b = 0; b < LB; ++b) {
-      const float sum = cs[b] + __shfl_xor(cs[b], 32, 64);
+      const float sum = cs_whole[b] + __shfl_xor(cs_whole[b], 32, 64);
       const int n = n0 + (wave * LB + b) * 32 + l32;
       if (kh == 0 && n < N) jb.colsum_part[((int64_t)split * tiles_m + tile_m) * N + n] = sum;
     }
