@@ -209,6 +209,9 @@ dense_chain_kernel(const chain_args q) {
       for (int b = 0; b < NB; ++b) acc[b] = ld4(s.bias + 4 * g + (16 * b < N ? 16 * b : 0));
     }
     const int64_t o = row * N + 4 * g;
+    // Before the wavefront that shares the SIMD while there are products: the two then take turns instead of splitting and multiplying at the
+    // same time (eight layers of 32768 x 256 276 -> 264 us, 60000 x 128 172 -> 162).
+    __builtin_amdgcn_s_setprio(1);
     const int chunks = (K + 31) / 32, halves = (N + 16 * NBS - 1) / (16 * NBS);
 #pragma unroll
     for (int c = 0; c < CH; ++c) {
@@ -279,6 +282,7 @@ dense_chain_kernel(const chain_args q) {
         }
       }
     }
+    __builtin_amdgcn_s_setprio(0);
     // All that was asked for is waited for here, so that the waits of the next layer do not stand behind this one's stores.
     wait_vmcnt_lgkmcnt0<0>();
     if ((flags & CF_P1) && chunks < CH) {
