@@ -177,14 +177,13 @@ void make_bessel_table(int S, int R, double cutoff, bessel_table* t) {
 // the edge alone, three divisions and the envelope, is found once per edge and read from LDS.  One thread per value: with
 // one per (edge, l) a thread's six values came one after the other.  Bound by fp64 instructions, about BASIS_INSTR a value.
 template <int EB>
-__global__ void __launch_bounds__(256)
-basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p, const bessel_table tab, float* __restrict__ rbf,
-                    float* __restrict__ rad) {
+__device__ __forceinline__ void basis_edges_D(int block, const float* __restrict__ dist, int64_t n_edges, int S, int R, int p, const bessel_table& tab,
+                                              float* __restrict__ rbf, float* __restrict__ rad) {
   extern __shared__ float rows_s[];   // [EB][F + 1]
   __shared__ double edge_s[3][EB];    // x = d / c, 1 / x, the envelope
   const int F = R + S * R, ld = F + 1;
   const int first = rbf ? 0 : R, last = rad ? F : R;   // the functions that are wanted
-  const int64_t e0 = (int64_t)blockIdx.x * EB;
+  const int64_t e0 = (int64_t)block * EB;
   const int ne = n_edges - e0 < EB ? (int)(n_edges - e0) : EB;
   if ((int)threadIdx.x < ne) {
     const double x = (double)dist[e0 + threadIdx.x] * tab.inv_cutoff;
@@ -213,6 +212,12 @@ basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int 
     for (int i = threadIdx.x; i < ne * R; i += 256) rbf[e0 * R + i] = rows_s[(i / R) * ld + i % R];
   if (rad)
     for (int i = threadIdx.x; i < ne * S * R; i += 256) rad[e0 * S * R + i] = rows_s[(i / (S * R)) * ld + R + i % (S * R)];
+}
+template <int EB>
+__global__ void __launch_bounds__(256)
+basis_edge_D_kernel(const float* __restrict__ dist, int64_t n_edges, int S, int R, int p, const bessel_table tab, float* __restrict__ rbf,
+                    float* __restrict__ rad) {
+  basis_edges_D<EB>(blockIdx.x, dist, n_edges, S, R, p, tab, rbf, rad);
 }
 
 // variant D, for forces: gd[e] = sum_n grad_rbf[e,n] d rbf_n / dd + sum_{l,n} grad_rad[e,l,n] d rad_ln / dd with
@@ -380,16 +385,29 @@ __device__ __forceinline__ void cos_runs(int block, const float* __restrict__ un
     done += len;
   }
 }
+struct cos_args {
+  const float* unit;
+  const int32_t *src, *dst, *row_ptr, *out_ptr, *out_list, *id_swap, *seg_ji, *seg_kj, *idx_kj, *idx_ji_kj;
+  int n_edges, n_triplets, n_blocks;
+  float *cos_ji, *cos_kj;
+};
 template <bool LONG>
+__device__ __forceinline__ void cos_graph(int b, const cos_args& q) {
+  if (b < q.n_blocks)
+    cos_runs<LONG, true>(b, q.unit, q.dst, q.row_ptr, q.out_ptr, q.out_list, q.id_swap, q.seg_kj, q.idx_ji_kj, q.n_edges, q.n_triplets, q.cos_kj);
+  else
+    cos_runs<LONG, false>(b - q.n_blocks, q.unit, q.src, q.row_ptr, q.out_ptr, q.out_list, q.id_swap, q.seg_ji, q.idx_kj, q.n_edges, q.n_triplets, q.cos_ji);
+}
+template <bool LONG>
+__global__ void __launch_bounds__(256) cos_graph_kernel(const cos_args q) { cos_graph<LONG>(blockIdx.x, q); }
+// Both parts of the basis of a small graph in one launch, the first `edge_blocks` workgroups on the edges: one is fp64 arithmetic, the other
+// memory latency, and neither fills the chip (43380 edges, 590 k triplets: 16.4 + 10.2 us one after the other, 20.1 together).
+template <bool LONG, int EB>
 __global__ void __launch_bounds__(256)
-cos_graph_kernel(const float* __restrict__ unit, const int32_t* __restrict__ src, const int32_t* __restrict__ dst,
-                 const int32_t* __restrict__ row_ptr, const int32_t* __restrict__ out_ptr, const int32_t* __restrict__ out_list,
-                 const int32_t* __restrict__ id_swap, const int32_t* __restrict__ seg_ji, const int32_t* __restrict__ seg_kj,
-                 const int32_t* __restrict__ idx_kj, const int32_t* __restrict__ idx_ji_kj, int n_edges, int n_triplets,
-                 int n_blocks, float* __restrict__ cos_ji, float* __restrict__ cos_kj) {
-  const int b = blockIdx.x;
-  if (b < n_blocks) cos_runs<LONG, true>(b, unit, dst, row_ptr, out_ptr, out_list, id_swap, seg_kj, idx_ji_kj, n_edges, n_triplets, cos_kj);
-  else cos_runs<LONG, false>(b - n_blocks, unit, src, row_ptr, out_ptr, out_list, id_swap, seg_ji, idx_kj, n_edges, n_triplets, cos_ji);
+basis_graph_D_kernel(const cos_args q, int edge_blocks, const float* __restrict__ dist, int S, int R, int p, const bessel_table tab,
+                     float* __restrict__ rbf, float* __restrict__ rad) {
+  if ((int)blockIdx.x < edge_blocks) basis_edges_D<EB>(blockIdx.x, dist, q.n_edges, S, R, p, tab, rbf, rad);
+  else cos_graph<LONG>((int)blockIdx.x - edge_blocks, q);
 }
 
 // out[q] = in[perm[q]].  For the kj-major copy of cos alpha the gathered values of neighbouring q lie a whole in-degree apart
@@ -431,8 +449,9 @@ inline int nblk(int64_t n) { return (int)((n + 255) / 256); }
 
 }  // namespace
 
-// the per-edge part of the two entry points
-static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const float* dist, int64_t n_edges, float* rbf, float* rad) {
+// The per-edge part of the two entry points, and with cos the cosines of the graph; *cos_done: whether the same launch did those.
+static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const float* dist, int64_t n_edges, float* rbf, float* rad,
+                       const cos_args* cos = nullptr, bool* cos_done = nullptr) {
   GP_REQUIRE(ctx, dims->cutoff > 0.f, "%s: cutoff must be positive", who);
   const int S = dims->num_spherical, R = dims->num_radial, p = dims->envelope_p;
   if (S < 1 || S > MAX_S || R < 1 || p < 1 || p > 16)
@@ -449,6 +468,17 @@ static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const 
       // edges per workgroup leave one value to a thread.  4 / 32 edges, 48 values each: 7 / 13 us at 4000 edges, 15 / 16 at
       // 12 000, 18 / 16 at 16 000, 31 / 26 at 32 000, 241 / 175 at 300 000
       const size_t row = sizeof(float) * (R + S * R + 1);
+      // In one launch with the cosines while those are a matter of latency (above); 1e8 of them take 0.22 ms of writes
+      if (cos && cos->n_triplets < 4 * 1000 * 1000) {
+        *cos_done = true;
+        const bool wide = cos->n_triplets >= LONG_LISTS * n_edges;
+        const int eb = n_edges >= 16384 ? 32 : 4, blocks = (int)((n_edges + eb - 1) / eb);
+        auto* kernel = wide ? (eb == 32 ? basis_graph_D_kernel<true, 32> : basis_graph_D_kernel<true, 4>)
+                            : (eb == 32 ? basis_graph_D_kernel<false, 32> : basis_graph_D_kernel<false, 4>);
+        kernel<<<(unsigned)(blocks + 2 * cos->n_blocks), 256, eb * row, st>>>(*cos, blocks, dist, S, R, p, tab, rbf, rad);
+        GP_LAUNCH_CHECK(ctx, "basis_graph_D_kernel");
+        return GP_OK;
+      }
       if (n_edges >= 16384)
         basis_edge_D_kernel<32><<<(unsigned)((n_edges + 31) / 32), 256, 32 * row, st>>>(dist, n_edges, S, R, p, tab, rbf, rad);
       else
@@ -507,14 +537,16 @@ extern "C" int gp_basis_forward_graph(gp_ctx* ctx, const gp_dims* dims, const fl
   const int64_t E = graph->n_edges, T = graph->n_triplets;
   GP_REQUIRE(ctx, E >= 0 && T >= 0, "gp_basis_forward_graph: negative size");
   if (E > INT32_MAX - 1 || T > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "gp_basis_forward_graph: sizes exceed int32");
-  GP_TRY(basis_edges(ctx, "gp_basis_forward_graph", dims, dist, E, rbf, rad));
-  if (E == 0 || T == 0) return GP_OK;
+  if (E == 0 || T == 0) return basis_edges(ctx, "gp_basis_forward_graph", dims, dist, E, rbf, rad);
   GP_REQUIRE(ctx, unit && src && dst && cos_alpha && cos_alpha_kj && graph->row_ptr && graph->out_ptr && graph->out_list &&
              graph->id_swap && graph->seg_ptr_ji && graph->seg_ptr_kj, "gp_basis_forward_graph: NULL pointer");
   const int blocks = (int)((E + 63) / 64);   // 64 edges per workgroup in both forms
-  (T >= LONG_LISTS * E ? cos_graph_kernel<true> : cos_graph_kernel<false>)<<<2 * (unsigned)blocks, 256, 0, ctx->stream>>>(
-      unit, src, dst, graph->row_ptr, graph->out_ptr, graph->out_list, graph->id_swap, graph->seg_ptr_ji, graph->seg_ptr_kj,
-      graph->idx_kj, graph->idx_ji_kj, (int)E, (int)T, blocks, cos_alpha, cos_alpha_kj);
+  const cos_args q{unit, src, dst, graph->row_ptr, graph->out_ptr, graph->out_list, graph->id_swap, graph->seg_ptr_ji, graph->seg_ptr_kj,
+                   graph->idx_kj, graph->idx_ji_kj, (int)E, (int)T, blocks, cos_alpha, cos_alpha_kj};
+  bool done = false;
+  GP_TRY(basis_edges(ctx, "gp_basis_forward_graph", dims, dist, E, rbf, rad, &q, &done));
+  if (done) return GP_OK;
+  (T >= LONG_LISTS * E ? cos_graph_kernel<true> : cos_graph_kernel<false>)<<<2 * (unsigned)blocks, 256, 0, ctx->stream>>>(q);
   GP_LAUNCH_CHECK(ctx, "cos_graph_kernel");
   return GP_OK;
 }
