@@ -58,9 +58,8 @@ int gp_create(gp_ctx** out, int device_id, void* hip_stream) {
   } else {
     c->dflag = nullptr;
   }
-  if (hipHostMalloc((void**)&c->hwords, 4 * sizeof(int64_t), hipHostMallocMapped) != hipSuccess) c->hwords = nullptr;
+  if (hipHostMalloc((void**)&c->hwords, 4 * sizeof(int64_t), hipHostMallocMapped | hipHostMallocCoherent) != hipSuccess) c->hwords = nullptr;
   if (c->hwords && hipHostGetDevicePointer((void**)&c->hwords_dev, c->hwords, 0) != hipSuccess) c->hwords_dev = nullptr;
-  if (hipEventCreateWithFlags(&c->count_event, hipEventDisableTiming) != hipSuccess) c->count_event = nullptr;
   const char* no_aux = getenv("GP_NO_AUX_STREAM");
   c->use_aux = !(no_aux && no_aux[0] == '1');
   const char* tm = getenv("GP_TRIPLET_MFMA");
@@ -82,7 +81,6 @@ void gp_destroy(gp_ctx* ctx) {
   if (ctx->aux_stream) (void)hipStreamDestroy(ctx->aux_stream);
   if (ctx->dflag) (void)hipHostFree(ctx->dflag);
   if (ctx->hwords) (void)hipHostFree(ctx->hwords);
-  if (ctx->count_event) (void)hipEventDestroy(ctx->count_event);
   delete ctx;
 }
 

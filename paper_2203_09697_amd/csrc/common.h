@@ -43,11 +43,10 @@ struct gp_ctx {
   int* dflag = nullptr;       // host address
   int* dflag_dev = nullptr;   // the same word as the device sees it
   // Results of the *_count calls: a few words of pinned host memory that kernels write (a copy and its wait cost more than the
-  // counting kernels of a small graph), and the event after which they are there.  The mutex is held from the launch that writes
+  // counting kernels of a small graph).  The mutex is held from the launch that writes
   // the words until they have been read: threads may count graphs on one context at the same time.
   int64_t* hwords = nullptr;
   int64_t* hwords_dev = nullptr;
-  hipEvent_t count_event = nullptr;
   std::mutex count_mutex;
 };
 
@@ -123,7 +122,7 @@ inline int gp_fail(gp_ctx* ctx, int code, const char* fmt, ...) {
 
 #define GP_REQUIRE_HOST_WORDS(ctx, who)                                                     \
   do {                                                                                      \
-    if (!(ctx)->hwords_dev || !(ctx)->count_event)                                          \
+    if (!(ctx)->hwords_dev)                                                                  \
       return gp_fail((ctx), GP_HIP_ERROR, "%s: the context has no pinned host memory", who); \
   } while (0)
 

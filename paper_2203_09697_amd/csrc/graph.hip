@@ -4,6 +4,9 @@
 // slots come from wavefront ballots and prefix counts, never from atomics' arrival order.
 #include <stdarg.h>
 
+#include <atomic>
+#include <chrono>
+
 #include "common.h"
 
 namespace {
@@ -644,6 +647,30 @@ int check_images(gp_ctx* ctx, const char* who, const float* cell, int r0, int r1
   return GP_OK;
 }
 
+// Waits for the first n host words, which the kernel launched last writes and which the caller had set to -1 before (the counts are never
+// negative): the words themselves are looked at, which shows them some microseconds before the stream's own wait would return.  After a
+// quarter of a second, or where the launch went wrong, the stream is waited for, so a kernel that never writes ends in its error.
+int wait_host_words(gp_ctx* ctx, int n) {
+  volatile int64_t* h = ctx->hwords;
+  const auto start = std::chrono::steady_clock::now();
+  for (;;) {
+    for (int spin = 0; spin < 256; ++spin) {
+      bool there = true;
+      for (int i = 0; i < n; ++i) there = there && h[i] >= 0;
+      if (there) {
+        std::atomic_thread_fence(std::memory_order_acquire);
+        return GP_OK;
+      }
+      __builtin_ia32_pause();
+    }
+    if (std::chrono::steady_clock::now() - start > std::chrono::milliseconds(250)) break;
+  }
+  GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  for (int i = 0; i < n; ++i)
+    if (h[i] < 0) return gp_fail(ctx, GP_HIP_ERROR, "a count did not arrive");
+  return GP_OK;
+}
+
 int edges_count_impl(gp_ctx* ctx, const char* who, const float* pos, const int32_t* graph_ptr, images_t im, int64_t n_atoms,
                      int32_t n_graphs, float cutoff, int32_t max_neighbors, void* ws, size_t ws_bytes, int64_t* n_edges) {
   GP_REQUIRE(ctx, n_edges, "%s: n_edges is NULL", who);
@@ -663,13 +690,15 @@ int edges_count_impl(gp_ctx* ctx, const char* who, const float* pos, const int32
   GP_LAUNCH_CHECK(ctx, "edges_kernel<count>");
   GP_REQUIRE_HOST_WORDS(ctx, who);
   std::lock_guard<std::mutex> words(ctx->count_mutex);
+  *(volatile int64_t*)ctx->hwords = -1;
   scan_exclusive_kernel<<<1, SCAN_THREADS, 0, ctx->stream>>>(w.deg, w.row_ptr, n_atoms, ctx->hwords_dev);
   GP_LAUNCH_CHECK(ctx, "scan_exclusive_kernel");
-  GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  GP_TRY(wait_host_words(ctx, 1));
   const int64_t total = *(volatile int64_t*)ctx->hwords;
   *n_edges = total;
-  if (total > INT32_MAX) return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld edges exceed int32", who, (long long)total);
-  return GP_OK;
+  if (total <= INT32_MAX) return GP_OK;
+  GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
+  return gp_fail(ctx, GP_INT32_OVERFLOW, "%s: %lld edges exceed int32", who, (long long)total);
 }
 
 int edges_fill_impl(gp_ctx* ctx, const char* who, const float* pos, const int32_t* graph_ptr, images_t im, int64_t n_atoms,
@@ -765,9 +794,9 @@ int check_lists(gp_ctx* ctx, const char* who, int64_t n_atoms, int64_t n_edges, 
 }
 
 // Opposite edges and both segment orders with the out-edge offsets, or the ji-major order alone.  w.seg_ji, seg_kj, out_ptr, id_swap
-// point where the results belong (the caller's arrays or the workspace's).  counted is recorded once the host words are there.
+// point where the results belong (the caller's arrays or the workspace's).
 int lists_pass(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_t* offset, const int32_t* row_ptr, int64_t n_atoms,
-               int64_t n_edges, const triplets_ws& w, bool with_kj, int64_t* host_words, hipEvent_t counted) {
+               int64_t n_edges, const triplets_ws& w, bool with_kj, int64_t* host_words) {
   hipStream_t st = ctx->stream;
   int32_t* out_deg = with_kj ? w.out_deg : nullptr;
   if (with_kj) GP_HIP(ctx, (hipError_t)gp_zero_async(st, out_deg, sizeof(int32_t) * n_atoms));
@@ -776,7 +805,6 @@ int lists_pass(gp_ctx* ctx, const int32_t* src, const int32_t* dst, const int32_
   (with_kj ? lists_sums_kernel<true> : lists_sums_kernel<false>)<<<(unsigned)nc, 256, 0, st>>>(src, dst, row_ptr, w.id_swap, out_deg, n_edges, w.sums);
   lists_mid_kernel<<<1, 1024, 0, st>>>(row_ptr, out_deg, with_kj ? (int)n_atoms : 0, nc, w.out_ptr, w.sums, w.total, host_words);
   GP_LAUNCH_CHECK(ctx, "list kernels");
-  if (counted) GP_HIP(ctx, hipEventRecord(counted, st));
   (with_kj ? lists_apply_kernel<true> : lists_apply_kernel<false>)<<<(unsigned)nc, 256, 0, st>>>(
       src, dst, row_ptr, w.id_swap, out_deg, w.out_ptr, w.arrival, n_edges, w.sums, w.total, w.seg_ji, w.seg_kj, w.out_tmp);
   GP_LAUNCH_CHECK(ctx, "lists_apply_kernel");
@@ -790,9 +818,11 @@ int lists_count(gp_ctx* ctx, const char* who, const int32_t* src, const int32_t*
                 int32_t* max_out) {
   GP_REQUIRE_HOST_WORDS(ctx, who);
   std::lock_guard<std::mutex> words(ctx->count_mutex);
-  GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, with_kj, ctx->hwords_dev, with_kj ? ctx->count_event : nullptr));
-  GP_HIP(ctx, with_kj ? hipEventSynchronize(ctx->count_event) : hipStreamSynchronize(ctx->stream));
   volatile int64_t* h = ctx->hwords;
+  h[0] = h[1] = h[2] = -1;
+  GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, with_kj, ctx->hwords_dev));
+  if (with_kj) GP_TRY(wait_host_words(ctx, 3));
+  else GP_HIP(ctx, hipStreamSynchronize(ctx->stream));
   *n_triplets = h[0];
   if (max_in) *max_in = (int32_t)h[1];
   if (max_out) *max_out = (int32_t)h[2];
@@ -853,7 +883,7 @@ int triplets_fill_impl(gp_ctx* ctx, const int32_t* src, const int32_t* dst, cons
   GP_REQUIRE(ctx, n_triplets == 0 || (idx_kj && idx_ji), "gp_triplets_fill: idx_kj/idx_ji is NULL");
   if (want_kj) {
     w.seg_ji = seg_ptr_ji; w.seg_kj = seg_ptr_kj;
-    GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, true, nullptr, nullptr));
+    GP_TRY(lists_pass(ctx, src, dst, offset, row_ptr, n_atoms, n_edges, w, true, nullptr));
   } else {
     GP_HIP(ctx, hipMemcpyAsync(seg_ptr_ji, w.seg_ji, sizeof(int32_t) * (n_edges + 1), hipMemcpyDeviceToDevice, st));
   }
