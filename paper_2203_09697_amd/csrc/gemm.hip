@@ -238,12 +238,14 @@ struct reduce_job {
   int splits, first;   // first workgroup
   int vec;             // 16-byte loads and stores, four columns to a lane; else one column
 };
+template <int JOBS>
 struct reduce_jobs {
-  reduce_job j[2 * GP_TN_JOBS_MAX];
+  reduce_job j[JOBS];
   int n;
 };
+template <int JOBS>
 __global__ void __launch_bounds__(RED_COLS* RED_LANES)
-reduce_parts_kernel(const reduce_jobs q) {
+reduce_parts_kernel(const reduce_jobs<JOBS> q) {
   __shared__ f32x4 red[RED_LANES][RED_COLS];
   int job = 0;
   while (job + 1 < q.n && (int)blockIdx.x >= q.j[job + 1].first) ++job;
@@ -281,8 +283,9 @@ reduce_parts_kernel(const reduce_jobs q) {
 }
 
 // collects the arrays of a launch
+template <int JOBS>
 struct reducer {
-  reduce_jobs q;
+  reduce_jobs<JOBS> q;
   int blocks = 0;
   double bytes = 0.0;
   reducer() { q.n = 0; }
@@ -296,14 +299,14 @@ struct reducer {
   int run(gp_ctx* ctx) {
     if (blocks == 0) return GP_OK;
     gp_prof_scope prof(ctx, "reduce_parts", 0.0, bytes);
-    reduce_parts_kernel<<<blocks, RED_COLS * RED_LANES, 0, ctx->stream>>>(q);
+    reduce_parts_kernel<JOBS><<<blocks, RED_COLS * RED_LANES, 0, ctx->stream>>>(q);
     GP_LAUNCH_CHECK(ctx, "reduce_parts_kernel");
     return GP_OK;
   }
 };
 int launch_reduce(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out, const float* part2, int splits2,
                   int64_t n2, float* out2) {
-  reducer r;
+  reducer<2> r;
   r.add(part, splits, n, out);
   r.add(part2, splits2, n2, out2, true);
   return r.run(ctx);
@@ -681,7 +684,7 @@ int gp_gemm_tn_group(gp_ctx* ctx, const gp_tn_product* p, int n, int64_t rows, f
   const int64_t s = gp_parts_tn_splits(rows, tiles), per = ((rows + s - 1) / s + 31) / 32 * 32;
   const int splits = (int)((rows + per - 1) / per);
   gp_tn_part_job jobs[GP_TN_JOBS_MAX];
-  reducer red;
+  reducer<2 * GP_TN_JOBS_MAX> red;
   int k = 0;
   for (int i = 0; i < n; ++i) {
     if (!mine[i]) continue;
@@ -734,7 +737,7 @@ int gp_reduce_parts(gp_ctx* ctx, const float* part, int splits, int64_t n, float
 }
 
 int gp_reduce_parts2(gp_ctx* ctx, const float* part, int splits, int64_t n, float* out, const float* part2, int64_t n2, float* out2) {
-  reducer r;
+  reducer<2> r;
   r.add(part, splits, n, out);
   r.add(part2, splits, n2, out2);
   return r.run(ctx);

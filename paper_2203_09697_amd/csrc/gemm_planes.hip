@@ -580,14 +580,15 @@ gemm_planes_kernel(const gemm_args g) {
 // error of one run grows with its length; products that share a launch have runs of thousands of rows.
 constexpr int TN_ROWS = 16, TN_BLOCK_B = 3 * FRAG_B;   // rows of a chunk, bytes of its three parts for 32 columns
 constexpr int TN_FOLD = 16;
+template <int JOBS>
 struct tn_args {
-  gp_tn_part_job j[GP_TN_JOBS_MAX];   // tiles first, first + 1, ... of a split belong to a product
+  gp_tn_part_job j[JOBS];   // tiles first, first + 1, ... of a split belong to a product
   int n, tiles;
   int64_t rows, per;
 };
-template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC, bool FOLD>
+template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC, bool FOLD, int JOBS>
 __global__ void __launch_bounds__(64 * WAVES_M * WAVES_N, OCC)
-gemm_parts_tn_kernel(const tn_args q) {
+gemm_parts_tn_kernel(const tn_args<JOBS> q) {
   constexpr int NW = WAVES_M * WAVES_N, BA = MB * WAVES_M, BB = NB * WAVES_N;   // 32-wide blocks of the operands
   constexpr int LA = BA / NW, LB = BB / NW;                                     // ... a wavefront loads
   static_assert(BA % NW == 0 && BB % NW == 0, "blocks are dealt evenly");
@@ -598,7 +599,8 @@ gemm_parts_tn_kernel(const tn_args q) {
   const int work = xcd_remap(blockIdx.x, gridDim.x);   // the tiles of a split (same rows) side by side
   const int split = work / q.tiles, t = work % q.tiles;
   int job = 0;
-  while (job + 1 < q.n && t >= q.j[job + 1].first) ++job;
+  if constexpr (JOBS > 1)
+    while (job + 1 < q.n && t >= q.j[job + 1].first) ++job;
   const gp_tn_part_job& jb = q.j[job];
   const int M = jb.M, N = jb.N, tile = t - jb.first;
   const int tiles_n = (N + 32 * BB - 1) / (32 * BB), tiles_m = (M + 32 * BA - 1) / (32 * BA);
@@ -750,10 +752,11 @@ gemm_parts_tn_kernel(const tn_args q) {
   else tile_epilogue_f32<MB, NB, MODE_TN>(g, acc, smem, m0, n0, wm * 32, wn * 32, split);
 }
 
-template <int MB, int NB, int WMS, int WNS, int OCC, bool FOLD>
+// JOBS: room for that many products in the launch's arguments (with room for 24, a launch takes a microsecond longer)
+template <int MB, int NB, int WMS, int WNS, int OCC, bool FOLD, int JOBS>
 int launch_parts_tn(gp_ctx* ctx, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits) {
   constexpr int BA = MB * WMS, BB = NB * WNS, NW = WMS * WNS;
-  tn_args q;
+  tn_args<JOBS> q;
   q.n = n; q.rows = rows; q.per = per;
   int64_t tiles = 0;
   double flops = 0.0, bytes = 0.0;
@@ -774,12 +777,12 @@ int launch_parts_tn(gp_ctx* ctx, const gp_tn_part_job* jobs, int n, int64_t rows
   constexpr size_t lds = lds_main > lds_epi ? lds_main : lds_epi;
   static bool raised = false;
   if (!raised && lds > 64 * 1024) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD>),
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD, JOBS>),
                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
       return gp_fail(ctx, GP_HIP_ERROR, "gemm: cannot raise the dynamic LDS limit to %zu bytes", lds);
     raised = true;
   }
-  gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(q);
+  gemm_parts_tn_kernel<MB, NB, WMS, WNS, OCC, FOLD, JOBS><<<dim3((unsigned)(tiles * splits)), 64 * NW, lds, ctx->stream>>>(q);
   GP_LAUNCH_CHECK(ctx, "gemm_parts_tn_kernel");
   return GP_OK;
 }
@@ -903,6 +906,8 @@ gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
 }
 
 int gp_parts_tn_launch(gp_ctx* ctx, bool big, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits) {
-  if (big) return launch_parts_tn<4, 2, 2, 4, 2, false>(ctx, jobs, n, rows, per, splits);
-  return launch_parts_tn<2, 2, 2, 2, 2, true>(ctx, jobs, n, rows, per, splits);
+  GP_REQUIRE(ctx, n >= 1 && n <= (big ? 1 : GP_TN_JOBS_MAX), "gemm_tn: number of products");
+  if (big) return launch_parts_tn<4, 2, 2, 4, 2, false, 1>(ctx, jobs, n, rows, per, splits);
+  if (n == 1) return launch_parts_tn<2, 2, 2, 2, 2, true, 1>(ctx, jobs, n, rows, per, splits);
+  return launch_parts_tn<2, 2, 2, 2, 2, true, GP_TN_JOBS_MAX>(ctx, jobs, n, rows, per, splits);
 }
