@@ -1,7 +1,7 @@
 // Output block (paper Sec. 3.3: the updated messages are summed per target atom, EdgeAggr, and
 // the sum is transformed by an MLP, NodeUpdate), forward and backward.
 //
-//   t_e = m_e * (rbf_e W_rbf)                       [E, emb]   radial weighting fused into the GEMM epilogue
+//   t_e = m_e * (rbf_e W_rbf)                       [E, emb]   radial weighting (not stored where there are at most 16 functions)
 //   h_i = sum_{e: dst[e] = i} t_e                   [N, emb]   in-edges of an atom are contiguous rows
 //   u   = h W_up;  u = act(u W_k + b_k), k < L      [N, out]
 //   P_i = u_i . w_final;  energy[g] (+)= sum_{i in g} P_i
@@ -12,6 +12,7 @@
 #include <stdarg.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "gemm.h"
 
@@ -44,6 +45,104 @@ out_atom_sum_kernel(const float* __restrict__ t, const int32_t* __restrict__ row
   for (; e < e1; ++e) s0 += t[(int64_t)e * H + f];
   h[i * H + f] = (s0 + s1) + (s2 + s3);
 }
+
+// Few radial functions (R <= RADIAL_MAX): the gate's column of W_rbf fits a lane's registers, and the edges' passes of the output block are one
+// kernel each that reads every row once.  As a product with K = R, a pass that gathers, one that multiplies and A^T B: 26 us forward
+// and 54 backward at 13230 edges x 256 x 6, so 14 and 21 (eight edges at a time in the sum: 3 more).
+constexpr int RADIAL_MAX = 16;
+template <int RM>
+struct gate_column {
+  float w[RM];
+  __device__ __forceinline__ void load(const float* __restrict__ W, int R, int H, int f) {
+#pragma unroll
+    for (int r = 0; r < RM; ++r) w[r] = r < R ? W[(int64_t)r * H + f] : 0.f;
+  }
+  // rbf: the R values of an edge (uniform in the wavefront)
+  __device__ __forceinline__ float at(const float* __restrict__ rbf, int R) const {
+    float g = 0.f;
+#pragma unroll
+    for (int r = 0; r < RM; ++r) g = __builtin_fmaf(r < R ? rbf[r] : 0.f, w[r], g);   // 0: an infinite value stays its own column's
+    return g;
+  }
+};
+
+// h[i, f] = sum over the in-edges e of atom i of m[e, f] (rbf_e W)[f]; one wavefront per (atom, 64 features)
+template <int RM>
+__global__ void __launch_bounds__(256)
+out_edge_sum_kernel(const float* __restrict__ m, const float* __restrict__ rbf, const float* __restrict__ W, const int32_t* __restrict__ row_ptr,
+                    int64_t n_atoms, int H, int R, float* __restrict__ h) {
+  const int chunks = (H + 63) / 64;
+  const int64_t w = (int64_t)blockIdx.x * WPB + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i = w / chunks;
+  if (i >= n_atoms) return;
+  const int f = (int)(w % chunks) * 64 + (threadIdx.x & 63);
+  if (f >= H) return;
+  gate_column<RM> col;
+  col.load(W, R, H, f);
+  const int e0 = row_ptr[i], e1 = row_ptr[i + 1];
+  constexpr int U = 4;   // edges at a time, each with a sum of its own
+  float s[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) s[u] = 0.f;
+  int e = e0;
+  for (; e + U - 1 < e1; e += U) {
+    float v[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) v[u] = m[(int64_t)(e + u) * H + f];
+#pragma unroll
+    for (int u = 0; u < U; ++u) s[u] = __builtin_fmaf(v[u], col.at(rbf + (int64_t)(e + u) * R, R), s[u]);
+  }
+  for (; e < e1; ++e) s[0] = __builtin_fmaf(m[(int64_t)e * H + f], col.at(rbf + (int64_t)e * R, R), s[0]);
+  h[i * H + f] = (s[0] + s[1]) + (s[2] + s[3]);
+}
+
+// grad_m[e, f] (+)= dh[dst[e], f] (rbf_e W)[f] and, with part, the sums of rbf[e, r] dh[dst[e], f] m[e, f] over a run of `per` edges; one
+// wavefront per (run, 64 features)
+template <int RM>
+__global__ void __launch_bounds__(256)
+out_edge_grad_kernel(const float* __restrict__ m, const float* __restrict__ rbf, const float* __restrict__ W, const float* __restrict__ dh,
+                     const int32_t* __restrict__ dst, int64_t n_edges, int64_t per, int H, int R, int accumulate, float* __restrict__ grad_m,
+                     float* __restrict__ part) {
+  const int chunks = (H + 63) / 64;
+  const int64_t w = (int64_t)blockIdx.x * WPB + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t run = w / chunks, e0 = run * per, e1 = e0 + per < n_edges ? e0 + per : n_edges;
+  if (e0 >= n_edges) return;
+  const int f = (int)(w % chunks) * 64 + (threadIdx.x & 63);
+  if (f >= H) return;
+  gate_column<RM> col;
+  col.load(W, R, H, f);
+  float dw[RM];
+#pragma unroll
+  for (int r = 0; r < RM; ++r) dw[r] = 0.f;
+  auto edges = [&](auto count, int64_t e) __attribute__((always_inline)) {
+    constexpr int U = decltype(count)::value;
+    float d[U], v[U], g0[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      d[u] = dh[(int64_t)dst[e + u] * H + f];
+      v[u] = part ? m[(e + u) * H + f] : 0.f;
+      g0[u] = accumulate ? grad_m[(e + u) * H + f] : 0.f;
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const float* q = rbf + (e + u) * R;
+      grad_m[(e + u) * H + f] = __builtin_fmaf(d[u], col.at(q, R), g0[u]);
+      const float dg = d[u] * v[u];
+#pragma unroll
+      for (int r = 0; r < RM; ++r) dw[r] = __builtin_fmaf(r < R ? q[r] : 0.f, dg, dw[r]);
+    }
+  };
+  int64_t e = e0;
+  for (; e + 3 < e1; e += 4) edges(std::integral_constant<int, 4>(), e);
+  for (; e < e1; ++e) edges(std::integral_constant<int, 1>(), e);
+  if (part) {
+#pragma unroll
+    for (int r = 0; r < RM; ++r)
+      if (r < R) part[(run * R + r) * H + f] = dw[r];
+  }
+}
+// runs of the edges: of 32, at most 1024
+int64_t edge_runs_most(int64_t E) { return std::min<int64_t>((E + 31) / 32, 1024); }
 
 // p[i] = u[i, :] . w; one wavefront per atom
 __global__ void __launch_bounds__(256)
@@ -126,7 +225,7 @@ size_t carve_out_saved(void* p, int64_t N, int H, int D, int L, out_saved* s) {
 struct out_scratch {
   float *tE;          // [E, H]: t in the forward pass, dt (then dt * m) in the backward pass
   float *p, *ga;      // [N]
-  float *du[2];       // [N, D]
+  float* du[GP_MAX_OUT_LAYERS + 1];   // [N, D] each: the gradients between the layers, which their weight gradients wait for together
   float *dh;          // [N, H]
   float* part;
   size_t part_bytes;
@@ -137,13 +236,15 @@ size_t carve_out_scratch(void* p, int64_t N, int64_t E, int H, int D, int R, int
   s->tE = c.take<float>(E * H);
   s->p = c.take<float>(N);
   s->ga = c.take<float>(N);
-  s->du[0] = c.take<float>(N * D);
-  s->du[1] = c.take<float>(N * D);
+  for (int k = 0; k <= L; ++k) s->du[k] = c.take<float>(N * D);
   s->dh = c.take<float>(N * H);
   size_t m = gp_gemm_tn_scratch(E, R, H);
-  m = std::max(m, gp_gemm_tn_scratch(N, H, D));
-  m = std::max(m, gp_gemm_tn_scratch(N, D, D));
-  m = std::max(m, gp_gemm_tn_scratch(N, D, 1));
+  if (R <= RADIAL_MAX) m = std::max(m, (size_t)edge_runs_most(E) * R * H * sizeof(float));
+  gp_tn_product all[GP_MAX_OUT_LAYERS + 2];
+  for (int k = 0; k < L; ++k) all[k] = gp_tn_product{nullptr, nullptr, D, D, nullptr, nullptr};
+  all[L] = gp_tn_product{nullptr, nullptr, H, D, nullptr, nullptr};
+  all[L + 1] = gp_tn_product{nullptr, nullptr, D, 1, nullptr, nullptr};
+  m = std::max(m, gp_gemm_tn_group_scratch(N, all, L + 2));
   s->part_bytes = m;
   s->part = (float*)c.take<char>(m);
   s->planes = c.take<char>((size_t)L * gp_align(gp_planes_bytes(D, D)) + gp_align(std::max(gp_planes_bytes(D, H), gp_planes_bytes(H, D))));
@@ -195,11 +296,16 @@ int gp_output_forward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_rad
   GP_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   gp_epilogue e;
-  if (n_edges > 0) {
-    e = gp_epilogue(); e.mul = m; e.out = sc.tE;
-    GP_TRY(gp_gemm_nn(ctx, rbf, w->W_rbf, n_edges, H, R, e));                         // t = (rbf W_rbf) * m
-  }
-  {
+  if (n_edges > 0 && R <= RADIAL_MAX) {
+    gp_prof_scope prof(ctx, "out_edge_sum", 2.0 * (double)n_edges * H * (R + 1), 4.0 * ((double)n_edges * (H + R) + (double)n_atoms * H));
+    (R <= 8 ? out_edge_sum_kernel<8> : out_edge_sum_kernel<RADIAL_MAX>)<<<wblk(n_atoms * ((H + 63) / 64)), 256, 0, st>>>(
+        m, rbf, w->W_rbf, row_ptr, n_atoms, H, R, s.h);
+    GP_LAUNCH_CHECK(ctx, "out_edge_sum_kernel");
+  } else {
+    if (n_edges > 0) {
+      e = gp_epilogue(); e.mul = m; e.out = sc.tE;
+      GP_TRY(gp_gemm_nn(ctx, rbf, w->W_rbf, n_edges, H, R, e));                       // t = (rbf W_rbf) * m
+    }
     gp_prof_scope prof(ctx, "out_atom_sum", (double)n_edges * H, 4.0 * ((double)n_edges * H + (double)n_atoms * H));
     out_atom_sum_kernel<<<wblk(n_atoms * ((H + 63) / 64)), 256, 0, st>>>(sc.tE, row_ptr, n_atoms, H, s.h);
     GP_LAUNCH_CHECK(ctx, "out_atom_sum_kernel");
@@ -244,8 +350,7 @@ int gp_output_backward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_ra
   GP_HIP(ctx, hipSetDevice(ctx->device));
   hipStream_t st = ctx->stream;
   gp_epilogue e;
-  float* du = sc.du[0];
-  float* other = sc.du[1];
+  float* du = sc.du[L];   // dz of layer L - 1
   out_seed_kernel<<<wblk(n_atoms), 256, 0, st>>>(grad_energy, graph_ptr, n_graphs, n_atoms, w->w_final, L > 0 ? s.z[L - 1] : nullptr, D,
                                                  sc.ga, du);                              // du = dz_{L-1}
   GP_LAUNCH_CHECK(ctx, "out_seed_kernel");
@@ -254,20 +359,30 @@ int gp_output_backward(gp_ctx* ctx, int32_t emb, int32_t out_emb, int32_t num_ra
   const void* p_layer[GP_MAX_OUT_LAYERS] = {};
   for (int k = 0; k < L; ++k) p_layer[k] = wp.add(w->W[k], n_atoms, D, D, 0);
   GP_TRY(wp.run());
-  const float* u_last = L > 0 ? s.u[L - 1] : s.u0;
-  if (grad_w) GP_TRY(gp_gemm_tn(ctx, u_last, sc.ga, n_atoms, D, 1, grad_w->w_final, nullptr, sc.part, sc.part_bytes));
+  gp_tn_product wg[GP_MAX_OUT_LAYERS + 2];
+  int n_wg = 0;
+  wg[n_wg++] = gp_tn_product{L > 0 ? s.u[L - 1] : s.u0, sc.ga, D, 1, grad_w ? grad_w->w_final : nullptr, nullptr};
   for (int k = L - 1; k >= 0; --k) {
-    const float* u_in = k > 0 ? s.u[k - 1] : s.u0;
-    if (grad_w) GP_TRY(gp_gemm_tn(ctx, u_in, du, n_atoms, D, D, grad_w->W[k], grad_w->b[k], sc.part, sc.part_bytes));
-    e = gp_epilogue(); e.out = other;
+    wg[n_wg++] = gp_tn_product{k > 0 ? s.u[k - 1] : s.u0, du, D, D, grad_w ? grad_w->W[k] : nullptr, grad_w ? grad_w->b[k] : nullptr};
+    e = gp_epilogue(); e.out = sc.du[k];
     if (k > 0) e.act = 2, e.zsrc = s.z[k - 1];
     GP_TRY(gp_gemm_nt_w(ctx, du, w->W[k], p_layer[k], n_atoms, D, D, e));               // dz_{k-1}, du_{-1} = du0
-    std::swap(du, other);
+    du = sc.du[k];
   }
-  if (grad_w) GP_TRY(gp_gemm_tn(ctx, s.h, du, n_atoms, H, D, grad_w->W_up, nullptr, sc.part, sc.part_bytes));
+  wg[n_wg++] = gp_tn_product{s.h, du, H, D, grad_w ? grad_w->W_up : nullptr, nullptr};
+  if (grad_w) GP_TRY(gp_gemm_tn_group(ctx, wg, n_wg, n_atoms, sc.part, sc.part_bytes));
   e = gp_epilogue(); e.out = sc.dh;
   GP_TRY(gp_gemm_nt_w(ctx, du, w->W_up, p_up, n_atoms, H, D, e));                       // dh
-  if (n_edges > 0) {
+  if (n_edges > 0 && R <= RADIAL_MAX) {
+    const int64_t per = (n_edges + edge_runs_most(n_edges) - 1) / edge_runs_most(n_edges), runs = (n_edges + per - 1) / per;
+    {
+      gp_prof_scope prof(ctx, "out_edge_grad", 4.0 * (double)n_edges * H * (R + 1), 4.0 * (double)n_edges * (3.0 * H + R));
+      (R <= 8 ? out_edge_grad_kernel<8> : out_edge_grad_kernel<RADIAL_MAX>)<<<wblk(runs * ((H + 63) / 64)), 256, 0, st>>>(
+          m, rbf, w->W_rbf, sc.dh, dst, n_edges, per, H, R, accumulate_grad_m, grad_m, grad_w ? sc.part : nullptr);
+      GP_LAUNCH_CHECK(ctx, "out_edge_grad_kernel");
+    }
+    if (grad_w) GP_TRY(gp_reduce_parts(ctx, sc.part, (int)runs, (int64_t)R * H, grad_w->W_rbf));
+  } else if (n_edges > 0) {
     {
       gp_prof_scope prof(ctx, "out_gather_rows", 0.0, 4.0 * ((double)n_edges * H + (double)n_atoms * H));
       out_gather_rows_kernel<<<nblk(n_edges * H), 256, 0, st>>>(sc.dh, dst, n_edges, H, sc.tE);   // dt

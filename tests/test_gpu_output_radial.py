@@ -1,0 +1,45 @@
+"""The edges' passes of the output block with few radial functions (kernels of their own up to 16, products above): both sizes of the kernels
+and the first count without one, features that end inside a wavefront's 64, atoms without edges, runs of edges that end early."""
+import numpy as np
+import pytest
+import torch
+
+import synth
+from tests import helpers as H
+from tests.test_gpu_output import _oracle_out
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("R", [1, 8, 9, 16, 17])
+@pytest.mark.parametrize("emb,edges", [(40, 1), (65, 33), (256, 1030), (64, 33000)])   # 33000: runs of more than 32
+def test_output_block(lib, R, emb, edges):
+    from paper_2203_09697_amd import binding_o as O
+    ctx, rng, N, L = lib.Context(0), np.random.default_rng(R + emb), 37, 2
+    dst = np.sort(rng.choice(np.setdiff1d(np.arange(N), [0, 5, 36]), edges))
+    row_ptr, gptr = np.searchsorted(dst, np.arange(N + 1)), np.array([0, 20, N])
+    m, rbf = rng.standard_normal((edges, emb)).astype(np.float32), rng.standard_normal((edges, R)).astype(np.float32)
+    coef = rng.standard_normal(2).astype(np.float32)
+    W = synth.weights_out(emb, 48, R, L, seed=3, bias_scale=0.2)
+    want_E, want_gm, want_W = _oracle_out(m, rbf, dst, gptr, N, W, coef)
+    Wd = lib.weights_to_device(W)
+    gW = {k: torch.empty_like(v) for k, v in Wd.items()}
+    sb, cb = O.gp_output_workspace(emb, 48, R, L, N, edges)
+    saved, scratch = (torch.empty(max(b, 8), dtype=torch.uint8, device="cuda:0") for b in (sb, cb))
+    dm, drbf, dptr = H.to_dev(m, torch.float32), H.to_dev(rbf, torch.float32), H.to_dev(gptr, torch.int32)
+    energy, gm = torch.empty(2, device="cuda:0"), torch.empty_like(dm)
+    O.gp_output_forward(ctx, Wd, dm, drbf, H.to_dev(row_ptr, torch.int32), dptr, False, energy, saved, scratch)
+    back = lambda acc, out, w: O.gp_output_backward(ctx, Wd, dm, drbf, H.to_dev(dst, torch.int32), dptr, N, H.to_dev(coef, torch.float32), saved, acc, out, w, scratch)
+    back(False, gm, gW)
+    base = torch.randn_like(gm)
+    twice = base.clone()
+    back(True, twice, None)
+    torch.cuda.synchronize()
+    # sums of at most 33000 products in fp32 by runs of a few dozen, and five small products of 1e-7 each
+    err = {"energy": H.rel_l2(energy.cpu().numpy(), want_E), "grad_m": H.rel_l2(gm.cpu().numpy(), want_gm)}
+    err.update({k: H.rel_l2(gW[k].cpu().numpy(), g) for k, g in want_W.items()})
+    print({k: "%.1e" % v for k, v in err.items()})
+    assert max(err.values()) < 3e-6
+    # on top of another gradient the sum is rounded once, to half an ulp of it (6e-8); norms, as above: triangle inequality
+    want = base.cpu().numpy().astype(np.float64) + want_gm
+    assert np.linalg.norm(twice.cpu().numpy() - want) <= 6e-8 * np.linalg.norm(want) + 3e-6 * np.linalg.norm(want_gm)
