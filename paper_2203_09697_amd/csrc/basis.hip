@@ -464,22 +464,23 @@ static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const 
       if (R > MAX_R_BESSEL) return gp_fail(ctx, GP_UNSUPPORTED_DIMS, "%s: num_radial=%d > %d", who, R, MAX_R_BESSEL);
       bessel_table tab;
       make_bessel_table(S, R, (double)dims->cutoff, &tab);
-      // 32 edges per workgroup fill the chip from about 16 000 edges on; below that the time is one value's latency, and 4
-      // edges per workgroup leave one value to a thread.  4 / 32 edges, 48 values each: 7 / 13 us at 4000 edges, 15 / 16 at
-      // 12 000, 18 / 16 at 16 000, 31 / 26 at 32 000, 241 / 175 at 300 000
+      // 32 edges per workgroup share the factors of an edge and fill the chip from about 12 000 edges on; below that the time is one
+      // value's latency, and 4 edges per workgroup leave one value to a thread.  4 / 32 edges, 48 values each: 4.8 / 8.3 us at 4000
+      // edges, 7.5 / 8.6 at 8000, 9.7 / 9.7 at 12 000, 11.9 / 9.8 at 16 000, 20 / 14 at 32 000, 164 / 85 at 300 000
+      const bool many = n_edges >= 12288;
       const size_t row = sizeof(float) * (R + S * R + 1);
       // In one launch with the cosines while those are a matter of latency (above); 1e8 of them take 0.22 ms of writes
       if (cos && cos->n_triplets < 4 * 1000 * 1000) {
         *cos_done = true;
         const bool wide = cos->n_triplets >= LONG_LISTS * n_edges;
-        const int eb = n_edges >= 16384 ? 32 : 4, blocks = (int)((n_edges + eb - 1) / eb);
+        const int eb = many ? 32 : 4, blocks = (int)((n_edges + eb - 1) / eb);
         auto* kernel = wide ? (eb == 32 ? basis_graph_D_kernel<true, 32> : basis_graph_D_kernel<true, 4>)
                             : (eb == 32 ? basis_graph_D_kernel<false, 32> : basis_graph_D_kernel<false, 4>);
         kernel<<<(unsigned)(blocks + 2 * cos->n_blocks), 256, eb * row, st>>>(*cos, blocks, dist, S, R, p, tab, rbf, rad);
         GP_LAUNCH_CHECK(ctx, "basis_graph_D_kernel");
         return GP_OK;
       }
-      if (n_edges >= 16384)
+      if (many)
         basis_edge_D_kernel<32><<<(unsigned)((n_edges + 31) / 32), 256, 32 * row, st>>>(dist, n_edges, S, R, p, tab, rbf, rad);
       else
         basis_edge_D_kernel<4><<<(unsigned)((n_edges + 3) / 4), 256, 4 * row, st>>>(dist, n_edges, S, R, p, tab, rbf, rad);
