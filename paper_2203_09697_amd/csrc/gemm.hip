@@ -229,7 +229,7 @@ gemm_f32_kernel(const gemm_args g) {
 // 16 column groups x 16 split lanes per workgroup: every lane issues its (few) 16-byte loads
 // back to back, the 16 lanes of a column group are combined in a fixed order through LDS, so
 // the result is reproducible.  The narrow arrays are handled the same way, one float
-// per column group.
+// per column group, summed in fp64: column sums of all edges, whose terms share a sign.
 constexpr int RED_COLS = 16, RED_LANES = 16;
 struct reduce_job {
   const float* part;
@@ -252,9 +252,9 @@ reduce_parts_kernel(const reduce_jobs<JOBS> q) {
   const reduce_job& r = q.j[job];
   const int block = (int)blockIdx.x - r.first;
   const int cg = threadIdx.x % RED_COLS, sl = threadIdx.x / RED_COLS;
-  f32x4 s = {0.f, 0.f, 0.f, 0.f};
   if (r.vec) {
     const int64_t i = ((int64_t)block * RED_COLS + cg) * 4;
+    f32x4 s = {0.f, 0.f, 0.f, 0.f};
     if (i < r.n) {
 #pragma unroll 8
       for (int z = sl; z < r.splits; z += RED_LANES) s += ld4(r.part + (int64_t)z * r.n + i);
@@ -268,16 +268,18 @@ reduce_parts_kernel(const reduce_jobs<JOBS> q) {
     }
   } else {
     const int64_t i = (int64_t)block * RED_COLS + cg;
+    double(*red1)[RED_COLS] = reinterpret_cast<double(*)[RED_COLS]>(red);
+    double s = 0.0;
     if (i < r.n) {
 #pragma unroll 8
-      for (int z = sl; z < r.splits; z += RED_LANES) s[0] += r.part[(int64_t)z * r.n + i];
+      for (int z = sl; z < r.splits; z += RED_LANES) s += (double)r.part[(int64_t)z * r.n + i];
     }
-    red[sl][cg] = s;
+    red1[sl][cg] = s;
     __syncthreads();
     if (sl == 0 && i < r.n) {
-      float t = red[0][cg][0];
-      for (int k = 1; k < RED_LANES; ++k) t += red[k][cg][0];
-      r.out[i] = t;
+      double t = red1[0][cg];
+      for (int k = 1; k < RED_LANES; ++k) t += red1[k][cg];
+      r.out[i] = (float)t;
     }
   }
 }

@@ -18,6 +18,8 @@
 // PFLOP/s in bf16 and 1.72 in fp16 from registers alone (2.47 with zeros), so fewer matrix instructions is what helps.
 #include <stdarg.h>
 
+#include <type_traits>
+
 #include <algorithm>
 
 #include "gemm_common.h"
@@ -576,14 +578,20 @@ gemm_planes_kernel(const gemm_args g) {
 // compute unit).  43380 rows, 2048 x 2048 1.91 ms, 256 x 256 42 us, 6 x 256 25; 13230, 256 x 256 19; 434, 256 x 256 7.7; 336, 32 x 32 6.1.  Two fp16
 // parts under shared scales take 1.38 ms, 39, 32, 19, 7.3 and 6.5, and lose what is 2^17 smaller than its neighbours; with every such
 // value sought out and added in fp32 they took 1.7 ms, 46, - and 27.
-// Every TN_FOLD chunks the sums, and those of the columns, go to a second set by fp32 additions (FOLD: not for lack of registers).  The matrix instruction's sums come out low (above), so the
-// error of one run grows with its length; products that share a launch have runs of thousands of rows.
+// Sums are of few chunks (FOLD: not for lack of registers), every second one of them with the sign of A's values turned, and go to a second
+// set by fp32 additions: the matrix instruction's sums come out low (above), and a run of a product that shares its launch has thousands of
+// rows.  Column sums are formed in fp64, eight rows at a time.  How many chunks: few where a run has few of them, more where the additions
+// to the second set would be many, and no fewer than the error asks for (4 in the place of 8 costs a training step of 43380 x 256 1 per
+// cent).  Relative error against 64 bits (1e-7) of a block's products of 256 x 256 together, and of one by itself in sums of one sign that
+// are as long as its runs: 434 rows 0.91 (1.04), 1500 1.26 (1.42), 7593 1.40 (1.62), 13230 1.47 (2.02), 22730 1.81 (2.42), 43380 1.82 (3.24),
+// 120000 1.88 (5.50); column sums 0.47 (0.85) to 0.25 (0.66).  Sums of 16 chunks and one sign: 1.23, 1.94, 2.47, 2.56, 2.69, 2.83, 3.17.
 constexpr int TN_ROWS = 16, TN_BLOCK_B = 3 * FRAG_B;   // rows of a chunk, bytes of its three parts for 32 columns
-constexpr int TN_FOLD = 16;
+// chunks of a sum, for runs of `per` rows
+inline int tn_fold(int64_t per) { return per <= 8 * TN_ROWS ? 2 : per <= 96 * TN_ROWS ? 4 : 8; }
 template <int JOBS>
 struct tn_args {
   gp_tn_part_job j[JOBS];   // tiles first, first + 1, ... of a split belong to a product
-  int n, tiles;
+  int n, tiles, fold;       // fold: chunks of a sum
   int64_t rows, per;
 };
 template <int MB, int NB, int WAVES_M, int WAVES_N, int OCC, bool FOLD, int JOBS>
@@ -650,26 +658,28 @@ gemm_parts_tn_kernel(const tn_args<JOBS> q) {
         }
     }
   };
-  float cs[LB], cs_whole[LB];
+  double cs[LB];
 #pragma unroll
-  for (int b = 0; b < LB; ++b) cs[b] = cs_whole[b] = 0.f;
+  for (int b = 0; b < LB; ++b) cs[b] = 0.0;
   const bool want_cs = jb.colsum_part != nullptr;
   // chunk c of the loaders' registers goes to LDS buffer u
-  auto store = [&](int c, int u) __attribute__((always_inline)) {
+  auto store = [&](int c, int u, uint32_t turn) __attribute__((always_inline)) {
     const bool mine = want_cs && c % tiles_m == tile_m;
 #pragma unroll
     for (int b = 0; b < NL; ++b) {
       const int blk = b < LA ? wave * LA + b : BA + wave * LB + b - LA;
       bf16x8 part[3];
+      if (FOLD && b < LA) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) raw[b][r] = __uint_as_float(__float_as_uint(raw[b][r]) ^ turn);
+      }
       parts8(raw[b], part);
       char* dst = lds + u * BUF_B + blk * TN_BLOCK_B + lane * 16;
 #pragma unroll
       for (int p = 0; p < 3; ++p) *reinterpret_cast<bf16x8*>(dst + p * FRAG_B) = part[p];
       if (b >= LA && mine) {
-        float sum = 0.f;
-#pragma unroll
-        for (int r = 0; r < 8; ++r) sum += raw[b][r];
-        cs[b - LA < 0 ? 0 : b - LA] += sum;
+        const float* r = raw[b];
+        cs[b - LA < 0 ? 0 : b - LA] += (double)(((r[0] + r[1]) + (r[2] + r[3])) + ((r[4] + r[5]) + (r[6] + r[7])));
       }
     }
   };
@@ -684,7 +694,7 @@ gemm_parts_tn_kernel(const tn_args<JOBS> q) {
         acc[i][j][v] = 0.f;
         if constexpr (FOLD) whole[i][j][v] = 0.f;
       }
-  auto multiply = [&](int u) __attribute__((always_inline)) {
+  auto multiply = [&](int u, auto begin) __attribute__((always_inline)) {   // begin: of a sum
     const char* sa = lds + u * BUF_B + wm * TN_BLOCK_B + lane * 16;
     const char* sb = lds + u * BUF_B + (BA + wn) * TN_BLOCK_B + lane * 16;
     bf16x8 b[NB][3];
@@ -701,47 +711,53 @@ gemm_parts_tn_kernel(const tn_args<JOBS> q) {
 #pragma unroll
       for (int x = 0; x < 6; ++x)
 #pragma unroll
-        for (int j = 0; j < NB; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[x]], b[j][PB[x]], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < NB; ++j)
+          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[PA[x]], b[j][PB[x]], decltype(begin)::value && x == 0 ? f32x16{} : acc[i][j], 0, 0, 0);
     }
   };
-  auto fold = [&]() __attribute__((always_inline)) {
+  auto fold = [&](float sign) __attribute__((always_inline)) {
     if constexpr (FOLD) {
 #pragma unroll
       for (int i = 0; i < MB; ++i)
 #pragma unroll
         for (int j = 0; j < NB; ++j)
 #pragma unroll
-          for (int v = 0; v < 16; ++v) {
-            whole[i][j][v] += acc[i][j][v];
-            acc[i][j][v] = 0.f;
-          }
+          for (int v = 0; v < 16; ++v) whole[i][j][v] = __builtin_fmaf(acc[i][j][v], sign, whole[i][j][v]);
     }
-#pragma unroll
-    for (int b = 0; b < LB; ++b) cs_whole[b] += cs[b], cs[b] = 0.f;
   };
 
   if (n_ch > 0) {
+    uint32_t turn = 0;         // of the values in the buffer that is filled next
+    float sign = 1.f;          // of the sums in acc
+    int left = q.fold, in = q.fold - 1;   // chunks until the next fold, and until the next turn of the loaders
     fetch(0);
-    store(0, 0);
+    store(0, 0, turn);
     fetch(1);
     __syncthreads();
     for (int c = 0; c < n_ch; ++c) {
       const int u = c & 1;
       if (c + 1 < n_ch) {
-        store(c + 1, u ^ 1);
+        if (FOLD && in == 0) turn ^= 0x80000000u, in = q.fold;
+        --in;
+        store(c + 1, u ^ 1, turn);
         fetch(c + 2);
       }
-      multiply(u);
-      if (c % TN_FOLD == TN_FOLD - 1) fold();
+      if (FOLD && left == q.fold) multiply(u, std::true_type());
+      else multiply(u, std::false_type());
+      if (FOLD && --left == 0) {
+        fold(sign);
+        sign = -sign;
+        left = q.fold;
+      }
       __syncthreads();
     }
+    if (left < q.fold) fold(sign);
   }
-  fold();
   __syncthreads();
   if (want_cs) {
 #pragma unroll
     for (int b = 0; b < LB; ++b) {
-      const float sum = cs_whole[b] + __shfl_xor(cs_whole[b], 32, 64);
+      const float sum = (float)(cs[b] + __shfl_xor(cs[b], 32, 64));
       const int n = n0 + (wave * LB + b) * 32 + l32;
       if (kh == 0 && n < N) jb.colsum_part[((int64_t)split * tiles_m + tile_m) * N + n] = sum;
     }
@@ -757,7 +773,7 @@ template <int MB, int NB, int WMS, int WNS, int OCC, bool FOLD, int JOBS>
 int launch_parts_tn(gp_ctx* ctx, const gp_tn_part_job* jobs, int n, int64_t rows, int64_t per, int splits) {
   constexpr int BA = MB * WMS, BB = NB * WNS, NW = WMS * WNS;
   tn_args<JOBS> q;
-  q.n = n; q.rows = rows; q.per = per;
+  q.n = n; q.rows = rows; q.per = per; q.fold = tn_fold(per);
   int64_t tiles = 0;
   double flops = 0.0, bytes = 0.0;
   for (int i = 0; i < n; ++i) {
