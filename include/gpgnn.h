@@ -50,7 +50,8 @@ const char* gp_version(void);
  * stream and join it before returning, so callers see single-stream semantics: the weight-gradient GEMMs of
  * the backward passes next to the input-gradient chain; in the variant-D block also the branch through the
  * target-edge projection and, from 2048 edges on, one half of the rows of the layers after the triplet sum
- * (the same arithmetic per row: the forward result does not depend on the setting).
+ * (the same arithmetic per row: the forward result does not depend on the setting).  A variant-D block of at most
+ * 256 columns and fewer than 2048 edges keeps to the context's stream, where its kernels are too short to gain.
  * gp_set_side_stream(ctx, 0) keeps everything on the context's stream, e.g. to time kernels one
  * at a time; the environment variable GP_NO_AUX_STREAM=1 has the same effect at gp_create. */
 int gp_set_side_stream(gp_ctx* ctx, int on);

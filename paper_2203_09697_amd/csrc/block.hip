@@ -58,18 +58,17 @@ size_t carve_saved_D(void* p, const gp_dims* d, int64_t E, saved_D* s) {
   return c.off;
 }
 
-// Gradients of the pre-activations of a block, one per dense layer over the edges and one for dxg; where the weight gradients are formed
-// together they all have to last, else three are used in turn.
-constexpr int DZ_MOST = 5 + 4 * GP_MAX_RES;
+// Gradients of the pre-activations of a block, one per dense layer over the edges, one for dxg and one for the gate; where the weight
+// gradients are formed together they all have to last, else four are used in turn.
+constexpr int DZ_MOST = 6 + 4 * GP_MAX_RES;
 // The weight gradients of a block are formed by a few launches for all of them where a product by itself would be cut into many
 // runs of the rows (gp_gemm_tn_group), i.e. below width 512.
 bool group_D(const gp_dims* d) { return d->emb < 512; }
-int dz_buffers_D(const gp_dims* d) { return group_D(d) ? 5 + 2 * (d->n_res_before + d->n_res_after) : 3; }
+int dz_buffers_D(const gp_dims* d) { return group_D(d) ? 6 + 2 * (d->n_res_before + d->n_res_after) : 4; }
 
 struct scratch_D {
   float* buf[3];     // [E,H] each: gradients of the messages between layers
-  float* dgate;      // [E,H]
-  float* dz[DZ_MOST];
+  float* dz[DZ_MOST];   // [E,H] each
   float *dF1, *dF2;  // [E,F]
   float* dQ;         // [E,S*B]
   float* P;          // [E,S,F]: per-edge factor of the gradient with respect to cos(alpha) (basis gradients only)
@@ -155,7 +154,6 @@ size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   gp_carver c(p);
   const size_t H = d->emb, F = d->int_emb, B = d->basis_emb, S = d->num_spherical, R = d->num_radial;
   for (int i = 0; i < 3; ++i) s->buf[i] = c.take<float>(E * H);
-  s->dgate = c.take<float>(E * H);
   for (int i = 0; i < dz_buffers_D(d); ++i) s->dz[i] = c.take<float>(E * H);
   s->dF1 = c.take<float>(E * F);
   s->dF2 = c.take<float>(E * F);
@@ -196,8 +194,13 @@ int check_weights_D(gp_ctx* ctx, const gp_dims* d, const gp_weights_D* w, const 
   return GP_OK;
 }
 
-// Below that many edges a block's kernels take 5 us each, no longer than an event and its wait on another stream take to issue.
-constexpr int64_t SIDE_MIN_ROWS = 2048;
+// From that many edges on the forward pass cuts the layers after the triplet sum into two halves of the rows.
+constexpr int64_t SPLIT_MIN_ROWS = 2048;
+// Whether a block is worth the side stream: not where its kernels are as short as an event and its wait on another stream take to issue.
+// Two blocks forward and backward, one stream / two (ms), 288 edges: width 64 0.31 / 0.48, 128 0.50 / 0.57, 256 1.00 / 1.05, 384 1.13 / 1.09,
+// 448 1.25 / 1.19, 512 1.88 / 1.57, 1024 2.76 / 2.15, 2048 5.15 / 4.18; 1494 edges: 0.38 / 0.48, 0.58 / 0.65, 1.07 / 1.10, 1.25 / 1.19, 1.41 / 1.31,
+// 2.27 / 1.91, 3.40 / 2.93, 7.05 / 6.02.
+bool side_D(const gp_dims* d, int64_t E) { return d->emb > 256 || E >= 2048; }
 
 // one residual layer forward: hout = hin + act(act(hin W1 + b1) W2 + b2); pl: the planes of W1 and W2
 int res_forward(gp_ctx* ctx, const float* hin, float* const* w, const void* const* pl, const res_saved& s, float* hout, int64_t E, int H) {
@@ -219,11 +222,12 @@ struct wgrads_D {
   int n_dz, at = 0, n = 0;
   gp_tn_product p[GP_TN_JOBS_MAX];
   wgrads_D(gp_ctx* c, gp_aux& a, scratch_D& s, const gp_dims* d, int64_t rows) : ctx(c), aux(a), sc(s), E(rows), group(group_D(d)), n_dz(dz_buffers_D(d)) {}
-  // room for the next gradient; with three buffers the side stream may still read what was in it
-  int take(float** dz) {
+  // Room for the next gradient.  Where the buffers are used in turn the side stream may still read what was in it, which a gradient that it
+  // writes itself (on_side) need not wait for.
+  int take(float** dz, bool on_side = false) {
     *dz = sc.dz[at];
     at = at + 1 == n_dz ? 0 : at + 1;
-    return group ? GP_OK : aux.before_write(*dz);
+    return group || on_side ? GP_OK : aux.before_write(*dz);
   }
   // W = A^T dz, b its column sums
   int add(const float* A, const float* dz, int M, int N, float* W, float* b) {
@@ -348,9 +352,9 @@ int gp_block_forward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, 
   // these widths is one round of workgroups whose loading, multiplying and storing phases coincide; the rows are cut
   // in two and the halves run as two chains on the two streams, out of step with each other (configuration 2:
   // 9.70 -> 9.40 ms per step; cutting the chain before the triplet sum as well: 9.51 ms).
-  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
+  gp_aux aux(ctx, side_D(dims, E));
   const int64_t half = ((E / 2 + 127) / 128) * 128;
-  const bool split = aux.active() && half < E;
+  const bool split = aux.active() && E >= SPLIT_MIN_ROWS && half < E;
   gp_epilogue e;
   e.out = s.Wrbf;
   GP_TRY(gp_gemm_nn(ctx, w->W_rbf1, w->W_rbf2, R, H, B, e));
@@ -472,7 +476,6 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   GP_HIP(ctx, hipSetDevice(ctx->device));
   const int H = dims->emb, F = dims->int_emb, B = dims->basis_emb, S = dims->num_spherical, R = dims->num_radial;
   const int64_t EH = E * H;
-  float* const dgate = sc.dgate;
   // rotating buffers for dh; `keep` is a gradient that must survive (the skip into m)
   const float* dh = grad_m_out;
   const float* keep = nullptr;
@@ -483,15 +486,15 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   };
 
   // Small graphs are launches and nothing else: one stream, all weight gradients at the end.  Otherwise they are formed on the side stream, in
-  // groups, each as soon as what enters it is there.
-  gp_aux aux(ctx, E >= SIDE_MIN_ROWS);
+  // groups or one by one, each as soon as what enters it is there.
+  gp_aux aux(ctx, side_D(dims, E));
   wgrads_D wg(ctx, aux, sc, dims, E);
   // dz of the last activation in the block
   const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
   const bool chain = chain_D(ctx, dims, w, E, {m_in, grad_m_out, grad_m_in, saved, scratch});
   chain_list ch;
   int pre = 0;   // steps before the triplet sum's gradients
-  float *dz_ji, *dz_kj, *dm_ji;
+  float *dz_ji, *dz_kj, *dgate, *dm_ji;
   gp_weight_planes wp(ctx, chain ? nullptr : sc.planes);
   const void *p_ji = wp.add(w->W_ji, E, H, H, 0), *p_kj = wp.add(w->W_kj, E, H, H, 0), *p_down = wp.add(w->W_down, E, H, F, 0),
              *p_up = wp.add(w->W_up, E, F, H, 0), *p_lin = wp.add(w->W_lin, E, H, H, 0);
@@ -550,6 +553,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
     pre = ch.n;
     GP_TRY(wg.take(&dz_kj));
+    GP_TRY(wg.take(&dgate));
     gp_chain_step& dn = ch.add(w->W_down, H, F, 0);
     dn.load = sc.dF2; dn.gate = 1; dn.z = s.z_kj; dn.mul = s.gate; dn.out2 = dz_kj; dn.out3 = dgate;
     gp_chain_step& kj = ch.add(w->W_kj, H, H, 0);                 // dm = kj path + ji path + skip
@@ -598,7 +602,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     // stream next to the chain through the triplet sum, whose kernels leave much of the chip idle; its input gradient
     // is added by the epilogue of the last GEMM below.
     GP_TRY(wg.add(s.a, dzcur, F, H, gw->W_up, nullptr));
-    GP_TRY(wg.take(&dz_ji));
+    GP_TRY(wg.take(&dz_ji, true));
     dm_ji = next_buf();
     GP_TRY(aux.on_aux(
         [&] {
@@ -654,6 +658,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     GP_TRY(gp_chain_run(ctx, H, ch.s, pre, ch.n, E, sc.planes));   // dz_kj, dgate and the result
   } else {
     GP_TRY(wg.take(&dz_kj));
+    GP_TRY(wg.take(&dgate));
     // dxg = dF2 W_down^T is not stored where its epilogue can take the gate apart (two launches: 26 + 48 us at 43380 x 256): planes, and
     // buffers that start on 16 bytes
     bool gate_fused = p_down != nullptr;
@@ -670,7 +675,14 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
       GP_TRY(gp_ew_gate_bwd(ctx, dxg, s.z_kj, s.gate, dz_kj, dgate, EH));                      // dz_kj, dgate
     }
   }
-  GP_TRY(wg.add(basis->rbf, dgate, R, H, sc.dWrbf, nullptr));
+  // The radial gate's gradients join the others of a group; one by one they stay on the main stream, which has less to do by then.
+  auto factors = [&] { return gp_factor_grads(ctx, sc.dWrbf, w->W_rbf1, w->W_rbf2, R, B, H, gw->W_rbf1, gw->W_rbf2); };
+  if (wg.group) {
+    GP_TRY(wg.add(basis->rbf, dgate, R, H, sc.dWrbf, nullptr));
+  } else {
+    GP_TRY(gp_gemm_tn(ctx, basis->rbf, dgate, E, R, H, sc.dWrbf, nullptr, sc.part, sc.part_bytes));
+    GP_TRY(factors());
+  }
   if (grad_rbf) {   // dL/drbf = dgate W_rbf^T
     gp_epilogue e; e.out = grad_rbf;
     if (accumulate_basis_grads) e.add_post = grad_rbf;
@@ -678,7 +690,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   }
   GP_TRY(wg.add(m_in, dz_kj, H, H, gw->W_kj, gw->b_kj));
   GP_TRY(wg.run());
-  GP_TRY(aux.on_aux([&] { return gp_factor_grads(ctx, sc.dWrbf, w->W_rbf1, w->W_rbf2, R, B, H, gw->W_rbf1, gw->W_rbf2); }, {}));
+  if (wg.group) GP_TRY(aux.on_aux(factors, {}));
   if (!chain) {
     GP_TRY(aux.before_write(dm_ji));   // the side stream's input gradient of the ji path
     gp_epilogue e; e.add_pre = dm_ji; e.add_post = keep; e.out = grad_m_in;
