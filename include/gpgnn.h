@@ -13,7 +13,9 @@
  *     caller; the library allocates no user-visible memory.  Temporary storage is
  *     a caller-provided workspace whose size is queried first.
  *   - All work is enqueued on the hipStream_t given to gp_create; only the
- *     *_count calls synchronise (they return a host scalar).
+ *     *_count calls synchronise (they return a host scalar): when they return, all work
+ *     before them on that stream is done, what they wrote is visible to every stream and
+ *     their workspace is idle (gp_graph_lists_count excepted, see there).
  *   - Arrays are row-major and contiguous.  Indices are int32, counts int64.
  *     A weight matrix is W[in, out]; a layer computes x @ W + b.
  *   - Edge e runs from source src[e] to target dst[e] (message m_st of Sec. 3.1).

@@ -42,9 +42,9 @@ struct gp_ctx {
   // gp_deferred_status.
   int* dflag = nullptr;       // host address
   int* dflag_dev = nullptr;   // the same word as the device sees it
-  // Results of the *_count calls: a few words of pinned host memory that kernels write (a copy and its wait cost more than the
-  // counting kernels of a small graph).  The mutex is held from the launch that writes
-  // the words until they have been read: threads may count graphs on one context at the same time.
+  // Results of the *_count calls: a few words of pinned host memory that kernels write and the host, which has set them to -1, looks at until
+  // they are there (a copy and its wait, or the stream's own wait, cost more than the counting kernels of a small graph).  The mutex is held
+  // from the launch that writes the words until they have been read: threads may count graphs on one context at the same time.
   int64_t* hwords = nullptr;
   int64_t* hwords_dev = nullptr;
   std::mutex count_mutex;

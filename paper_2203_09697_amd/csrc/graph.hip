@@ -42,9 +42,11 @@ scan_exclusive_kernel(const int32_t* __restrict__ in, int32_t* __restrict__ out,
     if (tid == SCAN_THREADS - 1) carry_s = before + incl;
     __syncthreads();
   }
+  // The host goes on when it sees the total: by then all that this workgroup wrote is visible to every stream (the barrier orders the
+  // workgroup's stores before the release), and nothing of the workspace is touched any more.
   if (tid == 0) {
     out[n] = (int32_t)carry_s;
-    *host_total = carry_s;
+    __hip_atomic_store(host_total, carry_s, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
   }
 }
 

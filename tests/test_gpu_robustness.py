@@ -62,3 +62,31 @@ def test_mode_change_between_forward_and_backward_is_rejected(lib):
     gm, _ = st.backward(gup)
     torch.cuda.synchronize()
     assert np.isfinite(gm.cpu().numpy()).all()
+
+
+def test_edges_filled_from_another_stream_after_the_count(lib):
+    """What gp_edges_count wrote to its workspace is complete when it returns: a context of another stream goes on with it at once.  (That it is
+    follows from the release before the host's word in scan_exclusive_kernel, not from a run that happens to agree.)"""
+    import ctypes as C
+
+    from paper_2203_09697_amd.binding import _ptr, load
+    other = torch.cuda.Stream()
+    one, two, dll = lib.Context(0), lib.Context(0, stream=other), load()
+    n = 30000   # 30 steps of the scan
+    size = C.c_size_t()
+    dll.gp_edges_workspace(C.c_int64(n), C.byref(size))
+    ws = torch.empty(size.value, dtype=torch.uint8, device="cuda:0")
+    gptr = torch.arange(0, n + 1, 30, dtype=torch.int32, device="cuda:0")
+    for seed in range(10):
+        gen = torch.Generator(device="cuda:0").manual_seed(seed)
+        pos = torch.rand((n, 3), generator=gen, device="cuda:0") * 6.0
+        want = lib.gp_edges(one, pos, gptr, 3.0)
+        torch.cuda.synchronize()
+        args = (_ptr(pos), _ptr(gptr), C.c_int64(n), C.c_int32(n // 30), C.c_float(3.0), C.c_int32(0), _ptr(ws), C.c_size_t(ws.numel()))
+        E = C.c_int64()
+        out = {k: torch.empty_like(want[k]) for k in ("src", "dst", "row_ptr", "dist", "unit")}
+        ws.zero_()
+        one.check(dll.gp_edges_count(one._h, *args, C.byref(E)))
+        two.check(dll.gp_edges_fill(two._h, *args, E, *(_ptr(out[k]) for k in ("src", "dst", "row_ptr", "dist", "unit"))))
+        other.synchronize()
+        assert E.value == want["n_edges"] and all(torch.equal(out[k], want[k]) for k in out)
