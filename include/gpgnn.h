@@ -324,7 +324,9 @@ typedef struct {
 
 /* Bytes of the activation buffer kept from forward to backward, and of scratch space.  n_atoms: gp_graph.n_atoms
  * of the graph the block will run on (0 if it carries no lists by centre atom); a scratch buffer sized with 0 is
- * accepted for any graph, the one-pass matrix-core triplet kernel of the bilinear block then stays unused. */
+ * accepted for any graph, the one-pass matrix-core triplet kernel of the bilinear block then stays unused.  Neither
+ * falls as the graph grows.  Scratch of variant D: seven arrays [E, emb] and some narrow ones; below emb = 512 two more
+ * for every residual layer and two for the others, until those come to 2 GiB, from where on they are not used. */
 int gp_block_workspace(const gp_dims* dims, int64_t n_atoms, int64_t n_edges, int64_t n_triplets,
                        size_t* saved_bytes /*host*/, size_t* scratch_bytes /*host*/);
 

@@ -60,11 +60,18 @@ size_t carve_saved_D(void* p, const gp_dims* d, int64_t E, saved_D* s) {
 
 // Gradients of the pre-activations of a block, one per dense layer over the edges, one for dxg and one for the gate; where the weight
 // gradients are formed together they all have to last, else four are used in turn.
-constexpr int DZ_MOST = 6 + 4 * GP_MAX_RES;
+constexpr int DZ_MOST = 6 + 4 * GP_MAX_RES, DZ_TURN = 4;
+int dz_private_D(const gp_dims* d) { return 6 + 2 * (d->n_res_before + d->n_res_after); }
 // The weight gradients of a block are formed by a few launches for all of them where a product by itself would be cut into many
-// runs of the rows (gp_gemm_tn_group), i.e. below width 512.
-bool group_D(const gp_dims* d) { return d->emb < 512; }
-int dz_buffers_D(const gp_dims* d) { return group_D(d) ? 6 + 2 * (d->n_res_before + d->n_res_after) : 4; }
+// runs of the rows (gp_gemm_tn_group), i.e. below width 512, and while the buffers that have to last for it take no more than 2 GiB
+// beyond the four: with three residual layers 262 thousand edges at width 256, a million at 64.  Training step of three blocks, one by
+// one / together (ms): width 256, 43 380 edges 5.42 / 5.19, 130 140 13.3 / 13.4, 260 280 26.2 / 26.2; 192, 260 280 22.7 / 21.6; 128, 260 280
+// 12.5 / 11.8, 515 137 24.4 / 23.7; 64, 260 280 7.65 / 7.10, 1 003 162 36.9 / 32.3 (up to 192 together with the chains below).
+constexpr int64_t GROUP_ROOM = (int64_t)1 << 31;
+int64_t group_rows_D(const gp_dims* d) { return d->emb >= 512 ? 0 : GROUP_ROOM / ((int64_t)sizeof(float) * d->emb * (dz_private_D(d) - DZ_TURN)); }
+bool group_D(const gp_dims* d, int64_t E) { return d->emb < 512 && E <= group_rows_D(d); }
+int dz_buffers_D(const gp_dims* d, int64_t E) { return group_D(d, E) ? dz_private_D(d) : DZ_TURN; }
+int64_t dz_stride_D(const gp_dims* d, int64_t E) { return (E * d->emb + 63) / 64 * 64; }   // floats from one to the next
 
 struct scratch_D {
   float* buf[3];     // [E,H] each: gradients of the messages between layers
@@ -73,9 +80,9 @@ struct scratch_D {
   float* dQ;         // [E,S*B]
   float* P;          // [E,S,F]: per-edge factor of the gradient with respect to cos(alpha) (basis gradients only)
   float* dWrbf;      // [R,H]
-  float* part;
-  float* part_aux;   // split-K partials of the GEMMs issued on the side stream
-  size_t part_bytes;
+  float* part;       // partial sums of the main stream's reductions, one at a time
+  float* part_aux;   // of those issued on the side stream, groups among them
+  size_t part_bytes, part_aux_bytes;
   void* planes;      // the weights of a call as operand planes (gemm_planes.hip) or as parts for its chains
   size_t planes_bytes;
 };
@@ -92,9 +99,10 @@ size_t part_bytes_one_D(const gp_dims* d, int64_t E) {
   return m;
 }
 
-size_t part_bytes_D(const gp_dims* d, int64_t E) {
+// ... of groups too; no smaller for more edges
+size_t part_bytes_aux_D(const gp_dims* d, int64_t E) {
   size_t m = part_bytes_one_D(d, E);
-  if (group_D(d)) {
+  if (group_rows_D(d) > 0) {
     gp_tn_product all[GP_TN_JOBS_MAX];
     int n = 0;
     auto add = [&](int a, int b) { all[n++] = gp_tn_product{nullptr, nullptr, a, b, nullptr, nullptr}; };
@@ -102,7 +110,7 @@ size_t part_bytes_D(const gp_dims* d, int64_t E) {
     add(d->num_radial, d->emb);
     add(d->int_emb, d->emb);
     add(d->emb, d->int_emb);
-    m = std::max(m, gp_gemm_tn_group_scratch(E, all, n));
+    m = std::max(m, gp_gemm_tn_group_scratch(std::min(E, group_rows_D(d)), all, n));
   }
   return m;
 }
@@ -131,7 +139,7 @@ size_t planes_bytes_D(const gp_dims* d) {
 // 9.51 / 8.87; 256, 13 668 edges 2.55 / 2.25, 27 028 3.68 / 3.63, 32 538 4.13 / 4.03, 43 380 5.16 / 5.36, 100 119 10.54 / 11.11: at that width
 // two workgroups of 64 rows fill a compute unit, and where some would come in a second round the layers' own launches are faster.
 bool chain_D(const gp_ctx* ctx, const gp_dims* d, const gp_weights_D* w, int64_t E, std::initializer_list<const void*> more) {
-  if (!ctx->f32_split || ctx->gemm_bf16 || !group_D(d) || !gp_chain_takes(d->emb, d->int_emb) || (d->emb > 192 && E > 32768)) return false;
+  if (!ctx->f32_split || ctx->gemm_bf16 || !gp_chain_takes(d->emb, d->int_emb) || (d->emb > 192 && E > 32768)) return false;
   uintptr_t a = (uintptr_t)w->b_ji | (uintptr_t)w->b_kj | (uintptr_t)w->b_lin;
   for (int r = 0; r < d->n_res_before; ++r) a |= (uintptr_t)w->res_before[r][1] | (uintptr_t)w->res_before[r][3];
   for (int r = 0; r < d->n_res_after; ++r) a |= (uintptr_t)w->res_after[r][1] | (uintptr_t)w->res_after[r][3];
@@ -154,15 +162,19 @@ size_t carve_scratch_D(void* p, const gp_dims* d, int64_t E, scratch_D* s) {
   gp_carver c(p);
   const size_t H = d->emb, F = d->int_emb, B = d->basis_emb, S = d->num_spherical, R = d->num_radial;
   for (int i = 0; i < 3; ++i) s->buf[i] = c.take<float>(E * H);
-  for (int i = 0; i < dz_buffers_D(d); ++i) s->dz[i] = c.take<float>(E * H);
+  // as many as are used at E, and no less room than a smaller graph's groups take
+  const int64_t stride = dz_stride_D(d, E), grouped = dz_private_D(d) * dz_stride_D(d, std::min(E, group_rows_D(d)));
+  float* const dz = c.take<float>(std::max(DZ_TURN * stride, grouped));
+  for (int i = 0; i < dz_buffers_D(d, E); ++i) s->dz[i] = dz + i * stride;
   s->dF1 = c.take<float>(E * F);
   s->dF2 = c.take<float>(E * F);
   s->dQ = c.take<float>(E * S * B);
   s->P = c.take<float>(E * S * F);
   s->dWrbf = c.take<float>(R * H);
-  s->part_bytes = part_bytes_D(d, E);
+  s->part_bytes = part_bytes_one_D(d, E);
   s->part = (float*)c.take<char>(s->part_bytes);
-  s->part_aux = (float*)c.take<char>(s->part_bytes);
+  s->part_aux_bytes = part_bytes_aux_D(d, E);
+  s->part_aux = (float*)c.take<char>(s->part_aux_bytes);
   s->planes_bytes = planes_bytes_D(d);
   s->planes = c.take<char>(s->planes_bytes);
   return c.off;
@@ -221,7 +233,7 @@ struct wgrads_D {
   bool group;
   int n_dz, at = 0, n = 0;
   gp_tn_product p[GP_TN_JOBS_MAX];
-  wgrads_D(gp_ctx* c, gp_aux& a, scratch_D& s, const gp_dims* d, int64_t rows) : ctx(c), aux(a), sc(s), E(rows), group(group_D(d)), n_dz(dz_buffers_D(d)) {}
+  wgrads_D(gp_ctx* c, gp_aux& a, scratch_D& s, const gp_dims* d, int64_t rows) : ctx(c), aux(a), sc(s), E(rows), group(group_D(d, rows)), n_dz(dz_buffers_D(d, rows)) {}
   // Room for the next gradient.  Where the buffers are used in turn the side stream may still read what was in it, which a gradient that it
   // writes itself (on_side) need not wait for.
   int take(float** dz, bool on_side = false) {
@@ -235,14 +247,14 @@ struct wgrads_D {
       p[n++] = gp_tn_product{A, dz, M, N, W, b};
       return GP_OK;
     }
-    return aux.on_aux([&] { return gp_gemm_tn(ctx, A, dz, E, M, N, W, b, sc.part_aux, sc.part_bytes); }, {dz});
+    return aux.on_aux([&] { return gp_gemm_tn(ctx, A, dz, E, M, N, W, b, sc.part_aux, sc.part_aux_bytes); }, {dz});
   }
   // forms what has been added, on the side stream
   int run() {
     if (n == 0) return GP_OK;
     const int k = n;
     n = 0;
-    return aux.on_aux([&] { return gp_gemm_tn_group(ctx, p, k, E, sc.part_aux, sc.part_bytes); }, {});
+    return aux.on_aux([&] { return gp_gemm_tn_group(ctx, p, k, E, sc.part_aux, sc.part_aux_bytes); }, {});
   }
 };
 
@@ -491,7 +503,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   wgrads_D wg(ctx, aux, sc, dims, E);
   // dz of the last activation in the block
   const float* z_first = dims->n_res_after > 0 ? s.after[dims->n_res_after - 1].z2 : s.z_lin;
-  const bool chain = chain_D(ctx, dims, w, E, {m_in, grad_m_out, grad_m_in, saved, scratch});
+  const bool chain = wg.group && chain_D(ctx, dims, w, E, {m_in, grad_m_out, grad_m_in, saved, scratch});   // its gradients all last
   chain_list ch;
   int pre = 0;   // steps before the triplet sum's gradients
   float *dz_ji, *dz_kj, *dgate, *dm_ji;
@@ -637,7 +649,7 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
   GP_TRY(aux.on_aux(
       [&] {
         return gp_tripD_weight_grads(ctx, sc.dF1, bwd_mfma ? nullptr : s.Bacc, basis->rad, sc.dQ, E, F, S, R, B, gw->W_sbf2,
-                                     gw->W_sbf1, sc.part_aux, sc.part_bytes);
+                                     gw->W_sbf1, sc.part_aux, sc.part_aux_bytes);
       },
       {}));
   // gradients with respect to the basis (forces, Sec. 3.2): radial part of the spherical basis from grad_Q, cos(alpha)

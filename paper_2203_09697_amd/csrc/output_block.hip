@@ -223,7 +223,7 @@ size_t carve_out_saved(void* p, int64_t N, int H, int D, int L, out_saved* s) {
   return c.off;
 }
 struct out_scratch {
-  float *tE;          // [E, H]: t in the forward pass, dt (then dt * m) in the backward pass
+  float *tE;          // [E, H]: t in the forward pass, dt (then dt * m) in the backward pass (only with more than RADIAL_MAX functions)
   float *p, *ga;      // [N]
   float* du[GP_MAX_OUT_LAYERS + 1];   // [N, D] each: the gradients between the layers, which their weight gradients wait for together
   float *dh;          // [N, H]
@@ -233,7 +233,7 @@ struct out_scratch {
 };
 size_t carve_out_scratch(void* p, int64_t N, int64_t E, int H, int D, int R, int L, out_scratch* s) {
   gp_carver c(p);
-  s->tE = c.take<float>(E * H);
+  s->tE = R > RADIAL_MAX ? c.take<float>(E * H) : nullptr;
   s->p = c.take<float>(N);
   s->ga = c.take<float>(N);
   for (int k = 0; k <= L; ++k) s->du[k] = c.take<float>(N * D);
