@@ -483,7 +483,7 @@ tn_plan_t tn_plan(int64_t rows, int M, int N) {
   if (s > max_s) s = max_s;
   if (s < 1) s = 1;
   p.most = (int)s;
-  int64_t per = (rows + s - 1) / s;
+  int64_t per = std::max<int64_t>((rows + s - 1) / s, 1);
   per = (per + BK - 1) / BK * BK;
   s = (rows + per - 1) / per;
   if (s < 1) s = 1;
@@ -708,7 +708,7 @@ static void colsum_plan(int64_t rows, int* blocks, int64_t* per) {
   int64_t b = (rows + 127) / 128;
   if (b > 1024) b = 1024;
   if (b < 1) b = 1;
-  *per = (rows + b - 1) / b;
+  *per = std::max<int64_t>((rows + b - 1) / b, 1);
   *blocks = (int)((rows + *per - 1) / *per);
   if (*blocks < 1) *blocks = 1;
 }

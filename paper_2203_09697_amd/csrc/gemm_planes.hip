@@ -916,7 +916,7 @@ gp_tn_parts_plan gp_parts_tn_plan(int64_t rows, int M, int N) {
   const int64_t tiles = (int64_t)p.tiles_m * ((N + T - 1) / T);
   const int64_t s = p.big ? std::max<int64_t>(std::min(256 / tiles, (rows + 255) / 256), 1) : gp_parts_tn_splits(rows, tiles);
   p.most = (int)s;
-  p.per = ((rows + s - 1) / s + 31) / 32 * 32;
+  p.per = std::max<int64_t>(((rows + s - 1) / s + 31) / 32 * 32, 32);   // no rows: one empty split, for the size of its scratch
   p.splits = (int)((rows + p.per - 1) / p.per);
   return p;
 }

@@ -18,7 +18,7 @@ def test_block_scratch(emb, before, after):
     d = _dims(emb, before, after)
     # on both sides of the size where the gradients of all layers no longer have a buffer each, and far beyond
     turn = 2 ** 31 // (4 * emb * max(2 * (before + after) + 2, 1))
-    sizes = [1, 1000, 40000, turn - 1, turn, turn + 1, 2 * turn, 10 ** 7, 4 * 10 ** 7]
+    sizes = [0, 1, 1000, 40000, turn - 1, turn, turn + 1, 2 * turn, 10 ** 7, 4 * 10 ** 7]
     got = {E: gp_block_workspace(d, E, 14 * E)[1] for E in sorted(sizes)}
     sizes = sorted(got)
     assert all(got[a] <= got[b] for a, b in zip(sizes, sizes[1:]))
