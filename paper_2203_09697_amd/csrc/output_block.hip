@@ -48,7 +48,8 @@ out_atom_sum_kernel(const float* __restrict__ t, const int32_t* __restrict__ row
 
 // Few radial functions (R <= RADIAL_MAX): the gate's column of W_rbf fits a lane's registers, and the edges' passes of the output block are one
 // kernel each that reads every row once.  As a product with K = R, a pass that gathers, one that multiplies and A^T B: 26 us forward
-// and 54 backward at 13230 edges x 256 x 6, so 14 and 21 (eight edges at a time in the sum: 3 more).
+// and 54 backward at 13230 edges x 256 x 6, so 14 and 26 (eight edges at a time in the sum: 3 more).  The gate of the backward pass is summed
+// in fp64, 5 us of these: in fp32 the gradient of the messages has 1 (6 functions) to 3 per cent (12) more error than with the product.
 constexpr int RADIAL_MAX = 16;
 template <int RM>
 struct gate_column {
@@ -57,12 +58,13 @@ struct gate_column {
 #pragma unroll
     for (int r = 0; r < RM; ++r) w[r] = r < R ? W[(int64_t)r * H + f] : 0.f;
   }
-  // rbf: the R values of an edge (uniform in the wavefront)
+  // rbf: the R values of an edge (uniform in the wavefront); the sum in T
+  template <class T>
   __device__ __forceinline__ float at(const float* __restrict__ rbf, int R) const {
-    float g = 0.f;
+    T g = 0;
 #pragma unroll
-    for (int r = 0; r < RM; ++r) g = __builtin_fmaf(r < R ? rbf[r] : 0.f, w[r], g);   // 0: an infinite value stays its own column's
-    return g;
+    for (int r = 0; r < RM; ++r) g += (T)(r < R ? rbf[r] : 0.f) * (T)w[r];   // 0: an infinite value stays its own column's
+    return (float)g;
   }
 };
 
@@ -90,9 +92,9 @@ out_edge_sum_kernel(const float* __restrict__ m, const float* __restrict__ rbf, 
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = m[(int64_t)(e + u) * H + f];
 #pragma unroll
-    for (int u = 0; u < U; ++u) s[u] = __builtin_fmaf(v[u], col.at(rbf + (int64_t)(e + u) * R, R), s[u]);
+    for (int u = 0; u < U; ++u) s[u] = __builtin_fmaf(v[u], col.template at<float>(rbf + (int64_t)(e + u) * R, R), s[u]);
   }
-  for (; e < e1; ++e) s[0] = __builtin_fmaf(m[(int64_t)e * H + f], col.at(rbf + (int64_t)e * R, R), s[0]);
+  for (; e < e1; ++e) s[0] = __builtin_fmaf(m[(int64_t)e * H + f], col.template at<float>(rbf + (int64_t)e * R, R), s[0]);
   h[i * H + f] = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
@@ -126,7 +128,7 @@ out_edge_grad_kernel(const float* __restrict__ m, const float* __restrict__ rbf,
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float* q = rbf + (e + u) * R;
-      grad_m[(e + u) * H + f] = __builtin_fmaf(d[u], col.at(q, R), g0[u]);
+      grad_m[(e + u) * H + f] = __builtin_fmaf(d[u], col.template at<double>(q, R), g0[u]);
       const float dg = d[u] * v[u];
 #pragma unroll
       for (int r = 0; r < RM; ++r) dw[r] = __builtin_fmaf(r < R ? q[r] : 0.f, dg, dw[r]);

@@ -43,3 +43,25 @@ def test_output_block(lib, R, emb, edges):
     # on top of another gradient the sum is rounded once, to half an ulp of it (6e-8); norms, as above: triangle inequality
     want = base.cpu().numpy().astype(np.float64) + want_gm
     assert np.linalg.norm(twice.cpu().numpy() - want) <= 6e-8 * np.linalg.norm(want) + 3e-6 * np.linalg.norm(want_gm)
+
+
+@pytest.mark.parametrize("R", [1, 6, 12, 16])
+def test_the_gate_of_the_backward_pass_is_rounded_once(lib, R):
+    """No layers, W_up = I, w_final = 1 and dL/dE = 1: grad_m is the gate itself, one rounding to fp32 (at most 6e-8, 2e-8 to 3e-8 in the norm); a sum
+    of 6 to 16 products in fp32 is 4e-8 to 7e-8 off."""
+    from paper_2203_09697_amd import binding_o as O
+    ctx, rng, N, emb, edges = lib.Context(0), np.random.default_rng(R), 50, 64, 5000
+    dst = np.sort(rng.integers(0, N, edges))
+    row_ptr, gptr = np.searchsorted(dst, np.arange(N + 1)), np.array([0, N])
+    m, rbf = rng.standard_normal((edges, emb)).astype(np.float32), rng.standard_normal((edges, R)).astype(np.float32)
+    W = dict(synth.weights_out(emb, emb, R, 0, seed=3), W_up=np.eye(emb, dtype=np.float32), w_final=np.ones(emb, np.float32))
+    Wd = lib.weights_to_device(W)
+    sb, cb = O.gp_output_workspace(emb, emb, R, 0, N, edges)
+    saved, scratch = (torch.empty(max(b, 8), dtype=torch.uint8, device="cuda:0") for b in (sb, cb))
+    dm, drbf, dptr = H.to_dev(m, torch.float32), H.to_dev(rbf, torch.float32), H.to_dev(gptr, torch.int32)
+    gm = torch.empty_like(dm)
+    O.gp_output_forward(ctx, Wd, dm, drbf, H.to_dev(row_ptr, torch.int32), dptr, False, torch.empty(1, device="cuda:0"), saved, scratch)
+    O.gp_output_backward(ctx, Wd, dm, drbf, H.to_dev(dst, torch.int32), dptr, N, torch.ones(1, device="cuda:0"), saved, False, gm, None, scratch)
+    err = H.rel_l2(gm.cpu().numpy(), rbf.astype(np.float64) @ W["W_rbf"].astype(np.float64))
+    print("R %d %.2e" % (R, err))
+    assert err < 3.2e-8
