@@ -103,8 +103,8 @@ __device__ __forceinline__ double series_j(int l, double x) {
   for (int k = 0; k < l; ++k) p *= x;
   return p * t;
 }
-// j_l(y) and, where PAIR, j_{l-1}(y) (l >= 1), y > 0 and inv = 1/y: the series below 0.6 (l + 1), where the upward recurrence has lost three of
-// its sixteen digits, and the recurrence from there on.
+// j_l(y) and, where PAIR, j_{l-1}(y) (l >= 1), y > 0 and inv = 1/y: the series below 0.6 (l + 1), and from there on the upward recurrence,
+// whose relative error is largest at that line: 5e-16 for l = 1, 7e-15 for l = 4, 6e-14 for l = 7, against 6e-8 of the rounding to fp32.
 template <bool PAIR>
 __device__ __forceinline__ double sph_bessel_dev(int l, double y, double inv, double* below) {
   if (l >= 1 && y < 0.6 * (double)(l + 1)) {
@@ -175,7 +175,7 @@ void make_bessel_table(int S, int R, double cutoff, bessel_table* t) {
 // variant D: rbf[E,R] and rad[E,S*R].  A workgroup evaluates all R + S*R functions of EB edges, lanes over edges first: a
 // wavefront then follows one or two orders l (their loops differ) and the results leave through LDS as whole rows.  What depends on
 // the edge alone, three divisions and the envelope, is found once per edge and read from LDS.  One thread per value: with
-// one per (edge, l) a thread's six values came one after the other.  Bound by fp64 instructions, about BASIS_INSTR a value.
+// one per (edge, l) a thread's six values came one after the other.  Bound by fp64 instructions.
 template <int EB>
 __device__ __forceinline__ void basis_edges_D(int block, const float* __restrict__ dist, int64_t n_edges, int S, int R, int p, const bessel_table& tab,
                                               float* __restrict__ rbf, float* __restrict__ rad) {
@@ -469,8 +469,10 @@ static int basis_edges(gp_ctx* ctx, const char* who, const gp_dims* dims, const 
       // edges, 7.5 / 8.6 at 8000, 9.7 / 9.7 at 12 000, 11.9 / 9.8 at 16 000, 20 / 14 at 32 000, 164 / 85 at 300 000
       const bool many = n_edges >= 12288;
       const size_t row = sizeof(float) * (R + S * R + 1);
-      // In one launch with the cosines while those are a matter of latency (above); 1e8 of them take 0.22 ms of writes
-      if (cos && cos->n_triplets < 4 * 1000 * 1000) {
+      // In one launch with the cosines while those do not fill the chip for long by themselves (above).  Apart / together: slabs, 0.2e6
+      // triplets 21.4 / 18.0 us, 1.6e6 26.5 / 20.3, 6.3e6 69 / 65, 12.5e6 122 / 120, 15.6e6 147 / 147, 24.9e6 259 / 267; boxes with long
+      // lists, 0.3e6 20.1 / 16.8, 2.2e6 25.0 / 18.5, 6.7e6 38 / 31, 14.3e6 59 / 53, 23.8e6 83 / 80
+      if (cos && cos->n_triplets < 16 * 1000 * 1000) {
         *cos_done = true;
         const bool wide = cos->n_triplets >= LONG_LISTS * n_edges;
         const int eb = many ? 32 : 4, blocks = (int)((n_edges + eb - 1) / eb);
@@ -562,8 +564,8 @@ int gp_grad_dist_bessel(gp_ctx* ctx, const gp_dims* dims, const float* dist, con
   bessel_table tab;
   make_bessel_table(S, R, (double)dims->cutoff, &tab);
   // Few terms: one thread per edge is not slower anywhere (9 terms: 7 us up to 16 000 edges; 36 us at 900 000, 77 with 4 lanes).
-  // From 16 terms on the lanes that keep the chip busy, 48 terms with 64 / 16 / 4 lanes per edge: 9 / 14 / 36 us at 336 edges,
-  // 15 / 12 / 36 at 4000, 42 / 24 / 35 at 16 000, 138 / 77 / 75 at 64 000, 612 / 336 / 299 at 300 000.
+  // From 16 terms on the lanes that keep the chip busy, 48 terms with 64 / 16 / 4 lanes per edge: 5.3 / 7.1 / 17 us at 336 edges,
+  // 7.4 / 7.0 / 16 at 4000, 18 / 13 / 16 at 16 000, 32 / 21 / 21 at 32 000, 61 / 36 / 36 at 64 000, 333 / 178 / 152 at 300 000.
   auto launch = [&](auto kernel, int lanes) {
     const int per = 256 / lanes;
     kernel<<<(unsigned)((n_edges + per - 1) / per), 256, 0, ctx->stream>>>(dist, grad_rbf, grad_rad, n_edges, S, R, dims->envelope_p, tab,
