@@ -612,18 +612,21 @@ int backward_D(gp_ctx* ctx, const gp_dims* dims, const gp_weights_D* w, const gp
     // h0 = x_ji + act(a W_up);  dh = dh0, dzcur = dz_up
     // The branch through x_ji = act(m W_ji + b_ji) needs dh0 only: all of it (dz_ji, both gradients) runs on the side
     // stream next to the chain through the triplet sum, whose kernels leave much of the chip idle; its input gradient
-    // is added by the epilogue of the last GEMM below.
+    // is added by the epilogue of the last GEMM below.  The weight gradient first where it does not join a group: with the input gradient
+    // ahead of it two blocks of 4656 edges x 512 take 2.51 ms instead of 2.44, of 5514 x 2048 13.4 instead of 13.2, of 5844 14.2 instead of
+    // 14.0, of 1884 6.6 instead of 6.7, and at width 1024 the same.
     GP_TRY(wg.add(s.a, dzcur, F, H, gw->W_up, nullptr));
     GP_TRY(wg.take(&dz_ji, true));
     dm_ji = next_buf();
     GP_TRY(aux.on_aux(
         [&] {
           GP_TRY(gp_ew_dsilu_mul(ctx, dh, s.z_ji, dz_ji, EH));
+          if (!wg.group) GP_TRY(gp_gemm_tn(ctx, m_in, dz_ji, E, H, H, gw->W_ji, gw->b_ji, sc.part_aux, sc.part_aux_bytes));
           gp_epilogue e; e.out = dm_ji;
           return gp_gemm_nt_w(ctx, dz_ji, w->W_ji, p_ji, E, H, H, e);
         },
         {dz_ji, dm_ji}));
-    GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
+    if (wg.group) GP_TRY(wg.add(m_in, dz_ji, H, H, gw->W_ji, gw->b_ji));
     if (aux.active()) GP_TRY(wg.run());
     {
       gp_epilogue e; e.out = sc.dF1;
