@@ -48,23 +48,27 @@ out_atom_sum_kernel(const float* __restrict__ t, const int32_t* __restrict__ row
 
 // Few radial functions (R <= RADIAL_MAX): the gate's column of W_rbf fits a lane's registers, and the edges' passes of the output block are one
 // kernel each that reads every row once.  As a product with K = R, a pass that gathers, one that multiplies and A^T B: 26 us forward
-// and 54 backward at 13230 edges x 256 x 6, so 14 and 26 (eight edges at a time in the sum: 3 more).  The gate of the backward pass is summed
-// in fp64, 5 us of these: in fp32 the gradient of the messages has 1 (6 functions) to 3 per cent (12) more error than with the product.
+// and 54 backward at 13230 edges x 256 x 6, so 20 and 23.  The gate is summed in fp64 in two chains, 5 us forward: in fp32 sums over five
+// edges have 10 (6 functions) to 39 per cent (16) more error than with the product (6.0e-8), so 10 less, and the gradient of the messages 1 to 3.
 constexpr int RADIAL_MAX = 16;
 template <int RM>
 struct gate_column {
-  float w[RM];
+  double w[RM];
   __device__ __forceinline__ void load(const float* __restrict__ W, int R, int H, int f) {
 #pragma unroll
-    for (int r = 0; r < RM; ++r) w[r] = r < R ? W[(int64_t)r * H + f] : 0.f;
+    for (int r = 0; r < RM; ++r) w[r] = r < R ? (double)W[(int64_t)r * H + f] : 0.0;
   }
-  // rbf: the R values of an edge (uniform in the wavefront); the sum in T
-  template <class T>
+  // value r of the R >= 1 of an edge (uniform in the wavefront), 0 beyond them: an infinite value stays its own column's.  Loaded either way, so
+  // that the loads of an edge are issued together instead of a branch for each.
+  static __device__ __forceinline__ float value(const float* __restrict__ rbf, int r, int R) {
+    const float x = rbf[r < R ? r : 0];
+    return r < R ? x : 0.f;
+  }
   __device__ __forceinline__ float at(const float* __restrict__ rbf, int R) const {
-    T g = 0;
+    double g[2] = {0.0, 0.0};
 #pragma unroll
-    for (int r = 0; r < RM; ++r) g += (T)(r < R ? rbf[r] : 0.f) * (T)w[r];   // 0: an infinite value stays its own column's
-    return (float)g;
+    for (int r = 0; r < RM; ++r) g[r & 1] = __builtin_fma((double)value(rbf, r, R), w[r], g[r & 1]);
+    return (float)(g[0] + g[1]);
   }
 };
 
@@ -92,9 +96,9 @@ out_edge_sum_kernel(const float* __restrict__ m, const float* __restrict__ rbf, 
 #pragma unroll
     for (int u = 0; u < U; ++u) v[u] = m[(int64_t)(e + u) * H + f];
 #pragma unroll
-    for (int u = 0; u < U; ++u) s[u] = __builtin_fmaf(v[u], col.template at<float>(rbf + (int64_t)(e + u) * R, R), s[u]);
+    for (int u = 0; u < U; ++u) s[u] = __builtin_fmaf(v[u], col.at(rbf + (int64_t)(e + u) * R, R), s[u]);
   }
-  for (; e < e1; ++e) s[0] = __builtin_fmaf(m[(int64_t)e * H + f], col.template at<float>(rbf + (int64_t)e * R, R), s[0]);
+  for (; e < e1; ++e) s[0] = __builtin_fmaf(m[(int64_t)e * H + f], col.at(rbf + (int64_t)e * R, R), s[0]);
   h[i * H + f] = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
@@ -128,10 +132,10 @@ out_edge_grad_kernel(const float* __restrict__ m, const float* __restrict__ rbf,
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const float* q = rbf + (e + u) * R;
-      grad_m[(e + u) * H + f] = __builtin_fmaf(d[u], col.template at<double>(q, R), g0[u]);
+      grad_m[(e + u) * H + f] = __builtin_fmaf(d[u], col.at(q, R), g0[u]);
       const float dg = d[u] * v[u];
 #pragma unroll
-      for (int r = 0; r < RM; ++r) dw[r] = __builtin_fmaf(r < R ? q[r] : 0.f, dg, dw[r]);
+      for (int r = 0; r < RM; ++r) dw[r] = __builtin_fmaf(col.value(q, r, R), dg, dw[r]);
     }
   };
   int64_t e = e0;

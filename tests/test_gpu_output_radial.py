@@ -65,3 +65,19 @@ def test_the_gate_of_the_backward_pass_is_rounded_once(lib, R):
     err = H.rel_l2(gm.cpu().numpy(), rbf.astype(np.float64) @ W["W_rbf"].astype(np.float64))
     print("R %d %.2e" % (R, err))
     assert err < 3.2e-8
+
+
+@pytest.mark.parametrize("R", [6, 12, 16])
+def test_the_gate_of_the_forward_pass_is_rounded_once(lib, R):
+    """One edge an atom, an atom a structure, no layers, W_up = I and one value in w_final: the energy is m times the gate, two roundings to fp32 of 2e-8
+    to 3e-8 each, 4e-8 together; with a gate summed in fp32 5e-8 (6 functions) to 8e-8 (16)."""
+    from paper_2203_09697_amd import binding_o as O
+    ctx, rng, N, emb = lib.Context(0), np.random.default_rng(R), 4000, 64
+    m, rbf = rng.standard_normal((N, emb)).astype(np.float32), rng.standard_normal((N, R)).astype(np.float32)
+    W = dict(synth.weights_out(emb, emb, R, 0, seed=3), W_up=np.eye(emb, dtype=np.float32), w_final=np.eye(emb, dtype=np.float32)[5])
+    saved, scratch = (torch.empty(max(b, 8), dtype=torch.uint8, device="cuda:0") for b in O.gp_output_workspace(emb, emb, R, 0, N, N))
+    energy, ptr = torch.empty(N, device="cuda:0"), H.to_dev(np.arange(N + 1), torch.int32)
+    O.gp_output_forward(ctx, lib.weights_to_device(W), H.to_dev(m, torch.float32), H.to_dev(rbf, torch.float32), ptr, ptr, False, energy, saved, scratch)
+    err = H.rel_l2(energy.cpu().numpy(), m[:, 5].astype(np.float64) * (rbf.astype(np.float64) @ W["W_rbf"][:, 5].astype(np.float64)))
+    print("R %d %.2e" % (R, err))
+    assert err < 4.5e-8
