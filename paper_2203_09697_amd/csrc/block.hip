@@ -67,6 +67,8 @@ int dz_private_D(const gp_dims* d) { return 6 + 2 * (d->n_res_before + d->n_res_
 // beyond the four: with three residual layers 262 thousand edges at width 256, a million at 64.  Training step of three blocks, one by
 // one / together (ms): width 256, 43 380 edges 5.42 / 5.19, 130 140 13.3 / 13.4, 260 280 26.2 / 26.2; 192, 260 280 22.7 / 21.6; 128, 260 280
 // 12.5 / 11.8, 515 137 24.4 / 23.7; 64, 260 280 7.65 / 7.10, 1 003 162 36.9 / 32.3 (up to 192 together with the chains below).
+// The width, two blocks: 384, 398 edges 1.23 / 1.11, 1884 1.37 / 1.22, 8698 2.04 / 1.93, 17 398 2.83 / 2.75; 448, 1.33 / 1.20, 1.48 / 1.36,
+// 2.38 / 2.35, 3.63 / 3.64; 512, 1.72 / 1.85, 2.07 / 2.14, 2.72 / 3.01, 4.10 / 4.38; 1024, 2.31 / 2.59, 2.79 / 3.17, 5.89 / 6.25, 10.5 / 11.0.
 constexpr int64_t GROUP_ROOM = (int64_t)1 << 31;
 int64_t group_rows_D(const gp_dims* d) { return d->emb >= 512 ? 0 : GROUP_ROOM / ((int64_t)sizeof(float) * d->emb * (dz_private_D(d) - DZ_TURN)); }
 bool group_D(const gp_dims* d, int64_t E) { return d->emb < 512 && E <= group_rows_D(d); }
